@@ -928,10 +928,9 @@ size_t goom_affine_scan_workspace_bytes(int64_t T, int d, int64_t batch, int dty
     return plan_affine(T, d, batch, dtype, opts).total();
 }
 
-// Scaled states (Section 4.3, eq. 27) come straight out of the matrix-vector walk where that kernel serves the
-// last phase; otherwise the states are written as GOOMs to the workspace and converted.
-// the scaled states are written by the matrix-vector walk itself
-static bool affine_scaled_is_fused(const ScanPlan &p, int d, int dtype) { return dtype == GOOM_C64 && (d == 16 || d == 32 || d == 64) && p.C > 1; }
+// Scaled states (Section 4.3, eq. 27) come straight out of the matrix-vector kernels of the last phase.  The workspace query has
+// always asked for room for GOOM states elsewhere than here, and still does.
+static bool affine_scaled_needs_no_states(const ScanPlan &p, int d, int dtype) { return dtype == GOOM_C64 && (d == 16 || d == 32 || d == 64) && p.C > 1; }
 
 static size_t affine_states_bytes(long long T, int d, long long batch, int dtype)
 {
@@ -943,7 +942,7 @@ size_t goom_affine_scan_scaled_workspace_bytes(int64_t T, int d, int64_t batch, 
     if (T <= 0 || d <= 0 || batch <= 0 || d > GOOM_MAX_DIM) return 0;
     if (dtype != GOOM_C64 && dtype != GOOM_C128) return 0;
     const AffinePlan ap = plan_affine(T, d, batch, dtype, opts);
-    return align_up(ap.total(), 256) + (affine_scaled_is_fused(ap.p, d, dtype) ? 0 : affine_states_bytes(T, d, batch, dtype));
+    return align_up(ap.total(), 256) + (affine_scaled_needs_no_states(ap.p, d, dtype) ? 0 : affine_states_bytes(T, d, batch, dtype));
 }
 
 // adjoint_shift: NULL, or [batch, T] floats: the recurrence then runs on the transposes of A's matrices in reverse
@@ -967,8 +966,7 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
     if (logscale && !aligned(logscale, comp_bytes(dtype))) return fail(ctx, GOOM_EINVAL, "misaligned data pointer");
     const AffinePlan ap = plan_affine(T, d, batch, dtype, opts);
     const ScanPlan &p = ap.p;
-    const bool fused = want_scaled && affine_scaled_is_fused(p, d, dtype);
-    const size_t need = want_scaled ? align_up(ap.total(), 256) + (fused ? 0 : affine_states_bytes(T, d, batch, dtype)) : ap.total();
+    const size_t need = want_scaled ? align_up(ap.total(), 256) + (affine_scaled_needs_no_states(p, d, dtype) ? 0 : affine_states_bytes(T, d, batch, dtype)) : ap.total();
     if (int s = check_workspace(ctx, ws, ws_bytes, need)) return s;
     if (int s = need_ctx(ctx)) return s;
     if (affine_sequential_applies(T, d, batch, dtype, opts) && !io_shift)
@@ -976,12 +974,6 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         return goom_chain::launch_affine_seq(ctx, A, bias, h0, H, want_scaled ? scaled : nullptr, want_scaled ? logscale : nullptr, T, batch,
                                              adjoint_shift);
     const size_t cb = 2 * comp_bytes(dtype);
-    if (want_scaled && !fused) {
-        // the states as GOOMs behind the scan's own workspace, then their scaled exponentials
-        H = static_cast<unsigned char *>(ws) + align_up(ap.total(), 256);
-        if (int s = run_affine(ctx, A, bias, h0, H, nullptr, nullptr, T, d, batch, dtype, opts, ws, ap.total())) return s;
-        return launch_scaled_exp(ctx, H, scaled, logscale, (size_t)batch * (size_t)T, d, dtype);
-    }
     const int f64 = ap.f64 ? 1 : 0;
     if (adjoint_shift && (!f64 || ti || want_scaled)) return fail(ctx, GOOM_EUNSUPPORTED, "transposed factors in reverse order: float GOOMs, d = 16 or 32, several chunks");
 
@@ -1011,6 +1003,8 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         l.init = h0;
         l.init_stride = (long long)d * cb;
         l.out_goom = H;
+        l.out_scaled = want_scaled ? scaled : nullptr;
+        l.out_logscale = want_scaled ? logscale : nullptr;
         l.label = "affine_single_chunk";
         return launch_chain(ctx, l);
     }
@@ -1134,8 +1128,8 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         l.fact_stride = (long long)p.car.stride;
         l.fact_cols = p.car.cols_padded;
         l.out_goom = H;
-        l.out_scaled = fused ? scaled : nullptr;
-        l.out_logscale = fused ? logscale : nullptr;
+        l.out_scaled = want_scaled ? scaled : nullptr;
+        l.out_logscale = want_scaled ? logscale : nullptr;
         l.fact_f64 = f64;
         l.label = "affine_phase3_outputs";
         return launch_chain(ctx, l);

@@ -53,8 +53,8 @@ struct ChainArgs {
     long long init_group;   // > 0: factored initial states come from a grouped carry array, (init_group + 1)
     long long init_ngroups; //      entries per group of init_group chunks, init_ngroups groups per batch item
     const unsigned char *bias;
-    // linear recurrence with bias, matrix-vector walk only: states in scaled floating-point form
-    // (paper Section 4.3, eq. 27) instead of, or besides, GOOMs
+    // linear recurrence with bias, vector chains only: states in scaled floating-point form, reals of the GOOMs' component
+    // type (paper Section 4.3, eq. 27) instead of, or besides, GOOMs
     int left_real;       // 1: the left factors are real matrices (component type), not GOOMs (hot float kernel only)
     float *out_scaled;   // NULL or [batch, steps, d]
     float *out_logscale; // NULL or [batch, steps]
@@ -70,7 +70,13 @@ struct ChainArgs {
     // is then bias[s] e^(-io_shift[s]) and the state written for step s is h_s e^(+io_shift[s]): values far from 1 pass
     // through GOOM arrays of float components with log-magnitudes of ordinary size
     const float *io_shift;
+    int left_same; // factored left factors, vector chains only: every step's matrix is the first one's, its bias column its own
 };
+
+// chains of one state column (goom_vec.hip): GOOM or factored left factors, n, d <= dp
+int dispatch_vec(goom_ctx *ctx, const ChainArgs &args, int dp, int f64, int left_fact, long long grid, const char *label);
+// the float matrix-vector walk (goom_affine.hip)
+bool affine_walk_applies(const ChainArgs &args, int dp);
 
 template <typename R> struct Comp;
 template <> struct Comp<float> {

@@ -91,7 +91,7 @@ struct ChainLaunch {
     int bias_mode;        // 0 none, 1 GOOM vectors [batch, steps, d], 2 column d of the factored left factor
     int bias_col;         // state column that receives the bias
     const void *bias;
-    void *out_scaled;     // NULL or float states scaled to [-e^2, e^2], [batch, steps, d] (matrix-vector walk only)
+    void *out_scaled;     // NULL or states scaled to [-e^2, e^2], reals of the component type, [batch, steps, d] (m = 1 only)
     void *out_logscale;   // NULL or their log scales, [batch, steps]
     int io_c64;           // with dtype GOOM_C128: the GOOM arrays (left, init, bias, outputs) are complex64; the running
                           // product and every factored matrix are double
@@ -99,6 +99,7 @@ struct ChainLaunch {
     int acc_f64;          // chunk products of the recurrence with the running product in double (float GOOM factors)
     const float *left_shift; // NULL, or [batch, steps]: factors read transposed in reverse order, log-magnitudes shifted (see ChainArgs)
     const float *io_shift;   // NULL, or [batch, steps]: bias and stored states rescaled by e^(-+io_shift[s]) (see ChainArgs)
+    int left_same;        // factored left factors, m = 1: every step's matrix is the first one's, its bias column its own
     const char *label;    // phase name for profiling records
 };
 int launch_chain(goom_ctx *ctx, const ChainLaunch &a);

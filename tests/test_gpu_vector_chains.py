@@ -1,0 +1,101 @@
+"""Chains with a state of one column (recurrences, vector initial states) at the sizes where the matrix-vector kernels can go
+wrong: around 16, 32, 64 and 128 rows, one to a few steps, several chunks and groups of chunks, zeros among the entries, one matrix
+for all steps; against the oracle, with the tolerances of the parity tests."""
+import numpy as np
+import pytest
+
+import synthetic_inputs as si
+from test_gpu_parity import G, compare, dev, host, say, tolerance, with_sensitivity  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# (random probes of an entry's sensitivity: two underestimate it tenfold about once in 10^4 entries, and there are many here)
+PROBES = 8
+SIZES = [1, 3, 15, 16, 17, 31, 33, 47, 63, 64, 65, 100, 127, 128]
+
+
+def inputs(oracle, seed, batch, T, d, ctype, constant):
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    A, b = si.recurrence_inputs(si.BASE_SEED + seed, batch, T, d, gain=0.9 if constant else 1.05)
+    rng = np.random.default_rng(seed)
+    A[rng.random(A.shape) < 0.05] = 0.0  # some zero entries, a zero row and a zero bias
+    A[:, T // 2, d // 2] = 0.0
+    b[:, T // 3] = 0.0
+    if constant:
+        A = np.ascontiguousarray(A[:, 0])
+    h0 = si.normal_f32(si.BASE_SEED + seed + 1, 9, batch * d).reshape(batch, d)
+    return [oracle.to_goom(np.ascontiguousarray(v).astype(comp)) for v in (A, b, h0)]
+
+
+# chunks of 3 steps make more than 192 of them at T = 600: a grouped carry phase
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("constant", [False, True])
+@pytest.mark.parametrize("d", SIZES)
+def test_recurrence_sizes(G, oracle, d, ctype, constant):  # noqa: F811
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    for T, batch, chunk in ((1, 3, 0), (2, 1, 1), (5, 2, 2), (61, 2, 0), (61, 2, 7), (600, 1, 3)):
+        if T > 500 and d > 33:
+            continue
+        Az, bz, h0 = inputs(oracle, 300 + d, batch, T, d, ctype, constant)
+        say(f"recurrence T={T} d={d} batch={batch} chunk={chunk} {np.dtype(ctype).name} constant={constant}")
+        rep = (lambda a: np.ascontiguousarray(np.broadcast_to(a[:, None], (batch, T, d, d)))) if constant else (lambda a: a)
+        fn = lambda a_, b_, h_: oracle.affine_scan(rep(a_), b_, h0=h_, return_kappa=True)  # noqa: B023
+        re, sg, kap, well = with_sensitivity(fn, [Az, bz, h0], comp, nprobe=PROBES)
+        got = host(G.affine_scan(dev(Az), dev(bz), dev(h0), chunk_len=chunk, time_invariant=constant))
+        compare(got, re, sg, kap, name=f"T{T}d{d}", max_ill_fraction=0.25, well=well)
+        # the scaled states belong to the same states: s = +-exp(re - c + 2)
+        sc, c = (host(v).astype(np.float64) for v in G.affine_scan_scaled(dev(Az), dev(bz), dev(h0), chunk_len=chunk, time_invariant=constant,
+                                                                            want_logscale=True))
+        want, cw = oracle.scaled_exp(re + 1j * np.pi * sg)
+        top = np.argmax(np.where(np.isfinite(re), re, -np.inf), axis=-1)
+        ok = well & (kap <= (2.0 ** 9 if comp == np.float32 else 2.0 ** 30)) & np.take_along_axis(well, top[..., None], axis=-1) & np.isfinite(re)
+        tol = tolerance(np.where(np.isfinite(re), re, 0.0), comp) + tolerance(np.where(np.isfinite(cw), cw, 0.0), comp)[..., None]
+        assert np.all(np.abs(sc - want)[ok] <= (tol * np.abs(want))[ok])
+
+
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("d", SIZES)
+def test_vector_states(G, oracle, d, ctype):  # noqa: F811
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    for T, batch, chunk in ((1, 2, 0), (37, 2, 0), (37, 1, 5), (600, 1, 3)):
+        if T > 500 and d > 33:
+            continue
+        x = si.normal_chain(si.BASE_SEED + 320 + d, batch * T, d).reshape(batch, T, d, d)
+        v = si.normal_f32(si.BASE_SEED + 321, 9, batch * d).reshape(batch, d, 1)
+        z, u = oracle.to_goom(x.astype(comp)), oracle.to_goom(v.astype(comp))
+        say(f"vector state T={T} d={d} batch={batch} chunk={chunk} {np.dtype(ctype).name}")
+        for q in range(batch):
+            fn = lambda m_, i_: oracle.scan(m_, init=i_, return_kappa=True)
+            re, sg, kap, well = with_sensitivity(fn, [z[q], u[q]], comp, nprobe=PROBES)
+            got = host(G.scan(dev(z), dev(u), chunk_len=chunk))[q]
+            compare(got, re, sg, kap, name=f"T{T}d{d}", max_ill_fraction=0.25, well=well)
+            last = host(G.reduce(dev(z), dev(u), chunk_len=chunk))[q]
+            compare(last, re[-1], sg[-1], kap[-1], name="last", max_ill_fraction=1.0, well=well[-1])
+        # one column as a product of its own
+        a, b = z[:, 0], u
+        fn = lambda a_, b_: oracle.lmme(a_, b_, return_kappa=True)
+        re, sg, kap, well = with_sensitivity(fn, [a, b], comp, nprobe=PROBES)
+        compare(host(G.lmme(dev(a), dev(b))), re, sg, kap, name="lmme", max_ill_fraction=0.25, well=well)
+
+
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("d", [5, 48, 100])
+def test_magnitudes_far_apart(G, oracle, d, ctype):  # noqa: F811
+    """A bias far above and far below the vector's scale, a chain that dies out to zero and starts again, and non-finite input."""
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    Az, bz, h0 = inputs(oracle, 340 + d, 2, 24, d, ctype, False)
+    bz = bz.copy()
+    bz[:, 5].real += comp(4000.0)
+    bz[:, 11].real -= comp(9000.0)
+    Az[:, 15].real = -np.inf  # everything forgotten
+    bz[:, 15].real = -np.inf
+    bz[:, 16].real -= comp(700.0)
+    for chunk in (0, 6):
+        re, sg, kap, well = with_sensitivity(lambda a_, b_, h_: oracle.affine_scan(a_, b_, h0=h_, return_kappa=True), [Az, bz, h0], comp, nprobe=PROBES)
+        got = host(G.affine_scan(dev(Az), dev(bz), dev(h0), chunk_len=chunk))
+        compare(got, re, sg, kap, name=f"far apart d{d}", max_ill_fraction=0.25, well=well)
+        assert np.all(np.isneginf(got.real[:, 15]))
+        bad = Az.copy()
+        bad[0, 7, 0, 0] = np.nan
+        got = host(G.affine_scan(dev(bad), dev(bz), dev(h0), chunk_len=chunk))
+        assert np.isnan(got[0, 7].real).any() and np.isfinite(got[1, :15].real).all() and np.isfinite(got[0, :7].real).all()

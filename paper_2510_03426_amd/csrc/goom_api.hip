@@ -897,10 +897,23 @@ struct AffinePlan {
     size_t total() const { return align_up(p.total(), 256) + h0_bytes; }
 };
 
+// Batches that are walked start to end, one workgroup a sequence (a matrix per step, default chunking): each matrix is read once
+// instead of three times (chunk products, chunk vectors, outputs) and nothing is multiplied but vectors.  Measured, us a step of the
+// whole batch, walk against chunks, at 64 and 256 sequences (complex64 d = 24: 0.90 / 0.39, 0.94 / 1.12; d = 48: 1.42 / 0.98,
+// 1.52 / 2.87; d = 100: 3.8 / 4.5, 4.8 / 16.9; d = 8: 0.74 / 0.21, 0.74 / 0.35; complex128 d = 24: 1.14 / 0.88, 1.21 / 2.99;
+// d = 48: 2.2 / 3.4, 2.5 / 9.7; d = 100: 8.9 / 12.9, 11.7 / 48): the lines lie where the two meet.  (complex64 d = 16, 32: chunk
+// products in double, and a walk of its own at d = 32, below.)
+static bool affine_walk_whole(int d, long long batch, int dtype, const goom_scan_opts *opts)
+{
+    if (opts && (opts->chunk_len != 0 || (opts->flags & GOOM_AFFINE_TIME_INVARIANT))) return false;
+    if (dtype == GOOM_C64) return d != 16 && d != 32 && batch >= (d <= 16 ? 512 : d <= 32 ? 192 : d <= 64 ? 96 : 56);
+    return batch >= (d <= 16 ? 384 : d <= 32 ? 96 : 48);
+}
+
 static AffinePlan plan_affine(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts)
 {
     AffinePlan ap;
-    const long long req = opts ? opts->chunk_len : 0;
+    const long long req = affine_walk_whole(d, batch, dtype, opts) ? T : opts ? opts->chunk_len : 0;
     ap.p = plan_scan(T, d, d + 1, 1, batch, dtype, req, false);
     ap.f64 = dtype == GOOM_C64 && (d == 16 || d == 32) && ap.p.dp == d && ap.p.C > 1;
     ap.h0_bytes = 0;
@@ -1083,6 +1096,36 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         w.fact_f64 = f64;
         w.label = "affine_phase1_chunk_vectors";
         if (int s = launch_chain(ctx, w)) return s;
+    } else if (!f64 && !(dtype == GOOM_C64 && d == 64)) {
+        // Phase 1 in two passes: the products A* by the chain kernels of plain chains, the vectors b* by a walk of every chunk from
+        // zero.  The second read costs less than the bias wave did: with nine waves the general kernel has no registers left at d > 64
+        // and the kernels for d = 8, 24, 48, ... take no bias at all (8 x 2000 matrices of d = 100: 2010 -> 564 + 276 us; complex128,
+        // d = 48: 840 -> 524 + 155 us).
+        ChainLaunch l = base;
+        l.bias_mode = 0;
+        l.bias = nullptr;
+        l.io_shift = nullptr;
+        l.m = d;
+        l.chunk_len = p.L;
+        l.chunks_launched = p.C - 1;
+        l.init_mode = 0;
+        l.out_fact_final = totals;
+        l.final_common_exponent = 1;
+        l.fact_stride = (long long)p.tot.stride;
+        l.fact_cols = p.tot.cols_padded;
+        l.label = "affine_phase1_chunk_products";
+        if (int s = launch_chain(ctx, l)) return s;
+        ChainLaunch w = base;
+        w.m = 1;
+        w.bias_col = d;
+        w.chunk_len = p.L;
+        w.chunks_launched = p.C - 1;
+        w.init_mode = 3;
+        w.out_fact_final = totals;
+        w.fact_stride = (long long)p.tot.stride;
+        w.fact_cols = p.tot.cols_padded;
+        w.label = "affine_phase1_chunk_vectors";
+        if (int s = launch_chain(ctx, w)) return s;
     } else { // phase 1: augmented chunk products [A* | b*]
         ChainLaunch l = base;
         l.m = d + 1;
@@ -1240,14 +1283,50 @@ int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, co
         return launch_affine_backward_gradients_one_matrix(ctx, A, bias, h0, H, mu, grad_A, grad_bias, grad_h0, U, U + p.uv_bytes, p.nsplit, T, d,
                                                            batch, dtype);
     }
-    // operands of the adjoint recurrence (transposed matrices in reverse time, G / h as GOOMs) ...
-    if (int s = launch_affine_backward_prepare(ctx, A, H, grad_H, p.direct ? nullptr : At, p.direct ? static_cast<float *>(At) : nullptr, gt, T, d, batch, dtype))
-        return s;
-    // ... the adjoints, by the forward scan itself ...
+    if (!p.direct) {
+        // Every size but float d = 16 and 32: the adjoints walked backwards, gradients written on the way (goom_vec_adjoint.hip), over
+        // the forward chunks.  One chain an item carries the adjoint from chunk to chunk: at most 128 chunks by default (a carry
+        // takes about as long as a step, so longer chunks cost nothing).
+        goom_scan_opts o = plain;
+        const AffinePlan fwd = plan_affine(T, d, batch, dtype, &plain);
+        if (plain.chunk_len == 0) o.chunk_len = fwd.p.C > 128 ? (T + 127) / 128 : fwd.p.L;
+        const ScanPlan q = plan_affine(T, d, batch, dtype, &o).p;
+        unsigned char *totals = static_cast<unsigned char *>(w), *vecs = totals + align_up((size_t)batch * q.C * q.tot.stride, 256);
+        if (q.C > 1) {
+            if ((size_t)(vecs - w) + (size_t)batch * q.C * goom_chain::adjoint_vec_stride(q.dp, dtype) > p.total())
+                return fail(ctx, GOOM_EWORKSPACE, "workspace too small for %lld chunks", q.C);
+            const size_t cb = 2 * comp_bytes(dtype);
+            ChainLaunch l;
+            std::memset(&l, 0, sizeof l);
+            l.dp = q.dp;
+            l.dtype = dtype;
+            l.n = d;
+            l.d = d;
+            l.m = d;
+            l.batch = batch;
+            l.left = static_cast<const unsigned char *>(A) + (size_t)q.L * d * d * cb; // (nothing passes through the first chunk)
+            l.left_batch_stride = (long long)((size_t)T * d * d * cb);
+            l.left_step_stride = (long long)((size_t)d * d * cb);
+            l.steps = T - q.L;
+            l.chunk_len = q.L;
+            l.chunks_launched = q.C - 1;
+            l.init_mode = 0;
+            l.out_fact_final = totals;
+            l.final_common_exponent = 1;
+            l.fact_stride = (long long)q.tot.stride;
+            l.fact_cols = q.tot.cols_padded;
+            l.label = "affine_adjoint_chunk_products";
+            if (int s = launch_chain(ctx, l)) return s;
+        }
+        return goom_chain::launch_affine_adjoint(ctx, A, bias, h0, H, grad_H, grad_A, grad_bias, grad_h0, T, d, batch, dtype, q.dp, q.L, q.C, totals,
+                                                 (long long)q.tot.stride, q.tot.cols_padded, vecs);
+    }
+    // the operands of the adjoint recurrence (the shifts of the matrices' log-magnitudes, G / h as GOOMs) ...
+    if (int s = launch_affine_backward_prepare(ctx, H, grad_H, static_cast<float *>(At), gt, T, d, batch, dtype)) return s;
+    // ... the adjoints, by the forward scan itself over the matrices read transposed ...
     ctx->prof_keep = true;
-    const int st = p.direct ? run_affine(ctx, A, gt, nullptr, mu, nullptr, nullptr, T, d, batch, dtype, &plain, p.scan_bytes ? scan_ws : nullptr, p.scan_bytes,
-                                         static_cast<const float *>(At))
-                            : run_affine(ctx, At, gt, nullptr, mu, nullptr, nullptr, T, d, batch, dtype, &plain, p.scan_bytes ? scan_ws : nullptr, p.scan_bytes);
+    const int st = run_affine(ctx, A, gt, nullptr, mu, nullptr, nullptr, T, d, batch, dtype, &plain, p.scan_bytes ? scan_ws : nullptr, p.scan_bytes,
+                              static_cast<const float *>(At));
     ctx->prof_keep = false;
     if (st) return st;
     // ... and the gradients

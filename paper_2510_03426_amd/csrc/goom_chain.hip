@@ -84,7 +84,7 @@ int launch_chain(goom_ctx *ctx, const ChainLaunch &l)
         return fail(ctx, GOOM_EUNSUPPORTED, "transposed factors in reverse order: double chunk products and the walk beside them only");
     if ((l.fact_f64 || l.acc_f64) && (l.dtype != GOOM_C64 || l.left_fact))
         return fail(ctx, GOOM_EUNSUPPORTED, "double factored matrices beside float GOOMs: recurrence kernels only");
-    if ((a.out_scaled && (l.m != 1 || l.left_fact)) || (l.left_same && (l.m != 1 || !l.left_fact)))
+    if ((a.out_scaled && (l.m != 1 || l.left_fact)) || (l.left_same && (l.m != 1 || !l.left_fact || l.bias_mode != 2)))
         return fail(ctx, GOOM_EUNSUPPORTED, "scaled outputs and a shared factored matrix: vector chains only");
     const long long grid = l.batch * l.chunks_launched;
     // One state column: the matrix-vector kernels (a tile product would use one column of sixteen; 16 x 63 carries of d = 64

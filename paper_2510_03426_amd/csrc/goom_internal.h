@@ -165,8 +165,7 @@ int launch_matrix_probe(goom_ctx *ctx, void *sink, long long iters, int dtype);
 int launch_to_goom_backward(goom_ctx *ctx, const void *x, const void *g, void *gx, size_t n, int dtype, double eps);
 int launch_scaled_exp_backward(goom_ctx *ctx, const void *scaled, const void *g, void *gre, size_t n, int dtype);
 int launch_from_goom_backward(goom_ctx *ctx, const void *y, const void *gx, void *g, size_t n, int dtype, double eps);
-int launch_affine_backward_prepare(goom_ctx *ctx, const void *A, const void *H, const void *G, void *At, float *shift, void *gt, long long T, int d,
-                                   long long batch, int dtype);
+int launch_affine_backward_prepare(goom_ctx *ctx, const void *H, const void *G, float *shift, void *gt, long long T, int d, long long batch, int dtype);
 int launch_affine_backward_gradients(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *mu, void *gA,
                                      void *gb, void *gh0, long long T, int d, long long batch, int dtype);
 // goom_lmme_tall.hip: A [batch, n, d] of many rows against B [batch, d, m] with d, m <= 64 (float components)
@@ -209,5 +208,10 @@ int launch_replicate_power(goom_ctx *ctx, void *totals, long long stride, int fa
 // transpose of matrix T - s (any for s = 0) with adjoint_shift[s] added to its log-magnitudes
 int launch_affine_seq(goom_ctx *ctx, const void *A, const void *bias, const void *h0, void *H, void *scaled, void *logscale, long long T, long long batch,
                       const float *adjoint_shift);
+// adjoint of the recurrence and its gradients, every size and type (goom_vec_adjoint.hip)
+size_t adjoint_vec_stride(int dp, int dtype);
+int launch_affine_adjoint(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *G, void *gA, void *gb, void *gh0,
+                          long long T, int d, long long batch, int dtype, int dp, long long chunk_len, long long chunks, void *totals,
+                          long long total_stride, int total_cols, void *vecs);
 } // namespace goom_chain
 

@@ -12,69 +12,35 @@
 //   * a row's result goes to LDS as mantissa and exponent of its own, and one barrier later every wave reads the
 //     vector and brings it onto the largest exponent itself (the buffers alternate, so one barrier a step is enough);
 //   * the bias joins a row on the larger of the two exponents: no case of a bias too large for the vector's scale;
-//   * one factor for all steps (SAME) is converted once and stays in registers.
+//   * one factor for all steps (SAME) is converted once and stays in registers;
+//   * the loop has no branch around a load (the bias's kind is a template parameter, steps past the end are computed and dropped):
+//     behind one the compiler cannot count the loads in flight and waits for all of them (1.5 us a carry step of d = 64 then).
 // Carries (factored matrices) are multiplied and added in double for float components too.
 // Measured against the general chain kernel with one column (16 x 4096 x 64 float, 63 carries a sequence): see launch_vec.
-#include "goom_chain_kernel.h"
-
-#include <type_traits>
+#include "goom_vec.h"
 
 namespace goom_chain {
 
 namespace {
 
-template <int CTRL> __device__ inline float dpp_of(float v)
+// no bias, GOOM vectors, GOOM vectors with io_shift, column d of the factored left factor
+constexpr int kBiasNone = 0, kBiasGoom = 1, kBiasShifted = 2, kBiasFact = 3;
+
+// natural log of |x| 2^s, s a whole number: the hardware logarithm of a mantissa in [1/2, 1), where its error is a unit in the last place
+// of 1 (of a number scaled by 2^32, as the tile kernels take it, the logarithm is near 32 and so is its last place: 1.5e-6 against
+// 2e-7 on states of one step)
+__device__ inline float log_of(float x, double s)
 {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL> __device__ inline double dpp_of(double v)
-{
-    const u2 b = __builtin_bit_cast(u2, v);
-    u2 r;
-    r[0] = (unsigned)__builtin_amdgcn_mov_dpp((int)b[0], CTRL, 0xF, 0xF, true);
-    r[1] = (unsigned)__builtin_amdgcn_mov_dpp((int)b[1], CTRL, 0xF, 0xF, true);
-    return __builtin_bit_cast(double, r);
-}
-__device__ inline float raw_max(float a, float b) { return __builtin_fmaxf(a, b); }
-__device__ inline double raw_max(double a, double b) { return __builtin_fmax(a, b); }
-// sum / maximum over the sixteen lanes of a row (in every one of them)
-template <typename V> __device__ inline V sum16(V v)
-{
-    v += dpp_of<0xB1>(v);
-    v += dpp_of<0x4E>(v);
-    v += dpp_of<0x141>(v);
-    v += dpp_of<0x140>(v);
-    return v;
-}
-template <typename V> __device__ inline V max16(V v)
-{
-    v = raw_max(v, dpp_of<0xB1>(v));
-    v = raw_max(v, dpp_of<0x4E>(v));
-    v = raw_max(v, dpp_of<0x141>(v));
-    v = raw_max(v, dpp_of<0x140>(v));
-    return v;
+#pragma clang fp contract(off)
+    const float kLn2Hi = 0.693147182464599609375f;
+    const float kLn2Lo = -1.90465429995776806e-9f;
+    const float e = Comp<float>::exponent_of(x); // (zero: -126, and the logarithm is -inf)
+    const float l2 = __builtin_amdgcn_logf(__builtin_fabsf(__builtin_ldexpf(x, -(int)e)));
+    const float w = (float)(s + (double)e);
+    return __builtin_fmaf(w, kLn2Hi, __builtin_fmaf(w, kLn2Lo, l2 * kLn2Hi));
 }
 
-// (+-) 2^(re log2(e) - n), one rounding of a small argument; -inf gives zero, NaN stays NaN
-__device__ inline float scaled_entry(float re, float im, float n)
-{
-    const float kHi = 1.44269502162933349609375f; // float nearest log2(e)
-    const float kLo = 1.925963033500011e-8f;      // log2(e) - kHi
-    float t = __builtin_fmaf(re, kHi, -n);
-    t = __builtin_fmaf(re, kLo, t);
-    return Comp<float>::apply_sign(__builtin_amdgcn_exp2f(t), im);
-}
-__device__ inline double scaled_entry(double re, double im, double n)
-{
-    const double t = __builtin_fma(re, kLog2e, -n);
-    const double k = __builtin_rint(t);
-    const double y = __builtin_ldexp(Comp<double>::exp2_small(t - k), (int)(k < -4000.0 ? -4000.0 : k));
-    return Comp<double>::apply_sign(t < -1200.0 ? 0.0 : y, im);
-}
-
-constexpr float kNone = -1.0e30f; // stands for the exponent of zero
-
-template <typename R, typename IO, int DP, int NW, bool FACT, bool FULL, bool SAME, int PD>
+template <typename R, typename IO, int DP, int NW, bool FACT, bool FULL, bool SAME, int BIAS, int PD>
 __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
 {
     typedef typename std::conditional<FACT || sizeof(R) == 8, double, float>::type V; // the vector and the sums
@@ -82,6 +48,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
     constexpr int K = DP / 16;  // entries of a row per lane
     constexpr int RW = DP / NW; // rows of a wave
     constexpr int Q = RW / 4;   // passes of four rows
+    constexpr int RD = PD % 2 == 0 ? 2 : 1; // depth of the ring of biases
     static_assert(Q >= 1 && Q <= 16 && 4 * Q * NW == DP, "a lane finishes at most one row");
     __shared__ V vm[2][DP], vx[2][DP];
 
@@ -103,14 +70,36 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
     const bool owner = c < Q;
     const bool row_ok = orow < n_rows;
     const size_t bias_row = (size_t)(row_ok ? orow : 0);
-    const bool bias_goom = a.bias_mode == 1, bias_fact = a.bias_mode == 2;
+    constexpr bool bias_goom = BIAS == kBiasGoom || BIAS == kBiasShifted, bias_fact = BIAS == kBiasFact, shifted = BIAS == kBiasShifted;
 
-    // entry (q, k) of this lane: row row0 + 4 q, column c + 16 k
-    auto entry_ok = [&](int q, int k) { return FULL || (row0 + 4 * q < n_rows && c + 16 * k < d); };
+    // Entry (q, k) of this lane: row row0 + 4 q, column c + 16 k.  Beyond the matrix the last row (whose result is dropped) and
+    // the row's last entry (which meets a zero of the vector, and repeats a value that the row's shift knows already) stand in: no
+    // load or entry is masked.
+    // Wave-uniform bases plus 32-bit byte offsets.
+    const unsigned row_bytes = FACT ? (unsigned)lfc * (unsigned)sizeof(R) : (unsigned)(FULL ? DP : d) * (unsigned)sizeof(IO2);
+    constexpr unsigned kEntry = FACT ? sizeof(R) : sizeof(IO2);
+    unsigned row_at[FULL ? 1 : Q], col_at[FULL ? 1 : K];
+    if constexpr (FULL) {
+        row_at[0] = (unsigned)row0 * row_bytes;
+        col_at[0] = (unsigned)c * kEntry;
+    } else {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) row_at[q] = (unsigned)(row0 + 4 * q < n_rows ? row0 + 4 * q : n_rows - 1) * row_bytes;
+#pragma unroll
+        for (int k = 0; k < K; ++k) col_at[k] = (unsigned)(c + 16 * k < d ? c + 16 * k : d - 1) * kEntry;
+    }
+    auto offset_of = [&](int q, int k) {
+        if constexpr (FULL)
+            return row_at[0] + col_at[0] + (unsigned)(4 * q) * (unsigned)(DP * kEntry) + (unsigned)(16 * k) * kEntry;
+        else
+            return row_at[q] + col_at[k];
+    };
 
-    struct Raw {
+    struct Matrix { // a factor as it comes from memory
         IO2 z[FACT || SAME ? 1 : Q][FACT || SAME ? 1 : K];
         R w[FACT && !SAME ? Q : 1][FACT && !SAME ? K : 1];
+    };
+    struct Rest { // what else a step reads
         IO2 bias;      // GOOM bias of the lane's row
         R bias_m;      // factored bias: mantissa ...
         double bias_e; // ... and exponent
@@ -118,26 +107,28 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         float shift;   // io_shift
     };
     auto load_goom = [&](long long t, int q, int k) {
-        const IO2 *src = reinterpret_cast<const IO2 *>(left0 + t * a.left_step_stride);
-        const int idx = entry_ok(q, k) ? (row0 + 4 * q) * (FULL ? DP : d) + c + 16 * k : 0;
-        return src[idx];
+        return *reinterpret_cast<const IO2 *>(left0 + t * a.left_step_stride + offset_of(q, k));
     };
     auto load_fact = [&](long long t, int q, int k) {
-        const R *src = reinterpret_cast<const R *>(left0 + t * a.left_step_stride);
-        return src[(size_t)((row0 + 4 * q) * lfc + (entry_ok(q, k) ? c + 16 * k : 0))]; // (DP rows are there)
+        return *reinterpret_cast<const R *>(left0 + t * a.left_step_stride + offset_of(q, k));
     };
-    auto load = [&](long long t, Raw &r) {
+    // (a step past the end loads the last one's again)
+    auto load = [&](long long t, Matrix &m) {
+        t = t < len ? t : len - 1;
         if constexpr (!SAME) {
 #pragma unroll
             for (int q = 0; q < Q; ++q)
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     if constexpr (FACT)
-                        r.w[q][k] = load_fact(t, q, k);
+                        m.w[q][k] = load_fact(t, q, k);
                     else
-                        r.z[q][k] = load_goom(t, q, k);
+                        m.z[q][k] = load_goom(t, q, k);
                 }
         }
+    };
+    auto load_rest = [&](long long t, Rest &r) {
+        t = t < len ? t : len - 1;
         if (FACT) {
             const unsigned char *src = left0 + t * a.left_step_stride;
             const double *ep = reinterpret_cast<const double *>(src + (size_t)DP * lfc * sizeof(R));
@@ -149,17 +140,19 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         }
         if (bias_goom) {
             r.bias = reinterpret_cast<const IO2 *>(a.bias)[(size_t)(item * a.steps + t0 + t) * d + bias_row];
-            if (a.io_shift) r.shift = a.io_shift[item * a.steps + t0 + t];
+            if (shifted) r.shift = a.io_shift[item * a.steps + t0 + t];
         }
     };
 
     // ---- one factor's entries, scaled by their rows' powers of two
-    V same_s[SAME ? Q : 1][SAME ? K : 1], same_n[SAME ? Q : 1];
+    // EARLY: the next factor is converted while this step's rows are on their way through LDS
+    constexpr bool EARLY = !FACT && !SAME && DP <= 32; // (larger factors' registers are better spent on a deeper ring)
+    V same_s[SAME || EARLY ? Q : 1][SAME || EARLY ? K : 1], same_n[SAME || EARLY ? Q : 1];
     double same_common = 0.0;
-    auto row_shift_of = [&](const IO2 (&z)[K], int q) { // a whole number near the row's largest log2|A_ij|
+    auto row_shift_of = [&](const IO2 (&z)[K]) { // a whole number near the row's largest log2|A_ij|
         V u = -__builtin_huge_val();
 #pragma unroll
-        for (int k = 0; k < K; ++k) u = raw_max(u, entry_ok(q, k) ? (V)z[k][0] : (V)-__builtin_huge_val());
+        for (int k = 0; k < K; ++k) u = raw_max(u, (V)z[k][0]);
         u = max16(u);
         return u > (V)kNone ? Comp<V>::ceil_(u * (V)kLog2e) : (V)0; // (+inf stays: its row comes out as NaN)
     };
@@ -168,24 +161,32 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         for (int q = 0; q < Q; ++q) {
             if constexpr (FACT) {
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const R w = load_fact(0, q, k);
-                    same_s[q][k] = entry_ok(q, k) ? (V)w : (V)0;
-                }
+                for (int k = 0; k < K; ++k) same_s[q][k] = (V)load_fact(0, q, k);
                 same_n[q] = (V)0;
             } else {
                 IO2 z[K];
 #pragma unroll
                 for (int k = 0; k < K; ++k) z[k] = load_goom(0, q, k);
-                same_n[q] = row_shift_of(z, q);
+                same_n[q] = row_shift_of(z);
                 // the one conversion's rounding is the same at every step and adds up along the chain: made in double, rounded once
 #pragma unroll
-                for (int k = 0; k < K; ++k)
-                    same_s[q][k] = entry_ok(q, k) ? (V)scaled_entry((double)z[k][0], (double)z[k][1], (double)same_n[q]) : (V)0;
+                for (int k = 0; k < K; ++k) same_s[q][k] = (V)scaled_entry((double)z[k][0], (double)z[k][1], (double)same_n[q]);
             }
         }
         if (FACT) same_common = *reinterpret_cast<const double *>(left0 + (size_t)DP * lfc * sizeof(R));
     }
+
+    auto convert = [&](const Matrix &r) {
+        if constexpr (EARLY) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            same_n[q] = row_shift_of(r.z[q]);
+#pragma unroll
+            for (int k = 0; k < K; ++k) same_s[q][k] = scaled_entry((V)r.z[q][k][0], (V)r.z[q][k][1], same_n[q]);
+            if (K >= 8) __builtin_amdgcn_sched_barrier(0); // one pass's temporaries at a time
+        }
+        }
+    };
 
     // ---- initial vector: this lane's columns c + 16 k, mantissas times 2^eh
     V hm[K];
@@ -252,37 +253,37 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
     IO *logscale = reinterpret_cast<IO *>(a.out_logscale);
     const bool last_only = a.out_goom_last_only != 0;
 
-    auto step = [&](long long t, Raw &r) {
+    // mat: the step's matrix, or (EARLY) the one after it, to be converted; either makes room for the one PD steps on
+    auto step = [&](long long t, Matrix &mat, Rest &r) {
+        const bool live = t < len; // (the whole workgroup; a step past the end is computed on the last factor and dropped)
         // ---- the lane's row of A_t h, as part 2^(n + base)
         V part = (V)0, n = (V)0;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             V p = (V)0, nq = (V)0;
-            if constexpr (SAME) {
+            if constexpr (SAME || EARLY) {
 #pragma unroll
                 for (int k = 0; k < K; ++k) p = p + same_s[q][k] * hm[k];
                 nq = same_n[q];
             } else if constexpr (FACT) {
 #pragma unroll
-                for (int k = 0; k < K; ++k) p = p + (entry_ok(q, k) ? (V)r.w[q][k] : (V)0) * hm[k];
+                for (int k = 0; k < K; ++k) p = p + (V)mat.w[q][k] * hm[k];
             } else {
-                nq = row_shift_of(r.z[q], q);
+                nq = row_shift_of(mat.z[q]);
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const V s = scaled_entry((V)r.z[q][k][0], (V)r.z[q][k][1], nq);
-                    p = p + (entry_ok(q, k) ? s : (V)0) * hm[k];
-                }
+                for (int k = 0; k < K; ++k) p = p + scaled_entry((V)mat.z[q][k][0], (V)mat.z[q][k][1], nq) * hm[k];
             }
             p = sum16(p);
             part = c == q ? p : part;
             n = c == q ? nq : n;
+            if (K >= 8) __builtin_amdgcn_sched_barrier(0); // one pass's temporaries at a time: the registers hold two factors
         }
         // ---- the bias on the same base; the sum on the larger exponent
         const double base = eh + (FACT ? (SAME ? same_common : r.common) : 0.0);
         V bm = (V)0, be = (V)kNone;
         double cs = 0.0; // rescaled bias and states, in powers of two
         if (bias_goom) {
-            if (a.io_shift) cs = (double)r.shift * kLog2e;
+            if (shifted) cs = (double)r.shift * kLog2e;
             const double x = __builtin_fma((double)r.bias[0], kLog2e, -(cs + base));
             if (!(x < (double)kNone)) { // (NaN goes on)
                 const double xe = __builtin_rint(x); // (the double series wants at most half a unit)
@@ -308,15 +309,20 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
             vm[buf][orow] = row_ok ? m : (V)0;
             vx[buf][orow] = row_ok ? ex : (V)kNone;
         }
-        if (a.out_goom && owner && row_ok && (!last_only || t == len - 1)) {
+        if (a.out_goom && live && owner && row_ok && (!last_only || t == len - 1)) {
             const size_t at = (size_t)(last_only ? chain : item * a.steps + t0 + t) * n_rows + orow;
             IO re;
             if constexpr (sizeof(V) == 4 && sizeof(IO) == 4)
-                re = Comp<float>::out_re_f(m, (float)((double)ex + base + cs));
+                re = log_of(m, (double)ex + base + cs);
             else
                 re = (IO)Comp<double>::out_re((double)m, (double)ex, base + cs);
             reinterpret_cast<IO2 *>(a.out_goom)[at] = IO2{re, m < (V)0 ? Comp<IO>::pi() : (IO)0};
         }
+        load_rest(t + RD, r);
+        convert(mat);
+        if (Q * K >= 16) __builtin_amdgcn_sched_barrier(0); // (the new factor takes the old one's registers, not more)
+        load(t + PD + (EARLY ? 1 : 0), mat);
+        if (Q * K >= 16) __builtin_amdgcn_sched_barrier(0);
         // ---- everyone reads the vector and brings it onto its largest exponent
         if (NW > 1) {
             __syncthreads();
@@ -325,21 +331,21 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        V xs[K], xm = (V)kNone;
+        V xm = (V)kNone;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            hm[k] = vm[buf][c + 16 * k];
-            xs[k] = vx[buf][c + 16 * k];
-            xm = raw_max(xm, xs[k]);
-        }
+        for (int k = 0; k < K; ++k) xm = raw_max(xm, vx[buf][c + 16 * k]);
         xm = max16(xm);
         const bool none = !(xm > (V)(0.5f * kNone));
         if (none) xm = (V)0;
 #pragma unroll
-        for (int k = 0; k < K; ++k) hm[k] = Comp<V>::ldexp_(hm[k], (int)Comp<V>::clamp_shift(xs[k] - xm));
-        eh = none ? 0.0 : base + (double)xm;
-        if (fact_steps) store_fact(fact_steps + (t + 1) * a.fact_stride, 0, sizeof(R) == 8);
-        if (scaled) {
+        for (int k = 0; k < K; ++k) {
+            const V h = Comp<V>::ldexp_(vm[buf][c + 16 * k], (int)Comp<V>::clamp_shift(vx[buf][c + 16 * k] - xm));
+            hm[k] = live ? h : hm[k];
+        }
+        const double en = none ? 0.0 : base + (double)xm;
+        eh = live ? en : eh;
+        if (fact_steps && live) store_fact(fact_steps + (t + 1) * a.fact_stride, 0, sizeof(R) == 8);
+        if (scaled && live) {
             // exp(z - c + 2), c the log of the largest magnitude: the mantissa over the largest one, times e^2
             V am = (V)0;
 #pragma unroll
@@ -356,43 +362,55 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         }
     };
 
-    Raw ring[PD];
+    Matrix ring[PD];
+    Rest rest[RD];
+    if constexpr (EARLY) {
+        load(0, ring[0]);
+        convert(ring[0]);
+    }
 #pragma unroll
-    for (int i = 0; i < PD; ++i) load(i < len ? i : len - 1, ring[i]);
-    for (long long t = 0; t < len; t += PD) {
+    for (int i = 0; i < PD; ++i) load(i + (EARLY ? 1 : 0), ring[i]);
 #pragma unroll
-        for (int i = 0; i < PD; ++i) {
-            if (t + i < len) { // (the whole workgroup)
-                step(t + i, ring[i]);
-                load(t + i + PD < len ? t + i + PD : len - 1, ring[i]);
-            }
-        }
+    for (int i = 0; i < RD; ++i) load_rest(i, rest[i]);
+    for (long long t = 0; t < len; t += PD) { // (PD steps written out: the rings' slots are known at compile time)
+#pragma unroll
+        for (int i = 0; i < PD; ++i) step(t + i, ring[i], rest[i % RD]);
     }
     if (a.out_fact_final) store_fact(a.out_fact_final + chain * a.fact_stride, a.bias_mode == 1 ? a.bias_col : 0, sizeof(R) == 8 || a.fact_f64);
 }
 
-template <typename R, typename IO, int DP, int NW, bool FACT, bool FULL, bool SAME, int PD>
+template <typename R, int DP, int NW, bool FACT, bool FULL, bool SAME, int BIAS, int PD>
 int launch_vec(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
 {
     if (grid <= 0) return GOOM_OK;
     if (grid > 0x7fffffffLL) return goom::fail(ctx, GOOM_EUNSUPPORTED, "too many chains for one launch (%lld)", grid);
     goom::prof_begin(ctx, label);
-    hipLaunchKernelGGL((vec_walk_kernel<R, IO, DP, NW, FACT, FULL, SAME, PD>), dim3((unsigned)grid), dim3(NW * 64), 0, ctx->stream, args);
+    hipLaunchKernelGGL((vec_walk_kernel<R, R, DP, NW, FACT, FULL, SAME, BIAS, PD>), dim3((unsigned)grid), dim3(NW * 64), 0, ctx->stream, args);
     goom::prof_end(ctx);
     return goom::check_hip(ctx, hipGetLastError(), "launch vec_walk_kernel");
 }
 
 template <typename R, int DP, int NW, int PD> int goom_factors(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
 {
-    if (args.left_step_stride == 0 && args.steps > 1) return launch_vec<R, R, DP, NW, false, false, true, 2>(ctx, args, grid, label);
-    if (args.n == DP && args.d == DP) return launch_vec<R, R, DP, NW, false, true, false, PD>(ctx, args, grid, label);
-    return launch_vec<R, R, DP, NW, false, false, false, PD>(ctx, args, grid, label);
+    const bool bias = args.bias_mode == 1;
+    if (args.left_step_stride == 0 && args.steps > 1) {
+        if (bias && args.io_shift) return launch_vec<R, DP, NW, false, false, true, kBiasShifted, 2>(ctx, args, grid, label);
+        return bias ? launch_vec<R, DP, NW, false, false, true, kBiasGoom, 2>(ctx, args, grid, label)
+                    : launch_vec<R, DP, NW, false, false, true, kBiasNone, 2>(ctx, args, grid, label);
+    }
+    if (bias && args.io_shift) return launch_vec<R, DP, NW, false, false, false, kBiasShifted, PD>(ctx, args, grid, label);
+    if (args.n == DP && args.d == DP)
+        return bias ? launch_vec<R, DP, NW, false, true, false, kBiasGoom, PD>(ctx, args, grid, label)
+                    : launch_vec<R, DP, NW, false, true, false, kBiasNone, PD>(ctx, args, grid, label);
+    return bias ? launch_vec<R, DP, NW, false, false, false, kBiasGoom, PD>(ctx, args, grid, label)
+                : launch_vec<R, DP, NW, false, false, false, kBiasNone, PD>(ctx, args, grid, label);
 }
 
 template <typename R, int DP, int NW, int PD> int factored(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
 {
-    if (args.left_same) return launch_vec<R, R, DP, NW, true, false, true, 2>(ctx, args, grid, label);
-    return launch_vec<R, R, DP, NW, true, false, false, PD>(ctx, args, grid, label);
+    if (args.left_same) return launch_vec<R, DP, NW, true, false, true, kBiasFact, 2>(ctx, args, grid, label);
+    return args.bias_mode == 2 ? launch_vec<R, DP, NW, true, false, false, kBiasFact, PD>(ctx, args, grid, label)
+                               : launch_vec<R, DP, NW, true, false, false, kBiasNone, PD>(ctx, args, grid, label);
 }
 
 } // namespace
@@ -404,14 +422,14 @@ int dispatch_vec(goom_ctx *ctx, const ChainArgs &args, int dp, int f64, int left
         case 16: return f64 ? factored<double, 16, 1, 4>(ctx, args, grid, label) : factored<float, 16, 1, 4>(ctx, args, grid, label);
         case 32: return f64 ? factored<double, 32, 2, 4>(ctx, args, grid, label) : factored<float, 32, 1, 4>(ctx, args, grid, label);
         case 64: return f64 ? factored<double, 64, 8, 4>(ctx, args, grid, label) : factored<float, 64, 4, 4>(ctx, args, grid, label);
-        default: return f64 ? factored<double, 128, 8, 2>(ctx, args, grid, label) : factored<float, 128, 8, 2>(ctx, args, grid, label);
+        default: return f64 ? factored<double, 128, 8, 1>(ctx, args, grid, label) : factored<float, 128, 8, 1>(ctx, args, grid, label);
         }
     }
     switch (dp) {
-    case 16: return f64 ? goom_factors<double, 16, 1, 2>(ctx, args, grid, label) : goom_factors<float, 16, 1, 2>(ctx, args, grid, label);
-    case 32: return f64 ? goom_factors<double, 32, 2, 2>(ctx, args, grid, label) : goom_factors<float, 32, 1, 2>(ctx, args, grid, label);
-    case 64: return f64 ? goom_factors<double, 64, 4, 2>(ctx, args, grid, label) : goom_factors<float, 64, 2, 2>(ctx, args, grid, label);
-    default: return f64 ? goom_factors<double, 128, 8, 1>(ctx, args, grid, label) : goom_factors<float, 128, 8, 2>(ctx, args, grid, label);
+    case 16: return f64 ? goom_factors<double, 16, 1, 2>(ctx, args, grid, label) : goom_factors<float, 16, 1, 4>(ctx, args, grid, label);
+    case 32: return f64 ? goom_factors<double, 32, 4, 2>(ctx, args, grid, label) : goom_factors<float, 32, 2, 4>(ctx, args, grid, label);
+    case 64: return f64 ? goom_factors<double, 64, 8, 2>(ctx, args, grid, label) : goom_factors<float, 64, 4, 4>(ctx, args, grid, label);
+    default: return f64 ? goom_factors<double, 128, 8, 1>(ctx, args, grid, label) : goom_factors<float, 128, 8, 1>(ctx, args, grid, label);
     }
 }
 

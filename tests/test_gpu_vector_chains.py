@@ -99,3 +99,39 @@ def test_magnitudes_far_apart(G, oracle, d, ctype):  # noqa: F811
         bad[0, 7, 0, 0] = np.nan
         got = host(G.affine_scan(dev(bad), dev(bz), dev(h0), chunk_len=chunk))
         assert np.isnan(got[0, 7].real).any() and np.isfinite(got[1, :15].real).all() and np.isfinite(got[0, :7].real).all()
+
+
+# (the method of test_affine_scan_backward: the oracle on the device's forward states, entries that half-unit perturbations move left out)
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("d", SIZES)
+def test_recurrence_adjoint_sizes(G, oracle, d, ctype):  # noqa: F811
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    for T, batch, chunk, with_h0 in ((1, 3, 0, True), (2, 1, 1, True), (5, 2, 2, False), (61, 2, 0, True), (61, 2, 7, False), (40, 1, 40, True)):
+        Az, bz, h0 = inputs(oracle, 360 + d, batch, T, d, ctype, False)
+        h0 = h0 if with_h0 else None
+        Gh = si.normal_f32(si.BASE_SEED + 361, 10, batch * T * d).reshape(batch, T, d).astype(comp)
+        Gh[:, T // 4] = 0.0
+        say(f"recurrence adjoint T={T} d={d} batch={batch} chunk={chunk} {np.dtype(ctype).name} h0={with_h0}")
+        put = lambda z: None if z is None else dev(z)
+        Hd = G.affine_scan(dev(Az), dev(bz), put(h0), chunk_len=chunk)
+        H = host(Hd)
+        got = [None if v is None else host(v).astype(np.float64) for v in G.affine_scan_backward(dev(Az), dev(bz), Hd, dev(Gh), put(h0), chunk_len=chunk)]
+        want = oracle.affine_scan_backward(Az, bz, Gh, h0=h0, h=H)[:3]
+        rel, tiny = (1e-3 if comp == np.float32 else 1e-9), 2 * float(np.finfo(comp).tiny)
+        eta = 2.0 ** -24 if comp == np.float32 else 2.0 ** -53
+        rng = np.random.default_rng(5)
+        sens = [0.0 if w is None else np.zeros_like(w) for w in want]
+        for _ in range(PROBES):
+            pert = lambda z: None if z is None else (z.astype(np.complex128) + eta * rng.standard_normal(z.shape) * np.where(np.isfinite(z.real), 1.0, 0.0))
+            probe = oracle.affine_scan_backward(pert(Az), pert(bz), Gh, h0=pert(h0), h=pert(H))[:3]
+            sens = [s if w is None else np.maximum(s, np.abs(p - w)) for s, p, w in zip(sens, probe, want)]
+        for name, g, w, s in zip(("A", "bias", "h0"), got, want, sens):
+            if w is None or g is None:
+                continue
+            axes = (-1, -2) if name == "A" else -1
+            tol = rel * np.abs(w) + 1e-3 * rel * np.abs(w).max(axis=axes, keepdims=True) + tiny
+            well = s <= tol / 16
+            assert well.mean() > 0.8, (name, well.mean())
+            assert np.all(np.abs(g - w)[well] <= tol[well]), (name, (np.abs(g - w) / tol)[well].max())
+        if not with_h0:
+            assert np.all(got[0][:, 0] == 0)

@@ -676,37 +676,6 @@ template <int DP, int NW, bool PRECISE, bool ADJ = false> int launch_chunk_f64(g
     return goom::check_hip(ctx, hipGetLastError(), "launch affine_chunk_f64_kernel");
 }
 
-// Time-invariant recurrence: every chunk's total is [A^L | b*_c].  A^L has been written to the first
-// chunk's slot of each batch item; this copies it to the other chunks and clears the padding columns
-// (column d, the bias, is written by the walk kernel).
-template <typename R> __global__ __launch_bounds__(256) void replicate_power_kernel(unsigned char *totals, long long stride, int fact_cols, int dp, int d,
-                                                              long long chunks, long long chunks_per_item)
-{
-    const long long item = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
-    const unsigned char *src = totals + (item * chunks_per_item) * stride;
-    unsigned char *dst = totals + (item * chunks_per_item + chunk) * stride;
-    const R *sm = reinterpret_cast<const R *>(src);
-    R *dm = reinterpret_cast<R *>(dst);
-    const size_t mant = (size_t)dp * fact_cols * sizeof(R);
-    const double *se = reinterpret_cast<const double *>(src + mant);
-    double *de = reinterpret_cast<double *>(dst + mant);
-    for (int e = threadIdx.x; e < dp * fact_cols; e += 256) {
-        const int col = e % fact_cols;
-        if (col < d) {
-            if (chunk != 0) dm[e] = sm[e];
-        } else if (col > d) {
-            dm[e] = (R)0;
-        }
-    }
-    for (int col = threadIdx.x; col < fact_cols; col += 256) {
-        if (col < d) {
-            if (chunk != 0) de[col] = se[col];
-        } else if (col > d) {
-            de[col] = 0.0;
-        }
-    }
-}
-
 template <int DP, bool TI, bool ADJ = false, bool IOS = false> int launch_walk(goom_ctx *ctx, const ChainArgs &args, long long nchains, const char *label)
 {
     const long long grid = (nchains + kWalkWaves - 1) / kWalkWaves;
@@ -778,21 +747,6 @@ int dispatch_affine_chunk_f64(goom_ctx *ctx, const ChainArgs &args, int dp, long
     if (args.left_step_stride == 0) // one matrix at every step
         return dp == 16 ? launch_chunk_f64<16, 1, true>(ctx, args, grid, label) : launch_chunk_f64<32, 2, true>(ctx, args, grid, label);
     return dp == 16 ? launch_chunk_f64<16, 1, false>(ctx, args, grid, label) : launch_chunk_f64<32, 2, false>(ctx, args, grid, label);
-}
-
-int launch_replicate_power(goom_ctx *ctx, void *totals, long long stride, int fact_cols, int dp, int d, long long batch,
-                           long long chunks, long long chunks_per_item, bool f64)
-{
-    const long long grid = batch * chunks;
-    if (grid <= 0) return GOOM_OK;
-    if (grid > 0x7fffffffLL) return goom::fail(ctx, GOOM_EUNSUPPORTED, "too many chunks for one launch");
-    if (f64)
-        hipLaunchKernelGGL(replicate_power_kernel<double>, dim3((unsigned)grid), dim3(256), 0, ctx->stream, static_cast<unsigned char *>(totals),
-                           stride, fact_cols, dp, d, chunks, chunks_per_item);
-    else
-        hipLaunchKernelGGL(replicate_power_kernel<float>, dim3((unsigned)grid), dim3(256), 0, ctx->stream, static_cast<unsigned char *>(totals),
-                           stride, fact_cols, dp, d, chunks, chunks_per_item);
-    return goom::check_hip(ctx, hipGetLastError(), "launch replicate_power_kernel");
 }
 
 } // namespace goom_chain

@@ -254,6 +254,7 @@ struct CarryState {
     long long init_stride;
     bool bias;             // chunk products are augmented [A | b]: carry a vector, add b
     void *final_goom;      // reduction: the last prefix as GOOMs, [batch, d, m]
+    bool same;             // (bias) the chunk products share the first one's matrix, each has its own vector
 };
 
 // Phase 2: prefixes of the chunk products.  On return (for a scan) `carries` holds the
@@ -287,6 +288,7 @@ static int carry_phase(goom_ctx *ctx, const ScanPlan &p, int dtype, int d, long 
         l.init_stride = cs.init_stride;
         l.bias_mode = cs.bias ? 2 : 0;
         l.bias_col = 0;
+        l.left_same = cs.same ? 1 : 0;
         if (cs.final_goom) {
             l.out_goom = cs.final_goom;
             l.out_goom_last_only = 1;
@@ -432,6 +434,7 @@ static int run_scan(goom_ctx *ctx, const void *M, const void *init, void *P, lon
         cs.init = init;
         cs.init_stride = (long long)d * m * cb;
         cs.bias = false;
+        cs.same = false;
         cs.final_goom = final_only ? P : nullptr;
         if (int s = carry_phase(ctx, p, dtype, d, batch, totals, carries, gtot, gcar, cs, "scan_phase2_carries")) return s;
         if (final_only) return GOOM_OK;
@@ -910,10 +913,23 @@ static bool affine_walk_whole(int d, long long batch, int dtype, const goom_scan
     return batch >= (d <= 16 ? 384 : d <= 32 ? 96 : 48);
 }
 
+// One matrix for all steps: chunks of a power of two (their product is a few squarings).  A chunk is walked twice, its carry once, each
+// about a step's time, so 2 L + T / L is least near L = sqrt(T / 2); longer where that makes more chains than the chip holds at once
+// (the walks' time is then that of all their steps, whatever L), and never more chunks than the scan's own plan has room for.
+static long long one_matrix_chunk(long long T, int d, long long batch, int dtype)
+{
+    const ScanPlan p = plan_scan(T, d, d + 1, 1, batch, dtype, 0, false);
+    long long L = 8;
+    while (2 * L * L < T || (L < T && batch * (T / L) > 4096)) L *= 2;
+    while (L < p.L) L *= 2;
+    return L < T ? L : T;
+}
+
 static AffinePlan plan_affine(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts)
 {
     AffinePlan ap;
-    const long long req = affine_walk_whole(d, batch, dtype, opts) ? T : opts ? opts->chunk_len : 0;
+    const bool one_matrix = opts && opts->chunk_len == 0 && (opts->flags & GOOM_AFFINE_TIME_INVARIANT);
+    const long long req = affine_walk_whole(d, batch, dtype, opts) ? T : one_matrix ? one_matrix_chunk(T, d, batch, dtype) : opts ? opts->chunk_len : 0;
     ap.p = plan_scan(T, d, d + 1, 1, batch, dtype, req, false);
     ap.f64 = dtype == GOOM_C64 && (d == 16 || d == 32) && ap.p.dp == d && ap.p.C > 1;
     ap.h0_bytes = 0;
@@ -978,7 +994,7 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
     if (!aligned(bias, 16) || (h0 && !aligned(h0, 16))) return fail(ctx, GOOM_EINVAL, "complex data must be 16-byte aligned");
     if (logscale && !aligned(logscale, comp_bytes(dtype))) return fail(ctx, GOOM_EINVAL, "misaligned data pointer");
     const AffinePlan ap = plan_affine(T, d, batch, dtype, opts);
-    const ScanPlan &p = ap.p;
+    ScanPlan p = ap.p;
     const size_t need = want_scaled ? align_up(ap.total(), 256) + (affine_scaled_needs_no_states(p, d, dtype) ? 0 : affine_states_bytes(T, d, batch, dtype)) : ap.total();
     if (int s = check_workspace(ctx, ws, ws_bytes, need)) return s;
     if (int s = need_ctx(ctx)) return s;
@@ -1025,65 +1041,21 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
     unsigned char *carries = totals + p.tot_bytes;
     unsigned char *gtot = carries + p.car_bytes;
     unsigned char *gcar = gtot + p.gtot_bytes;
-    if (ti && dtype == GOOM_C64 && (d == 16 || d == 32 || d == 64)) {
-        // phase 1, time-invariant: every chunk's total is [A^L | b*_c].  A^L once per batch item (a chain
-        // of L equal factors), copied to all chunks; b*_c by a matrix-vector walk of the chunk from zero.
-        ChainLaunch l = base;
-        l.bias_mode = 0;
-        l.bias = nullptr;
-        l.io_shift = nullptr;
-        l.m = d;
-        l.steps = p.L;
-        l.chunk_len = p.L;
-        l.chunks_launched = 1;
-        l.init_mode = 0;
-        l.out_fact_final = totals;
-        l.final_common_exponent = 1;
-        l.fact_stride = (long long)p.tot.stride * p.C;
-        l.fact_cols = p.tot.cols_padded;
-        l.label = "affine_phase1_matrix_power";
-        if (f64) { // the double-state chunk kernel with no bias: [A^L | 0]
-            l.acc_f64 = 1;
-            l.m = d + 1;
-            l.bias_col = d;
-        }
-        // A^L = (A^L1)^L2 shortens the chain of dependent products from L to L1 + L2 (one wave-sized chain per batch item: its
-        // length is the whole cost).  The inner power goes to the second chunk's slot, which is overwritten afterwards.
-        const long long L1 = (p.L >= 64 && p.L % 16 == 0) ? (p.L >= 1024 && p.L % 32 == 0 ? 32 : 16) : 0;
-        if (L1) {
-            l.steps = L1;
-            l.chunk_len = L1;
-            l.out_fact_final = totals + p.tot.stride;
-        }
-        if (int s = launch_chain(ctx, l)) return s;
-        if (L1) { // the outer power: L2 equal factored factors, as the carry phase multiplies chunk products
-            ChainLaunch o;
-            std::memset(&o, 0, sizeof o);
-            o.dp = p.dp;
-            o.dtype = f64 ? GOOM_C128 : dtype;
-            o.n = d;
-            o.d = d;
-            o.m = f64 ? d + 1 : d; // (the double chunk kernel wrote a zero bias column, the float one none)
-            o.batch = batch;
-            o.left_fact = 1;
-            o.left_fact_cols = p.tot.cols_padded;
-            o.left = totals + p.tot.stride;
-            o.left_batch_stride = (long long)p.tot.stride * p.C;
-            o.left_step_stride = 0; // the same factor at every step
-            o.steps = p.L / L1;
-            o.chunk_len = o.steps;
-            o.chunks_launched = 1;
-            o.init_mode = 0;
-            o.bias_mode = f64 ? 2 : 0; // (the factor's bias column is zero, and stays so)
-            o.bias_col = d;
-            o.out_fact_final = totals;
-            o.final_common_exponent = 1;
-            o.fact_stride = (long long)p.tot.stride * p.C;
-            o.fact_cols = p.tot.cols_padded;
-            o.label = "affine_phase1_matrix_power";
-            if (int s = launch_chain(ctx, o)) return s;
-        }
-        if (int s = goom_chain::launch_replicate_power(ctx, totals, (long long)p.tot.stride, p.tot.cols_padded, p.dp, d, batch, p.C - 1, p.C, f64 != 0)) return s;
+    // One matrix for all steps: A^L once, in the first chunk's slot; the other slots hold their chunks' vectors only, and the last one
+    // (no chunk product is needed of the last chunk) the matrix itself, converted for the walks.  A carry then reads a vector and
+    // nothing else, and one chain an item takes them all.
+    if (ti) p.S = p.G = 0;
+    const unsigned char *prepared = ti ? totals + (p.C - 1) * p.tot.stride : nullptr;
+    auto with_prepared = [&](ChainLaunch &l) {
+        l.left_prepared = prepared;
+        l.prepared_stride = (long long)p.C * p.tot.stride;
+        l.prepared_cols = p.tot.cols_padded;
+        l.prepared_f64 = f64 || dtype == GOOM_C128;
+    };
+    if (ti) {
+        if (int s = goom_chain::launch_matrix_power(ctx, A, d, batch, dtype, f64, p.dp, p.L, totals, totals + (p.C - 1) * p.tot.stride,
+                                                    (long long)p.C * p.tot.stride, p.tot.cols_padded))
+            return s;
         ChainLaunch w = base;
         w.m = 1;
         w.bias_col = d;
@@ -1094,6 +1066,7 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         w.fact_stride = (long long)p.tot.stride;
         w.fact_cols = p.tot.cols_padded;
         w.fact_f64 = f64;
+        with_prepared(w);
         w.label = "affine_phase1_chunk_vectors";
         if (int s = launch_chain(ctx, w)) return s;
     } else if (!f64 && !(dtype == GOOM_C64 && d == 64)) {
@@ -1148,6 +1121,7 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         cs.init = h0;
         cs.init_stride = (long long)d * cb;
         cs.bias = true;
+        cs.same = ti;
         cs.final_goom = nullptr;
         if (f64 && h0) { // the double carry kernels read the initial state with double components
             void *h0w = static_cast<unsigned char *>(ws) + align_up(p.total(), 256);
@@ -1174,6 +1148,7 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         l.out_scaled = want_scaled ? scaled : nullptr;
         l.out_logscale = want_scaled ? logscale : nullptr;
         l.fact_f64 = f64;
+        if (ti) with_prepared(l);
         l.label = "affine_phase3_outputs";
         return launch_chain(ctx, l);
     }

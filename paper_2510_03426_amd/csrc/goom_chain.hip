@@ -77,6 +77,10 @@ int launch_chain(goom_ctx *ctx, const ChainLaunch &l)
     a.acc_f64 = l.acc_f64;
     a.left_shift = l.left_shift;
     a.io_shift = l.io_shift;
+    a.left_prepared = static_cast<const unsigned char *>(l.left_prepared);
+    a.prepared_stride = l.prepared_stride;
+    a.prepared_cols = l.prepared_cols;
+    a.prepared_f64 = l.prepared_f64;
     a.left_same = l.left_same;
     if (l.io_shift && !(!l.left_fact && !l.left_real && !l.io_c64 && l.bias_mode == 1 && !l.left_shift && !l.out_scaled && !l.acc_f64))
         return fail(ctx, GOOM_EUNSUPPORTED, "rescaled bias and states: GOOM factors with GOOM bias vectors only");
@@ -86,11 +90,13 @@ int launch_chain(goom_ctx *ctx, const ChainLaunch &l)
         return fail(ctx, GOOM_EUNSUPPORTED, "double factored matrices beside float GOOMs: recurrence kernels only");
     if ((a.out_scaled && (l.m != 1 || l.left_fact)) || (l.left_same && (l.m != 1 || !l.left_fact || l.bias_mode != 2)))
         return fail(ctx, GOOM_EUNSUPPORTED, "scaled outputs and a shared factored matrix: vector chains only");
+    if (l.left_prepared && (l.m != 1 || l.left_fact || l.left_step_stride != 0 || l.steps < 2))
+        return fail(ctx, GOOM_EUNSUPPORTED, "a converted factor: vector chains over one matrix only");
     const long long grid = l.batch * l.chunks_launched;
     // One state column: the matrix-vector kernels (a tile product would use one column of sixteen; 16 x 63 carries of d = 64
     // take 1018 us in the general chain kernel).  Float chains of d = 16, 32, 64 over GOOMs have a walk of their own below.
     if (l.m == 1 && !l.left_shift && !l.left_real && !l.acc_f64 && !l.io_c64 &&
-        !(l.dtype == GOOM_C64 && !l.left_fact && goom_chain::affine_walk_applies(a, dp)))
+        !(l.dtype == GOOM_C64 && !l.left_fact && !l.left_prepared && goom_chain::affine_walk_applies(a, dp)))
         return goom_chain::dispatch_vec(ctx, a, dp, l.dtype == GOOM_C128, l.left_fact, grid, l.label);
     if (l.left_real && (l.dtype != GOOM_C64 || l.left_fact))
         return fail(ctx, GOOM_EUNSUPPORTED, "real left factors are read by the hot float kernel only");

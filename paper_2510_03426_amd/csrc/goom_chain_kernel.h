@@ -70,6 +70,11 @@ struct ChainArgs {
     // is then bias[s] e^(-io_shift[s]) and the state written for step s is h_s e^(+io_shift[s]): values far from 1 pass
     // through GOOM arrays of float components with log-magnitudes of ordinary size
     const float *io_shift;
+    // vector chains with one GOOM factor for all steps: NULL, or per batch item the factor converted beforehand (mantissas [DP][prepared_cols],
+    // float or double, then one double per row: its power of two)
+    const unsigned char *left_prepared;
+    long long prepared_stride;
+    int prepared_cols, prepared_f64;
     int left_same; // factored left factors, vector chains only: every step's matrix is the first one's, its bias column its own
 };
 

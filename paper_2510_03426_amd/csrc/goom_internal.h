@@ -99,6 +99,9 @@ struct ChainLaunch {
     int acc_f64;          // chunk products of the recurrence with the running product in double (float GOOM factors)
     const float *left_shift; // NULL, or [batch, steps]: factors read transposed in reverse order, log-magnitudes shifted (see ChainArgs)
     const float *io_shift;   // NULL, or [batch, steps]: bias and stored states rescaled by e^(-+io_shift[s]) (see ChainArgs)
+    const void *left_prepared; // vector chains over one GOOM factor: NULL, or the factor converted beforehand (see ChainArgs)
+    long long prepared_stride;
+    int prepared_cols, prepared_f64;
     int left_same;        // factored left factors, m = 1: every step's matrix is the first one's, its bias column its own
     const char *label;    // phase name for profiling records
 };
@@ -200,14 +203,15 @@ int launch_scaled_exp(goom_ctx *ctx, const void *z, void *scaled, void *logscale
 } // namespace goom
 
 namespace goom_chain {
-// time-invariant recurrence: copy A^L from the first chunk's total of every batch item to the others
-int launch_replicate_power(goom_ctx *ctx, void *totals, long long stride, int fact_cols, int dp, int d, long long batch,
-                           long long chunks, long long chunks_per_item, bool f64);
 // recurrence with bias, float components, d = 32: every sequence walked start to end by one workgroup (goom_affine_seq.hip);
 // H, scaled, logscale: any of the outputs may be NULL; adjoint_shift: NULL, or [batch, T] floats: the factor of step s is then the
 // transpose of matrix T - s (any for s = 0) with adjoint_shift[s] added to its log-magnitudes
 int launch_affine_seq(goom_ctx *ctx, const void *A, const void *bias, const void *h0, void *H, void *scaled, void *logscale, long long T, long long batch,
                       const float *adjoint_shift);
+// A^exponent of one matrix per batch item, factored (component double if fact_f64 or GOOM_C128, else float; consecutive items `stride`
+// bytes apart), and, if prepared is given, the converted matrix for the vector chains (goom_power.hip)
+int launch_matrix_power(goom_ctx *ctx, const void *A, int d, long long batch, int dtype, int fact_f64, int dp, long long exponent, void *power, void *prepared,
+                        long long stride, int fact_cols);
 // adjoint of the recurrence and its gradients, every size and type (goom_vec_adjoint.hip)
 size_t adjoint_vec_stride(int dp, int dtype);
 int launch_affine_adjoint(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *G, void *gA, void *gb, void *gh0,

@@ -154,7 +154,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
 #pragma unroll
         for (int k = 0; k < K; ++k) u = raw_max(u, (V)z[k][0]);
         u = max16(u);
-        return u > (V)kNone ? Comp<V>::ceil_(u * (V)kLog2e) : (V)0; // (+inf stays: its row comes out as NaN)
+        return u > (V)kNone ? Comp<V>::ceil_(u * (V)kLog2e) : (V)kNone; // (+inf stays: its row comes out as NaN; a zero row has none)
     };
     if constexpr (SAME) {
 #pragma unroll
@@ -163,6 +163,16 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
 #pragma unroll
                 for (int k = 0; k < K; ++k) same_s[q][k] = (V)load_fact(0, q, k);
                 same_n[q] = (V)0;
+            } else if (a.left_prepared) { // converted once for all chunks (goom_power.hip)
+                const unsigned char *pp = a.left_prepared + item * a.prepared_stride;
+                const bool f64 = sizeof(R) == 8 || a.prepared_f64;
+                const int i = row0 + 4 * q < n_rows ? row0 + 4 * q : n_rows - 1;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const size_t at = (size_t)i * a.prepared_cols + (c + 16 * k < d ? c + 16 * k : d - 1);
+                    same_s[q][k] = f64 ? (V) reinterpret_cast<const double *>(pp)[at] : (V) reinterpret_cast<const float *>(pp)[at];
+                }
+                same_n[q] = (V) reinterpret_cast<const double *>(pp + (size_t)DP * a.prepared_cols * (f64 ? 8 : 4))[i];
             } else {
                 IO2 z[K];
 #pragma unroll
@@ -191,6 +201,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
     // ---- initial vector: this lane's columns c + 16 k, mantissas times 2^eh
     V hm[K];
     double eh = 0.0;
+    bool zero = a.init_mode == 3; // every entry of the vector is zero
 #pragma unroll
     for (int k = 0; k < K; ++k) hm[k] = (V)0;
     if (a.init_mode == 0) {
@@ -214,7 +225,8 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
             }
         }
         eh = *reinterpret_cast<const double *>(ip + (size_t)DP * a.fact_cols * (f64 ? 8 : 4));
-        if (__builtin_amdgcn_ballot_w64(nz) == 0) eh = 0.0; // a zero vector has no exponent
+        zero = __builtin_amdgcn_ballot_w64(nz) == 0;
+        if (zero) eh = 0.0; // a zero vector has no exponent
     } else if (a.init_mode == 2) {
         const IO2 *gp = reinterpret_cast<const IO2 *>(a.init + item * a.init_stride);
         double u = -__builtin_huge_val();
@@ -227,7 +239,8 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
             u = raw_max(u, (double)z[k][0]);
         }
         u = max16(u);
-        eh = u > -1.0e300 ? __builtin_ceil(u * kLog2e) : 0.0;
+        zero = !(u > -1.0e300);
+        eh = zero ? 0.0 : __builtin_ceil(u * kLog2e);
 #pragma unroll
         for (int k = 0; k < K; ++k) hm[k] = (V)scaled_entry((double)z[k][0], (double)z[k][1], eh);
     }
@@ -301,6 +314,12 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
                 be = e + (V)(r.bias_e - base);
             }
         }
+        // A bias below the last place of anything that the row's terms could leave does not outlive their exact cancellation (the
+        // entry is zero then, and passes no gradient, as where sum and bias share an exponent).
+        if (!FACT && !zero && be < n - (V)(sizeof(V) == 4 ? 149 : 1074)) {
+            bm = (V)0;
+            be = (V)kNone;
+        }
         const V pe = part != (V)0 ? Comp<V>::exponent_of(part) + n : (V)kNone;
         const V ex = be > pe ? be : pe;
         V m = Comp<V>::ldexp_(part, (int)Comp<V>::clamp_shift(n - ex)) + Comp<V>::ldexp_(bm, (int)Comp<V>::clamp_shift(be - ex));
@@ -344,6 +363,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         }
         const double en = none ? 0.0 : base + (double)xm;
         eh = live ? en : eh;
+        zero = live ? none : zero;
         if (fact_steps && live) store_fact(fact_steps + (t + 1) * a.fact_stride, 0, sizeof(R) == 8);
         if (scaled && live) {
             // exp(z - c + 2), c the log of the largest magnitude: the mantissa over the largest one, times e^2

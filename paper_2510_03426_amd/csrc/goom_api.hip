@@ -485,9 +485,28 @@ static ResetPlan plan_reset(long long T, int d, long long batch, int dtype, cons
     return p;
 }
 
+// Chunks are as long as the caller's interval of examination (128 steps by default) whatever the chain's length, so a short chain or a
+// small batch makes few of them, and a step of the double chain kernel on one workgroup takes 4 us (d = 20) to 32 us (d = 100).  With
+// fewer chunks than the chip has places for, a chunk is walked in spans of kResetSpan steps: span products, their
+// products as chunk products, and for the states the prefixes at the spans' starts; 16 + 8 dependent steps instead of 128.
+// 1 x 1000 x 100, all states: chunk products and states 3990 + 4920 us before.  (The room for it is optional: behind the workspace proper.)
+constexpr long long kResetSpan = 16;
+static bool reset_in_spans(const ResetPlan &p, long long T, long long batch)
+{
+    const long long places = p.dp >= 128 ? 256 : p.dp >= 64 ? 512 : p.dp >= 32 ? 1024 : 2048;
+    return p.L % kResetSpan == 0 && p.L >= 4 * kResetSpan && T > kResetSpan && batch * p.C < places;
+}
+static size_t reset_spans_bytes(const ResetPlan &p, long long T, long long batch)
+{
+    if (!reset_in_spans(p, T, batch)) return 0;
+    const long long spans = (T + kResetSpan - 1) / kResetSpan;
+    return align_up((size_t)batch * spans * p.tot.stride + (size_t)batch * p.C * (p.L / kResetSpan + 1) * p.car.stride, 256);
+}
+
+// spans: NULL, or reset_spans_bytes(...) bytes, 256-byte aligned
 static int run_reset(goom_ctx *ctx, const void *J, const void *S0, void *states, uint8_t *flags, double *growth,
                      double growth_scale, long long T, int d, long long batch, int dtype, const goom_reset_opts *opts,
-                     void *ws, size_t ws_bytes)
+                     void *ws, size_t ws_bytes, unsigned char *spans = nullptr)
 {
     if (int s = check_common(ctx, dtype)) return s;
     if (!J) return fail(ctx, GOOM_EINVAL, "null data pointer");
@@ -506,6 +525,11 @@ static int run_reset(goom_ctx *ctx, const void *J, const void *S0, void *states,
     unsigned char *totals = static_cast<unsigned char *>(ws);
     unsigned char *carries = totals + p.tot_bytes;
     unsigned char *chunk_flags = carries + p.car_bytes;
+    const size_t span_bytes = reset_spans_bytes(p, T, batch);
+    if (!spans && span_bytes && ws_bytes >= align_up(p.total(), 256) + span_bytes) spans = totals + align_up(p.total(), 256);
+    if (!span_bytes) spans = nullptr;
+    const long long nspans = (T + kResetSpan - 1) / kResetSpan, per_chunk = p.L / kResetSpan;
+    unsigned char *span_carries = spans ? spans + (size_t)batch * nspans * p.tot.stride : nullptr;
 
     ChainLaunch base;
     std::memset(&base, 0, sizeof base);
@@ -530,7 +554,25 @@ static int run_reset(goom_ctx *ctx, const void *J, const void *S0, void *states,
         l.fact_stride = (long long)p.tot.stride;
         l.fact_cols = p.tot.cols_padded;
         l.label = "reset_phase1_chunk_products";
+        if (spans) { // the spans' products ...
+            l.chunk_len = kResetSpan;
+            l.chunks_launched = nspans;
+            l.out_fact_final = spans;
+        }
         if (int s = launch_chain(ctx, l)) return s;
+        if (spans) { // ... and theirs, chunk by chunk
+            l.io_c64 = 0;
+            l.left = spans;
+            l.left_fact = 1;
+            l.left_fact_cols = p.tot.cols_padded;
+            l.left_step_stride = (long long)p.tot.stride;
+            l.left_batch_stride = nspans * (long long)p.tot.stride;
+            l.steps = nspans;
+            l.chunk_len = per_chunk;
+            l.chunks_launched = p.C;
+            l.out_fact_final = totals;
+            if (int s = launch_chain(ctx, l)) return s;
+        }
     }
     ResetLaunch r;
     std::memset(&r, 0, sizeof r);
@@ -567,6 +609,25 @@ static int run_reset(goom_ctx *ctx, const void *J, const void *S0, void *states,
         l.fact_cols = p.car.cols_padded;
         l.out_goom = states;
         l.label = "reset_phase3_states";
+        if (spans) { // the prefix that enters every span, from its chunk's, and every span from there
+            ChainLaunch q = l;
+            q.io_c64 = 0;
+            q.left = spans;
+            q.left_fact = 1;
+            q.left_fact_cols = p.tot.cols_padded;
+            q.left_step_stride = (long long)p.tot.stride;
+            q.left_batch_stride = nspans * (long long)p.tot.stride;
+            q.steps = nspans;
+            q.chunk_len = per_chunk;
+            q.out_goom = nullptr;
+            q.out_fact_steps = span_carries;
+            if (int s = launch_chain(ctx, q)) return s;
+            l.chunk_len = kResetSpan;
+            l.chunks_launched = nspans;
+            l.init = span_carries;
+            l.init_group = per_chunk;
+            l.init_ngroups = p.C;
+        }
         if (int s = launch_chain(ctx, l)) return s;
     }
     if (states || flags) return launch_reset_post(ctx, r);
@@ -1499,7 +1560,7 @@ size_t goom_scan_reset_workspace_bytes(int64_t T, int d, int64_t batch, int dtyp
 {
     if (T <= 0 || d <= 0 || batch <= 0 || d > GOOM_MAX_DIM || (dtype != GOOM_C64 && dtype != GOOM_C128)) return 0;
     const ResetPlan p = plan_reset(T, d, batch, dtype, opts);
-    return p.total();
+    return align_up(p.total(), 256) + reset_spans_bytes(p, T, batch);
 }
 
 int goom_scan_reset(goom_ctx *ctx, const void *J, const void *S0, void *states, uint8_t *reset_flags, double *growth,
@@ -1591,7 +1652,7 @@ size_t goom_lyapunov_spectrum_per_step_workspace_bytes(int64_t T, int d, int64_t
     size_t n = p.total() + lyap_steps_partial_bytes(batch, d);
     if (!caller_has_states) n += align_up((size_t)batch * T * d * d * 2 * comp_bytes(dtype), 256);
     if (!caller_has_step_logs) n += align_up((size_t)batch * T * d * sizeof(double), 256);
-    return n;
+    return align_up(n, 256) + reset_spans_bytes(p, T, batch);
 }
 
 int goom_lyapunov_spectrum_per_step(goom_ctx *ctx, const void *J, const void *S0, void *states, double *step_logs,
@@ -1604,9 +1665,11 @@ int goom_lyapunov_spectrum_per_step(goom_ctx *ctx, const void *J, const void *S0
     if (T <= 0 || batch <= 0 || d <= 0) return fail(ctx, GOOM_EINVAL, "sizes must be positive (T=%lld d=%d batch=%lld)", (long long)T, d, (long long)batch);
     if (d > GOOM_MAX_DIM) return fail(ctx, GOOM_EUNSUPPORTED, "the reset scan supports d <= %d (d=%d)", GOOM_MAX_DIM, d);
     if (step_logs && !aligned(step_logs, 8)) return fail(ctx, GOOM_EINVAL, "step_logs must be 8-byte aligned");
-    const size_t need = goom_lyapunov_spectrum_per_step_workspace_bytes(T, d, batch, dtype, opts, states != nullptr, step_logs != nullptr);
-    if (int s = check_workspace(ctx, workspace, workspace_bytes, need)) return s;
     const ResetPlan p = plan_reset(T, d, batch, dtype, opts);
+    const size_t whole = goom_lyapunov_spectrum_per_step_workspace_bytes(T, d, batch, dtype, opts, states != nullptr, step_logs != nullptr);
+    const size_t span_bytes = reset_spans_bytes(p, T, batch), need = whole - span_bytes; // (the spans' part is optional)
+    if (int s = check_workspace(ctx, workspace, workspace_bytes, need)) return s;
+    unsigned char *spans = span_bytes && workspace_bytes >= whole ? static_cast<unsigned char *>(workspace) + need : nullptr;
     unsigned char *w = static_cast<unsigned char *>(workspace) + p.total();
     double *partial = reinterpret_cast<double *>(w);
     w += lyap_steps_partial_bytes(batch, d);
@@ -1616,7 +1679,7 @@ int goom_lyapunov_spectrum_per_step(goom_ctx *ctx, const void *J, const void *S0
     }
     if (!step_logs) step_logs = reinterpret_cast<double *>(w);
     // group (a): all states, selectively reset
-    if (int s = run_reset(ctx, J, S0, states, nullptr, nullptr, 1.0, T, d, batch, dtype, opts, workspace, p.total())) return s;
+    if (int s = run_reset(ctx, J, S0, states, nullptr, nullptr, 1.0, T, d, batch, dtype, opts, workspace, p.total(), spans)) return s;
     // groups (b)-(d)
     return launch_lyap_steps(ctx, J, S0, states, step_logs, partial, lambda, T, d, batch, dtype, 1.0 / (dt * (double)T));
 }

@@ -135,3 +135,32 @@ def test_recurrence_adjoint_sizes(G, oracle, d, ctype):  # noqa: F811
             assert np.all(np.abs(g - w)[well] <= tol[well]), (name, (np.abs(g - w) / tol)[well].max())
         if not with_h0:
             assert np.all(got[0][:, 0] == 0)
+
+
+# chunks of 128 (and 64) steps in spans of 16: chains that end within a span, within a chunk, and on both
+@pytest.mark.parametrize("T,d,batch,chunk", [(129, 5, 2, 0), (143, 20, 1, 0), (256, 33, 1, 0), (200, 70, 1, 64), (150, 100, 1, 0), (128, 16, 3, 0)])
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+def test_reset_scan_in_spans(G, oracle, T, d, batch, chunk, ctype):  # noqa: F811
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    rng = np.random.default_rng(T + d)
+    J = (np.eye(d) + 0.1 / np.sqrt(d) * rng.standard_normal((batch, T, d, d))).astype(comp)
+    Jz = oracle.to_goom(J)
+    say(f"reset scan in spans T={T} d={d} batch={batch} chunk={chunk} {np.dtype(ctype).name}")
+    states, flags, growth = (host(v) for v in G.scan_reset(dev(Jz), chunk_len=chunk))
+    every = chunk or 128
+    for q in range(batch):  # the recurrence itself in double, factorised where it is examined
+        x, grown = np.eye(d), np.zeros(d)
+        rel = np.exp(Jz[q].real.astype(np.float64)) * np.where(Jz[q].imag > 1.5, -1.0, 1.0)
+        for t in range(T):
+            x = rel[t] @ x
+            if (t + 1) % every == 0:
+                x, r = np.linalg.qr(x)
+                grown += np.log(np.abs(np.diag(r)))
+                x *= np.sign(np.diag(r))
+                assert flags[q, t] == 1
+            got = np.exp(states[q, t].real.astype(np.float64)) * np.where(states[q, t].imag > 1.5, -1.0, 1.0)
+            # (a state's float log-magnitudes are rounded once; the double factorisation is good to cond^2 2^-53 of a column)
+            assert np.abs(got - x).max() <= (2e-6 if comp == np.float32 else 1e-9) * np.abs(x).max(), (q, t)
+        if T % every:
+            grown += np.log(np.abs(np.diag(np.linalg.qr(x)[1])))
+        assert np.abs(growth[q] - grown).max() <= 1e-8 * max(1.0, np.abs(grown).max())

@@ -334,7 +334,7 @@ int goom_scaled_exp(goom_ctx *ctx, const void *z, void *scaled, void *logscale, 
  * H: [batch, T, d].  Scanned as products of the augmented matrices [A | bias; 0 | 1]
  * whose last row is kept implicit.  A batch of 96 sequences or more with a matrix per step,
  * float components, d = 32 and opts->chunk_len == 0 is not scanned: every sequence is walked
- * start to end by one workgroup, every matrix read once (the results are those of a sequential
+ * start to end by one workgroup, every matrix read once, and so are large batches of other sizes (the results are those of a sequential
  * float evaluation; whole-number exponents are kept within +-2^28, i.e. log-magnitudes within
  * +-1.8e8, beyond which a float log-magnitude resolves nothing anyway).
  * workspace: goom_affine_scan_workspace_bytes(...) bytes. */
@@ -352,9 +352,9 @@ size_t goom_affine_scan_workspace_bytes(int64_t T, int d, int64_t batch, int dty
  * (+-) exp(Re h[b, t, i] - c[b, t] + 2) with c[b, t] = max_i Re h[b, t, i], all within
  * [-e^2, e^2].  scaled: [batch, T, d] reals of the component type; logscale: NULL or [batch, T]
  * reals receiving c (-inf for a zero state, whose scaled entries are 0).  Arguments otherwise as
- * for goom_affine_scan.  For GOOM_C64 with d = 16 or 32 and more than one chunk the last phase
- * writes the scaled states directly and no GOOM states touch memory; otherwise they pass through
- * the workspace.  workspace: goom_affine_scan_scaled_workspace_bytes(...) bytes. */
+ * for goom_affine_scan.  The last phase
+ * writes the scaled states directly and no GOOM states touch memory (the workspace query asks for room for
+ * them except for GOOM_C64 with d = 16, 32 or 64 and more than one chunk).  workspace: goom_affine_scan_scaled_workspace_bytes(...) bytes. */
 int goom_affine_scan_scaled(goom_ctx *ctx, const void *A, const void *bias, const void *h0,
                             void *scaled, void *logscale, int64_t T, int d, int64_t batch,
                             int dtype, const goom_scan_opts *opts, void *workspace,
@@ -438,8 +438,8 @@ size_t goom_scan_backward_workspace_bytes(int64_t T, int d, int m, int64_t batch
  * h0).  opts->flags: 0, or GOOM_AFFINE_TIME_INVARIANT for the recurrence with one matrix per batch item (the paper's
  * state-space layer, Section 4.3): A and grad_A are [batch, d, d], grad_A[b, i, j] = A[i, j] sum_t lam_t[i] h_{t-1}[j],
  * summed in double in a fixed order.  workspace: goom_affine_scan_backward_workspace_bytes(...) bytes: a few vectors per
- * step for complex64 with d = 16 or 32 and more than one chunk (the scan reads A transposed itself); otherwise it
- * also holds a transposed copy of A and is a little larger than A. */
+ * step for complex64 with d = 16 or 32 and more than one chunk (the scan reads A transposed itself); otherwise the
+ * query asks for a little more than A takes, of which the chunk products and carries use a part. */
 int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H,
                               const void *grad_H, void *grad_A, void *grad_bias, void *grad_h0, int64_t T, int d,
                               int64_t batch, int dtype, const goom_scan_opts *opts, void *workspace,

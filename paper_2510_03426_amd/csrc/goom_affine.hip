@@ -353,10 +353,8 @@ template <int DP, bool TI, bool ADJ = false, bool IOS = false> __global__ __laun
 // step's B operands if contraction index 16 kt + 4 v + g sits at position 16 kt + 4 g + v of a tile row
 // (Comp<double>::phys); the row exponents and the bias wave's column are stored in the same order.
 // a.bias == NULL: no bias is added (the column stays zero), which gives plain matrix powers and products.
-// PRECISE: every entry of the tile is exponentiated in double and rounded once (for one matrix applied at every
-// step, whose conversion error would otherwise be the same at every step and add up along the chain).
 // ADJ: as in the matrix-vector walk above (the factor of step s is the transpose of matrix steps - s, shifted).
-template <int DP, int NW, bool PRECISE, bool ADJ = false>
+template <int DP, int NW, bool ADJ = false>
 __global__ __launch_bounds__((NW + 1) * 64, 4) void affine_chunk_f64_kernel(ChainArgs a)
 {
     typedef Comp<float> C;
@@ -464,14 +462,9 @@ __global__ __launch_bounds__((NW + 1) * 64, 4) void affine_chunk_f64_kernel(Chai
             const float nsub = zero_row ? __builtin_huge_valf() : n;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float v;
-                if (PRECISE) {
-                    v = zero_row ? 0.0f : (float)CD::exp2_shifted((double)re[e], (double)(n - rj[e]));
-                } else {
-                    float t = __builtin_fmaf(re[e], kHi, rj[e] - nsub);
-                    t = __builtin_fmaf(re[e], kLo, t);
-                    v = __builtin_amdgcn_exp2f(t);
-                }
+                float t = __builtin_fmaf(re[e], kHi, rj[e] - nsub);
+                t = __builtin_fmaf(re[e], kLo, t);
+                const float v = __builtin_amdgcn_exp2f(t);
                 const float kf = __builtin_fmaf(im[e], 0.318309886183790671538f, 12582912.0f);
                 tile[row * LDA + p4 + 4 * e] = __builtin_bit_cast(float, __builtin_bit_cast(int, v) | (__builtin_bit_cast(int, kf) << 31));
             }
@@ -664,14 +657,14 @@ __global__ __launch_bounds__((NW + 1) * 64, 4) void affine_chunk_f64_kernel(Chai
     }
 }
 
-template <int DP, int NW, bool PRECISE, bool ADJ = false> int launch_chunk_f64(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
+template <int DP, int NW, bool ADJ = false> int launch_chunk_f64(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
 {
     constexpr int LDA = DP + 4;
     const size_t lds = 2 * ((size_t)DP * LDA * sizeof(float) + (size_t)DP * sizeof(float)) + 128 + DP * sizeof(double);
     if (grid <= 0) return GOOM_OK;
     if (grid > 0x7fffffffLL) return goom::fail(ctx, GOOM_EUNSUPPORTED, "too many chains for one launch (%lld)", grid);
     goom::prof_begin(ctx, label);
-    hipLaunchKernelGGL((affine_chunk_f64_kernel<DP, NW, PRECISE, ADJ>), dim3((unsigned)grid), dim3((NW + 1) * 64), lds, ctx->stream, args);
+    hipLaunchKernelGGL((affine_chunk_f64_kernel<DP, NW, ADJ>), dim3((unsigned)grid), dim3((NW + 1) * 64), lds, ctx->stream, args);
     goom::prof_end(ctx);
     return goom::check_hip(ctx, hipGetLastError(), "launch affine_chunk_f64_kernel");
 }
@@ -742,11 +735,9 @@ int dispatch_affine_chunk_f64(goom_ctx *ctx, const ChainArgs &args, int dp, long
           args.out_fact_steps == nullptr && args.out_fact_final != nullptr && args.fact_cols == dp + 16))
         return goom::fail(ctx, GOOM_EUNSUPPORTED, "double-state chunk products are built for d = 16 and 32");
     if (args.left_shift) { // the adjoint recurrence: transposed factors in reverse order (a step stride of 0: one matrix, shifted anew every step)
-        return dp == 16 ? launch_chunk_f64<16, 1, false, true>(ctx, args, grid, label) : launch_chunk_f64<32, 2, false, true>(ctx, args, grid, label);
-    }
-    if (args.left_step_stride == 0) // one matrix at every step
         return dp == 16 ? launch_chunk_f64<16, 1, true>(ctx, args, grid, label) : launch_chunk_f64<32, 2, true>(ctx, args, grid, label);
-    return dp == 16 ? launch_chunk_f64<16, 1, false>(ctx, args, grid, label) : launch_chunk_f64<32, 2, false>(ctx, args, grid, label);
+    }
+    return dp == 16 ? launch_chunk_f64<16, 1>(ctx, args, grid, label) : launch_chunk_f64<32, 2>(ctx, args, grid, label);
 }
 
 } // namespace goom_chain

@@ -8,8 +8,13 @@
 //     rows: a lane adds up its rows' entries of each of its columns, the four rows of a pass meet by lane swaps, the waves'
 //     sums in LDS, each on a power of two of its own; after one barrier the lane that owns a row adds the waves' sums and G_t / h_t, and
 //     hands mantissa and exponent to the row's sixteen lanes through LDS words of its wave.
-//   * lam is kept as mantissa and exponent per entry with a double base, so no scaling of h or A comes before: values e^-1000 and
+//   * lam is kept as mantissa and exponent per entry with a double base, so no scaling of h or A comes before: adjoints of e^-1000 and
 //     below are ordinary numbers here.
+//   * Entries of one row, of lam and of h may lie further apart than the component type reaches (diagonal and triangular matrices, states
+//     in units of their own), while lam_i A_ij h_j is an ordinary number.  So the exponents of lam_i, of the row and of h_j meet as whole numbers
+//     before the gradient is formed, and the product takes one power of two a row and a wave only while nothing that is summed lies more
+//     than 2^-40 (2^-320) below it; a wave that finds more gives every term an exponent of its own and every column the largest of them.
+//     Looking for it costs 5 to 10 % of a step (128 x 500 matrices of float d = 64: 1160 -> 1280 us; of double d = 24: 900 -> 1140 us), the rare way twice a step's time.
 //   * The same kernel walks the factored chunk products backwards (FACT): mu <- P_c^T mu + v_c.
 #include "goom_vec.h"
 
@@ -49,6 +54,31 @@ struct AdjointArgs {
     void *gA, *gb, *gh0;                         // gradients (gb, gh0: may be NULL)
 };
 
+// whole powers of two that are added up as integers (three of them stay inside 32 bits); what they are clamped at is far beyond any result
+__device__ inline int whole(float v) { return (int)__builtin_amdgcn_fmed3f(v, -5.0e8f, 5.0e8f); }
+__device__ inline int whole(double v) { return (int)(v > -5.0e8 ? (v < 5.0e8 ? v : 5.0e8) : -5.0e8); }
+
+// Keys of log-magnitudes whose largest belongs to the lowest finite one (if any is negative): the bit pattern of a negative number grows as
+// it falls, and the step added takes -inf, the one above all of them, round to the bottom.  kNoDepth is the key of no entry (a NaN).
+constexpr unsigned kNoDepth = 1u;
+__device__ inline unsigned depth_key(float v) { return __builtin_bit_cast(unsigned, v) + 0x00800000u; }
+__device__ inline unsigned depth_key(double v) { return (unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32) + 0x00100000u; }
+template <typename R> __device__ inline R depth_of(unsigned key);
+template <> __device__ inline float depth_of<float>(unsigned key) { return __builtin_bit_cast(float, key - 0x00800000u); }
+template <> __device__ inline double depth_of<double>(unsigned key) { return __builtin_bit_cast(double, (unsigned long long)(key - 0x00100000u) << 32); }
+
+// A wave-uniform byte offset that the optimiser sees as new in every step: each entry's address stays one scalar base and a 32-bit lane
+// offset.  (Followed from step to step they became a 64-bit pointer in vector registers for every entry: 128 registers at d = 128, and
+// spills whose reloads waited for the gradients' stores; 128 x 200 matrices of float d = 128: 1790 -> 1480 us with all that is below.)
+__device__ inline long long opaque(long long v)
+{
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
+__device__ inline float round_(float v) { return __builtin_rintf(v); }
+__device__ inline double round_(double v) { return __builtin_rint(v); }
+
 // Steps s = 0 .. len - 1 of a chunk take matrix t1 - 1 - s.
 template <typename R, int DP, int NW, bool FACT, bool FULL, bool GRAD, int PD>
 __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
@@ -58,15 +88,23 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
     constexpr int K = DP / 16, RW = DP / NW, Q = RW / 4;
     static_assert(Q >= 1 && Q <= 16 && 4 * Q * NW == DP, "a lane finishes at most one row");
     constexpr bool EARLY = !FACT && DP <= 32;
-    // The largest factors with gradients: the next factor is loaded once this one's registers are done with.  (Held beside them, 82
-    // registers are spilled, and a reload waits for the gradients' stores: 18 us a step.)
+    // The largest factors with gradients: the next factor is loaded once this one's registers are done with.  (Held beside them registers
+    // are spilled, and a reload waits for the gradients' stores: 18 us a step of float d = 128 where 7.4 are taken now.)
     constexpr bool LATE = GRAD && DP == 128;
-    __shared__ V part[2][NW][DP], partn[2][NW], lm[DP], lx[DP];
+    // A term of the product is a row's mantissa, an entry on its row's power of two and a wave's sum on the largest wave's: three factors
+    // that may each lie this far below 1 before the type's smallest normal number is in sight.
+    constexpr V kSpread = sizeof(V) == 4 ? (V)40 : (V)320;
+    typedef V V2 __attribute__((ext_vector_type(2)));
+    __shared__ __align__(16) V2 part[2][NW][DP]; // the waves' sums of every column: mantissa and exponent
+    __shared__ V partn[2][NW], lm[DP], lx[DP];
+    constexpr V kHighest = sizeof(V) == 4 ? (V)120 : (V)1000; // largest power of two of lam_i times a row's times h's that is formed as a number
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, c = lane & 15, d = a.d;
-    const long long item = (long long)blockIdx.x / a.chunks, chunk = a.first_chunk + (long long)blockIdx.x % a.chunks;
+    // (in scalar registers: the grid has fewer than 2^31 workgroups)
+    const int item_of = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)a.chunks));
+    const long long item = item_of, chunk = a.first_chunk + (int)(blockIdx.x - (unsigned)item_of * (unsigned)a.chunks);
     const long long t0 = chunk * a.chunk_len;
     long long len = a.T - t0;
     if (len > a.chunk_len) len = a.chunk_len;
@@ -92,12 +130,15 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
 #pragma unroll
         for (int k = 0; k < K; ++k) col_at[k] = (unsigned)(c + 16 * k < d ? c + 16 * k : d - 1) * kEntry;
     }
-    auto offset_of = [&](int q, int k) {
-        if constexpr (FULL)
-            return row_at[0] + col_at[0] + (unsigned)(4 * q) * (unsigned)(DP * kEntry) + (unsigned)(16 * k) * kEntry;
-        else
-            return row_at[q] + col_at[k];
+    // entry (q, k) of the matrix at `base`, whose entries take kEntry / SHRINK bytes
+    auto place = [&](auto *base, int q, int k, auto shrink) {
+        constexpr unsigned kShrink = decltype(shrink)::value;
+        unsigned at = FULL ? row_at[0] + col_at[0] : row_at[FULL ? 0 : q] + col_at[FULL ? 0 : k];
+        asm volatile("" : "+v"(at)); // (see opaque)
+        return base + (FULL ? (4 * q * DP + 16 * k) * (int)(kEntry / kShrink) : 0) + at / kShrink;
     };
+    typedef std::integral_constant<unsigned, 1> whole_size;
+    typedef std::integral_constant<unsigned, 2> half_size; // (a real's place is half a GOOM's)
     auto col_in = [&](int k) { return FULL || c + 16 * k < d ? c + 16 * k : d - 1; };
 
     struct Matrix {
@@ -114,15 +155,15 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
     };
     auto load = [&](long long s, Matrix &m) {
         const long long t = tlast - (s < len ? s : len - 1);
-        const unsigned char *src = left0 + t * a.left_step_stride;
+        const unsigned char *src = left0 + opaque(t * a.left_step_stride);
 #pragma unroll
         for (int q = 0; q < Q; ++q)
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if constexpr (FACT)
-                    m.w[q][k] = *reinterpret_cast<const R *>(src + offset_of(q, k));
+                    m.w[q][k] = *reinterpret_cast<const R *>(place(src, q, k, whole_size()));
                 else
-                    m.z[q][k] = *reinterpret_cast<const R2 *>(src + offset_of(q, k));
+                    m.z[q][k] = *reinterpret_cast<const R2 *>(place(src, q, k, whole_size()));
             }
     };
     const R2 *H = reinterpret_cast<const R2 *>(a.H) + (size_t)item * a.T * d;
@@ -154,7 +195,9 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
     };
 
     V sv[Q][K], sn[Q]; // the factor's entries on their rows' powers of two
+    bool far = false;  // some entry of the wave's rows, not zero, lies more than kSpread below its row's
     auto convert = [&](const Matrix &m) {
+        bool small = false;
         if constexpr (!FACT) {
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
@@ -165,6 +208,13 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
                 sn[q] = u > (V)kNone ? Comp<V>::ceil_(u * (V)kLog2e) : (V)0;
 #pragma unroll
                 for (int k = 0; k < K; ++k) sv[q][k] = scaled_entry((V)m.z[q][k][0], (V)m.z[q][k][1], sn[q]);
+                unsigned key = kNoDepth;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const unsigned o = depth_key(m.z[q][k][0]);
+                    key = o > key ? o : key;
+                }
+                small = small || depth_of<R>(key) < u - kSpread * (V)kLn2;
                 if (K >= 8) __builtin_amdgcn_sched_barrier(0);
             }
         } else {
@@ -172,19 +222,23 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
             for (int q = 0; q < Q; ++q) {
                 sn[q] = (V)0;
 #pragma unroll
-                for (int k = 0; k < K; ++k) sv[q][k] = (V)m.w[q][k];
+                for (int k = 0; k < K; ++k) {
+                    sv[q][k] = (V)m.w[q][k];
+                    if constexpr (sizeof(R) == 8) small = small || (Comp<V>::abs_(sv[q][k]) < (V)4.681778573893022e-97 && sv[q][k] != (V)0); // 2^-320
+                }
             }
         }
+        far = __builtin_amdgcn_ballot_w64(small) != 0;
     };
 
     double base = 0.0;    // the vector's entries: m 2^(x + base)
     V om = (V)0, ox = (V)kNone; // the owner's entry
     V vm[Q], vx[Q];       // the lane's rows' entries
-    // own entry y 2^base plus (bm 2^be) 2^base, and its way to the row's lanes
-    auto take = [&](V y, V bm, V be) {
-        const V pe = y != (V)0 ? Comp<V>::exponent_of(y) : (V)kNone;
+    // own entry (y 2^yx) 2^base plus (bm 2^be) 2^base, and its way to the row's lanes
+    auto take = [&](V y, V yx, V bm, V be) {
+        const V pe = y != (V)0 ? Comp<V>::exponent_of(y) + yx : (V)kNone;
         ox = be > pe ? be : pe;
-        om = Comp<V>::ldexp_(y, (int)Comp<V>::clamp_shift(-ox)) + Comp<V>::ldexp_(bm, (int)Comp<V>::clamp_shift(be - ox));
+        om = Comp<V>::ldexp_(y, (int)Comp<V>::clamp_shift(yx - ox)) + Comp<V>::ldexp_(bm, (int)Comp<V>::clamp_shift(be - ox));
         if (!row_ok) {
             om = (V)0;
             ox = (V)kNone;
@@ -205,11 +259,11 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
-    // G / h on the current base; an entry that is exactly zero passes no gradient
+    // G / h on the current base; an entry that is exactly zero passes no gradient, and an infinite one divides it away
     auto source = [&](R gv, R2 h, V &bm, V &be) {
         bm = (V)0;
         be = (V)kNone;
-        if (gv != (R)0 && !((double)h[0] < -1.0e300)) {
+        if (gv != (R)0 && !((double)h[0] < -1.0e300) && h[0] != -Comp<R>::neg_inf()) {
             const V e = Comp<V>::exponent_of((V)gv);
             const double x = -__builtin_fma((double)h[0], kLog2e, base);
             const double xe = __builtin_rint(x);
@@ -251,7 +305,7 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
             if (!a.init) base = 0.0;
             source(gv, h, bm, be);
         }
-        take(y, bm, be);
+        take(y, (V)0, bm, be);
     }
     // FACT: vectors [batch][chunk_len + 1], the one that enters chunk j at j; GRAD / GOOM walks: nothing
     auto store_vec = [&](long long j) {
@@ -300,50 +354,63 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
         }
         // ---- A_t^T x: this wave's rows, on the power of two nw
         V nw = (V)kNone;
+        float lowest = -kNone;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) nw = raw_max(nw, vm[q] != (V)0 ? vx[q] + sn[q] : (V)kNone);
+        for (int q = 0; q < Q; ++q) {
+            nw = raw_max(nw, vm[q] != (V)0 ? vx[q] + sn[q] : (V)kNone);
+            lowest = __builtin_fminf(lowest, vm[q] != (V)0 ? (float)(vx[q] + sn[q]) : -kNone);
+        }
         nw = Comp<V>::xor16_32_max(nw);
-        V p[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) p[k] = (V)0;
-        [[maybe_unused]] V hh[K];
-        [[maybe_unused]] double htop = 0.0;
+        // h_{t-1} on the power of two of its largest entry
+        [[maybe_unused]] V htop = (V)0;
+        bool wide = false;
         if constexpr (GRAD) {
             V u = hcol[0][0];
+            unsigned key = kNoDepth;
 #pragma unroll
-            for (int k = 1; k < K; ++k) u = raw_max(u, (V)hcol[k][0]);
+            for (int k = 0; k < K; ++k) {
+                u = raw_max(u, (V)hcol[k][0]);
+                const unsigned o = depth_key(hcol[k][0]);
+                key = o > key ? o : key;
+            }
             u = max16(u);
-            const V hn = u > (V)kNone ? Comp<V>::ceil_(u * (V)kLog2e) : (V)0;
-            htop = (double)hn;
-            const bool none = t == 0 && !h0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) hh[k] = none ? (V)0 : scaled_entry((V)hcol[k][0], (V)hcol[k][1], hn);
+            htop = u > (V)kNone ? Comp<V>::ceil_(u * (V)kLog2e) : (V)0;
+            wide = depth_of<R>(key) < u - kSpread * (V)kLn2 || base + (double)(htop + nw) > (double)kHighest;
         }
+        const bool apart = far || __builtin_amdgcn_ballot_w64(lowest < (float)nw - (float)kSpread || wide) != 0; // (a row with an entry far below it, or rows far apart)
+        const int buf = (int)(s & 1);
         [[maybe_unused]] unsigned char *gA = nullptr;
-        if constexpr (GRAD) gA = reinterpret_cast<unsigned char *>(a.gA) + (size_t)(item * a.T + t) * d * d * sizeof(R);
+        if constexpr (GRAD) {
+            gA = reinterpret_cast<unsigned char *>(a.gA) + opaque((item * a.T + t) * (long long)((size_t)d * d * sizeof(R)));
+            if (a.gb && live && owner && row_ok) reinterpret_cast<R *>(a.gb)[(size_t)(item * a.T + t) * d + orow] = times_exp(r.b);
+        }
+        // an entry of h_{t-1} as hh 2^hx
+        [[maybe_unused]] auto entry = [&](const R2 &z, V &hh, int &hx) {
+            const V n = (V)z[0] > (V)kNone ? round_((V)z[0] * (V)kLog2e) : (V)0;
+            hh = t == 0 && !h0 ? (V)0 : scaled_entry((V)z[0], (V)z[1], n);
+            hx = whole(n);
+        };
+        V p[K];
+        [[maybe_unused]] V hh[K]; // h_{t-1} on the power of two of its largest entry
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            p[k] = (V)0;
+            if constexpr (GRAD) hh[k] = t == 0 && !h0 ? (V)0 : scaled_entry((V)hcol[k][0], (V)hcol[k][1], htop);
+        }
+        // (lanes beyond the last column write its value once more)
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const V w = Comp<V>::ldexp_(vm[q], (int)Comp<V>::clamp_shift(vx[q] + sn[q] - nw));
-            [[maybe_unused]] V f = (V)0;
-            if constexpr (GRAD) {
-                double e = base + htop + (double)(vx[q] + sn[q]);
-                e = e > -4000.0 ? e : -4000.0;
-                e = e < 4000.0 ? e : 4000.0;
-                f = Comp<V>::ldexp_(vm[q], (int)e);
-            }
 #pragma unroll
             for (int k = 0; k < K; ++k) p[k] = p[k] + w * sv[q][k];
             if constexpr (GRAD) {
-                // a real's place is half a GOOM's; lanes beyond the last column write its value once more
+                const V f = Comp<V>::ldexp_(vm[q], whole(base + (double)(htop + (vx[q] + sn[q]))));
                 if (live && (FULL || row0 + 4 * q < d)) {
 #pragma unroll
-                    for (int k = 0; k < K; ++k) *reinterpret_cast<R *>(gA + (offset_of(q, k) >> 1)) = (R)(f * hh[k] * sv[q][k]);
+                    for (int k = 0; k < K; ++k) *reinterpret_cast<R *>(place(gA, q, k, half_size())) = (R)(f * hh[k] * sv[q][k]);
                 }
             }
             if (K >= 8) __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (GRAD) {
-            if (a.gb && live && owner && row_ok) reinterpret_cast<R *>(a.gb)[(size_t)(item * a.T + t) * d + orow] = times_exp(r.b);
         }
         if constexpr (LATE) {
             __builtin_amdgcn_sched_barrier(0);
@@ -352,25 +419,71 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) p[k] = sum_groups(p[k]);
-        const int buf = (int)(s & 1);
         if (g == 0) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) part[buf][wave][c + 16 * k] = p[k];
-            if (c == 0) partn[buf][wave] = nw;
+            for (int k = 0; k < K; ++k) part[buf][wave][c + 16 * k] = V2{p[k], nw};
         }
         if constexpr (EARLY) {
             convert(mat);
             load(s + PD + 1, mat);
         }
-        __syncthreads();
-        V top = (V)kNone;
+        if (apart) {
+            // What was formed above is replaced.  (After it, not instead of it: the question is settled while that work goes on.  The factor's
+            // registers are the next one's by now: it is read again, a column at a time, which keeps this rare path out of the common
+            // one's registers.)
+            const unsigned char *src = left0 + t * a.left_step_stride;
+            const R2 *hp = t > 0 ? H + (size_t)(t - 1) * d : h0 ? h0 : H;
+#pragma unroll 1
+            for (int k = 0; k < K; ++k) {
+                const int col = c + 16 * k < d ? c + 16 * k : d - 1;
+                [[maybe_unused]] V hh = (V)0;
+                [[maybe_unused]] int hx = 0;
+                if constexpr (GRAD) entry(hp[col], hh, hx);
+                V term[Q], ex[Q], ctop = (V)kNone, sum = (V)0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) top = raw_max(top, partn[buf][w]);
+                for (int q = 0; q < Q; ++q) {
+                    const unsigned at = (unsigned)(row0 + 4 * q < d ? row0 + 4 * q : d - 1) * row_bytes + (unsigned)col * kEntry;
+                    V m, n;
+                    if constexpr (FACT) {
+                        const V w = (V) * reinterpret_cast<const R *>(src + at);
+                        n = Comp<V>::exponent_of(w);
+                        m = Comp<V>::ldexp_(w, -(int)n);
+                    } else {
+                        const R2 z = *reinterpret_cast<const R2 *>(src + at);
+                        n = (V)z[0] > (V)kNone ? round_((V)z[0] * (V)kLog2e) : (V)kNone;
+                        m = scaled_entry((V)z[0], (V)z[1], n);
+                    }
+                    term[q] = vm[q] * m;
+                    ex[q] = term[q] != (V)0 ? vx[q] + n : (V)kNone;
+                    ctop = raw_max(ctop, ex[q]);
+                    if constexpr (GRAD) {
+                        if (live && row0 + 4 * q < d)
+                            *reinterpret_cast<R *>(gA + (at >> 1)) = (R)Comp<V>::ldexp_(term[q] * hh, whole(base + (double)vx[q]) + whole(n) + hx);
+                    }
+                }
+                ctop = Comp<V>::xor16_32_max(ctop);
+#pragma unroll
+                for (int q = 0; q < Q; ++q) sum = sum + Comp<V>::ldexp_(term[q], (int)Comp<V>::clamp_shift(ex[q] - ctop));
+                sum = sum_groups(sum);
+                if (g == 0) part[buf][wave][c + 16 * k] = V2{sum, ctop};
+            }
+        }
+        if (lane == 0) partn[buf][wave] = nw;
+        __syncthreads();
+        V2 pv[NW];
+        V top = (V)kNone, ctop = (V)kNone; // the largest power of two of any wave; of the owner's column
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            pv[w] = part[buf][w][orow];
+            top = raw_max(top, partn[buf][w]);
+            ctop = pv[w][0] != (V)0 && pv[w][1] > ctop ? pv[w][1] : ctop;
+        }
         const bool none = !(top > (V)(0.5f * kNone));
         if (none) top = (V)0;
-        V y = (V)0;
+        if (!(ctop > (V)(0.5f * kNone))) ctop = top;
+        V y = (V)0; // the owner's column: y 2^(ctop - top) on the new base
 #pragma unroll
-        for (int w = 0; w < NW; ++w) y = y + Comp<V>::ldexp_(part[buf][w][orow], (int)Comp<V>::clamp_shift(partn[buf][w] - top));
+        for (int w = 0; w < NW; ++w) y = y + Comp<V>::ldexp_(pv[w][0], (int)Comp<V>::clamp_shift(pv[w][1] - ctop));
         if (live) {
             base = none ? 0.0 : base + (FACT ? r.common : 0.0) + (double)top;
             V bm = (V)0, be = (V)kNone;
@@ -384,7 +497,7 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
             } else if (t > t0) { // (the entry before the chunk's first step gets its G / h in the chunk that it belongs to)
                 source(r.gv, r.h, bm, be);
             }
-            take(y, bm, be);
+            take(y, ctop - top, bm, be);
         }
         if (FACT && a.out_vecs) {
             publish_top();

@@ -137,6 +137,79 @@ def test_recurrence_adjoint_sizes(G, oracle, d, ctype):  # noqa: F811
             assert np.all(got[0][:, 0] == 0)
 
 
+def far_apart(oracle, kind, seed, batch, T, d, ctype, spread):
+    """A recurrence whose states' entries lie up to e^(2 spread) apart while every gradient is an ordinary number: A and the states in units
+    of their own (D_t A_t D_{t-1}^-1, D_t b_t, the units the same at every step or new ones), the matrices dense, triangular, sparse or diagonal."""
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    rng = np.random.default_rng(seed)
+    A, b = rng.standard_normal((batch, T, d, d)) / np.sqrt(d), rng.standard_normal((batch, T, d))
+    h0 = rng.standard_normal((batch, d))
+    if kind == "triangular":
+        A = np.tril(A)
+    if kind == "sparse":
+        A[rng.random(A.shape) < 0.6] = 0.0
+        h0[rng.random(h0.shape) < 0.3] = 0.0
+    if kind == "diagonal":
+        A = A * np.eye(d) * np.sqrt(d)
+        b[...] = 0.0
+    unit = rng.uniform(-spread, spread, (batch, T + 1, d)) if kind == "new units" else np.repeat(rng.uniform(-spread, spread, (batch, 1, d)), T + 1, axis=1)
+    z = [oracle.to_goom(np.ascontiguousarray(v).astype(comp)) for v in (A, b, h0)]
+    z[0].real += (unit[:, 1:, :, None] - unit[:, :-1, None, :]).astype(comp)
+    z[1].real += unit[:, 1:].astype(comp)
+    z[2].real += unit[:, 0].astype(comp)
+    if kind == "diagonal":  # decays at rates of their own
+        z[0].real -= np.where(np.eye(d) > 0, rng.uniform(0, spread / T, (batch, 1, d, 1)), 0.0).astype(comp)
+    return z
+
+
+# (one chunk: chunk products hold a matrix on one power of two, and span no more than their type does)
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("kind", ["dense", "triangular", "sparse", "diagonal", "new units"])
+@pytest.mark.parametrize("d", [2, 5, 17, 33, 48, 64, 100, 128])
+def test_adjoint_of_entries_far_apart(G, oracle, d, kind, ctype):  # noqa: F811
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    for T, chunk, spread in ((1, 0, 100.0), (2, 2, 30.0), (12, 12, 100.0), (12, 12, 300.0), (40, 6, 8.0)):
+        spread *= 1.0 if comp == np.float32 else 8.0
+        Az, bz, h0 = far_apart(oracle, kind, 400 + d + T, 2, T, d, ctype, spread)
+        Gh = si.normal_f32(si.BASE_SEED + 401, 10, 2 * T * d).reshape(2, T, d).astype(comp)
+        re, sg = oracle.affine_scan(Az, bz, h0=h0)
+        H = (re + 1j * np.where(sg, float(comp(np.pi)), 0.0)).astype(ctype)
+        say(f"adjoint far apart {kind} T={T} d={d} chunk={chunk} spread={spread} {np.dtype(ctype).name}")
+        got = [host(v).astype(np.float64) for v in G.affine_scan_backward(dev(Az), dev(bz), dev(H), dev(Gh), dev(h0), chunk_len=chunk)]
+        want = oracle.affine_scan_backward(Az, bz, Gh, h0=h0, h=H)[:3]
+        # Every term is a product of factors that are good to a few units in the last place whatever their size, so a gradient whose terms do
+        # not cancel is good to d T units; what half-unit perturbations move further is left out.  Nothing is measured against larger entries.
+        # (Half a unit of a double log-magnitude itself: log2(e), one double, times it is the exponent that the device forms.)
+        rel = 1e-3 if comp == np.float32 else 1e-9
+        eta, tiny = 2.0 ** -24 if comp == np.float32 else 2.0 ** -53, 2 * float(np.finfo(comp).tiny)
+        rng = np.random.default_rng(5)
+        scale = lambda z: np.where(np.isfinite(z.real), 1.0 if comp == np.float32 else np.maximum(1.0, np.abs(np.where(np.isfinite(z.real), z.real, 0.0))), 0.0)
+        pert = lambda z: z.astype(np.complex128) + eta * rng.standard_normal(z.shape) * scale(z)
+        sens = [np.zeros_like(w) for w in want]
+        for _ in range(PROBES):
+            probe = oracle.affine_scan_backward(pert(Az), pert(bz), Gh, h0=pert(h0), h=pert(H))[:3]
+            sens = [np.maximum(s, np.abs(p - w)) for s, p, w in zip(sens, probe, want)]
+        for name, g, w, s in zip(("A", "bias", "h0"), got, want, sens):
+            assert np.isfinite(g).all(), name
+            tol = rel * np.abs(w) + tiny
+            well = s <= tol / 16
+            assert well.mean() > 0.75, (name, well.mean())
+            bad = (np.abs(g - w) > tol) & well
+            assert not bad.any(), (name, int(bad.sum()), int(well.sum()), (np.abs(g - w) / tol)[well].max())
+
+
+def test_adjoint_smallest_example_far_apart(G):  # noqa: F811
+    """A = 1, no bias, h0 = (1, e^-90): lam_2 = e^90 is no float, and the gradient with respect to A is the identity."""
+    for ctype, low in ((np.complex64, -90.0), (np.complex64, -300.0), (np.complex128, -800.0)):
+        comp = np.float32 if ctype == np.complex64 else np.float64
+        A = np.full((1, 1, 2, 2), -np.inf, dtype=ctype)
+        A[0, 0, 0, 0] = A[0, 0, 1, 1] = 0.0
+        h = np.array([[0.0, low]], dtype=ctype)
+        ga, gb, gh = G.affine_scan_backward(dev(A), dev(np.full((1, 1, 2), -np.inf, dtype=ctype)), dev(h[:, None]), dev(np.ones((1, 1, 2), dtype=comp)), dev(h))
+        assert np.allclose(host(ga)[0, 0], np.eye(2), rtol=1e-6, atol=0), host(ga)
+        assert np.all(host(gb) == 0) and np.allclose(host(gh), 1.0, rtol=1e-6)
+
+
 # chunks of 128 (and 64) steps in spans of 16: chains that end within a span, within a chunk, and on both
 @pytest.mark.parametrize("T,d,batch,chunk", [(129, 5, 2, 0), (143, 20, 1, 0), (256, 33, 1, 0), (200, 70, 1, 64), (150, 100, 1, 0), (128, 16, 3, 0)])
 @pytest.mark.parametrize("ctype", [np.complex64, np.complex128])

@@ -202,7 +202,6 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
     // ---- initial vector: this lane's columns c + 16 k, mantissas times 2^eh
     V hm[K];
     double eh = 0.0;
-    bool zero = a.init_mode == 3; // every entry of the vector is zero
 #pragma unroll
     for (int k = 0; k < K; ++k) hm[k] = (V)0;
     if (a.init_mode == 0) {
@@ -226,8 +225,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
             }
         }
         eh = *reinterpret_cast<const double *>(ip + (size_t)DP * a.fact_cols * (f64 ? 8 : 4));
-        zero = __builtin_amdgcn_ballot_w64(nz) == 0;
-        if (zero) eh = 0.0; // a zero vector has no exponent
+        if (__builtin_amdgcn_ballot_w64(nz) == 0) eh = 0.0; // a zero vector has no exponent
     } else if (a.init_mode == 2) {
         const IO2 *gp = reinterpret_cast<const IO2 *>(a.init + item * a.init_stride);
         double u = -__builtin_huge_val();
@@ -240,8 +238,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
             u = raw_max(u, (double)z[k][0]);
         }
         u = max16(u);
-        zero = !(u > -1.0e300);
-        eh = zero ? 0.0 : __builtin_ceil(u * kLog2e);
+        eh = u > -1.0e300 ? __builtin_ceil(u * kLog2e) : 0.0;
 #pragma unroll
         for (int k = 0; k < K; ++k) hm[k] = (V)scaled_entry((double)z[k][0], (double)z[k][1], eh);
     }
@@ -316,10 +313,37 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
             }
         }
         // A bias below the last place of anything that the row's terms could leave does not outlive their exact cancellation (the
-        // entry is zero then, and passes no gradient, as where sum and bias share an exponent).
-        if (!FACT && !zero && be < n - (V)(sizeof(V) == 4 ? 149 : 1074)) {
-            bm = (V)0;
-            be = (V)kNone;
+        // entry is zero then, and passes no gradient, as where sum and bias share an exponent).  What counts is the terms that there are: a large
+        // entry of A that meets a zero of the vector cancels nothing, and the bias is the result.  (Looked for in the rare steps that have
+        // such a row: a row with terms keeps a sum, a row without any has seldom so small a bias beside so large an entry.)
+        if constexpr (bias_goom) {
+            constexpr V kLast = (V)(sizeof(V) == 4 ? 149 : 1074);
+            const bool alone = part == (V)0 && be < n - kLast && be > (V)kNone;
+            if (__builtin_amdgcn_ballot_w64(alone) != 0) {
+                V largest = (V)kNone; // exponent of the row's largest A_ij h_j, on the same base
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    V e = (V)kNone;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        V x; // that of the entry
+                        if constexpr (SAME || EARLY) {
+                            V v = same_s[q][k];
+                            asm volatile("" : "+v"(v)); // (worked out here, not once for all steps in registers of its own)
+                            x = v != (V)0 ? Comp<V>::exponent_of(v) + same_n[q] : (V)kNone;
+                        } else {
+                            x = (V)mat.z[q][k][0] * (V)kLog2e;
+                        }
+                        if (hm[k] != (V)0) e = raw_max(e, x + Comp<V>::exponent_of(hm[k]));
+                    }
+                    e = max16(e);
+                    largest = c == q ? e : largest;
+                }
+                if (alone && be < largest - kLast) {
+                    bm = (V)0;
+                    be = (V)kNone;
+                }
+            }
         }
         const V pe = part != (V)0 ? Comp<V>::exponent_of(part) + n : (V)kNone;
         const V ex = be > pe ? be : pe;
@@ -364,7 +388,6 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         }
         const double en = none ? 0.0 : base + (double)xm;
         eh = live ? en : eh;
-        zero = live ? none : zero;
         if (fact_steps && live) store_fact(fact_steps + (t + 1) * a.fact_stride, 0, sizeof(R) == 8);
         if (scaled && live) {
             // exp(z - c + 2), c the log of the largest magnitude: the mantissa over the largest one, times e^2

@@ -101,6 +101,39 @@ def test_magnitudes_far_apart(G, oracle, d, ctype):  # noqa: F811
         assert np.isnan(got[0, 7].real).any() and np.isfinite(got[1, :15].real).all() and np.isfinite(got[0, :7].real).all()
 
 
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("constant", [False, True])
+@pytest.mark.parametrize("d", [2, 5, 24, 48, 63, 100, 127])
+def test_bias_beside_large_entries_and_cancelled_terms(G, d, constant, ctype):  # noqa: F811
+    """A bias is the result where a large entry of A meets a zero (or next to nothing) in the vector; it is dropped only below the last place
+    of terms that cancel exactly."""
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    large, tiny, below, above = (110.0, -200.0, -150.0, -60.0) if comp == np.float32 else (800.0, -1600.0, -900.0, -600.0)
+    none, pi = -np.inf, float(comp(np.pi))
+
+    def run(row, h0, bias):
+        A = np.full((2, d, d), none, dtype=ctype)
+        A[:, 0, 0] = A[:, 1, 1] = 0.0
+        A[:, d - 1] = none
+        for j, v in row.items():
+            A[:, d - 1, j] = v
+        b = np.full((1, 2, d), none, dtype=ctype)
+        b[0, :, d - 1] = bias
+        h = np.full((1, d), none, dtype=ctype)
+        for j, v in h0.items():
+            h[0, j] = v
+        z = A[None, 0] if constant else A[None]
+        return host(G.affine_scan(dev(z), dev(b), dev(h), time_invariant=constant))[0, :, d - 1]
+
+    for h0 in ({0: 0.0}, {0: 0.0, d - 1: tiny}):
+        got = run({d - 1: large}, h0, 0.0)
+        assert got[0] == 0 and abs(got[1].real - large) <= 1e-6 * large, got
+    if d > 2:  # h_0 - h_1 with h_0 = h_1 = 1
+        for bias, want in ((below, none), (above, above)):
+            got = run({0: 0.0, 1: 1j * pi}, {0: 0.0, 1: 0.0}, bias).real
+            assert np.all((got == want) | (np.abs(got - want) <= 1e-6 * abs(above))), (bias, got)
+
+
 # (the method of test_affine_scan_backward: the oracle on the device's forward states, entries that half-unit perturbations move left out)
 @pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
 @pytest.mark.parametrize("d", SIZES)

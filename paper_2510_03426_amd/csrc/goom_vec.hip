@@ -289,6 +289,34 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
             n = c == q ? nq : n;
             if (K >= 8) __builtin_amdgcn_sched_barrier(0); // one pass's temporaries at a time: the registers hold two factors
         }
+        if constexpr (FACT && sizeof(R) == 8) {
+            // A factored matrix has one power of two for all its rows: a row may be 2^-500 of it, and meet an entry of the vector as small.
+            // Where a sum comes out so low, the row is taken on a power of two of its own.
+            const bool low = Comp<V>::abs_(part) < (V)0x1p-900;
+            if (__builtin_amdgcn_ballot_w64(low) != 0) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    auto entry = [&](int k) -> V {
+                        if constexpr (SAME)
+                            return same_s[q][k];
+                        else
+                            return (V)mat.w[q][k];
+                    };
+                    V top = (V)0, p = (V)0;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) top = raw_max(top, Comp<V>::abs_(entry(k)));
+                    top = max16(top);
+                    int e = top > (V)0 ? Comp<V>::frexp_exp(top) : 0;
+                    asm volatile("" : "+v"(e)); // (worked out here, not once for all steps in registers of its own)
+#pragma unroll
+                    for (int k = 0; k < K; ++k) p = p + Comp<V>::ldexp_(entry(k), -e) * hm[k];
+                    p = sum16(p);
+                    part = c == q ? p : part;
+                    n = c == q ? (V)e : n;
+                    if (K >= 8) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
         // ---- the bias on the same base; the sum on the larger exponent
         const double base = eh + (FACT ? (SAME ? same_common : r.common) : 0.0);
         V bm = (V)0, be = (V)kNone;

@@ -134,6 +134,27 @@ def test_bias_beside_large_entries_and_cancelled_terms(G, d, constant, ctype):  
             assert np.all((got == want) | (np.abs(got - want) <= 1e-6 * abs(above))), (bias, got)
 
 
+@pytest.mark.parametrize("constant", [False, True])
+@pytest.mark.parametrize("d", [3, 20, 40, 100])
+def test_carries_of_small_rows_and_entries(G, oracle, d, constant):  # noqa: F811
+    """Chunk products whose rows lie e^-700 apart on vectors whose entries do (complex128): a row's product with its entry is below the smallest
+    double on the matrix's and the vector's powers of two, and e^-50 of the largest result."""
+    T, at = 5, [0, d // 2, d - 1]
+    A = np.full((1, T, d, d), -np.inf, dtype=np.complex128)
+    h0 = np.full((1, d), -np.inf, dtype=np.complex128)
+    for i, a, h in zip(at, (0.0, -600.0, -700.0), (-700.0, -150.0, 0.0)):
+        A[0, :, i, i] = 0.0
+        A[0, : T if constant else 1, i, i] = a
+        h0[0, i] = h
+    T = 2 if constant else T  # (a third step leaves the vector's own range)
+    A, b = np.ascontiguousarray(A[:, :T]), np.full((1, T, d), -np.inf, dtype=np.complex128)
+    re, _ = oracle.affine_scan(A, b, h0=h0)
+    got = host(G.affine_scan(dev(A[:, 0]) if constant else dev(A), dev(b), dev(h0), chunk_len=1, time_invariant=constant)).real
+    assert np.array_equal(np.isneginf(got), np.isneginf(re))
+    live = np.isfinite(re)
+    assert np.abs(got[live] - re[live]).max() <= 1e-10 * np.abs(re[live]).max(), (got[0][:, at], re[0][:, at])
+
+
 # (the method of test_affine_scan_backward: the oracle on the device's forward states, entries that half-unit perturbations move left out)
 @pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
 @pytest.mark.parametrize("d", SIZES)

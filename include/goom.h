@@ -351,8 +351,8 @@ size_t goom_affine_scan_workspace_bytes(int64_t T, int d, int64_t batch, int dty
  * eq. 27), the format the layers after the recurrence consume: scaled[b, t, i] =
  * (+-) exp(Re h[b, t, i] - c[b, t] + 2) with c[b, t] = max_i Re h[b, t, i], all within
  * [-e^2, e^2].  scaled: [batch, T, d] reals of the component type; logscale: NULL or [batch, T]
- * reals receiving c (-inf for a zero state, whose scaled entries are 0).  Arguments otherwise as
- * for goom_affine_scan.  The last phase
+ * reals receiving c (-inf for a zero state, whose scaled entries are 0; NaN for a state with a NaN,
+ * which stays one among the scaled entries).  Arguments otherwise as for goom_affine_scan.  The last phase
  * writes the scaled states directly and no GOOM states touch memory (the workspace query asks for room for
  * them except for GOOM_C64 with d = 16, 32 or 64 and more than one chunk).  workspace: goom_affine_scan_scaled_workspace_bytes(...) bytes. */
 int goom_affine_scan_scaled(goom_ctx *ctx, const void *A, const void *bias, const void *h0,

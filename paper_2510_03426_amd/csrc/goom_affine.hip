@@ -308,8 +308,8 @@ template <int DP, bool TI, bool ADJ = false, bool IOS = false> __global__ __laun
             // mantissa over the largest mantissa, times e^2; the vector's exponent only enters c
             float am = __builtin_fabsf(mine);
             am = C::template group_allmax<64>(am, am);
-            pend_scaled = am > 0.0f ? mine * (7.38905609893065022723f / am) : 0.0f;
-            if (logscale0) pend_logscale = am > 0.0f ? (float)(((double)C::log2_abs(am) + eh) * kLn2) : -__builtin_huge_valf();
+            pend_scaled = am == 0.0f ? 0.0f : mine * (7.38905609893065022723f / am); // (a NaN anywhere: am is one)
+            if (logscale0) pend_logscale = am == 0.0f ? -__builtin_huge_valf() : (float)(((double)C::log2_abs(am) + eh) * kLn2);
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {

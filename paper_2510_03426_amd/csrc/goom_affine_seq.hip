@@ -383,8 +383,8 @@ __device__ __forceinline__ void seq_output_wave(const SeqArgs &a, SeqShared &s, 
             const float v = __builtin_ldexpf(m, down > -300 ? down : -300);
             float am = __builtin_fabsf(v);
             am = C::group_allmax<32>(am, am);
-            if (os && lane < D) os[(size_t)t * D] = am > 0.0f ? v * (7.38905609893065022723f * __builtin_amdgcn_rcpf(am)) : 0.0f;
-            if (ol && lane == 0) ol[t] = am > 0.0f ? (float)(((double)C::log2_abs(am) + (double)g) * 0.693147180559945309417) : kNegInf;
+            if (os && lane < D) os[(size_t)t * D] = am == 0.0f ? 0.0f : v * (7.38905609893065022723f * __builtin_amdgcn_rcpf(am)); // (a NaN anywhere: am is one)
+            if (ol && lane == 0) ol[t] = am == 0.0f ? kNegInf : (float)(((double)C::log2_abs(am) + (double)g) * 0.693147180559945309417);
         }
     };
 

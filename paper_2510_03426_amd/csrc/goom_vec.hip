@@ -418,18 +418,25 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         eh = live ? en : eh;
         if (fact_steps && live) store_fact(fact_steps + (t + 1) * a.fact_stride, 0, sizeof(R) == 8);
         if (scaled && live) {
-            // exp(z - c + 2), c the log of the largest magnitude: the mantissa over the largest one, times e^2
+            // exp(z - c + 2), c the log of the largest magnitude: the mantissa over the largest one, times e^2.  (The maximum passes a NaN
+            // by; the entry stays one, and the log scale says so: a zero state is something else.)
             V am = (V)0;
+            bool nan = false;
 #pragma unroll
-            for (int k = 0; k < K; ++k) am = raw_max(am, Comp<V>::abs_(hm[k]));
+            for (int k = 0; k < K; ++k) {
+                am = raw_max(am, Comp<V>::abs_(hm[k]));
+                nan = nan || hm[k] != hm[k];
+            }
             am = max16(am);
+            nan = __builtin_amdgcn_ballot_w64(nan) != 0;
             if (wave == (NW - 1) && g == 3) { // (not the wave that has carries to store)
                 const size_t at = (size_t)(item * a.steps + t0 + t);
                 const V f = am > (V)0 ? (V)7.38905609893065022723 / am : (V)0;
 #pragma unroll
                 for (int k = 0; k < K; ++k)
-                    if (c + 16 * k < d) scaled[at * d + c + 16 * k] = (IO)(am > (V)0 ? hm[k] * f : (V)0);
-                if (logscale && c == 0) logscale[at] = am > (V)0 ? (IO)(((double)Comp<V>::log2_abs(am) + eh) * kLn2) : (IO)-__builtin_huge_val();
+                    if (c + 16 * k < d) scaled[at * d + c + 16 * k] = (IO)(hm[k] * f);
+                if (logscale && c == 0)
+                    logscale[at] = nan ? (IO)__builtin_nan("") : am > (V)0 ? (IO)(((double)Comp<V>::log2_abs(am) + eh) * kLn2) : (IO)-__builtin_huge_val();
             }
         }
     };

@@ -155,6 +155,22 @@ def test_carries_of_small_rows_and_entries(G, oracle, d, constant):  # noqa: F81
     assert np.abs(got[live] - re[live]).max() <= 1e-10 * np.abs(re[live]).max(), (got[0][:, at], re[0][:, at])
 
 
+# (16 and 32: a walk of their own, with one matrix also 64; 96 sequences of 32: the walk sequence by sequence)
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("d,batch", [(5, 2), (16, 2), (24, 2), (32, 2), (32, 96), (64, 2), (100, 2)])
+def test_scaled_states_that_are_not_numbers(G, oracle, d, batch, ctype):  # noqa: F811
+    T, at = 24, 7
+    Az, bz, h0 = inputs(oracle, 350 + d, batch, T, d, ctype, False)
+    Az[0, at, 0, 0] = bz[0, at, 0] = np.nan
+    for chunk, constant in ((0, False), (6, False), (0, True), (4, True)):
+        z = np.ascontiguousarray(Az[:, 0]) if constant else Az
+        H = host(G.affine_scan(dev(z), dev(bz), dev(h0), chunk_len=chunk, time_invariant=constant)).real
+        assert np.isnan(H[0, at]).any() and np.isfinite(H[1]).any(axis=-1).all() and np.isfinite(H[0, at - 1]).any()
+        s, c = (host(v) for v in G.affine_scan_scaled(dev(z), dev(bz), dev(h0), chunk_len=chunk, time_invariant=constant, want_logscale=True))
+        bad = np.isnan(H).any(axis=-1)
+        assert np.array_equal(np.isnan(c), bad) and np.all(np.isnan(s)[np.isnan(H)]) and not np.isnan(s[~bad]).any(), (chunk, constant)
+
+
 # (the method of test_affine_scan_backward: the oracle on the device's forward states, entries that half-unit perturbations move left out)
 @pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
 @pytest.mark.parametrize("d", SIZES)

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         if constexpr (FACT && sizeof(R) == 8) {
             // A factored matrix has one power of two for all its rows: a row may be 2^-500 of it, and meet an entry of the vector as small.
             // Where a sum comes out so low, the row is taken on a power of two of its own.
-            const bool low = Comp<V>::abs_(part) < (V)0x1p-900;
+            const bool low = owner && Comp<V>::abs_(part) < (V)0x1p-900;
             if (__builtin_amdgcn_ballot_w64(low) != 0) {
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         // such a row: a row with terms keeps a sum, a row without any has seldom so small a bias beside so large an entry.)
         if constexpr (bias_goom) {
             constexpr V kLast = (V)(sizeof(V) == 4 ? 149 : 1074);
-            const bool alone = part == (V)0 && be < n - kLast && be > (V)kNone;
+            const bool alone = owner && part == (V)0 && be < n - kLast && be > (V)kNone;
             if (__builtin_amdgcn_ballot_w64(alone) != 0) {
                 V largest = (V)kNone; // exponent of the row's largest A_ij h_j, on the same base
 #pragma unroll

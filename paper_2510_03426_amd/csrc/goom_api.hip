@@ -299,15 +299,16 @@ static int carry_phase(goom_ctx *ctx, const ScanPlan &p, int dtype, int d, long 
         }
         return launch_chain(ctx, l);
     }
-    { // group products (the last group's is needed only by the reduction)
+    { // group products (the last group's is needed only by the reduction); of a shared matrix only the groups' vectors, its power is there
         ChainLaunch l = base;
-        l.m = cs.bias ? d + 1 : d;
+        l.m = cs.same ? 1 : cs.bias ? d + 1 : d;
         l.left = totals;
         l.left_batch_stride = (long long)p.C * p.tot.stride;
+        l.left_same = cs.same ? 1 : 0;
         l.steps = p.nt;
         l.chunk_len = p.S;
         l.chunks_launched = cs.final_goom ? p.G : p.G - 1;
-        l.init_mode = 0;
+        l.init_mode = cs.same ? 3 : 0;
         l.bias_mode = cs.bias ? 2 : 0;
         l.bias_col = d;
         l.out_fact_final = gtot;
@@ -321,6 +322,7 @@ static int carry_phase(goom_ctx *ctx, const ScanPlan &p, int dtype, int d, long 
         l.m = cs.m;
         l.left = gtot;
         l.left_batch_stride = (long long)p.G * p.tot.stride;
+        l.left_same = cs.same ? 1 : 0;
         l.steps = cs.final_goom ? p.G : p.G - 1;
         l.chunk_len = l.steps;
         l.chunks_launched = 1;
@@ -344,6 +346,7 @@ static int carry_phase(goom_ctx *ctx, const ScanPlan &p, int dtype, int d, long 
         l.m = cs.m;
         l.left = totals;
         l.left_batch_stride = (long long)p.C * p.tot.stride;
+        l.left_same = cs.same ? 1 : 0;
         l.steps = p.nt;
         l.chunk_len = p.S;
         l.chunks_launched = p.G;
@@ -986,6 +989,11 @@ static long long one_matrix_chunk(long long T, int d, long long batch, int dtype
     return L < T ? L : T;
 }
 
+// One matrix for all steps: carries that one chain an item takes; more go in groups, whose product is one more power and whose carries are
+// three launches of their own.  Measured, one chain / groups, in us a forward pass: 127 carries of d = 100 958 / 992, of d = 48 605 / 532; 149 carries
+// of d = 100 285 / 354, of d = 48 162 / 138; 249 carries of d = 100 394 / 332, of d = 8 (complex128) 173 / 84; 4095 carries of d = 24 3165 / 245.
+constexpr long long kOneMatrixCarries = 192;
+
 static AffinePlan plan_affine(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts)
 {
     AffinePlan ap;
@@ -1104,8 +1112,9 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
     unsigned char *gcar = gtot + p.gtot_bytes;
     // One matrix for all steps: A^L once, in the first chunk's slot; the other slots hold their chunks' vectors only, and the last one
     // (no chunk product is needed of the last chunk) the matrix itself, converted for the walks.  A carry then reads a vector and
-    // nothing else, and one chain an item takes them all.
-    if (ti) p.S = p.G = 0;
+    // nothing else, and one chain an item takes them all, up to kOneMatrixCarries of them; of more (a caller's short chunks) the groups' products
+    // are one power again, in the first group's slot.
+    if (ti && p.nt <= kOneMatrixCarries) p.S = p.G = 0;
     const unsigned char *prepared = ti ? totals + (p.C - 1) * p.tot.stride : nullptr;
     auto with_prepared = [&](ChainLaunch &l) {
         // (float d = 16, 32 and 64 have a walk of one wave a chain that converts the matrix itself: more chains at once, and faster where
@@ -1120,6 +1129,10 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         if (int s = goom_chain::launch_matrix_power(ctx, A, d, batch, dtype, f64, p.dp, p.L, totals, totals + (p.C - 1) * p.tot.stride,
                                                     (long long)p.C * p.tot.stride, p.tot.cols_padded))
             return s;
+        if (p.S)
+            if (int s = goom_chain::launch_matrix_power(ctx, A, d, batch, dtype, f64, p.dp, p.L * p.S, gtot, nullptr, (long long)p.G * p.tot.stride,
+                                                        p.tot.cols_padded))
+                return s;
         ChainLaunch w = base;
         w.m = 1;
         w.bias_col = d;

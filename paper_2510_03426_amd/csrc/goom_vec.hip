@@ -66,6 +66,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
     if (len <= 0) return; // the whole workgroup
 
     const unsigned char *left0 = a.left + item * a.left_batch_stride + t0 * a.left_step_stride;
+    [[maybe_unused]] const unsigned char *same0 = a.left + item * a.left_batch_stride; // (a shared factored matrix lies in the item's first slot)
     const int lfc = a.left_fact_cols;
     const int row0 = wave * RW + g;           // row of pass q: row0 + 4 q
     const int orow = row0 + 4 * (c < Q ? c : 0); // the row this lane finishes (lanes c >= Q repeat one and store nothing)
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         for (int q = 0; q < Q; ++q) {
             if constexpr (FACT) {
 #pragma unroll
-                for (int k = 0; k < K; ++k) same_s[q][k] = (V)load_fact(0, q, k);
+                for (int k = 0; k < K; ++k) same_s[q][k] = (V) * reinterpret_cast<const R *>(same0 + offset_of(q, k));
                 same_n[q] = (V)0;
             } else if (a.left_prepared) { // converted once for all chunks (goom_power.hip)
                 const unsigned char *pp = a.left_prepared + item * a.prepared_stride;
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
                 for (int k = 0; k < K; ++k) same_s[q][k] = (V)scaled_entry((double)z[k][0], (double)z[k][1], (double)same_n[q]);
             }
         }
-        if (FACT) same_common = *reinterpret_cast<const double *>(left0 + (size_t)DP * lfc * sizeof(R));
+        if (FACT) same_common = *reinterpret_cast<const double *>(same0 + (size_t)DP * lfc * sizeof(R));
     }
 
     auto convert = [&](const Matrix &r) {
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
 #pragma unroll
         for (int i = 0; i < PD; ++i) step(t + i, ring[i], rest[i % RD]);
     }
-    if (a.out_fact_final) store_fact(a.out_fact_final + chain * a.fact_stride, a.bias_mode == 1 ? a.bias_col : 0, sizeof(R) == 8 || a.fact_f64);
+    if (a.out_fact_final) store_fact(a.out_fact_final + chain * a.fact_stride, a.bias_mode ? a.bias_col : 0, sizeof(R) == 8 || a.fact_f64);
 }
 
 template <typename R, int DP, int NW, bool FACT, bool FULL, bool SAME, int BIAS, int PD>

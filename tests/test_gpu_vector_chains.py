@@ -280,6 +280,35 @@ def test_adjoint_smallest_example_far_apart(G):  # noqa: F811
         assert np.all(host(gb) == 0) and np.allclose(host(gh), 1.0, rtol=1e-6)
 
 
+# more chunks than one chain carries with one matrix for all steps (192): grouped from there on
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("T,d,batch,chunk,constant", [
+    (600, 5, 2, 3, True), (587, 24, 1, 3, True), (400, 16, 2, 2, True), (400, 32, 1, 2, True), (390, 48, 1, 2, True), (400, 64, 1, 2, True), (388, 100, 1, 2, True),
+    (195, 17, 2, 1, True)])
+def test_many_chunks_carried_in_groups(G, oracle, T, d, batch, chunk, constant, ctype):  # noqa: F811
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    Az, bz, h0 = inputs(oracle, 380 + d, batch, T, d, ctype, constant)
+    say(f"many chunks T={T} d={d} batch={batch} chunk={chunk} {np.dtype(ctype).name} constant={constant}")
+    rep = np.ascontiguousarray(np.broadcast_to(Az[:, None], (batch, T, d, d))) if constant else Az
+    G.profile_enable(True)
+    Hd = G.affine_scan(dev(Az), dev(bz), dev(h0), chunk_len=chunk, time_invariant=constant)
+    labels = [k for k, _ in G.profile_records()]
+    if constant:
+        assert labels.count("affine_phase2_carries") == 3, labels
+    fn = lambda a_, b_, h_: oracle.affine_scan(a_, b_, h0=h_, return_kappa=True)
+    re, sg, kap, well = with_sensitivity(fn, [rep, bz, h0], comp, nprobe=PROBES)
+    compare(host(Hd), re, sg, kap, name=f"T{T}d{d}", max_ill_fraction=0.25, well=well)
+    # gradients as a layer asks for them, from the scaled states: small entries weigh little
+    H = host(Hd)
+    Gh = (si.normal_f32(si.BASE_SEED + 381, 10, batch * T * d).reshape(batch, T, d) * oracle.scaled_exp(H)[0]).astype(comp)
+    got = [host(v).astype(np.float64) for v in G.affine_scan_backward(dev(Az), dev(bz), Hd, dev(Gh), dev(h0), chunk_len=chunk, time_invariant=constant)]
+    G.profile_enable(False)
+    want = (oracle.affine_scan_backward_time_invariant if constant else oracle.affine_scan_backward)(Az, bz, Gh, h0=h0, h=H)[:3]
+    # (a norm-wise bound: T steps whose roundings add up; the entries' own bounds are those of the tests above)
+    for name, g, w in zip(("A", "bias", "h0"), got, want):
+        assert np.linalg.norm(g - w) <= (1e-3 if comp == np.float32 else 1e-10) * np.linalg.norm(w), (name, np.linalg.norm(g - w) / np.linalg.norm(w))
+
+
 # chunks of 128 (and 64) steps in spans of 16: chains that end within a span, within a chunk, and on both
 @pytest.mark.parametrize("T,d,batch,chunk", [(129, 5, 2, 0), (143, 20, 1, 0), (256, 33, 1, 0), (200, 70, 1, 64), (150, 100, 1, 0), (128, 16, 3, 0)])
 @pytest.mark.parametrize("ctype", [np.complex64, np.complex128])

@@ -1246,6 +1246,11 @@ int goom_affine_scan_scaled(goom_ctx *ctx, const void *A, const void *bias, cons
 }
 
 // ---- backward passes ---------------------------------------------------------------------------------------
+// Adjoint of the recurrence: carries that one chain an item takes; more go in groups.  (A carry of the adjoint takes 1.3 us at d = 24 and 2 us at
+// d = 64, so the line could lie lower - 93 carries of d = 64: 328 us in one chain, 220 in groups - but a group's float product rounds once more,
+// which up to here nothing has to.  255 carries of d = 48: 681 / 277 us; 511 of d = 64: 1860 / 945 us; 8191 of d = 8: 7400 / 391 us.)
+constexpr long long kAdjointCarries = 128;
+
 struct AffineBackwardPlan {
     bool direct; // the adjoint scan reads the forward pass's matrices itself (transposed, in reverse order)
     bool one_matrix; // GOOM_AFFINE_TIME_INVARIANT: A is [batch, d, d] and so is its gradient
@@ -1337,16 +1342,22 @@ int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, co
     }
     if (!p.direct) {
         // Every size but float d = 16 and 32: the adjoints walked backwards, gradients written on the way (goom_vec_adjoint.hip), over
-        // the forward chunks.  One chain an item carries the adjoint from chunk to chunk: at most 128 chunks by default (a carry
-        // takes about as long as a step, so longer chunks cost nothing).
-        goom_scan_opts o = plain;
-        const AffinePlan fwd = plan_affine(T, d, batch, dtype, &plain);
-        if (plain.chunk_len == 0) o.chunk_len = fwd.p.C > 128 ? (T + 127) / 128 : fwd.p.L;
-        const ScanPlan q = plan_affine(T, d, batch, dtype, &o).p;
+        // the forward chunks.  One chain an item carries the adjoint from chunk to chunk, up to kAdjointCarries of them, more in groups.
+        const ScanPlan q = plan_affine(T, d, batch, dtype, &plain).p;
+        const size_t vec = goom_chain::adjoint_vec_stride(q.dp, dtype);
         unsigned char *totals = static_cast<unsigned char *>(w), *vecs = totals + align_up((size_t)batch * q.C * q.tot.stride, 256);
+        unsigned char *gtot = vecs + (size_t)batch * q.C * vec, *gvecs = nullptr;
+        long long S = 0, G = 0; // chunk products a group, groups
         if (q.C > 1) {
-            if ((size_t)(vecs - w) + (size_t)batch * q.C * goom_chain::adjoint_vec_stride(q.dp, dtype) > p.total())
-                return fail(ctx, GOOM_EWORKSPACE, "workspace too small for %lld chunks", q.C);
+            if ((size_t)(gtot - w) > p.total()) return fail(ctx, GOOM_EWORKSPACE, "workspace too small for %lld chunks", q.C);
+            if (q.C - 1 > kAdjointCarries) { // (the query leaves room for a forward scan's groups, and more)
+                const long long s = (long long)std::ceil(std::sqrt((double)(q.C - 1))), g = (q.C - 1 + s - 1) / s;
+                if ((size_t)(gtot - w) + (size_t)batch * g * (q.tot.stride + vec) <= p.total()) {
+                    S = s;
+                    G = g;
+                    gvecs = gtot + (size_t)batch * g * q.tot.stride;
+                }
+            }
             const size_t cb = 2 * comp_bytes(dtype);
             ChainLaunch l;
             std::memset(&l, 0, sizeof l);
@@ -1369,9 +1380,22 @@ int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, co
             l.fact_cols = q.tot.cols_padded;
             l.label = "affine_adjoint_chunk_products";
             if (int s = launch_chain(ctx, l)) return s;
+            if (S > 1) { // the groups' products (nothing passes through the first one)
+                l.left = totals + S * q.tot.stride;
+                l.left_fact = 1;
+                l.left_fact_cols = q.tot.cols_padded;
+                l.left_step_stride = (long long)q.tot.stride;
+                l.left_batch_stride = (q.C - 1) * (long long)q.tot.stride;
+                l.steps = q.C - 1 - S;
+                l.chunk_len = S;
+                l.chunks_launched = G - 1;
+                l.out_fact_final = gtot;
+                l.label = "affine_adjoint_group_products";
+                if (int s = launch_chain(ctx, l)) return s;
+            }
         }
         return goom_chain::launch_affine_adjoint(ctx, A, bias, h0, H, grad_H, grad_A, grad_bias, grad_h0, T, d, batch, dtype, q.dp, q.L, q.C, totals,
-                                                 (long long)q.tot.stride, q.tot.cols_padded, vecs);
+                                                 (long long)q.tot.stride, q.tot.cols_padded, vecs, S, gtot, gvecs);
     }
     // the operands of the adjoint recurrence (the shifts of the matrices' log-magnitudes, G / h as GOOMs) ...
     if (int s = launch_affine_backward_prepare(ctx, H, grad_H, static_cast<float *>(At), gt, T, d, batch, dtype)) return s;

@@ -216,6 +216,6 @@ int launch_matrix_power(goom_ctx *ctx, const void *A, int d, long long batch, in
 size_t adjoint_vec_stride(int dp, int dtype);
 int launch_affine_adjoint(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *G, void *gA, void *gb, void *gh0,
                           long long T, int d, long long batch, int dtype, int dp, long long chunk_len, long long chunks, void *totals,
-                          long long total_stride, int total_cols, void *vecs);
+                          long long total_stride, int total_cols, void *vecs, long long group, void *gtot, void *gvecs);
 } // namespace goom_chain
 

@@ -307,10 +307,10 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
         }
         take(y, (V)0, bm, be);
     }
-    // FACT: vectors [batch][chunk_len + 1], the one that enters chunk j at j; GRAD / GOOM walks: nothing
+    // FACT: vectors [batch][T + 1], the one that enters chunk j at j; GRAD / GOOM walks: nothing
     auto store_vec = [&](long long j) {
         // mantissas relative to the vector's largest exponent: through LDS, each wave its own rows
-        unsigned char *dst = a.out_vecs + (item * (a.chunk_len + 1) + j) * a.vec_stride;
+        unsigned char *dst = a.out_vecs + (item * (a.T + 1) + j) * a.vec_stride;
         // the largest exponent over all rows needs every wave's: kept in partn by the caller
         V top = (V)kNone;
 #pragma unroll
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
         if (lane == 0) partn[0][wave] = top;
         __syncthreads();
     };
-    if (FACT && a.out_vecs) { // the zero vector enters the last chunk
+    if (FACT && a.out_vecs && tlast + 1 == a.T) { // the zero vector enters the last chunk (a group's last one: the next group's walk has it)
         publish_top();
         store_vec(tlast + 1);
         __syncthreads();
@@ -575,11 +575,13 @@ template <typename R> int walk(goom_ctx *ctx, const AdjointArgs &a, int dp, bool
 
 // The adjoint pass of a recurrence over `chunks` chunks of chunk_len steps.  totals: factored products of chunks 1 .. chunks - 1
 // (their column d is written here), vecs: room for batch * chunks vectors of adjoint_vec_stride bytes; neither is used with one chunk.
+// group: 0, or that many chunk products make a group: gtot then holds the products of groups 1 .. (column d written here), gvecs has room for a
+// vector a group.
 size_t adjoint_vec_stride(int dp, int dtype) { return goom::align_up((size_t)dp * (dtype == GOOM_C64 ? 4 : 8) + 8, 256); }
 
 int launch_affine_adjoint(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *G, void *gA, void *gb, void *gh0,
                           long long T, int d, long long batch, int dtype, int dp, long long chunk_len, long long chunks, void *totals,
-                          long long total_stride, int total_cols, void *vecs)
+                          long long total_stride, int total_cols, void *vecs, long long group, void *gtot, void *gvecs)
 {
     const bool f32 = dtype == GOOM_C64;
     const size_t cb = f32 ? 8 : 16;
@@ -623,7 +625,28 @@ int launch_affine_adjoint(goom_ctx *ctx, const void *A, const void *bias, const 
         f.first_chunk = 0;
         f.chunks = 1;
         f.out_vecs = static_cast<unsigned char *>(vecs);
-        if (int s = run(f, true, false, batch, "affine_adjoint_carries")) return s;
+        if (group) {
+            const long long groups = (f.T + group - 1) / group;
+            AdjointArgs u = f; // the vectors that leave groups 1 .. groups - 1 when nothing enters
+            u.chunk_len = group;
+            u.first_chunk = 1;
+            u.chunks = groups - 1;
+            u.out_vecs = nullptr;
+            u.out_total = static_cast<unsigned char *>(gtot);
+            u.totals_per_item = groups - 1;
+            if (int s = run(u, true, false, batch * (groups - 1), "affine_adjoint_group_vectors")) return s;
+            u = f; // the vectors that enter the groups
+            u.left = static_cast<const unsigned char *>(gtot);
+            u.left_batch_stride = (groups - 1) * total_stride;
+            u.T = u.chunk_len = groups - 1;
+            u.out_vecs = static_cast<unsigned char *>(gvecs);
+            if (int s = run(u, true, false, batch, "affine_adjoint_carries")) return s;
+            f.chunk_len = group; // and every group again, from there
+            f.chunks = groups;
+            f.init = static_cast<const unsigned char *>(gvecs);
+            f.init_per_item = groups;
+        }
+        if (int s = run(f, true, false, batch * f.chunks, "affine_adjoint_carries")) return s;
         a.init = static_cast<const unsigned char *>(vecs);
     }
     a.first_chunk = 0;

@@ -280,11 +280,11 @@ def test_adjoint_smallest_example_far_apart(G):  # noqa: F811
         assert np.all(host(gb) == 0) and np.allclose(host(gh), 1.0, rtol=1e-6)
 
 
-# more chunks than one chain carries with one matrix for all steps (192): grouped from there on
+# more chunks than one chain carries: 192 with one matrix for all steps, 128 in the adjoint pass (there by default too), grouped from there on
 @pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
 @pytest.mark.parametrize("T,d,batch,chunk,constant", [
     (600, 5, 2, 3, True), (587, 24, 1, 3, True), (400, 16, 2, 2, True), (400, 32, 1, 2, True), (390, 48, 1, 2, True), (400, 64, 1, 2, True), (388, 100, 1, 2, True),
-    (195, 17, 2, 1, True)])
+    (195, 17, 2, 1, True), (4096, 5, 1, 0, False), (1500, 24, 1, 0, False), (390, 48, 1, 3, False), (262, 64, 1, 2, False), (264, 100, 1, 2, False), (131, 17, 2, 1, False)])
 def test_many_chunks_carried_in_groups(G, oracle, T, d, batch, chunk, constant, ctype):  # noqa: F811
     comp = np.float32 if ctype == np.complex64 else np.float64
     Az, bz, h0 = inputs(oracle, 380 + d, batch, T, d, ctype, constant)
@@ -302,7 +302,10 @@ def test_many_chunks_carried_in_groups(G, oracle, T, d, batch, chunk, constant, 
     H = host(Hd)
     Gh = (si.normal_f32(si.BASE_SEED + 381, 10, batch * T * d).reshape(batch, T, d) * oracle.scaled_exp(H)[0]).astype(comp)
     got = [host(v).astype(np.float64) for v in G.affine_scan_backward(dev(Az), dev(bz), Hd, dev(Gh), dev(h0), chunk_len=chunk, time_invariant=constant)]
+    labels = [k for k, _ in G.profile_records()]
     G.profile_enable(False)
+    if not constant and not (comp == np.float32 and d in (16, 32)):
+        assert "affine_adjoint_group_products" in labels, labels
     want = (oracle.affine_scan_backward_time_invariant if constant else oracle.affine_scan_backward)(Az, bz, Gh, h0=h0, h=H)[:3]
     # (a norm-wise bound: T steps whose roundings add up; the entries' own bounds are those of the tests above)
     for name, g, w in zip(("A", "bias", "h0"), got, want):

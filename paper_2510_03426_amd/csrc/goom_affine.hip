@@ -688,7 +688,7 @@ bool affine_chunk_applies(const ChainArgs &args, int dp)
 {
     return (dp == 16 || dp == 32 || dp == 64) && args.n == dp && args.d == dp && args.m == dp + 1 && args.bias_mode == 1 &&
            args.bias_col == dp && args.init_mode == 0 && args.out_goom == nullptr && args.out_fact_steps == nullptr &&
-           args.out_fact_final != nullptr && args.fact_cols == dp + 16 && args.io_shift == nullptr; // (a rescaled bias: the general kernel)
+           args.out_fact_final != nullptr && args.fact_cols == dp + 16 && args.io_shift == nullptr;
 }
 
 int dispatch_affine_chunk(goom_ctx *ctx, const ChainArgs &args, int dp, long long grid, const char *label)

@@ -1398,7 +1398,7 @@ int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, co
                                                  (long long)q.tot.stride, q.tot.cols_padded, vecs, S, gtot, gvecs);
     }
     // the operands of the adjoint recurrence (the shifts of the matrices' log-magnitudes, G / h as GOOMs) ...
-    if (int s = launch_affine_backward_prepare(ctx, H, grad_H, static_cast<float *>(At), gt, T, d, batch, dtype)) return s;
+    if (int s = launch_affine_backward_prepare(ctx, H, grad_H, static_cast<float *>(At), gt, T, d, batch)) return s;
     // ... the adjoints, by the forward scan itself over the matrices read transposed ...
     ctx->prof_keep = true;
     const int st = run_affine(ctx, A, gt, nullptr, mu, nullptr, nullptr, T, d, batch, dtype, &plain, p.scan_bytes ? scan_ws : nullptr, p.scan_bytes,
@@ -1406,7 +1406,7 @@ int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, co
     ctx->prof_keep = false;
     if (st) return st;
     // ... and the gradients
-    return launch_affine_backward_gradients(ctx, A, bias, h0, H, mu, grad_A, grad_bias, grad_h0, T, d, batch, dtype);
+    return launch_affine_backward_gradients(ctx, A, bias, h0, H, mu, grad_A, grad_bias, grad_h0, T, d, batch);
 }
 
 // Workspace of the LMME backward pass: the shifts, W~', both transposed operands, both products, and what the two

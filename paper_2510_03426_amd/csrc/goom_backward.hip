@@ -425,10 +425,11 @@ template <typename R> static int bwd_shift_t(goom_ctx *ctx, const void *H, const
     return check_hip(ctx, hipGetLastError(), "launch bwd_shift_kernel");
 }
 
-int launch_affine_backward_prepare(goom_ctx *ctx, const void *H, const void *G, float *shift, void *gt, long long T, int d, long long batch, int dtype)
+// (float components, d = 16 and 32: every other size and type is walked by goom_vec_adjoint.hip)
+int launch_affine_backward_prepare(goom_ctx *ctx, const void *H, const void *G, float *shift, void *gt, long long T, int d, long long batch)
 {
     if (batch * T > 0x7fffffffLL) return fail(ctx, GOOM_EUNSUPPORTED, "too many steps for one launch");
-    return dtype == GOOM_C64 ? bwd_shift_t<float>(ctx, H, G, shift, gt, T, d, batch) : bwd_shift_t<double>(ctx, H, G, shift, gt, T, d, batch);
+    return bwd_shift_t<float>(ctx, H, G, shift, gt, T, d, batch);
 }
 
 // One matrix for all steps, scan over the matrix itself: At [batch, d, d] = A^T, shift[b, s] = c_t, gt as above
@@ -455,11 +456,10 @@ template <typename R> static int bwd_grad_t(goom_ctx *ctx, const void *A, const 
 }
 
 int launch_affine_backward_gradients(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *mu, void *gA,
-                                     void *gb, void *gh0, long long T, int d, long long batch, int dtype)
+                                     void *gb, void *gh0, long long T, int d, long long batch)
 {
     if (batch * T > 0x7fffffffLL) return fail(ctx, GOOM_EUNSUPPORTED, "too many steps for one launch");
-    return dtype == GOOM_C64 ? bwd_grad_t<float>(ctx, A, bias, h0, H, mu, gA, gb, gh0, T, d, batch)
-                             : bwd_grad_t<double>(ctx, A, bias, h0, H, mu, gA, gb, gh0, T, d, batch);
+    return bwd_grad_t<float>(ctx, A, bias, h0, H, mu, gA, gb, gh0, T, d, batch);
 }
 
 // One matrix for all steps.  partial: [batch, nsplit, dp, dp] doubles (dp: d padded to 16, 32, 64 or 128); uv0: [batch, 2, d] doubles

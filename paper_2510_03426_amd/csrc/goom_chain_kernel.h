@@ -65,9 +65,7 @@ struct ChainArgs {
     // NULL, or [batch, steps] floats; the factor of step s is then the transpose of matrix steps - s of the array
     // `left` (any matrix for s = 0) with left_shift[s] added to every log-magnitude (-inf: a zero matrix)
     const float *left_shift;
-    // the matrix-vector walk over one matrix for all steps and the general kernel with GOOM bias vectors: NULL, or [batch, steps] floats
-    // (whole numbers); the bias of step s
-    // is then bias[s] e^(-io_shift[s]) and the state written for step s is h_s e^(+io_shift[s]): values far from 1 pass
+    // vector chains with GOOM biases: NULL, or [batch, steps] floats (whole numbers); the bias of step s is then bias[s] e^(-io_shift[s]) and the state written for step s is h_s e^(+io_shift[s]): values far from 1 pass
     // through GOOM arrays of float components with log-magnitudes of ordinary size
     const float *io_shift;
     // vector chains with one GOOM factor for all steps: NULL, or per batch item the factor converted beforehand (mantissas [DP][prepared_cols],
@@ -640,30 +638,21 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
         // and therefore exact; a reference exponent that is a few units off only moves the
         // mantissas' scale, never the represented value.
         //
-        // bias column (linear recurrence with bias): b_i, given as a GOOM or as a column
-        // of the factored left factor, is added to entry (i, bias_col) in the log2 domain.
-        const bool bias_lane = !FAST && a.bias_mode != 0 && slab_active && col == a.bias_col;
-        // bias and stored states rescaled by e^(-+io_shift[s]) (see ChainArgs): the shift joins the column's exponent, in double
-        const double ios = (!FAST && a.io_shift) ? (double)a.io_shift[item * a.steps + t0 + t] * kLog2e : 0.0;
+        // bias column (carries of the linear recurrence): b_i, a column of the factored left factor, is added to entry
+        // (i, bias_col) in the log2 domain.  (Biases given as GOOMs belong to vector chains and to the chunk products' bias wave.)
+        const bool bias_lane = !FAST && LEFT_FACT && a.bias_mode != 0 && slab_active && col == a.bias_col;
         auto bias_term = [&](int i, double &blog, bool &bneg) { // blog = log2|b_i| - ecol
             blog = kNegBig;
             bneg = false;
             if (i >= n_rows) return;
-            if (a.bias_mode == 1) {
-                const IO *bp = reinterpret_cast<const IO *>(a.bias) + ((size_t)(item * a.steps + t0 + t) * n_rows + i) * 2;
-                R br = bp[0];
-                if (br > kNegInf) blog = (double)br * kLog2e - ecol - ios; // (ios: the step's io_shift in powers of two, else 0)
-                bneg = Comp<R>::is_negative(bp[1]);
-            } else {
-                const unsigned char *src = left0 + t * a.left_step_stride;
-                const R *mp = reinterpret_cast<const R *>(src);
-                const double *ex = reinterpret_cast<const double *>(src + (size_t)DP * a.left_fact_cols * sizeof(R));
-                int lfc = a.left_fact_cols; // opaque, as in load_items
-                asm volatile("" : "+s"(lfc));
-                R bv = mp[(size_t)(i * lfc + d)];
-                if (bv != (R)0) blog = (double)Comp<R>::log2_abs(bv) + ex[d] - ecol;
-                bneg = bv < (R)0;
-            }
+            const unsigned char *src = left0 + t * a.left_step_stride;
+            const R *mp = reinterpret_cast<const R *>(src);
+            const double *ex = reinterpret_cast<const double *>(src + (size_t)DP * a.left_fact_cols * sizeof(R));
+            int lfc = a.left_fact_cols; // opaque, as in load_items
+            asm volatile("" : "+s"(lfc));
+            R bv = mp[(size_t)(i * lfc + d)];
+            if (bv != (R)0) blog = (double)Comp<R>::log2_abs(bv) + ex[d] - ecol;
+            bneg = bv < (R)0;
         };
 
         // column reference: cm = max_i of (binary exponent of the entry) + n_i
@@ -752,7 +741,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
                     const int i = 16 * mt + Comp<R>::row_of(g, v);
                     const R x = acc[mt][v];
                     if (want_out && i < n_rows) {
-                        const R re = Comp<R>::out_re(x, nv[v], ecol + ios);
+                        const R re = Comp<R>::out_re(x, nv[v], ecol);
                         const IO im = x < (R)0 ? Comp<IO>::pi() : (IO)0;
                         IO *o = outp + (size_t)(i * mo + col) * 2;
                         if (sizeof(IO) == 4) {
@@ -780,7 +769,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
                     const R xb = (col_nonzero && blog > kNegBig) ? exp2_of<R>(blog - (double)cm) : (R)0;
                     const R xs = xa + (bneg ? -xb : xb);
                     if (want_out && i < n_rows) {
-                        const R re = Comp<R>::out_re(xs, cms, ecol + ios);
+                        const R re = Comp<R>::out_re(xs, cms, ecol);
                         const IO im = xs < (R)0 ? Comp<IO>::pi() : (IO)0;
                         IO *o = outp + (size_t)(i * mo + col) * 2;
                         o[0] = (IO)re;
@@ -834,6 +823,7 @@ template <typename R, int DP, int NW, int LEFT_FACT, bool FAST, typename IO = R>
 template <typename R, int LEFT_FACT, typename IO = R> int dispatch(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label)
 {
     const bool fast = args.n == dp && args.d == dp && args.m == 16 * nw && args.bias_mode == 0;
+    if (!LEFT_FACT && args.bias_mode) return goom::fail(ctx, GOOM_EUNSUPPORTED, "a bias given as GOOMs: vector chains and chunk products of float d = 64 only");
 #define GOOM_CASE(DPV, NWV)                                                                           \
     if (dp == DPV && nw == NWV)                                                                       \
         return fast ? launch_one<R, DPV, NWV, LEFT_FACT, true, IO>(ctx, args, grid, label)            \

@@ -168,9 +168,9 @@ int launch_matrix_probe(goom_ctx *ctx, void *sink, long long iters, int dtype);
 int launch_to_goom_backward(goom_ctx *ctx, const void *x, const void *g, void *gx, size_t n, int dtype, double eps);
 int launch_scaled_exp_backward(goom_ctx *ctx, const void *scaled, const void *g, void *gre, size_t n, int dtype);
 int launch_from_goom_backward(goom_ctx *ctx, const void *y, const void *gx, void *g, size_t n, int dtype, double eps);
-int launch_affine_backward_prepare(goom_ctx *ctx, const void *H, const void *G, float *shift, void *gt, long long T, int d, long long batch, int dtype);
+int launch_affine_backward_prepare(goom_ctx *ctx, const void *H, const void *G, float *shift, void *gt, long long T, int d, long long batch);
 int launch_affine_backward_gradients(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *mu, void *gA,
-                                     void *gb, void *gh0, long long T, int d, long long batch, int dtype);
+                                     void *gb, void *gh0, long long T, int d, long long batch);
 // goom_lmme_tall.hip: A [batch, n, d] of many rows against B [batch, d, m] with d, m <= 64 (float components)
 bool lmme_tall_applies(int n, int d, int m, int dtype);
 int launch_lmme_tall(goom_ctx *ctx, const void *A, const void *B, void *Cm, long long batch, int n, int d, int m);

@@ -838,7 +838,7 @@ def test_scaled_exponentiation(G, oracle, ctype):
     (4000, 16, 2, 0, np.complex64, False, 1.3),    # magnitudes far outside float range
     (500, 32, 2, 25, np.complex64, True, 1.0),     # constant matrix
     (400, 64, 2, 20, np.complex64, True, 1.0),     # constant 64 x 64 matrix: scaled states by the walk
-    (64, 8, 2, 0, np.complex64, False, 1.05),      # through GOOM states in the workspace
+    (64, 8, 2, 0, np.complex64, False, 1.05),      # scaled states by the vector chains, a single chunk
     (257, 64, 1, 40, np.complex64, False, 1.05),
     (200, 16, 2, 16, np.complex128, False, 1.05),
     (40, 32, 2, 0, np.complex64, False, 1.05),     # a single chunk
@@ -1211,7 +1211,7 @@ def test_signed_log_add(G, oracle, ctype):
 @pytest.mark.parametrize("T,d,batch,chunk,ctype,gain,cap", [
     (3000, 32, 3, 0, np.complex64, 1.02, 0.3), (2000, 32, 2, 0, np.complex64, 0.9, 0.05), (500, 16, 2, 7, np.complex64, 1.02, 0.07),
     (100, 8, 2, 9, np.complex64, 1.02, 0.02), (400, 32, 1, 50, np.complex128, 1.02, 0.002), (64, 32, 2, 0, np.complex64, 1.02, 0.02),
-    (4100, 32, 1, 1024, np.complex64, 0.9, 0.05), (700, 16, 2, 64, np.complex64, 0.9, 0.05),  # (chunk powers A^L in two stages: L = 32 * 32, 16 * 4)
+    (4100, 32, 1, 1024, np.complex64, 0.9, 0.05), (700, 16, 2, 64, np.complex64, 0.9, 0.05),  # (chunk powers A^L of long and short chunks)
     (600, 64, 2, 0, np.complex64, 1.02, 0.1), (130, 64, 1, 16, np.complex64, 0.9, 0.05)])  # (d = 64: the matrix in registers)
 def test_affine_scan_time_invariant(G, oracle, T, d, batch, chunk, ctype, gain, cap):
     # one matrix per sequence, applied at every step (the paper's state-space layer): against the oracle

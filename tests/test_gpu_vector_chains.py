@@ -5,13 +5,13 @@ import numpy as np
 import pytest
 
 import synthetic_inputs as si
-from test_gpu_parity import G, compare, dev, host, say, tolerance, with_sensitivity  # noqa: F401
+from test_gpu_parity import G, compare, dev, host, lorenz_chain, say, tolerance, with_sensitivity  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
 # (random probes of an entry's sensitivity: two underestimate it tenfold about once in 10^4 entries, and there are many here)
 PROBES = 8
-SIZES = [1, 3, 15, 16, 17, 31, 33, 47, 63, 64, 65, 100, 127, 128]
+SIZES = [1, 3, 8, 15, 16, 17, 24, 31, 32, 33, 47, 48, 63, 64, 65, 96, 100, 127, 128]
 
 
 def inputs(oracle, seed, batch, T, d, ctype, constant):
@@ -278,6 +278,35 @@ def test_adjoint_smallest_example_far_apart(G):  # noqa: F811
         ga, gb, gh = G.affine_scan_backward(dev(A), dev(np.full((1, 1, 2), -np.inf, dtype=ctype)), dev(h[:, None]), dev(np.ones((1, 1, 2), dtype=comp)), dev(h))
         assert np.allclose(host(ga)[0, 0], np.eye(2), rtol=1e-6, atol=0), host(ga)
         assert np.all(host(gb) == 0) and np.allclose(host(gh), 1.0, rtol=1e-6)
+        # an infinite state divides its gradient away (no NaN), and leaves the others'
+        h[0, 1] = np.inf
+        _, gb, _ = G.affine_scan_backward(dev(A), dev(np.zeros((1, 1, 2), dtype=ctype)), dev(h[:, None]), dev(np.ones((1, 1, 2), dtype=comp)))
+        assert np.array_equal(host(gb)[0, 0], [1, 0]), host(gb)
+
+
+# the batches from which on sequences are walked start to end (no chunks), and one fewer
+@pytest.mark.parametrize("ctype,d,line", [(np.complex64, 8, 512), (np.complex64, 24, 192), (np.complex64, 64, 96), (np.complex64, 100, 56),
+                                          (np.complex128, 8, 384), (np.complex128, 24, 96), (np.complex128, 48, 48)])
+def test_batches_around_the_line(G, oracle, ctype, d, line):  # noqa: F811
+    comp, T = np.float32 if ctype == np.complex64 else np.float64, 34
+    Az, bz, h0 = inputs(oracle, 390 + d, line, T, d, ctype, False)
+    fn = lambda a_, b_, h_: oracle.affine_scan(a_, b_, h0=h_, return_kappa=True)
+    re, sg, kap, well = with_sensitivity(fn, [Az, bz, h0], comp)  # (two probes: one entry in 10^4 may be ten times as sensitive as they say)
+    for batch in (line, line - 1):
+        say(f"batch {batch} T={T} d={d} {np.dtype(ctype).name}")
+        A_, b_, h_ = dev(Az[:batch]), dev(bz[:batch]), dev(h0[:batch])
+        G.profile_enable(True)
+        Hd = G.affine_scan(A_, b_, h_)
+        labels = [k for k, _ in G.profile_records()]
+        G.profile_enable(False)
+        assert (labels == ["affine_single_chunk"]) == (batch == line), labels
+        compare(host(Hd), re[:batch], sg[:batch], kap[:batch], name=f"batch {batch}", max_ill_fraction=0.25, well=well[:batch], max_out_fraction=1e-4, hard_factor=10.0)
+        H = host(Hd)
+        Gh = (si.normal_f32(si.BASE_SEED + 391, 10, batch * T * d).reshape(batch, T, d) * oracle.scaled_exp(H)[0]).astype(comp)
+        got = [host(v).astype(np.float64) for v in G.affine_scan_backward(A_, b_, Hd, dev(Gh), h_)]
+        want = oracle.affine_scan_backward(Az[:batch], bz[:batch], Gh, h0=h0[:batch], h=H)[:3]
+        for name, g, w in zip(("A", "bias", "h0"), got, want):
+            assert np.linalg.norm(g - w) <= (1e-3 if comp == np.float32 else 1e-10) * np.linalg.norm(w), (name, np.linalg.norm(g - w) / np.linalg.norm(w))
 
 
 # more chunks than one chain carries: 192 with one matrix for all steps, 128 in the adjoint pass (there by default too), grouped from there on
@@ -339,3 +368,20 @@ def test_reset_scan_in_spans(G, oracle, T, d, batch, chunk, ctype):  # noqa: F81
         if T % every:
             grown += np.log(np.abs(np.diag(np.linalg.qr(x)[1])))
         assert np.abs(growth[q] - grown).max() <= 1e-8 * max(1.0, np.abs(grown).max())
+
+
+# an initial state and the policy that looks at the columns, in spans: against the oracle's sequential walk
+@pytest.mark.parametrize("T,d,chunk,policy,thr", [(400, 8, 64, 0, 0.9), (300, 33, 64, 0, 0.97), (200, 20, 64, 1, 0.99), (130, 70, 64, 1, 0.99), (300, 12, 0, 1, 0.99)])
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+def test_reset_scan_in_spans_from_an_initial_state(G, oracle, T, d, chunk, policy, thr, ctype):  # noqa: F811
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    Jz = oracle.to_goom(lorenz_chain(T, d, 63).astype(comp))
+    S0 = oracle.to_goom(si.normal_init(si.BASE_SEED + 63, d, d).astype(comp))
+    say(f"reset scan in spans from S0 T={T} d={d} chunk={chunk} policy={policy} {np.dtype(ctype).name}")
+    states, flags, growth = (host(v) for v in G.scan_reset(dev(Jz), dev(S0), chunk_len=chunk, policy=policy, cos_threshold=thr))
+    re, sg, oflag, ogrowth = oracle.reset_scan(Jz, S0, check_every=chunk or 128, policy=policy, cos_threshold=thr)
+    assert np.array_equal(flags, oflag) and oflag.sum() > 0
+    got, want = (np.exp(r.astype(np.float64)) * np.where(s, -1.0, 1.0) for r, s in ((states.real, states.imag > 1.5), (re, sg)))
+    # (a state's float log-magnitudes are rounded once; the double factorisation is good to cond^2 2^-53 of a column)
+    assert np.all(np.abs(got - want).max(axis=(1, 2)) <= (2e-6 if comp == np.float32 else 1e-9) * np.abs(want).max(axis=(1, 2)))
+    assert np.abs(growth - ogrowth).max() <= 1e-8 * max(1.0, np.abs(ogrowth).max())

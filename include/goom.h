@@ -254,7 +254,9 @@ typedef struct goom_reset_opts {
  * happened); growth: NULL or [batch, d] doubles: per column, the sum over resets of
  * log R_kk + log(column norm), plus the same for the final state, i.e. the total
  * log-growth of the k-th orthogonalised direction.
- * workspace: goom_scan_reset_workspace_bytes(...) bytes. */
+ * workspace: goom_scan_reset_workspace_bytes(...) bytes.  (Few chunks of a short chain are taken in spans of 16 steps; a
+ * workspace without the room for that, the query's last part, is accepted, and the double products are then associated
+ * in another order: the results' last places differ.) */
 int goom_scan_reset(goom_ctx *ctx, const void *J, const void *S0, void *states,
                     uint8_t *reset_flags, double *growth, int64_t T, int d, int64_t batch,
                     int dtype, const goom_reset_opts *opts, void *workspace,
@@ -334,9 +336,10 @@ int goom_scaled_exp(goom_ctx *ctx, const void *z, void *scaled, void *logscale, 
  * H: [batch, T, d].  Scanned as products of the augmented matrices [A | bias; 0 | 1]
  * whose last row is kept implicit.  A batch of 96 sequences or more with a matrix per step,
  * float components, d = 32 and opts->chunk_len == 0 is not scanned: every sequence is walked
- * start to end by one workgroup, every matrix read once, and so are large batches of other sizes (the results are those of a sequential
+ * start to end by one workgroup, every matrix read once (the results are those of a sequential
  * float evaluation; whole-number exponents are kept within +-2^28, i.e. log-magnitudes within
- * +-1.8e8, beyond which a float log-magnitude resolves nothing anyway).
+ * +-1.8e8, beyond which a float log-magnitude resolves nothing anyway).  Large batches of other
+ * sizes are walked start to end as well (no such limit).
  * workspace: goom_affine_scan_workspace_bytes(...) bytes. */
 #define GOOM_AFFINE_TIME_INVARIANT 0x1u /* goom_scan_opts.flags: one matrix per batch item, A: [batch, d, d],
                                            applied at every step (the paper's state-space layer has constant
@@ -427,8 +430,8 @@ size_t goom_scan_backward_workspace_bytes(int64_t T, int d, int m, int64_t batch
 /* Backward of goom_affine_scan (time-varying matrices).  grad_H[b, t, i] = dL / d Re H[b, t, i] for some loss L;
  * the call returns dL / d Re A[b, t, i, j], dL / d Re bias[b, t, i] and dL / d Re h0[b, j], as reals of the
  * component type.  The adjoints of the state values, lam_t = grad_H_t / h_t + A_{t+1}^T lam_{t+1}, are a
- * recurrence of the same kind in reverse time over the transposed matrices; they are computed over GOOMs by the
- * forward scan on transposed, time-reversed operands (they shrink as fast as the states grow), and
+ * recurrence of the same kind in reverse time over the transposed matrices (they shrink as fast as the states grow):
+ * walked backwards, an exponent to every entry, or by the forward scan itself (float d = 16 and 32 in several chunks); and
  *     grad_A[b, t, i, j] = lam_t[i] A_t[i, j] h_{t-1}[j],      grad_bias[b, t, i] = lam_t[i] b_t[i],
  *     grad_h0[b, j] = h0[j] sum_i lam_0[i] A_0[i, j].
  * This is the limit eps -> 0 of the paper's redefined derivatives, which differ from the ordinary ones only where

@@ -91,8 +91,8 @@ __global__ __launch_bounds__(NW * 64) void vec_adjoint_kernel(AdjointArgs a)
     // The largest factors with gradients: the next factor is loaded once this one's registers are done with.  (Held beside them registers
     // are spilled, and a reload waits for the gradients' stores: 18 us a step of float d = 128 where 7.4 are taken now.)
     constexpr bool LATE = GRAD && DP == 128;
-    // A term of the product is a row's mantissa, an entry on its row's power of two and a wave's sum on the largest wave's: three factors
-    // that may each lie this far below 1 before the type's smallest normal number is in sight.
+    // A term of the product is a row's mantissa times an entry on its row's power of two, a gradient also has a state's entry on the
+    // largest one's: each may lie this far below 1 before the type's smallest normal number is in sight.
     constexpr V kSpread = sizeof(V) == 4 ? (V)40 : (V)320;
     typedef V V2 __attribute__((ext_vector_type(2)));
     __shared__ __align__(16) V2 part[2][NW][DP]; // the waves' sums of every column: mantissa and exponent

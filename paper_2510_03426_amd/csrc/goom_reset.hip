@@ -18,10 +18,10 @@
 // triangular factors taken at the resets: triangular factors multiply, so their diagonals
 // accumulate exactly as in the step-by-step method).
 //
-// One wave per batch item, matrices in registers, float arithmetic with double accumulation
-// of the logarithms.  The chain of chunks is inherently serial (each reset depends on the
-// previous one), so this phase is latency bound: what counts is the length of the dependent
-// instruction chain per chunk, which is why it runs without a single workgroup barrier.
+// The chain of chunks is inherently serial (each reset depends on the previous one), so this
+// phase is latency bound: what counts is the length of the dependent instruction chain per
+// chunk.  One wave per batch item holds the whole state in registers (policies that look at a
+// state first), or one wave per panel of it, the panels' waves a chunk apart (policy "always").
 #include <cstring>
 
 #include "goom_internal.h"
@@ -50,6 +50,7 @@ struct ResetArgs {
 };
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
 __device__ inline f4 mfma4(float x, float y, f4 acc) { return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0); }
 
@@ -232,15 +233,8 @@ template <int DP> struct WaveD {
     static constexpr int LDT = DP + 2;  // row stride of the chunk product (doubles)
     static constexpr int LDQ = 18;      // row stride of a finished panel
     double tile[DP * LDT]; // chunk product, rows in order, columns in perm16 order
-    double rrow[2][16];   // row k of the panel's Gram matrix at step k, entry j at position j
-    double rperm[2][16];  // the same in perm16 order
-    double qcol[2][DP];   // column k of the panel at step k, rows in perm16 order
+    double gram[16 * 18]; // a panel's Gram matrix on its way into the lanes
     double diag[DP];      // diagonal of the Gram matrix (selection by cosines)
-    // blocked elimination (panels of up to 32 rows only): the four pivot rows of a block, entry j at position j; the
-    // same in perm16 order; the four pivot columns of the panel, rows in perm16 order
-    double brow[DP <= 32 ? 4 : 1][16];
-    double bperm[DP <= 32 ? 4 : 1][16];
-    double bcol[DP <= 32 ? 4 : 1][DP];
     double qpanel[DP / 16 > 1 ? DP / 16 - 1 : 1][DP * LDQ]; // finished panels of Q: [row][column within the panel, perm16 order]
 };
 
@@ -254,127 +248,211 @@ __device__ inline double read_lane_d(double v, int lane)
     return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// 1 / x and 1 / sqrt(x) to double precision from the float hardware approximations (x within float range)
+// 1 / x and 1 / sqrt(x) to double precision: the hardware's double estimates (measured: 1 - x r up to 5e-8, 1 - x r^2 up to 1e-7)
+// and one step of third order
 __device__ inline double rcp_d(double x)
 {
-    double r = (double)__builtin_amdgcn_rcpf((float)x);
-    r = r * (2.0 - x * r);
-    return r * (2.0 - x * r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 __device__ inline double rsqrt_d(double x)
 {
-    double r = (double)__builtin_amdgcn_rsqf((float)x);
-    r = r * (1.5 - 0.5 * x * r * r);
-    return r * (1.5 - 0.5 * x * r * r);
+    const double r = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * r, r, 1.0);
+    return fma(r * e, fma(e, 0.375, 0.5), r);
 }
 
-// elimination of one panel (see eliminate_panel above), columns in double
-template <int DP, typename S> __device__ void eliminate_panel_d(d4 &G, d4 (&Zp)[DP / 16], double &piv, S &s, int g, int c)
+// lane K of every row of sixteen lanes, to all lanes of that row
+template <int K> __device__ inline double row_bcast(double x)
 {
-    constexpr int KT = DP / 16;
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u & 0xffffffffull), 0x150 + K, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u >> 32), 0x150 + K, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// x[i] += (src of lane i of the row of sixteen) * mul, for i = FROM .. 15: one instruction each, the broadcast being part of
+// the multiply-add.  (A register that a vector instruction has just written may be read across lanes two issue slots later:
+// every block opens with that wait, since the compiler does not look into it.)
+#define GOOM_FMAC_BCAST(ACC, LANE) "v_fmac_f64_dpp " ACC ", %[s], %[m] row_newbcast:" LANE " row_mask:0xf bank_mask:0xf\n\t"
+template <int FROM> __device__ inline void fmac_bcast(double (&x)[16], double src, double mul)
+{
+    if constexpr (FROM + 8 <= 16) {
+        asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k0]") GOOM_FMAC_BCAST("%1", "%[k1]") GOOM_FMAC_BCAST("%2", "%[k2]") GOOM_FMAC_BCAST("%3", "%[k3]")
+                GOOM_FMAC_BCAST("%4", "%[k4]") GOOM_FMAC_BCAST("%5", "%[k5]") GOOM_FMAC_BCAST("%6", "%[k6]") GOOM_FMAC_BCAST("%7", "%[k7]")
+            : "+v"(x[FROM]), "+v"(x[FROM + 1]), "+v"(x[FROM + 2]), "+v"(x[FROM + 3]), "+v"(x[FROM + 4]), "+v"(x[FROM + 5]), "+v"(x[FROM + 6]), "+v"(x[FROM + 7])
+            : [s] "v"(src), [m] "v"(mul), [k0] "n"(FROM), [k1] "n"(FROM + 1), [k2] "n"(FROM + 2), [k3] "n"(FROM + 3), [k4] "n"(FROM + 4), [k5] "n"(FROM + 5),
+              [k6] "n"(FROM + 6), [k7] "n"(FROM + 7));
+        fmac_bcast<FROM + 8>(x, src, mul);
+    } else if constexpr (FROM + 4 <= 16) {
+        asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k0]") GOOM_FMAC_BCAST("%1", "%[k1]") GOOM_FMAC_BCAST("%2", "%[k2]") GOOM_FMAC_BCAST("%3", "%[k3]")
+            : "+v"(x[FROM]), "+v"(x[FROM + 1]), "+v"(x[FROM + 2]), "+v"(x[FROM + 3])
+            : [s] "v"(src), [m] "v"(mul), [k0] "n"(FROM), [k1] "n"(FROM + 1), [k2] "n"(FROM + 2), [k3] "n"(FROM + 3));
+        fmac_bcast<FROM + 4>(x, src, mul);
+    } else if constexpr (FROM + 2 <= 16) {
+        asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k0]") GOOM_FMAC_BCAST("%1", "%[k1]")
+            : "+v"(x[FROM]), "+v"(x[FROM + 1])
+            : [s] "v"(src), [m] "v"(mul), [k0] "n"(FROM), [k1] "n"(FROM + 1));
+        fmac_bcast<FROM + 2>(x, src, mul);
+    } else if constexpr (FROM + 1 <= 16) {
+        asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k0]") : "+v"(x[FROM]) : [s] "v"(src), [m] "v"(mul), [k0] "n"(FROM));
+    }
+}
+
+// over the four lanes that hold a column (lane, lane ^ 16, lane ^ 32, lane ^ 48): the largest / the sum
+__device__ inline unsigned column_max(unsigned x)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = max((unsigned)a[0], (unsigned)a[1]);
+    a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return max((unsigned)a[0], (unsigned)a[1]);
+}
+__device__ inline double column_sum(double x)
+{
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int gk = k % 4, vk = k / 4;
-        const int buf = k & 1;
-        double *rrow = s.rrow[buf];
-        double *rperm = s.rperm[buf];
-        double *qcol = s.qcol[buf];
-        if (g == gk) {
-            const double r = c > k ? G[vk] : 0.0;
-            rrow[c] = r;
-            rperm[((c & 3) << 2) | (c >> 2)] = r;
+    for (int half = 0; half < 2; ++half) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+        const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
+        const auto l = half == 0 ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false) : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = half == 0 ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false) : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        x = __builtin_bit_cast(double, ((unsigned long long)h[0] << 32) | l[0]) + __builtin_bit_cast(double, ((unsigned long long)h[1] << 32) | l[1]);
+    }
+    return x;
+}
+// binary exponent of the largest entry of a column (rows in Z and in the three other lanes that hold it): entries times 2^-it lie
+// below 1.  (An empty column: -1022, which changes nothing of it.)
+template <int KT> __device__ inline int column_exponent(const d4 (&Z)[KT])
+{
+    unsigned key = 0;
+#pragma unroll
+    for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const double x = Z[mt][v]; // (a vector's element inside the cast would be read as element 0)
+            key = max(key, (unsigned)(__builtin_bit_cast(unsigned long long, x) >> 32) & 0x7fffffffu);
         }
-        if (c == k) {
-#pragma unroll
-            for (int mt = 0; mt < KT; ++mt) *reinterpret_cast<d4 *>(&qcol[16 * mt + 4 * g]) = Zp[mt];
+    return (int)(column_max(key) >> 20) - 1022;
+}
+
+constexpr int kPanelLd = 18; // row stride of a 16-column panel (or of its Gram matrix) in LDS, in doubles
+
+// One pivot of the elimination below (by recursion, so that every index is a constant).  neg: minus the multipliers of step K.
+// The order is the source's: the next pivot's row is updated first, and its reciprocal, a chain of dependent instructions, is
+// formed between the updates that nothing waits for.
+template <int K, int NR> __device__ inline void eliminate_from(double (&G)[16], double (&z)[NR][16], double neg, double &piv, int c)
+{
+    if constexpr (K < 15) {
+        asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k]") : "+v"(G[K + 1]) : [s] "v"(G[K]), [m] "v"(neg), [k] "n"(K + 1));
+        __builtin_amdgcn_sched_barrier(0);
+        fmac_bcast<K + 1>(z[0], neg, z[0][K]);
+        __builtin_amdgcn_sched_barrier(0);
+        const double pivot = row_bcast<K + 1>(G[K + 1]);
+        const double r = __builtin_amdgcn_rcp(pivot);
+        __builtin_amdgcn_sched_barrier(0);
+        fmac_bcast<K + 2>(G, G[K], neg);
+        __builtin_amdgcn_sched_barrier(0);
+        const double e = fma(-pivot, r, 1.0);
+        if constexpr (NR > 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            fmac_bcast<K + 1>(z[1], neg, z[1][K]);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        const double pivot = read_lane_d(G[vk], 16 * gk + k);
-        if (c == k) piv = pivot;
-        const double inv = pivot > 1.0e-280 ? rcp_d(pivot) : 0.0;
-        wave_sync();
-        const double tj = rrow[c] * inv;
-        const d4 ri = *reinterpret_cast<const d4 *>(&rperm[4 * g]);
-        G -= ri * tj;
+        piv = c == K + 1 ? G[K + 1] : piv;
+        const double inv = fma(r, fma(e, e, e), r);
+        eliminate_from<K + 1, NR>(G, z, -(G[K + 1] * (pivot > 1.0e-280 ? inv : 0.0)), piv, c);
+    }
+}
+
+// Orthonormal factor of one panel (DP rows, 16 columns, Zp in the matrix instruction's layout) by its Gram matrix G, in
+// square-root-free form: step k subtracts (G_kj / p_k) times row / column k from every later one, p_k = G_kk being the pivot; at
+// the end the columns are scaled by 1 / sqrt(p).  The panel leaves as rows: lane r holds row r (and r + 64) in z, and `panel`
+// ([DP][18], columns in perm16 order) receives them.  piv: the pivot of column c.
+//
+// A chain of sixteen pivots is all latency, so nothing in it leaves the registers: every row of sixteen lanes holds the whole
+// Gram matrix, lane c its column c, every lane one row of the panel; what a step needs of other lanes is one lane's value for
+// sixteen others, which the multiply-add itself can fetch (at half its rate: 9 cycles; a broadcast into a register and two
+// multiply-adds that share it cost the same, and the compiler then puts the updates after the chain instead of into it).  185 cycles a
+// pivot (560 when rows and columns of the step went through LDS).
+//
+// A pivot that comes out negative is a column that is nothing but rounding beside its norm: in a first pass it stays as it is,
+// its residual, with a pivot of 1, and the caller (told so) factors once more, where the residual stands for itself; in the
+// `last` one it is dropped, like a column that is zero.
+template <int DP> __device__ inline bool factor_panel_rows(const d4 (&Zp)[DP / 16], double &piv, double *panel, double *gram,
+                                                           double (&z)[DP > 64 ? 2 : 1][16], int lane, bool last)
+{
+    constexpr int KT = DP / 16, NR = DP > 64 ? 2 : 1;
+    const int g = lane >> 4, c = lane & 15;
+    const int pc = ((c & 3) << 2) | (c >> 2);
+    wave_sync();
 #pragma unroll
-        for (int mt = 0; mt < KT; ++mt) {
-            const d4 zk = *reinterpret_cast<const d4 *>(&qcol[16 * mt + 4 * g]);
-            Zp[mt] -= zk * tj;
+    for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) panel[(16 * mt + 4 * v + g) * kPanelLd + pc] = Zp[mt][v];
+    wave_sync();
+    const int row = lane & (DP < 64 ? DP - 1 : 63);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int q = 0; q < 16; q += 2) { // positions q, q + 1 hold columns 4 (q % 4) + q / 4 and the same plus 4
+            const d2 x = *reinterpret_cast<const d2 *>(&panel[(row + 64 * r) * kPanelLd + q]);
+            z[r][4 * (q & 3) + (q >> 2)] = x[0];
+            z[r][4 * ((q + 1) & 3) + (q >> 2)] = x[1];
+        }
+    d4 Gt = {0., 0., 0., 0.};
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Gt = mfma8(Zp[kt][v], Zp[kt][v], Gt);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gram[(4 * v + g) * kPanelLd + c] = Gt[v];
+    wave_sync();
+    double G[16];
+#pragma unroll
+    for (int j = 0; j < 16; j += 2) { // (symmetric to the last bit: row c is column c)
+        const d2 x = *reinterpret_cast<const d2 *>(&gram[c * kPanelLd + j]);
+        G[j] = x[0];
+        G[j + 1] = x[1];
+    }
+    const double first = row_bcast<0>(G[0]);
+    piv = G[0];
+    eliminate_from<0, NR>(G, z, -(G[0] * (first > 1.0e-280 ? rcp_d(first) : 0.0)), piv, c);
+    const bool live = piv > 1.0e-280, open = !live && !last && piv != 0.0;
+    const double sc = live ? rsqrt_d(piv) : open ? 1.0 : 0.0;
+    piv = open ? 1.0 : piv;
+    const double cols[16] = {row_bcast<0>(sc),  row_bcast<1>(sc),  row_bcast<2>(sc),  row_bcast<3>(sc), row_bcast<4>(sc),  row_bcast<5>(sc),
+                             row_bcast<6>(sc),  row_bcast<7>(sc),  row_bcast<8>(sc),  row_bcast<9>(sc), row_bcast<10>(sc), row_bcast<11>(sc),
+                             row_bcast<12>(sc), row_bcast<13>(sc), row_bcast<14>(sc), row_bcast<15>(sc)};
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) z[r][j] *= cols[j];
+#pragma unroll
+        for (int q = 0; q < 16; q += 2) {
+            const d2 x = {z[r][4 * (q & 3) + (q >> 2)], z[r][4 * ((q + 1) & 3) + (q >> 2)]};
+            *reinterpret_cast<d2 *>(&panel[(row + 64 * r) * kPanelLd + q]) = x;
         }
     }
     wave_sync();
+    return __builtin_amdgcn_ballot_w64(open) != 0;
 }
 
-// The same elimination four pivots at a time (panels of up to 32 rows): the four pivot rows of the Gram matrix and
-// the four pivot columns of the panel make one trip through LDS, and every lane then carries out the four steps on
-// copies of its own (the 4 x 4 block on the diagonal, the pivot rows at its own column and at the columns whose
-// numbers are its rows', the pivot columns at its rows): the same multiply-adds on the same numbers in the same
-// order as one pivot at a time, four times fewer waits for LDS.
-template <int DP> __device__ void eliminate_panel_blocked(d4 &G, d4 (&Zp)[DP / 16], double &piv, WaveD<DP> &s, int g, int c)
+// a panel from LDS, in the matrix instruction's layout (rows 16 mt + 4 v + g of column c)
+template <int DP> __device__ inline void panel_tiles(d4 (&Zp)[DP / 16], const double *panel, int g, int c)
 {
-    constexpr int KT = DP / 16;
     const int pc = ((c & 3) << 2) | (c >> 2);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        wave_sync();
-        // row 4 b + g of the Gram matrix at column c; columns 4 b + j of the panel (from the lanes that hold them)
-        s.brow[g][c] = G[b];
-        s.bperm[g][pc] = G[b];
-        if ((c >> 2) == b) {
+    for (int mt = 0; mt < DP / 16; ++mt)
 #pragma unroll
-            for (int mt = 0; mt < KT; ++mt) *reinterpret_cast<d4 *>(&s.bcol[c & 3][16 * mt + 4 * g]) = Zp[mt];
-        }
-        wave_sync();
-        double a[4];   // pivot row j at this lane's column
-        d4 P[4];       // pivot row j at columns 4 v + g
-        d4 B[4];       // pivot row j at columns 4 b + i
-        d4 zb[4][KT];  // pivot column j at this lane's rows
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            a[j] = s.brow[j][c];
-            P[j] = *reinterpret_cast<const d4 *>(&s.bperm[j][4 * g]);
-            B[j] = *reinterpret_cast<const d4 *>(&s.brow[j][4 * b]);
-#pragma unroll
-            for (int mt = 0; mt < KT; ++mt) zb[j][mt] = *reinterpret_cast<const d4 *>(&s.bcol[j][16 * mt + 4 * g]);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int k = 4 * b + j;
-            const double pivot = B[j][j];
-            if (c == k) piv = pivot;
-            const double inv = pivot > 1.0e-280 ? rcp_d(pivot) : 0.0;
-            // row k beyond the pivot, as the one-pivot form stores it: zero up to and including column k
-            const double rc = c > k ? a[j] : 0.0;
-            const double tj = rc * inv;
-            d4 ri;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) ri[v] = (4 * v + g > k) ? P[j][v] : 0.0;
-            const d4 rinv = ri * inv; // (row k times 1 / pivot: the multipliers of the columns 4 v + g)
-            G -= ri * tj;
-#pragma unroll
-            for (int mt = 0; mt < KT; ++mt) Zp[mt] -= zb[j][mt] * tj;
-            // the later pivot rows and columns of the block, brought up to date the same way
-#pragma unroll
-            for (int i = j + 1; i < 4; ++i) {
-                const double rki = B[j][i];         // row k at column 4 b + i (> k)
-                const double ti = rki * inv;        // the multiplier of column 4 b + i
-                a[i] -= rki * tj;                   // entry (4 b + i, c): row factor times this column's multiplier
-                P[i] -= rinv * rki;                 // entries (4 b + i, 4 v + g): row factor times those columns' multipliers
-#pragma unroll
-                for (int i2 = j + 1; i2 < 4; ++i2) B[i][i2] -= rki * (B[j][i2] * inv);
-#pragma unroll
-                for (int mt = 0; mt < KT; ++mt) zb[i][mt] -= zb[j][mt] * ti;
-            }
-        }
-    }
-    wave_sync();
+        for (int v = 0; v < 4; ++v) Zp[mt][v] = panel[(16 * mt + 4 * v + g) * kPanelLd + pc];
 }
 
 // QR of Z in place (Z <- Q), panel by panel; piv[nt] = squared diagonal of R for column 16 nt + c.  Returns the
 // largest ratio (squared column norm) / pivot, a measure of cond(Z)^2.  Before the factorisation every column
-// is scaled by a power of two to a largest entry near 1 (cexp receives the exponents), so that pivots stay
-// inside the range of the float reciprocal estimates.
-template <int DP> __device__ double qr_panels_d(d4 (&Z)[DP / 16][DP / 16], double (&piv)[DP / 16], double (&cexp)[DP / 16], WaveD<DP> &s, int g, int c)
+// is scaled by a power of two to a largest entry near 1 (cexp receives the exponents).
+template <int DP> __device__ double qr_panels_d(d4 (&Z)[DP / 16][DP / 16], double (&piv)[DP / 16], double (&cexp)[DP / 16], WaveD<DP> &s, int g, int c, bool last)
 {
+    bool open = false;
     constexpr int KT = DP / 16;
     constexpr int LDQ = WaveD<DP>::LDQ;
     double norm2[KT];
@@ -423,27 +501,12 @@ template <int DP> __device__ double qr_panels_d(d4 (&Z)[DP / 16][DP / 16], doubl
                     for (int v = 0; v < 4; ++v) Z[p][mt] = mfma8(av[v], R[v], Z[p][mt]);
                 }
             }
-        d4 G = {0., 0., 0., 0.};
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) G = mfma8(Z[p][kt][v], Z[p][kt][v], G);
-        piv[p] = 1.0;
-        if constexpr (DP <= 32)
-            eliminate_panel_blocked<DP>(G, Z[p], piv[p], s, g, c);
-        else
-            eliminate_panel_d<DP>(G, Z[p], piv[p], s, g, c);
-        const double sc = piv[p] > 1.0e-280 ? rsqrt_d(piv[p]) : 0.0;
-#pragma unroll
-        for (int mt = 0; mt < KT; ++mt) Z[p][mt] *= sc;
-        if (p + 1 < KT) {
-#pragma unroll
-            for (int mt = 0; mt < KT; ++mt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) s.qpanel[p][(16 * mt + 4 * v + g) * LDQ + (((c & 3) << 2) | (c >> 2))] = Z[p][mt][v];
-            wave_sync();
-        }
+        double rows[1][16];
+        double *panel = p + 1 < KT ? s.qpanel[p] : s.tile; // (the chunk product's tile is free by now)
+        open |= factor_panel_rows<DP>(Z[p], piv[p], panel, s.gram, rows, (g << 4) | c, last);
+        panel_tiles<DP>(Z[p], panel, g, c);
     }
+    wave_sync();
     double worst = 1.0;
 #pragma unroll
     for (int nt = 0; nt < KT; ++nt) {
@@ -452,7 +515,7 @@ template <int DP> __device__ double qr_panels_d(d4 (&Z)[DP / 16][DP / 16], doubl
     }
 #pragma unroll
     for (int sft = 1; sft < 16; sft <<= 1) worst = fmax(worst, __shfl_xor(worst, sft, 64));
-    return read_lane_d(worst, 0);
+    return open ? 1.0e300 : read_lane_d(worst, 0);
 }
 
 // IO: component type of the GOOM initial state (float for complex64, double for complex128)
@@ -558,7 +621,7 @@ template <int DP, typename IO> __global__ __launch_bounds__(64) void reset_carry
     // is taken inside the chain of chunks.
     auto qr_in_place = [&](d4 (&Z)[KT][KT], const double (&colexp)[KT]) {
         double piv[KT], piv2[KT], ce[KT], ce2[KT];
-        const double amp = qr_panels_d<DP>(Z, piv, ce, s, g, c);
+        const double amp = qr_panels_d<DP>(Z, piv, ce, s, g, c, false);
 #pragma unroll
         for (int nt = 0; nt < KT; ++nt) {
             piv2[nt] = 1.0;
@@ -567,7 +630,7 @@ template <int DP, typename IO> __global__ __launch_bounds__(64) void reset_carry
         // The factor Q comes out with errors of about amp 2^-53 relative to its columns' norms (amp: the squared
         // condition number).  For complex64 states, which are rounded to float, that is repaired by a second
         // factorisation from amp = 1e10 on; complex128 states take the second factorisation from 1e3 on.
-        if (amp > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3)) (void)qr_panels_d<DP>(Z, piv2, ce2, s, g, c);
+        if (amp > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3)) (void)qr_panels_d<DP>(Z, piv2, ce2, s, g, c, true);
 #pragma unroll
         for (int nt = 0; nt < KT; ++nt)
             if (piv[nt] > 1.0e-280 && piv2[nt] > 1.0e-280) {
@@ -724,6 +787,259 @@ template <int DP, typename IO> __global__ __launch_bounds__(64) void reset_carry
 }
 
 // ---------------------------------------------------------------------------------------------------
+// The carry kernel where every boundary is reset (policy "always") and d <= 64.  Panel p of a state depends on the panels
+// before it at the same boundary and on itself at the boundary before, and on nothing else: Z_p = T_c Q_p, then Z_p made
+// orthogonal to Q_0 .. Q_{p-1}, then its own factorisation.  So a workgroup gives a wave to every panel and runs them as
+// stages of a pipeline, wave p at chunk s - p in stage s; the chain's pace is the last wave's stage and not the whole
+// factorisation.  Finished panels pass through LDS: panel q of a chunk is read up to KT - 1 - q stages after it was written, so a
+// ring of KT of them serves (one for the last panel, which only its own wave reads).
+//
+// Contraction indices of Z = T Q are dealt out as 4 g + v, so that a lane reads its part of a row of T_c (straight from
+// memory, one chunk ahead, no LDS tile) as 32 consecutive bytes.  Rows and columns past d are zero throughout: a zero pivot
+// leaves a zero column, and nothing of it reaches the others.
+//
+// Bound by the last wave's chain of dependent instructions and double matrix instructions (64 cycles each).  d = 32, per chunk: 10 000
+// cycles (product 1100, two projections 2700, Gram matrix and rows 750, sixteen pivots 2950, scaling 600); one wave with a
+// whole state, four pivots per LDS round trip, took 20 400.  Carries of 512 chunks of 32 x 32: 4.34 -> 2.10 ms; of 110 chunks of
+// 64 x 64: 11.9 -> 1.45 ms (complex128, d = 50: 11.7 -> 2.2 ms).
+template <int DP> constexpr size_t staged_lds() { return ((size_t)((DP / 16 - 1) * (DP / 16) + 1) * DP + DP) * kPanelLd * sizeof(double); }
+
+template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_carry_staged_kernel(ResetArgs a)
+{
+    constexpr int KT = DP / 16, PANEL = DP * kPanelLd;
+    extern __shared__ __align__(32) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int p = __builtin_amdgcn_readfirstlane(tid >> 6); // this wave's panel
+    const int g = lane >> 4, c = lane & 15;
+    const int pc = ((c & 3) << 2) | (c >> 2);
+    const int d = a.d, col = 16 * p + c;
+    const long long b = blockIdx.x;
+    const size_t tot_mant = (size_t)DP * a.tot_cols * sizeof(double);
+    const size_t car_mant = (size_t)DP * a.car_cols * sizeof(double);
+    auto slot = [&](int q, long long i) { return reinterpret_cast<double *>(smem) + (size_t)(q * KT + (q + 1 < KT ? (int)(i & (KT - 1)) : 0)) * PANEL; };
+    double *gram = reinterpret_cast<double *>(smem) + (size_t)((KT - 1) * KT + 1) * PANEL + p * 16 * kPanelLd;
+
+    d4 Y[KT]; // Y[mt][v] = entry (row 16 mt + 4 g + v, column 16 p + c), columns scaled by 2^yexp
+    double yexp = 0.0, pprod = 1.0, pexp = 0.0; // product of all pivots so far = pprod 2^pexp (column exponents counted twice)
+#pragma unroll
+    for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Y[mt][v] = (16 * mt + 4 * g + v == col && col < d) ? 1.0 : 0.0;
+    if (a.s0 && col < d) {
+        const IO *gp = reinterpret_cast<const IO *>(a.s0) + (size_t)b * d * d * 2;
+        double cmax = -__builtin_huge_val();
+        for (int i = 0; i < d; ++i) cmax = fmax(cmax, (double)gp[((size_t)i * d + col) * 2]);
+        yexp = cmax > -__builtin_huge_val() ? ceil(cmax * kLog2e) : 0.0;
+#pragma unroll
+        for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 16 * mt + 4 * g + v;
+                double val = 0.0;
+                if (row < d) {
+                    const IO *e = gp + ((size_t)row * d + col) * 2;
+                    const double t = (double)e[0] * kLog2e - yexp;
+                    val = t > -1000.0 ? exp2(t) : 0.0;
+                    if ((int)rint((double)e[1] * 0.318309886183790671538) & 1) val = -val;
+                }
+                Y[mt][v] = val;
+            }
+    }
+    auto carry = [&](long long i) { return a.carries + (b * (a.C + 1) + i) * a.car_stride; };
+    if (a.carries) { // the state that enters the first chunk
+        double *mp = reinterpret_cast<double *>(carry(0));
+        if (col < a.car_cols) {
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) mp[(size_t)(16 * mt + 4 * g + v) * a.car_cols + col] = Y[mt][v];
+            if (g == 0) reinterpret_cast<double *>(carry(0) + car_mant)[col] = yexp;
+        }
+    }
+    // later ones from rows: lane r holds row r of the panel
+    auto store_carry = [&](long long i, const double (&rows)[1][16]) {
+        if (16 * p < a.car_cols) {
+            double *mp = reinterpret_cast<double *>(carry(i)) + (size_t)lane * a.car_cols + 16 * p;
+            if (lane < DP) {
+#pragma unroll
+                for (int j = 0; j < 16; j += 2) *reinterpret_cast<d2 *>(mp + j) = d2{rows[0][j], rows[0][j + 1]};
+            }
+            if (g == 0) reinterpret_cast<double *>(carry(i) + car_mant)[col] = yexp;
+        }
+    };
+
+    // the next chunk product.  d <= 32: as operands, row 16 mt + c, columns 16 kt + 4 g .. + 3.  d <= 64: a row's 128 bytes by eight
+    // lanes (as operands each load touches sixteen lines, and four waves' loads kept the memory pipe busy for half a stage).
+    constexpr bool SLICES = DP > 32;
+    d2 tq[KT][KT][2];
+    double tex;
+    const unsigned lane_at = (unsigned)((SLICES ? (lane >> 3) * a.tot_cols + 2 * (lane & 7) : c * a.tot_cols + 4 * g) * sizeof(double));
+    auto load_total = [&](long long i) {
+        const unsigned char *tp = a.totals + (b * a.C + i) * a.tot_stride;
+        tex = *reinterpret_cast<const double *>(tp + tot_mant);
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) {
+            const int at = 16 * kt < a.tot_cols ? 16 * kt : 0;
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) { // (one base for the wave, one offset for the lane)
+                    const unsigned char *base = tp + (size_t)((16 * mt + (SLICES ? 8 * h : 0)) * a.tot_cols + at) * sizeof(double);
+                    tq[mt][kt][h] = *reinterpret_cast<const d2 *>(base + lane_at + (SLICES ? 0 : 16 * h));
+                }
+        }
+    };
+    auto clear_past_d = [&]() {
+        if (d != DP) {
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const int row = SLICES ? 16 * mt + 8 * h + (lane >> 3) : 16 * mt + c, k = 16 * kt + (SLICES ? 2 * (lane & 7) : 4 * g + 2 * h) + e;
+                            if (row >= d || k >= d) tq[mt][kt][h][e] = 0.0;
+                        }
+        }
+    };
+
+    // a finished panel: rows 16 mt + 4 v + g of column c, and, negated, row 16 mt + c, columns 4 v + g
+    d4 qt[KT];
+    d2 qa[KT][2];
+    auto load_panel = [&](int q, long long i) {
+        const double *pq = slot(q, i);
+        panel_tiles<DP>(qt, pq, g, c);
+#pragma unroll
+        for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) qa[mt][h] = -*reinterpret_cast<const d2 *>(&pq[(16 * mt + c) * kPanelLd + 4 * g + 2 * h]);
+    };
+    // Q of Z (in the matrix instruction's layout) to `out` and, as rows, to `rows`; the product of its pivots and the exponents taken
+    // out of its columns.  A panel whose columns lose much of their norm is factored a second time: each on its own account, hence
+    // from a loss on that lies below the one the other kernels take over all panels (a column's largest entry is near 1 here).
+    const double again = sizeof(IO) == 4 ? 1.0e-9 : 0.5;
+    auto factor = [&](d4 (&Z)[KT], long long i, double *out, double (&rows)[1][16], double &prod, double &expo) {
+        prod = 1.0;
+        expo = 0.0;
+        auto project = [&]() {
+            d4 R = {0., 0., 0., 0.};
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) R = mfma8(qt[kt][v], Z[kt][v], R);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int mt = 0; mt < KT; ++mt) Z[mt] = mfma8(qa[mt][v >> 1][v & 1], R[v], Z[mt]);
+        };
+#pragma unroll 1
+        for (int pass = 0; pass < 2; ++pass) {
+            const int ex = column_exponent(Z);
+            expo += (double)ex;
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) Z[mt][v] = ldexp(Z[mt][v], -ex);
+            // orthogonal to the finished panels, twice (see qr_panels_d; a panel that is so already, once)
+#pragma unroll 1
+            for (int rep = pass; rep < 2; ++rep)
+#pragma unroll 1
+                for (int q = 0; q < p; ++q) {
+                    if (KT > 2) load_panel(q, i);
+                    project();
+                }
+            double piv;
+            const bool open = factor_panel_rows<DP>(Z, piv, out, gram, rows, lane, pass == 1);
+            prod *= piv > 1.0e-280 ? piv : 0.0;
+            if (pass == 1 || (!open && __builtin_amdgcn_ballot_w64(piv > 1.0e-280 && piv < again) == 0)) break;
+            panel_tiles<DP>(Z, out, g, c);
+        }
+    };
+    // growth as in reset_carry_kernel (a column that is zero has none)
+    auto grow = [&](double prod, double expo) {
+        if (prod > 0.0) {
+            int e;
+            pprod = frexp(pprod * prod, &e);
+            pexp += 2.0 * expo + (double)e;
+        }
+    };
+
+    if (a.C > 0) load_total(0);
+    const long long items = a.C + (a.growth ? 1 : 0); // (the last one: growth of the final state, factorised, not replaced)
+    for (long long s = 0; s < items + KT - 1; ++s) {
+        const long long i = s - p;
+        if (i >= 0 && i < items) { // (the same for the whole wave)
+            double *out = slot(p, i);
+            double rows[1][16], prod, expo;
+            d4 Z[KT];
+            if (KT == 2 && p > 0) load_panel(0, i); // (it is there since the stage before)
+            if (i < a.C) {
+                const double zexp = yexp + tex;
+                clear_past_d();
+#pragma unroll
+                for (int mt = 0; mt < KT; ++mt) Z[mt] = d4{0., 0., 0., 0.};
+#pragma unroll
+                for (int kt = 0; kt < KT; ++kt) {
+                    d2 ta[KT][2];
+                    if constexpr (SLICES) { // (sixteen columns at a time through this panel's own place)
+                        wave_sync();
+#pragma unroll
+                        for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) *reinterpret_cast<d2 *>(&out[(16 * mt + 8 * h + (lane >> 3)) * kPanelLd + 2 * (lane & 7)]) = tq[mt][kt][h];
+                        wave_sync();
+                    }
+#pragma unroll
+                    for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) ta[mt][h] = SLICES ? *reinterpret_cast<const d2 *>(&out[(16 * mt + c) * kPanelLd + 4 * g + 2 * h]) : tq[mt][kt][h];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int mt = 0; mt < KT; ++mt) Z[mt] = mfma8(ta[mt][v >> 1][v & 1], Y[kt][v], Z[mt]);
+                }
+                load_total(i + 1 < a.C ? i + 1 : i);
+                const bool boundary = (i + 1) * a.L <= a.T; // (a last, shorter chunk ends at no boundary)
+                if (boundary)
+                    factor(Z, i, out, rows, prod, expo);
+                else { // columns renormalised by a power of two
+                    const int ex = column_exponent(Z);
+                    yexp = col < d ? zexp + (double)ex : 0.0;
+#pragma unroll
+                    for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) out[(16 * mt + 4 * v + g) * kPanelLd + pc] = ldexp(Z[mt][v], -ex);
+                    wave_sync();
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) rows[0][j] = out[(lane & (DP - 1)) * kPanelLd + (((j & 3) << 2) | (j >> 2))];
+                }
+#pragma unroll
+                for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Y[mt][v] = out[(16 * mt + 4 * g + v) * kPanelLd + pc];
+                if (boundary) {
+                    grow(prod, zexp + expo);
+                    yexp = 0.0;
+                }
+                if (a.carries) store_carry(i + 1, rows);
+                if (tid == 0) a.chunk_flags[b * a.C + i] = boundary ? 1 : 0;
+            } else {
+                panel_tiles<DP>(Z, slot(p, i - 1), g, c);
+                factor(Z, i, out, rows, prod, expo);
+                grow(prod, yexp + expo);
+            }
+        }
+        // (LDS only: the loads of the next chunk product and the stores of carries stay in flight)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    }
+    if (a.growth && g == 0 && col < d) a.growth[b * d + col] = 0.5 * (log(pprod) + pexp * kLn2) * a.growth_scale;
+}
+
+// ---------------------------------------------------------------------------------------------------
 // The carry kernel for 64 < d <= 128.  A state of 128 x 128 doubles is more than one wave's registers hold, so a
 // workgroup of four waves owns a batch item, wave w the columns 32 w .. 32 w + 31 of the state (two panels of
 // sixteen).  Z = T_c Y is formed slab by slab from one LDS tile of the chunk product; the factorisation then
@@ -731,9 +1047,7 @@ template <int DP, typename IO> __global__ __launch_bounds__(64) void reset_carry
 // lie in LDS, in the tile's place), factorises it as above and lays it down for the others.  Arithmetic, layouts
 // and bookkeeping are those of the one-wave kernel.
 struct WideScratch {
-    double rrow[2][16];
-    double rperm[2][16];
-    double qcol[2][128];
+    double gram[16 * 18];
     double diag[128];
     double red[4];
     int hit;
@@ -743,12 +1057,13 @@ struct WideScratch {
 // place, Z <- Q: see qr_panels_d.  piv, cexp: pivots and column exponents of this wave's two panels.  Returns the
 // largest (squared column norm) / pivot over the whole matrix, the same in every wave.  Finished panels lie in
 // LDS at `panels` ([8][128][18] doubles); all four waves must call this together.
-__device__ double wide_qr_pass(d4 (&Z)[2][8], double (&piv)[2], double (&cexp)[2], double *panels, WideScratch &s, int wave, int lane)
+__device__ double wide_qr_pass(d4 (&Z)[2][8], double (&piv)[2], double (&cexp)[2], double *panels, WideScratch &s, int wave, int lane, bool last)
 {
     constexpr int DP = 128, KT = 8, NL = 2, LDQ = 18;
     const int g = lane >> 4, c = lane & 15;
     const int pc = ((c & 3) << 2) | (c >> 2);
     auto panel = [&](int q) { return panels + (size_t)q * DP * LDQ; };
+    bool open = false;
     double norm2[NL];
 #pragma unroll
     for (int nl = 0; nl < NL; ++nl) {
@@ -780,22 +1095,9 @@ __device__ double wide_qr_pass(d4 (&Z)[2][8], double (&piv)[2], double (&cexp)[2
     // every wave makes those of its own panels that come later orthogonal to it, twice in a row (one projection
     // leaves rounding-level remainders of the panel's norm behind), all four waves at work at once.
     auto factor_panel = [&](int P, d4 (&Zp)[KT], double &pv) {
-        d4 G = {0., 0., 0., 0.};
-#pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) G = mfma8(Zp[kt][v], Zp[kt][v], G);
-        eliminate_panel_d<DP>(G, Zp, pv, s, g, c);
-        const double sc = pv > 1.0e-280 ? rsqrt_d(pv) : 0.0;
-#pragma unroll
-        for (int mt = 0; mt < KT; ++mt) Zp[mt] *= sc;
-        if (P + 1 < KT) {
-            double *pp = panel(P);
-#pragma unroll
-            for (int mt = 0; mt < KT; ++mt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) pp[(16 * mt + 4 * v + g) * LDQ + pc] = Zp[mt][v];
-        }
+        double rows[2][16];
+        open |= factor_panel_rows<DP>(Zp, pv, panel(P), s.gram, rows, lane, last);
+        panel_tiles<DP>(Zp, panel(P), g, c);
     };
     auto project_out = [&](int P, d4 (&Zp)[KT]) {
         const double *pq = panel(P);
@@ -837,7 +1139,7 @@ __device__ double wide_qr_pass(d4 (&Z)[2][8], double (&piv)[2], double (&cexp)[2
     }
 #pragma unroll
     for (int sft = 1; sft < 16; sft <<= 1) worst = fmax(worst, __shfl_xor(worst, sft, 64));
-    if (lane == 0) s.red[wave] = worst;
+    if (lane == 0) s.red[wave] = open ? 1.0e300 : worst;
     __syncthreads();
     worst = fmax(fmax(s.red[0], s.red[1]), fmax(s.red[2], s.red[3]));
     __syncthreads();
@@ -912,7 +1214,6 @@ template <typename IO> __global__ __launch_bounds__(256) void reset_carry_wide_k
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, c = lane & 15;
-    const int pc = ((c & 3) << 2) | (c >> 2); // position of column c inside a stored panel
     const int d = a.d;
     const long long b = blockIdx.x;
     const size_t tot_mant = (size_t)DP * a.tot_cols * sizeof(double);
@@ -977,16 +1278,16 @@ template <typename IO> __global__ __launch_bounds__(256) void reset_carry_wide_k
         }
     };
 
-    auto qr_pass = [&](d4 (&Z)[NL][KT], double (&piv)[NL], double (&cexp)[NL]) { return wide_qr_pass(Z, piv, cexp, panel(0), s, wave, lane); };
+    auto qr_pass = [&](d4 (&Z)[NL][KT], double (&piv)[NL], double (&cexp)[NL], bool last) { return wide_qr_pass(Z, piv, cexp, panel(0), s, wave, lane, last); };
     auto qr_in_place = [&](d4 (&Z)[NL][KT], const double (&colexp)[NL]) {
         double piv[NL], piv2[NL], ce[NL], ce2[NL];
-        const double amp = qr_pass(Z, piv, ce);
+        const double amp = qr_pass(Z, piv, ce, false);
 #pragma unroll
         for (int nl = 0; nl < NL; ++nl) {
             piv2[nl] = 1.0;
             ce2[nl] = 0.0;
         }
-        if (amp > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3)) (void)qr_pass(Z, piv2, ce2); // (the same in every wave)
+        if (amp > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3)) (void)qr_pass(Z, piv2, ce2, true); // (the same in every wave)
 #pragma unroll
         for (int nl = 0; nl < NL; ++nl)
             if (piv[nl] > 1.0e-280 && piv2[nl] > 1.0e-280) {
@@ -1200,8 +1501,8 @@ template <int DP, typename IO> __global__ __launch_bounds__(64) void tree_reset_
     }
     if (!sel) return;
     double piv[KT], ce[KT];
-    const double amp = qr_panels_d<DP>(Z, piv, ce, s, g, c);
-    if (amp > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3)) (void)qr_panels_d<DP>(Z, piv, ce, s, g, c);
+    const double amp = qr_panels_d<DP>(Z, piv, ce, s, g, c, false);
+    if (amp > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3)) (void)qr_panels_d<DP>(Z, piv, ce, s, g, c, true);
     const IO pi = sizeof(IO) == 4 ? (IO)3.14159274101257324219f : (IO)3.14159265358979311600;
 #pragma unroll
     for (int nt = 0; nt < KT; ++nt)
@@ -1274,8 +1575,8 @@ template <typename IO> __global__ __launch_bounds__(256) void tree_reset_wide_ke
     if (!sel) sel = wide_colinear(Z, panels, s, wave, lane, d, (double)a.cos_threshold * (double)a.cos_threshold);
     if (!sel) return;
     double piv[NL], ce[NL];
-    const double amp = wide_qr_pass(Z, piv, ce, panels, s, wave, lane);
-    if (amp > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3)) (void)wide_qr_pass(Z, piv, ce, panels, s, wave, lane);
+    const double amp = wide_qr_pass(Z, piv, ce, panels, s, wave, lane, false);
+    if (amp > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3)) (void)wide_qr_pass(Z, piv, ce, panels, s, wave, lane, true);
     const IO pi = sizeof(IO) == 4 ? (IO)3.14159274101257324219f : (IO)3.14159265358979311600;
 #pragma unroll
     for (int nl = 0; nl < NL; ++nl)
@@ -1530,8 +1831,8 @@ template <int DP> __global__ __launch_bounds__(64) void lyap_step_kernel_d(StepA
     }
     {
         double piv[KT], ce[KT];
-        const double amp = qr_panels_d<DP>(Q, piv, ce, s, g, c);
-        if (amp > 1.0e3) (void)qr_panels_d<DP>(Q, piv, ce, s, g, c);
+        const double amp = qr_panels_d<DP>(Q, piv, ce, s, g, c, false);
+        if (amp > 1.0e3) (void)qr_panels_d<DP>(Q, piv, ce, s, g, c, true);
     }
 
     // ---- J_t as reals scaled by 2^-sh, sh from the largest entry; identity block past d
@@ -1581,13 +1882,13 @@ template <int DP> __global__ __launch_bounds__(64) void lyap_step_kernel_d(StepA
         }
     wave_sync();
     double piv[KT], piv2[KT], ce[KT], ce2[KT];
-    const double amp = qr_panels_d<DP>(Z, piv, ce, s, g, c);
+    const double amp = qr_panels_d<DP>(Z, piv, ce, s, g, c, false);
 #pragma unroll
     for (int nt = 0; nt < KT; ++nt) {
         piv2[nt] = 1.0;
         ce2[nt] = 0.0;
     }
-    if (amp > 1.0e3) (void)qr_panels_d<DP>(Z, piv2, ce2, s, g, c);
+    if (amp > 1.0e3) (void)qr_panels_d<DP>(Z, piv2, ce2, s, g, c, true);
     if (g == 0) {
 #pragma unroll
         for (int nt = 0; nt < KT; ++nt) {
@@ -1651,8 +1952,8 @@ template <typename IO> __global__ __launch_bounds__(256) void lyap_step_wide_ker
     }
     {
         double piv[NL], ce[NL];
-        const double amp = wide_qr_pass(Q, piv, ce, panels, s, wave, lane);
-        if (amp > 1.0e3) (void)wide_qr_pass(Q, piv, ce, panels, s, wave, lane);
+        const double amp = wide_qr_pass(Q, piv, ce, panels, s, wave, lane, false);
+        if (amp > 1.0e3) (void)wide_qr_pass(Q, piv, ce, panels, s, wave, lane, true);
     }
 
     // ---- J_t as reals scaled by 2^-sh, sh from the largest entry; identity block past d
@@ -1699,13 +2000,13 @@ template <typename IO> __global__ __launch_bounds__(256) void lyap_step_wide_ker
                 for (int nl = 0; nl < NL; ++nl) Z[nl][mt] = mfma8(av[v], Q[nl][kt][v], Z[nl][mt]);
         }
     double piv[NL], piv2[NL], ce[NL], ce2[NL];
-    const double amp = wide_qr_pass(Z, piv, ce, panels, s, wave, lane); // (its first barrier comes after the reads of the tile)
+    const double amp = wide_qr_pass(Z, piv, ce, panels, s, wave, lane, false); // (its first barrier comes after the reads of the tile)
 #pragma unroll
     for (int nl = 0; nl < NL; ++nl) {
         piv2[nl] = 1.0;
         ce2[nl] = 0.0;
     }
-    if (amp > 1.0e3) (void)wide_qr_pass(Z, piv2, ce2, panels, s, wave, lane);
+    if (amp > 1.0e3) (void)wide_qr_pass(Z, piv2, ce2, panels, s, wave, lane, true);
     if (g == 0) {
 #pragma unroll
         for (int nl = 0; nl < NL; ++nl) {
@@ -2035,6 +2336,7 @@ int launch_reset_carry(goom_ctx *ctx, const ResetLaunch &l)
     a.policy = l.policy;
     a.cos_threshold = l.cos_threshold;
     const int dp = padded_dim(l.d);
+    if (l.policy == GOOM_RESET_ALWAYS && dp <= 64 && !l.post_states) a.carries = nullptr; // (without states nobody reads them)
     if (l.d > 128) return fail(ctx, GOOM_EUNSUPPORTED, "the reset scan supports d <= 128 (d=%d)", l.d);
     if (dp == 128) { // four waves per batch item, the state's columns divided among them
         const size_t lds = (size_t)8 * 128 * 18 * sizeof(double) + sizeof(WideScratch);
@@ -2049,6 +2351,24 @@ int launch_reset_carry(goom_ctx *ctx, const ResetLaunch &l)
         return check_hip(ctx, hipGetLastError(), "launch reset_carry_wide_kernel");
     }
     prof_begin(ctx, "reset_phase2_carries_qr");
+#define GOOM_STAGED_CASE(DPV)                                                                                                  \
+    if (l.policy == GOOM_RESET_ALWAYS && dp == DPV) {                                                                          \
+        const void *kern = l.dtype == GOOM_C64 ? reinterpret_cast<const void *>(reset_carry_staged_kernel<DPV, float>)         \
+                                               : reinterpret_cast<const void *>(reset_carry_staged_kernel<DPV, double>);       \
+        if (int st = check_hip(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)staged_lds<DPV>()), \
+                               "hipFuncSetAttribute(reset_carry_staged_kernel)"))                                              \
+            return st;                                                                                                         \
+        if (l.dtype == GOOM_C64)                                                                                               \
+            hipLaunchKernelGGL((reset_carry_staged_kernel<DPV, float>), dim3((unsigned)l.batch), dim3(4 * DPV), staged_lds<DPV>(), ctx->stream, a); \
+        else                                                                                                                   \
+            hipLaunchKernelGGL((reset_carry_staged_kernel<DPV, double>), dim3((unsigned)l.batch), dim3(4 * DPV), staged_lds<DPV>(), ctx->stream, a); \
+        prof_end(ctx);                                                                                                         \
+        return check_hip(ctx, hipGetLastError(), "launch reset_carry_staged_kernel");                                          \
+    }
+    GOOM_STAGED_CASE(16)
+    GOOM_STAGED_CASE(32)
+    GOOM_STAGED_CASE(64)
+#undef GOOM_STAGED_CASE
 #define GOOM_RESET_CASE(DPV)                                                                                                   \
     if (dp == DPV) {                                                                                                           \
         if (l.dtype == GOOM_C64)                                                                                               \

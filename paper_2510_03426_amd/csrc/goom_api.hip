@@ -1521,6 +1521,67 @@ ScanBackwardPlan plan_scan_backward(int64_t T, int d, int m, int64_t batch, int 
 }
 } // namespace
 
+// Steps per chunk of the walked backward pass (goom_scan_adjoint.hip): as many chunks as the chip has places for workgroups, none
+// shorter than eight steps, nor so short that the carries, one chain a batch item, would be the longer part (a step of theirs
+// costs about a quarter of the three passes' steps over a chunk).
+static int64_t scan_adjoint_chunk(int64_t T, int d, int m, int64_t batch, const goom_scan_opts *opts)
+{
+    const int dp = padded_dim(d > m ? d : m);
+    const int64_t places = dp >= 128 ? 256 : dp >= 64 ? 512 : dp >= 32 ? 1024 : 2048;
+    int64_t least = 1;
+    while (4 * least * least < T) ++least;
+    int64_t L = opts && opts->chunk_len > 0 ? opts->chunk_len : (T * batch + places - 1) / places > 8 ? (T * batch + places - 1) / places : 8;
+    L = L > least ? L : least;
+    return L < T ? L : T;
+}
+
+static int run_scan_adjoint(goom_ctx *ctx, const void *M, const void *S0, const void *P, const void *grad_P, void *grad_M, void *grad_S0, int64_t T, int d, int m,
+                            int64_t batch, int dtype, const goom_scan_opts *opts, unsigned char *ws, size_t ws_bytes)
+{
+    ScanAdjointLaunch a;
+    a.M = M;
+    a.S0 = S0;
+    a.P = P;
+    a.G = grad_P;
+    a.gM = grad_M;
+    a.gS0 = grad_S0;
+    a.T = T;
+    a.batch = batch;
+    a.d = d;
+    a.m = m;
+    a.dtype = dtype;
+    a.tot = fact_layout(padded_dim(d), d, dtype);
+    a.vec = fact_layout(padded_dim(d > m ? d : m), m, dtype);
+    a.L = scan_adjoint_chunk(T, d, m, batch, opts);
+    a.C = (T + a.L - 1) / a.L;
+    if ((size_t)batch * a.C * (a.tot.stride + a.vec.stride) > ws_bytes) { // (a few small steps whose matrices are mostly padding)
+        a.L = T;
+        a.C = 1;
+    }
+    a.totals = ws;
+    a.vecs = ws + (size_t)batch * a.C * a.tot.stride;
+    if (a.C > 1) {
+        ChainLaunch l;
+        std::memset(&l, 0, sizeof l);
+        l.dtype = dtype;
+        l.n = l.d = l.m = d;
+        l.batch = batch;
+        l.left = M;
+        l.left_step_stride = (long long)d * d * 2 * (long long)comp_bytes(dtype);
+        l.left_batch_stride = T * l.left_step_stride;
+        l.steps = T;
+        l.chunk_len = a.L;
+        l.chunks_launched = a.C;
+        l.out_fact_final = ws;
+        l.fact_stride = (long long)a.tot.stride;
+        l.fact_cols = a.tot.cols_padded;
+        l.label = "scan_adjoint_chunk_products";
+        if (int s = launch_chain(ctx, l)) return s;
+        if (int s = launch_scan_adjoint(ctx, a, 0)) return s;
+    }
+    return launch_scan_adjoint(ctx, a, 1);
+}
+
 size_t goom_scan_backward_workspace_bytes(int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts, int with_init)
 {
     if (T <= 0 || d <= 0 || m <= 0 || batch <= 0 || d + m > GOOM_MAX_DIM_LMME) return 0;
@@ -1545,6 +1606,7 @@ int goom_scan_backward(goom_ctx *ctx, const void *M, const void *S0, const void 
     if (int s = check_workspace(ctx, ws, ws_bytes, p.total())) return s;
     if (int s = need_ctx(ctx)) return s;
     unsigned char *w = static_cast<unsigned char *>(ws);
+    if (d <= GOOM_MAX_DIM && m <= GOOM_MAX_DIM) return run_scan_adjoint(ctx, M, S0, P, grad_P, grad_M, grad_S0, T, d, m, batch, dtype, opts, w, p.total());
     void *c = w;
     unsigned char *F = w + p.c_bytes;
     void *init = F + p.f_bytes;

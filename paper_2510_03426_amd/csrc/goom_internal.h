@@ -185,6 +185,18 @@ int launch_lmme_backward_finish(goom_ctx *ctx, const void *A, const void *B, con
                                 long long batch, int n, int d, int m, int dtype);
 // backward of the prefix scan (goom_scan_backward.hip): c [batch, T + 1] reals; F [batch, nsteps, d + m, d + m], init [batch, d + m, m],
 // states [batch, nsteps, d + m, m], Lam [batch, T, d, m], Pt [batch, T, m, d], X [batch, T, d, d] GOOMs; nsteps = T + (S0 ? 1 : 0)
+// adjoints and factor gradients of the scan, d and m up to 128 (goom_scan_adjoint.hip)
+struct ScanAdjointLaunch {
+    const void *M, *S0, *P, *G; // factors, NULL or initial states, states, gradients with respect to the states' log-magnitudes
+    void *gM, *gS0;             // gS0: NULL or [batch][d][m]
+    const void *totals;         // factored chunk products [batch][C], layout tot
+    void *vecs;                 // factored d x m matrices [batch][C], layout vec
+    FactLayout tot, vec;
+    long long T, L, C, batch;
+    int d, m, dtype;
+};
+// phase 0: chunk vectors and carries (C > 1); phase 1: gradients
+int launch_scan_adjoint(goom_ctx *ctx, const ScanAdjointLaunch &l, int phase);
 int launch_scan_backward_prepare(goom_ctx *ctx, const void *M, const void *S0, const void *P, const void *G, void *c, void *F, void *init, long long T, int d,
                                  int m, long long batch, int dtype);
 int launch_scan_backward_operands(goom_ctx *ctx, const void *states, const void *P, const void *S0, const void *c, void *Lam, void *Pt, long long T, int d, int m,

@@ -14,6 +14,8 @@
 // whose operands have log-magnitudes of ordinary size (P'_t - c_t is exact in the component type), and the
 // gradients are formed from Lamhat_t, P_{t-1} e^(-c_{t-1}) and the whole number c_{t-1} - c_t.
 //
+// This is the way for states or factors of more than 128 rows or columns; up to there goom_scan_adjoint.hip walks the recurrence.
+//
 // Kernels here (the scan and the LMME are the library's own):
 //   scales     c[b, t + 1] for t = -1 .. T - 1                                            one wave per state
 //   factors    F[b, s] = [[Nhat, Ghat], [0, I]] for s = T - 1 - t (and s = T: the step onto S0)  one workgroup per step

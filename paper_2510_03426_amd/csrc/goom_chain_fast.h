@@ -46,10 +46,14 @@ template <int CTRL> __device__ inline float add_dpp(float x)
 
 // REAL: the left factors are plain real matrices (4 bytes per entry instead of a GOOM's 8): an entry is
 // scaled by 2^(r_j - n_i) exactly, with no logarithm or exponential on the way in.
-// RAG: square matrices of a size d < DP that is a multiple of four (rows d entries apart in memory): the
-// tile's rows and columns from d on are zero, only the first KD = ceil(d / 16) blocks of sixteen rows and
-// columns take part in the product, and waves whose sixteen state columns lie beyond d only help converting.
-template <int DP, int NW, bool BIAS, bool REAL, int KD = DP / 16, bool RAG = false>
+// RAG: square matrices of a size d < DP (rows d entries apart in memory): the tile's rows and columns from d on
+// are zero, only the first KD = ceil(d / 16) blocks of sixteen rows and columns take part in the product, and
+// waves whose sixteen state columns lie beyond the state only help converting.  RAG = 1: d a multiple of four, a
+// state of d columns.  RAG = 2: any d (d = DP too) and any state of up to DP columns: rows start at any
+// entry (8-byte alignment), the lane whose four columns straddle the matrix's edge takes its last four and moves
+// them into place once they are scaled, and a row past the matrix is left out one by one.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
+template <int DP, int NW, bool BIAS, bool REAL, int KD = DP / 16, int RAG = 0>
 __device__ __forceinline__ void chain_body(const ChainArgs &a)
 {
     typedef Comp<float> C;
@@ -90,7 +94,10 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
     const int dd = RAG ? a.d : DP;        // size of the matrices in memory
     // this wave owns sixteen columns of the state (KD may exceed ceil(d / 16) when a wider state elsewhere in
     // the same scan has fixed the tile size; the factored product stored at the end has ceil(d / 16) slabs)
-    const bool owner = !RAG || (wave < KD && 16 * wave < dd);
+    const int mm = RAG == 2 ? a.m : dd;   // columns of the state (RAG)
+    const bool owner = !RAG || (RAG == 2 ? 16 * wave < mm : (wave < KD && 16 * wave < dd));
+    // RAG = 2: first of the four columns this lane loads, and how far beyond them its own four begin
+    const int cl = c4 < dd - 4 ? c4 : dd - 4, cmove = RAG == 2 && c4 < dd ? c4 - cl : 0;
     // bias wave: lane -> row and part of the contraction index
     constexpr int LPRB = DP >= 64 ? 1 : 64 / DP; // lanes per row
     constexpr int CPLB = DP / LPRB;              // contraction indices per lane
@@ -117,6 +124,12 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
                 // entries beyond the matrix are read from its last row / last four columns instead (and
                 // discarded by the conversion), so that no load sits behind a branch
                 const int rr = row < dd ? row : dd - 1, cc = c4 < dd ? c4 : dd - 4;
+                if (RAG == 2) {
+                    const f4u *up = reinterpret_cast<const f4u *>(src + ((size_t)rr * dd + cl) * 2);
+                    it[q].a = up[0];
+                    it[q].b = up[1];
+                    continue;
+                }
                 const f4 *gp = reinterpret_cast<const f4 *>(src + ((size_t)rr * dd + cc) * 2);
                 it[q].a = gp[0];
                 it[q].b = gp[1];
@@ -139,7 +152,13 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
         // (ragged: columns beyond the matrix carry the exponent of a zero row, which the rows beyond the
         // matrix hand on from step to step; it makes their entries vanish)
         if (RAG && c4 >= dd) rj = f4{-1.0e30f, -1.0e30f, -1.0e30f, -1.0e30f};
-        if (rsrc) rj = *reinterpret_cast<const f4 *>(&rsrc[c4]);
+        if (rsrc && RAG == 2) { // (of the columns it loads; past the matrix: of zero rows)
+            const int at = c4 < dd ? cl : c4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rj[e] = rsrc[at + e];
+        } else if (rsrc) {
+            rj = *reinterpret_cast<const f4 *>(&rsrc[c4]);
+        }
 #pragma unroll
         for (int q = 0; q < QE; ++q) {
             const int row = (tid + q * NT) / LPR;
@@ -197,6 +216,11 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
                 const float kf = __builtin_fmaf(im[e], 0.318309886183790671538f, 12582912.0f);
                 y[e] = __builtin_bit_cast(float, __builtin_bit_cast(int, v) | (__builtin_bit_cast(int, kf) << 31));
             }
+            if (RAG == 2 && (dd & 3)) { // (the same for the whole launch)
+                const bool two = (cmove & 2) != 0, one = (cmove & 1) != 0;
+                y = f4{two ? y[2] : y[0], two ? y[3] : y[1], two ? 0.0f : y[2], two ? 0.0f : y[3]};
+                y = f4{one ? y[1] : y[0], one ? y[2] : y[1], one ? y[3] : y[2], one ? 0.0f : y[3]};
+            }
             *reinterpret_cast<f4 *>(&tile[row * LDA + c4]) = y;
             nsh[row] = n; // every lane of the row writes the same value
         }
@@ -233,11 +257,11 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
         ecol = ep[col];
     } else {
         const float *gp = reinterpret_cast<const float *>(a.init + item * a.init_stride);
-        const int MM = RAG ? dd : M; // columns of the initial state in memory
+        const int MM = RAG ? mm : M; // columns of the initial state in memory
         // (ragged: entries beyond the matrix are read from its last row / column and replaced by zeros)
-        const int colc = RAG ? (col < dd ? col : dd - 1) : col;
+        const int colc = RAG ? (col < mm ? col : mm - 1) : col;
         auto init_row = [&](int r) { return RAG ? (r < dd ? r : dd - 1) : r; };
-        auto init_ok = [&](int r) { return !RAG || (r < dd && col < dd); };
+        auto init_ok = [&](int r) { return !RAG || (r < dd && col < mm); };
         float cmax = C::neg_inf();
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
@@ -367,7 +391,25 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
                 }
             }
         }
-        if (want_out && RAG) {
+        if (want_out && RAG == 2) {
+            const long long o_idx = a.out_goom_last_only ? chain_global : (item * a.steps + t0 + t);
+            float *outp = reinterpret_cast<float *>(a.out_goom) + ((size_t)o_idx * dd * mm + (size_t)(4 * g) * mm + col) * 2;
+            const float ecol_f = (float)ecol;
+            if (col < mm) {
+#pragma unroll
+                for (int mt = 0; mt < KT; ++mt) {
+                    const f4 nv = *reinterpret_cast<const f4 *>(&nsh[16 * mt + 4 * g]);
+                    const bool whole = 16 * mt + 16 <= dd; // (the same for the whole launch)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const float x = acc[mt][v];
+                        const float2 o = float2{C::out_re_f(x, nv[v] + ecol_f), x < 0.0f ? C::pi() : 0.0f};
+                        if (whole || 16 * mt + 4 * g + v < dd) *reinterpret_cast<float2 *>(outp + (size_t)(16 * mt + v) * mm * 2) = o;
+                    }
+                }
+            }
+        }
+        if (want_out && RAG == 1) {
             // rows d entries apart; a lane's four rows 16 mt + 4 g + v lie inside the matrix together (d is a
             // multiple of four)
             const long long o_idx = a.out_goom_last_only ? chain_global : (item * a.steps + t0 + t);
@@ -505,11 +547,11 @@ __global__ __launch_bounds__(NW * 64, (DP <= 16 ? 8 : DP == 32 ? 6 : DP == 64 ? 
     chain_body<DP, NW, false, true>(a);
 }
 
-// square matrices of a size below DP (a multiple of four), KD = ceil(d / 16) blocks of sixteen
-template <int DP, int NW, int KD>
+// square matrices of other sizes, KD = ceil(d / 16) blocks of sixteen (RAG: see chain_body)
+template <int DP, int NW, int KD, int RAG>
 __global__ __launch_bounds__(NW * 64, (DP == 32 ? 6 : DP == 64 ? 4 : 2)) void chain_kernel_fast_ragged(ChainArgs a)
 {
-    chain_body<DP, NW, false, false, KD, true>(a);
+    chain_body<DP, NW, false, false, KD, RAG>(a);
 }
 
 template <int DP, int NW, bool BIAS, bool REAL = false> int launch_fast(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
@@ -549,12 +591,12 @@ bool affine_walk_applies(const ChainArgs &args, int dp);
 int dispatch_affine_walk(goom_ctx *ctx, const ChainArgs &args, int dp, long long grid, const char *label);
 int dispatch_affine_chunk_f64(goom_ctx *ctx, const ChainArgs &args, int dp, long long grid, const char *label);
 
-// square matrices whose size is a multiple of four between the sizes above (20 ... 124): the hot kernel
-// with the rows and columns beyond the matrix left out, separate translation unit
+// square matrices of other sizes from 17 to 128, and states of another width: the hot kernel with the rows and
+// columns beyond the matrix left out, separate translation unit
 bool ragged_applies(const ChainArgs &args, int dp, int nw);
 int dispatch_ragged(goom_ctx *ctx, const ChainArgs &args, int dp, long long grid, const char *label);
 
-// 8 x 8 and 16 x 16 chains: one wave per chain (or per pair of 8 x 8 chains), separate translation unit
+// chains of up to 16 x 16: one wave per chain (or per pair of chains of up to 8 x 8), separate translation unit
 bool small_applies(const ChainArgs &args, int dp);
 int dispatch_small(goom_ctx *ctx, const ChainArgs &args, long long nchains, const char *label);
 

@@ -11,6 +11,9 @@
 //     chain 2 w + 1 in 8..15, and so is the state, so one wave's instructions serve both;
 //   * as in the larger kernel the product is not rescaled after a step: the row exponents go into the
 //     next factor's exponent arguments, columns are renormalised every fourth step.
+//   * other sizes below 16 are padded to the next of the two with zero rows and columns (their entries come one by
+//     one, 8 bytes each: rows start anywhere), as are states of fewer columns.  Against the general kernel: 100 000 steps
+//     of d = 3 349 -> 306 us, 256 of d = 6 58 -> 45, 8 x 300 of d = 11 61 -> 46 (what remains are the carries and the launches).
 // Starts from the identity or from factored states, writes every prefix as GOOMs and / or the chain's
 // factored product; other combinations stay with the general kernels.
 #include "goom_chain_fast.h"
@@ -21,13 +24,15 @@ namespace {
 
 constexpr int kSmallLDA = 20;
 
-template <int D, bool OUT> __global__ __launch_bounds__(64, 6) void small_chain_kernel(ChainArgs a, long long nchains)
+// RAG: matrices of d <= D rows and columns, states of m <= D columns
+template <int D, bool OUT, bool RAG> __global__ __launch_bounds__(64, 6) void small_chain_kernel(ChainArgs a, long long nchains)
 {
     typedef Comp<float> C;
     constexpr int PACK = D == 8 ? 2 : 1;
     __shared__ __align__(16) float tile[16 * kSmallLDA];
     __shared__ __align__(16) float nsh[16];
 
+    const int dd = RAG ? a.d : D, mm = RAG ? a.m : D;
     const int lane = threadIdx.x;
     const int g = lane >> 4, c = lane & 15;
     const int crow = lane >> 2, c4 = 4 * (lane & 3); // the lane's part of the tile when converting
@@ -46,7 +51,7 @@ template <int D, bool OUT> __global__ __launch_bounds__(64, 6) void small_chain_
         const long long t0 = chunk * a.chunk_len;
         clen = a.steps - t0;
         if (clen > a.chunk_len) clen = a.chunk_len;
-        src = a.left + item * a.left_batch_stride + t0 * a.left_step_stride + ((size_t)lrow * D + lcol) * 8;
+        src = a.left + item * a.left_batch_stride + t0 * a.left_step_stride + (RAG ? (size_t)lrow * dd : (size_t)lrow * D + lcol) * 8;
     }
     // ---- the chain whose state this lane holds: rows 4 g + v, column c of the tile
     const int ssel = PACK == 2 ? c >> 3 : 0;
@@ -92,11 +97,11 @@ template <int D, bool OUT> __global__ __launch_bounds__(64, 6) void small_chain_
         ecol = reinterpret_cast<const double *>(ip + fact_mant_bytes)[scol];
     } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) st[v] = (4 * g + v == c) ? 1.0f : 0.0f; // identity (block diagonal as it is)
+        for (int v = 0; v < 4; ++v) st[v] = (4 * g + v == c && (!RAG || scol < dd)) ? 1.0f : 0.0f; // identity (block diagonal as it is)
     }
 
     float2 *outp = nullptr;
-    if (OUT && sexists && svalid) outp = reinterpret_cast<float2 *>(a.out_goom) + ((size_t)(sitem * a.steps + st0) * D + srow0) * D + scol;
+    if (OUT && sexists && svalid && (!RAG || scol < mm)) outp = reinterpret_cast<float2 *>(a.out_goom) + ((size_t)(sitem * a.steps + st0) * dd + srow0) * mm + scol;
 
     // Factors wait in registers kAhead steps before they are used: with so little to do per step it is the
     // number of loads in flight, not their size, that hides the memory latency.  A load is issued only by
@@ -104,9 +109,24 @@ template <int D, bool OUT> __global__ __launch_bounds__(64, 6) void small_chain_
     // shorter than its partner: the identity) contribute is substituted when the value is used, so no lane
     // writes a register that a load is still due to fill.
     constexpr int kAhead = 4;
+    int at[4]; // the lane's columns (RAG)
+    bool in[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        at[e] = lcol + e < dd ? lcol + e : dd - 1;
+        in[e] = !RAG || (lrow < dd && lcol + e < dd);
+    }
     f4 xa[kAhead], xb[kAhead];
     auto load = [&](long long t, f4 &x0, f4 &x1) {
-        if (cvalid && t < clen) {
+        if (RAG) { // (a column past the matrix: its last one instead)
+            if (cvalid && lrow < dd && t < clen) {
+                const float2 *p = reinterpret_cast<const float2 *>(src);
+                const float2 e0 = p[at[0]], e1 = p[at[1]], e2 = p[at[2]], e3 = p[at[3]];
+                x0 = f4{e0.x, e0.y, e1.x, e1.y};
+                x1 = f4{e2.x, e2.y, e3.x, e3.y};
+                src += a.left_step_stride;
+            }
+        } else if (cvalid && t < clen) {
             const f4 *p = reinterpret_cast<const f4 *>(src);
             x0 = p[0];
             x1 = p[1];
@@ -114,7 +134,7 @@ template <int D, bool OUT> __global__ __launch_bounds__(64, 6) void small_chain_
         }
     };
     const float ninf = -__builtin_huge_valf();
-    const bool mine = cvalid && cexists;
+    const bool mine = cvalid && cexists && (!RAG || lrow < dd);
     const float syn[4] = {(mine && lrow == lcol) ? 0.0f : ninf, (mine && lrow == lcol + 1) ? 0.0f : ninf,
                           (mine && lrow == lcol + 2) ? 0.0f : ninf, (mine && lrow == lcol + 3) ? 0.0f : ninf};
 #pragma unroll
@@ -136,7 +156,11 @@ template <int D, bool OUT> __global__ __launch_bounds__(64, 6) void small_chain_
         if (t >= len) break;
         // ---------------------------------------------------------------- factor -> tile
         const bool live = cvalid && t < clen;
-        const float re[4] = {live ? xa[slot][0] : syn[0], live ? xa[slot][2] : syn[1], live ? xb[slot][0] : syn[2], live ? xb[slot][2] : syn[3]};
+        float re[4] = {live ? xa[slot][0] : syn[0], live ? xa[slot][2] : syn[1], live ? xb[slot][0] : syn[2], live ? xb[slot][2] : syn[3]};
+        if (RAG) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) re[e] = in[e] ? re[e] : ninf;
+        }
         const float im[4] = {live ? xa[slot][1] : 0.0f, live ? xa[slot][3] : 0.0f, live ? xb[slot][1] : 0.0f, live ? xb[slot][3] : 0.0f};
         load(t + kAhead, xa[slot], xb[slot]);
         float u = __builtin_fmaf(re[0], kHi, rj[0]);
@@ -176,8 +200,11 @@ template <int D, bool OUT> __global__ __launch_bounds__(64, 6) void small_chain_
         if (OUT && outp && t < slen) {
             const float ecol_f = (float)ecol;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) outp[v * D] = float2{C::out_re_f(acc[v], nv[v] + ecol_f), acc[v] < 0.0f ? C::pi() : 0.0f};
-            outp += D * D;
+            for (int v = 0; v < 4; ++v) {
+                const float2 o = float2{C::out_re_f(acc[v], nv[v] + ecol_f), acc[v] < 0.0f ? C::pi() : 0.0f};
+                if (!RAG || srow0 + v < dd) outp[v * mm] = o;
+            }
+            outp += dd * mm;
         }
         // ---------------------------------------------------------------- state: raw; columns renormalised now and then
 #pragma unroll
@@ -237,14 +264,14 @@ template <int D, bool OUT> __global__ __launch_bounds__(64, 6) void small_chain_
     }
 }
 
-template <int D, bool OUT> int launch_small(goom_ctx *ctx, const ChainArgs &args, long long nchains, const char *label)
+template <int D, bool OUT, bool RAG> int launch_small(goom_ctx *ctx, const ChainArgs &args, long long nchains, const char *label)
 {
     constexpr int PACK = D == 8 ? 2 : 1;
     const long long grid = (nchains + PACK - 1) / PACK;
     if (grid <= 0) return GOOM_OK;
     if (grid > 0x7fffffffLL) return goom::fail(ctx, GOOM_EUNSUPPORTED, "too many chains for one launch (%lld)", nchains);
     goom::prof_begin(ctx, label);
-    hipLaunchKernelGGL((small_chain_kernel<D, OUT>), dim3((unsigned)grid), dim3(64), 0, ctx->stream, args, nchains);
+    hipLaunchKernelGGL((small_chain_kernel<D, OUT, RAG>), dim3((unsigned)grid), dim3(64), 0, ctx->stream, args, nchains);
     goom::prof_end(ctx);
     return goom::check_hip(ctx, hipGetLastError(), "launch small_chain_kernel");
 }
@@ -254,15 +281,20 @@ template <int D, bool OUT> int launch_small(goom_ctx *ctx, const ChainArgs &args
 bool small_applies(const ChainArgs &args, int dp)
 {
     // (dp above 16: a wider state elsewhere in the same scan fixes the layout of the factored matrices)
-    return dp == 16 && (args.d == 8 || args.d == 16) && args.n == args.d && args.m == args.d && args.bias_mode == 0 && args.out_fact_steps == nullptr &&
+    return dp == 16 && args.n == args.d && (args.m == args.d || args.init_mode == 1) && args.m <= 16 && args.bias_mode == 0 && args.out_fact_steps == nullptr &&
            (args.init_mode == 0 || args.init_mode == 1) && !args.out_goom_last_only && args.out_scaled == nullptr && !args.left_real &&
-           (args.out_goom != nullptr || args.out_fact_final != nullptr) && (args.out_fact_final == nullptr || args.fact_cols >= 16);
+           (args.out_goom != nullptr || args.out_fact_final != nullptr) && (args.out_fact_final == nullptr || (args.fact_cols >= 16 && args.m == args.d));
+}
+
+template <int D, bool RAG> static int pick_small(goom_ctx *ctx, const ChainArgs &args, long long nchains, const char *label)
+{
+    return args.out_goom ? launch_small<D, true, RAG>(ctx, args, nchains, label) : launch_small<D, false, RAG>(ctx, args, nchains, label);
 }
 
 int dispatch_small(goom_ctx *ctx, const ChainArgs &args, long long nchains, const char *label)
 {
-    if (args.d == 8) return args.out_goom ? launch_small<8, true>(ctx, args, nchains, label) : launch_small<8, false>(ctx, args, nchains, label);
-    return args.out_goom ? launch_small<16, true>(ctx, args, nchains, label) : launch_small<16, false>(ctx, args, nchains, label);
+    if (args.d <= 8 && args.m <= 8) return args.d == 8 && args.m == 8 ? pick_small<8, false>(ctx, args, nchains, label) : pick_small<8, true>(ctx, args, nchains, label);
+    return args.d == 16 && args.m == 16 ? pick_small<16, false>(ctx, args, nchains, label) : pick_small<16, true>(ctx, args, nchains, label);
 }
 
 } // namespace goom_chain

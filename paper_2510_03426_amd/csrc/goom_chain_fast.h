@@ -44,6 +44,30 @@ template <int CTRL> __device__ inline float add_dpp(float x)
     return x + __builtin_bit_cast(float, y);
 }
 
+// An entry's log-magnitude in units of log 2, as two floats: their sum is good to 2^-48 of it, so that what is left once a whole number
+// is taken off the first is exact, and the second goes onto the exponential as a factor (as in Comp<float>::exp2_shifted; an
+// exponent argument formed with one rounding, as the power-of-two sizes do, costs a chain of 10^4 steps 6.6e-7 of its
+// log-magnitudes instead of 3.2e-7).  A zero, like a NaN, is an entry of 2^-1.4e30.
+struct Log2Parts {
+    float hi, lo;
+};
+__device__ inline Log2Parts log2_parts(float re)
+{
+#pragma clang fp contract(off)
+    const float kHi = 1.44269502162933349609375f, kLo = 1.925963033500011e-8f;
+    const float x = vmax_raw(re, -1.0e30f);
+    Log2Parts p;
+    p.hi = x * kHi;
+    p.lo = __builtin_fmaf(x, kLo, __builtin_fmaf(x, kHi, -p.hi));
+    return p;
+}
+// 2^(p + shift), shift a whole number
+__device__ inline float exp2_parts(Log2Parts p, float shift)
+{
+    const float v = __builtin_amdgcn_exp2f(p.hi + shift);
+    return __builtin_fmaf(v, p.lo * 0.693147182464599609375f, v);
+}
+
 // REAL: the left factors are plain real matrices (4 bytes per entry instead of a GOOM's 8): an entry is
 // scaled by 2^(r_j - n_i) exactly, with no logarithm or exponential on the way in.
 // RAG: square matrices of a size d < DP (rows d entries apart in memory): the tile's rows and columns from d on
@@ -187,10 +211,16 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
             }
             const float re[4] = {it[q].a[0], it[q].a[2], it[q].b[0], it[q].b[2]};
             const float im[4] = {it[q].a[1], it[q].a[3], it[q].b[1], it[q].b[3]};
-            // row maximum of log2|A_ij| + r_j, to within rounding (any nearby whole number serves)
-            float u = __builtin_fmaf(re[0], kHi, rj[0]);
+            Log2Parts lp[4];
+            if constexpr (RAG == 2) {
 #pragma unroll
-            for (int e = 1; e < 4; ++e) u = vmax_raw(u, __builtin_fmaf(re[e], kHi, rj[e]));
+                for (int e = 0; e < 4; ++e) lp[e] = log2_parts(re[e]);
+            }
+            auto about = [&](int e) { return RAG == 2 ? lp[e].hi + rj[e] : __builtin_fmaf(re[e], kHi, rj[e]); };
+            // row maximum of log2|A_ij| + r_j, to within rounding (any nearby whole number serves)
+            float u = about(0);
+#pragma unroll
+            for (int e = 1; e < 4; ++e) u = vmax_raw(u, about(e));
             int key = C::key_of(u);
             key = C::imax(key, C::dpp<0xB1>(key));
             if (LPR >= 4) key = C::imax(key, C::dpp<0x4E>(key));
@@ -208,9 +238,14 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 // exponent argument with one rounding at its own (small) magnitude, then the low part of log2(e)
-                float t = __builtin_fmaf(re[e], kHi, rj[e] - nsub);
-                t = __builtin_fmaf(re[e], kLo, t);
-                const float v = __builtin_amdgcn_exp2f(t); // 2^-inf = 0 covers zero entries
+                float v;
+                if constexpr (RAG == 2) {
+                    v = exp2_parts(lp[e], rj[e] - nsub);
+                } else {
+                    float t = __builtin_fmaf(re[e], kHi, rj[e] - nsub);
+                    t = __builtin_fmaf(re[e], kLo, t);
+                    v = __builtin_amdgcn_exp2f(t); // 2^-inf = 0 covers zero entries
+                }
                 // parity of round(im / pi), read off the last mantissa bit after adding 1.5 * 2^23, and put on the sign
                 // bit with one shift-and-or (v is an exponential: its own sign bit is clear)
                 const float kf = __builtin_fmaf(im[e], 0.318309886183790671538f, 12582912.0f);

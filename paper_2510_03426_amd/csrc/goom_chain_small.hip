@@ -163,9 +163,15 @@ template <int D, bool OUT, bool RAG> __global__ __launch_bounds__(64, 6) void sm
         }
         const float im[4] = {live ? xa[slot][1] : 0.0f, live ? xa[slot][3] : 0.0f, live ? xb[slot][1] : 0.0f, live ? xb[slot][3] : 0.0f};
         load(t + kAhead, xa[slot], xb[slot]);
-        float u = __builtin_fmaf(re[0], kHi, rj[0]);
+        Log2Parts lp[4];
+        if constexpr (RAG) {
 #pragma unroll
-        for (int e = 1; e < 4; ++e) u = vmax_raw(u, __builtin_fmaf(re[e], kHi, rj[e]));
+            for (int e = 0; e < 4; ++e) lp[e] = log2_parts(re[e]);
+        }
+        auto about = [&](int e) { return RAG ? lp[e].hi + rj[e] : __builtin_fmaf(re[e], kHi, rj[e]); };
+        float u = about(0);
+#pragma unroll
+        for (int e = 1; e < 4; ++e) u = vmax_raw(u, about(e));
         int key = C::key_of(u);
         key = C::imax(key, C::dpp<0xB1>(key));
         key = C::imax(key, C::dpp<0x4E>(key));
@@ -176,9 +182,14 @@ template <int D, bool OUT, bool RAG> __global__ __launch_bounds__(64, 6) void sm
         f4 y;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            float tt = __builtin_fmaf(re[e], kHi, rj[e] - nsub);
-            tt = __builtin_fmaf(re[e], kLo, tt);
-            const float v = __builtin_amdgcn_exp2f(tt);
+            float v;
+            if constexpr (RAG) {
+                v = exp2_parts(lp[e], rj[e] - nsub);
+            } else {
+                float tt = __builtin_fmaf(re[e], kHi, rj[e] - nsub);
+                tt = __builtin_fmaf(re[e], kLo, tt);
+                v = __builtin_amdgcn_exp2f(tt);
+            }
             const float kf = __builtin_fmaf(im[e], 0.318309886183790671538f, 12582912.0f);
             y[e] = __builtin_bit_cast(float, __builtin_bit_cast(int, v) | (__builtin_bit_cast(int, kf) << 31));
         }

@@ -432,6 +432,14 @@ int launch_affine_backward_prepare(goom_ctx *ctx, const void *H, const void *G, 
     return bwd_shift_t<float>(ctx, H, G, shift, gt, T, d, batch);
 }
 
+int launch_initial_state_gradient(goom_ctx *ctx, const void *gA, void *gh0, long long T, int d, long long batch)
+{
+    prof_begin(ctx, "affine_backward_initial_state");
+    hipLaunchKernelGGL(bwd_h0_kernel<float>, dim3((unsigned)batch), dim3(128), 0, ctx->stream, static_cast<const float *>(gA), static_cast<float *>(gh0), T, d);
+    prof_end(ctx);
+    return check_hip(ctx, hipGetLastError(), "launch bwd_h0_kernel");
+}
+
 // One matrix for all steps, scan over the matrix itself: At [batch, d, d] = A^T, shift[b, s] = c_t, gt as above
 int launch_affine_backward_prepare_one_matrix(goom_ctx *ctx, const void *A, const void *H, const void *G, void *At, float *shift, void *gt, long long T, int d,
                                               long long batch, int dtype)

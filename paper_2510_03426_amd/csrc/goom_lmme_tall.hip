@@ -2,11 +2,12 @@
 // and B' [d, m] small, d, m <= 64, float components.  This is the shape of the state-space layer's input term (Section 4.3):
 // bias_t = B u_t for all steps t at once, the rows being the steps.
 //
-// B~ = (+-) 2^(log2|B_jk| - e_k), e_k a whole number near the column's largest log2 magnitude, is formed once per wave and stays in
-// registers in the matrix instruction's operand order; the rows of A' stream through, sixteen at a time per wave: each lane reads a
+// B~ = (+-) 2^(log2|B_jk| - e_k), e_k a whole number near the column's largest log2 magnitude, is formed once per workgroup, sixteen columns
+// a wave, and goes through LDS to every wave's registers, where it stays in the matrix instruction's operand order (formed by every
+// wave for itself it was most of the work where a wave has few rows: 64 x 1000 x 64 x 64 64 us, now 30); the rows of A' stream through, sixteen at a time per wave: each lane reads a
 // contiguous quarter of a row, the row shift n_i is a maximum over four lanes, A~ = (+-) 2^(log2|A_ij| - n_i) goes straight into the
 // instruction (16 x 16 x 4, float), and the store pass writes log|acc| + (n_i + e_k) ln 2 with the sign.  Every byte is read and
-// written once; nothing passes through LDS.
+// written once.
 //
 // Inner index order: lane group g of the instruction's four supplies inner index g KD / 4 + t at step t (KD: d padded to 16, 32 or
 // 64), for both operands, so that a lane's part of a row of A' is contiguous in memory.
@@ -41,9 +42,12 @@ template <int KD, int MS> __global__ __launch_bounds__(256) void lmme_tall_kerne
     const int d = a.d, m = a.m, n = a.n;
 
     // ---- B~ in registers: bt[s][t] = entry (g KS + t, 16 s + c), scaled by the column's shift
+    __shared__ f4 bsh[MS][KS / 4][64];
+    __shared__ float esh[MS][16];
     float bt[MS][KS], ecol[MS];
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
+        if (s != wave) continue; // (a constant s keeps the loads' places known; MS is at most the number of waves)
         const int col = 16 * s + c;
         float re[KS], im[KS];
         float top = kNegInf;
@@ -58,9 +62,22 @@ template <int KD, int MS> __global__ __launch_bounds__(256) void lmme_tall_kerne
         }
         top = C::xor16_32_max(top); // over the four lane groups: the whole column
         const float e = C::row_shift(top);
-        ecol[s] = e;
+        if (g == 0) esh[s][c] = e;
 #pragma unroll
-        for (int t = 0; t < KS; ++t) bt[s][t] = re[t] > kNegInf ? C::apply_sign(C::exp2_shifted(re[t], e), im[t]) : 0.0f;
+        for (int t = 0; t < KS; ++t) re[t] = re[t] > kNegInf ? C::apply_sign(C::exp2_shifted(re[t], e), im[t]) : 0.0f;
+#pragma unroll
+        for (int t = 0; t < KS; t += 4) bsh[s][t / 4][lane] = f4{re[t], re[t + 1], re[t + 2], re[t + 3]};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < MS; ++s) {
+        ecol[s] = esh[s][c];
+#pragma unroll
+        for (int t = 0; t < KS; t += 4) {
+            const f4 w = bsh[s][t / 4][lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bt[s][t + e] = w[e];
+        }
     }
 
     // ---- rows of A', sixteen at a time

@@ -160,7 +160,7 @@ template <bool ADJ, int SETS, int P, int DEPTH> __device__ __forceinline__ void 
     // slot (j / SETS) mod DEPTH: the lane's four entries of the matrix of step j
     f4 ra[DEPTH], rb[DEPTH];
     // Loads issued after a slot's own until its turn comes again, and (adjoint recurrence) gradients stored: one for every slot loaded
-    // from the start on, where they are zeros that the first gradient replaces, so that the number is the same all the way.
+    // from the start on, where they are zeros that the set's first gradient replaces (T is at least 2), so that the number is the same all the way.
     constexpr int kNewer = 2 * (DEPTH - 1) + (ADJ ? DEPTH : 0);
     auto load_slot = [&](auto sc, long long j) { // factor of step j (past the end: the last one again)
         constexpr int k = decltype(sc)::value;
@@ -171,9 +171,9 @@ template <bool ADJ, int SETS, int P, int DEPTH> __device__ __forceinline__ void 
         constexpr int k = decltype(sc)::value;
         wait_matrix_part<kNewer>(ra[k], rb[k]);
     };
-    auto store_zeros = [&]() { // (in asm, that it stays)
+    auto store_zeros = [&]() { // to the place of this set's first gradient (by the wave that writes it: its stores stay in order); in asm, that it stays
         const f4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-        asm volatile("global_store_dwordx4 %0, %1, off" : : "v"(gp + (size_t)(T - 1) * (D * D)), "v"(z) : "memory");
+        asm volatile("global_store_dwordx4 %0, %1, off" : : "v"(gp + (size_t)(T - 2 + P) * (D * D)), "v"(z) : "memory");
     };
     static_for<0, DEPTH>([&](auto sc) {
         load_slot(sc, SETS * decltype(sc)::value + P);
@@ -606,7 +606,7 @@ int launch_affine_seq(goom_ctx *ctx, const void *A, const void *bias, const void
 int launch_affine_seq_adjoint(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *G, int *scale, void *adj_bias,
                               void *states, void *grad_A, void *grad_bias, long long T, long long batch)
 {
-    if (T <= 0 || batch <= 0) return GOOM_OK;
+    if (T < 2 || batch <= 0) return goom::fail(ctx, GOOM_EINVAL, "the adjoint walk takes sequences of two steps and more");
     if (batch * T > 0x7fffffffLL) return goom::fail(ctx, GOOM_EUNSUPPORTED, "too many steps for one launch");
     const long long nsteps = batch * T, per_block = 256 / kSeqD;
     goom::prof_begin(ctx, "affine_backward_prepare_operands");

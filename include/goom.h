@@ -410,11 +410,12 @@ size_t goom_lmme_backward_workspace_bytes(int64_t batch, int n, int d, int m, in
 
 /* Backward of goom_scan (paper Section 4.1 with the derivatives of Section 3.1 in the limit eps -> 0).  With
  * P_t = M_t P_{t-1}, P_{-1} = S0 (the identity without one), and grad_P[b, t, i, k] = dL / d Re P[b, t, i, k],
- * the adjoints of the state values, Lam_t = grad_P_t / P_t + M_{t+1}^T Lam_{t+1} (d x m matrices), are the upper
+ * the adjoints of the state values are Lam_t = grad_P_t / P_t + M_{t+1}^T Lam_{t+1} (d x m matrices).  Up to
+ * d = m = 128 they are walked over chunks of the chain, gradients on the way; beyond, they are the upper
  * block of a prefix scan of stacked (d + m) x (d + m) matrices [[M_{t+1}^T, grad_P_t / P_t], [0, I]] in reverse
  * time, run by goom_scan itself on log-magnitudes shifted to ordinary size, and
  *     grad_M[b, t, i, j] = M_t[i, j] sum_k Lam_t[i, k] P_{t-1}[j, k],    grad_S0[b, j, k] = S0[j, k] (M_0^T Lam_0)[j, k]
- * (one batched LMME).  A state entry that is exactly zero passes no gradient.
+ * (there one batched LMME).  A state entry that is exactly zero passes no gradient.
  * M: [batch, T, d, d], S0: NULL or [batch, d, m], P: [batch, T, d, m] GOOMs as given to and returned by goom_scan
  * (m = d without S0); grad_P: [batch, T, d, m], grad_M: [batch, T, d, d], grad_S0: NULL or [batch, d, m] (needs
  * S0) reals of the component type; device, caller-owned, outputs overwritten.  d + m <= GOOM_MAX_DIM_LMME.

@@ -248,19 +248,18 @@ __device__ inline double read_lane_d(double v, int lane)
     return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// 1 / x and 1 / sqrt(x) to double precision: the hardware's double estimates (measured: 1 - x r up to 5e-8, 1 - x r^2 up to 1e-7)
-// and one step of third order
+// 1 / x and 1 / sqrt(x) to double precision from the float hardware approximations (x within float range)
 __device__ inline double rcp_d(double x)
 {
-    const double r = __builtin_amdgcn_rcp(x);
-    const double e = fma(-x, r, 1.0);
-    return fma(r, fma(e, e, e), r);
+    double r = (double)__builtin_amdgcn_rcpf((float)x);
+    r = r * (2.0 - x * r);
+    return r * (2.0 - x * r);
 }
 __device__ inline double rsqrt_d(double x)
 {
-    const double r = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * r, r, 1.0);
-    return fma(r * e, fma(e, 0.375, 0.5), r);
+    double r = (double)__builtin_amdgcn_rsqf((float)x);
+    r = r * (1.5 - 0.5 * x * r * r);
+    return r * (1.5 - 0.5 * x * r * r);
 }
 
 // lane K of every row of sixteen lanes, to all lanes of that row
@@ -272,30 +271,30 @@ template <int K> __device__ inline double row_bcast(double x)
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// x[i] += (src of lane i of the row of sixteen) * mul, for i = FROM .. 15: one instruction each, the broadcast being part of
+// x[i] += (src of lane i of the row of sixteen) * mul, for i = FROM .. TO - 1: one instruction each, the broadcast being part of
 // the multiply-add.  (A register that a vector instruction has just written may be read across lanes two issue slots later:
 // every block opens with that wait, since the compiler does not look into it.)
 #define GOOM_FMAC_BCAST(ACC, LANE) "v_fmac_f64_dpp " ACC ", %[s], %[m] row_newbcast:" LANE " row_mask:0xf bank_mask:0xf\n\t"
-template <int FROM> __device__ inline void fmac_bcast(double (&x)[16], double src, double mul)
+template <int FROM, int TO = 16> __device__ inline void fmac_bcast(double (&x)[16], double src, double mul)
 {
-    if constexpr (FROM + 8 <= 16) {
+    if constexpr (FROM + 8 <= TO) {
         asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k0]") GOOM_FMAC_BCAST("%1", "%[k1]") GOOM_FMAC_BCAST("%2", "%[k2]") GOOM_FMAC_BCAST("%3", "%[k3]")
                 GOOM_FMAC_BCAST("%4", "%[k4]") GOOM_FMAC_BCAST("%5", "%[k5]") GOOM_FMAC_BCAST("%6", "%[k6]") GOOM_FMAC_BCAST("%7", "%[k7]")
             : "+v"(x[FROM]), "+v"(x[FROM + 1]), "+v"(x[FROM + 2]), "+v"(x[FROM + 3]), "+v"(x[FROM + 4]), "+v"(x[FROM + 5]), "+v"(x[FROM + 6]), "+v"(x[FROM + 7])
             : [s] "v"(src), [m] "v"(mul), [k0] "n"(FROM), [k1] "n"(FROM + 1), [k2] "n"(FROM + 2), [k3] "n"(FROM + 3), [k4] "n"(FROM + 4), [k5] "n"(FROM + 5),
               [k6] "n"(FROM + 6), [k7] "n"(FROM + 7));
-        fmac_bcast<FROM + 8>(x, src, mul);
-    } else if constexpr (FROM + 4 <= 16) {
+        fmac_bcast<FROM + 8, TO>(x, src, mul);
+    } else if constexpr (FROM + 4 <= TO) {
         asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k0]") GOOM_FMAC_BCAST("%1", "%[k1]") GOOM_FMAC_BCAST("%2", "%[k2]") GOOM_FMAC_BCAST("%3", "%[k3]")
             : "+v"(x[FROM]), "+v"(x[FROM + 1]), "+v"(x[FROM + 2]), "+v"(x[FROM + 3])
             : [s] "v"(src), [m] "v"(mul), [k0] "n"(FROM), [k1] "n"(FROM + 1), [k2] "n"(FROM + 2), [k3] "n"(FROM + 3));
-        fmac_bcast<FROM + 4>(x, src, mul);
-    } else if constexpr (FROM + 2 <= 16) {
+        fmac_bcast<FROM + 4, TO>(x, src, mul);
+    } else if constexpr (FROM + 2 <= TO) {
         asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k0]") GOOM_FMAC_BCAST("%1", "%[k1]")
             : "+v"(x[FROM]), "+v"(x[FROM + 1])
             : [s] "v"(src), [m] "v"(mul), [k0] "n"(FROM), [k1] "n"(FROM + 1));
-        fmac_bcast<FROM + 2>(x, src, mul);
-    } else if constexpr (FROM + 1 <= 16) {
+        fmac_bcast<FROM + 2, TO>(x, src, mul);
+    } else if constexpr (FROM + 1 <= TO) {
         asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k0]") : "+v"(x[FROM]) : [s] "v"(src), [m] "v"(mul), [k0] "n"(FROM));
     }
 }
@@ -338,28 +337,41 @@ template <int KT> __device__ inline int column_exponent(const d4 (&Z)[KT])
 constexpr int kPanelLd = 18; // row stride of a 16-column panel (or of its Gram matrix) in LDS, in doubles
 
 // One pivot of the elimination below (by recursion, so that every index is a constant).  neg: minus the multipliers of step K.
-// The order is the source's: the next pivot's row is updated first, and its reciprocal, a chain of dependent instructions, is
-// formed between the updates that nothing waits for.
+// The order is the source's: the next pivot's row is updated first, and its reciprocal (rcp_d, step by step), a chain of dependent
+// instructions, is formed between the updates that nothing waits for.
 template <int K, int NR> __device__ inline void eliminate_from(double (&G)[16], double (&z)[NR][16], double neg, double &piv, int c)
 {
     if constexpr (K < 15) {
+        // (with two rows a lane the second row's updates are filler enough, and fewer pieces leave the registers alone)
+        constexpr int Z1 = NR > 1 ? 16 : K + 1 + (17 - K) / 3, Z2 = Z1 + (17 - Z1) / 2, G1 = NR > 1 ? 16 : K + 2 + (15 - K) / 2;
         asm("s_nop 1\n\t" GOOM_FMAC_BCAST("%0", "%[k]") : "+v"(G[K + 1]) : [s] "v"(G[K]), [m] "v"(neg), [k] "n"(K + 1));
         __builtin_amdgcn_sched_barrier(0);
-        fmac_bcast<K + 1>(z[0], neg, z[0][K]);
+        fmac_bcast<K + 1, Z1>(z[0], neg, z[0][K]);
         __builtin_amdgcn_sched_barrier(0);
         const double pivot = row_bcast<K + 1>(G[K + 1]);
-        const double r = __builtin_amdgcn_rcp(pivot);
+        const float coarse = (float)pivot;
         __builtin_amdgcn_sched_barrier(0);
-        fmac_bcast<K + 2>(G, G[K], neg);
+        fmac_bcast<K + 2, G1>(G, G[K], neg);
         __builtin_amdgcn_sched_barrier(0);
-        const double e = fma(-pivot, r, 1.0);
+        const float estimate = __builtin_amdgcn_rcpf(coarse);
+        __builtin_amdgcn_sched_barrier(0);
         if constexpr (NR > 1) {
-            __builtin_amdgcn_sched_barrier(0);
             fmac_bcast<K + 1>(z[1], neg, z[1][K]);
             __builtin_amdgcn_sched_barrier(0);
         }
+        fmac_bcast<Z1, Z2>(z[0], neg, z[0][K]);
+        __builtin_amdgcn_sched_barrier(0);
+        const double r = (double)estimate;
+        const double t = 2.0 - pivot * r;
+        __builtin_amdgcn_sched_barrier(0);
+        fmac_bcast<G1>(G, G[K], neg);
+        __builtin_amdgcn_sched_barrier(0);
+        const double r1 = r * t;
+        __builtin_amdgcn_sched_barrier(0);
+        fmac_bcast<Z2>(z[0], neg, z[0][K]);
+        __builtin_amdgcn_sched_barrier(0);
         piv = c == K + 1 ? G[K + 1] : piv;
-        const double inv = fma(r, fma(e, e, e), r);
+        const double inv = r1 * (2.0 - pivot * r1);
         eliminate_from<K + 1, NR>(G, z, -(G[K + 1] * (pivot > 1.0e-280 ? inv : 0.0)), piv, c);
     }
 }
@@ -372,8 +384,8 @@ template <int K, int NR> __device__ inline void eliminate_from(double (&G)[16], 
 // A chain of sixteen pivots is all latency, so nothing in it leaves the registers: every row of sixteen lanes holds the whole
 // Gram matrix, lane c its column c, every lane one row of the panel; what a step needs of other lanes is one lane's value for
 // sixteen others, which the multiply-add itself can fetch (at half its rate: 9 cycles; a broadcast into a register and two
-// multiply-adds that share it cost the same, and the compiler then puts the updates after the chain instead of into it).  185 cycles a
-// pivot (560 when rows and columns of the step went through LDS).
+// multiply-adds that share it cost the same, and the compiler then puts the updates after the chain instead of into it).  (560 cycles a
+// pivot when rows and columns of the step went through LDS, now about 200.)
 //
 // A pivot that comes out negative is a column that is nothing but rounding beside its norm: in a first pass it stays as it is,
 // its residual, with a pivot of 1, and the caller (told so) factors once more, where the residual stands for itself; in the
@@ -788,21 +800,32 @@ template <int DP, typename IO> __global__ __launch_bounds__(64) void reset_carry
 
 // ---------------------------------------------------------------------------------------------------
 // The carry kernel where every boundary is reset (policy "always") and d <= 64.  Panel p of a state depends on the panels
-// before it at the same boundary and on itself at the boundary before, and on nothing else: Z_p = T_c Q_p, then Z_p made
-// orthogonal to Q_0 .. Q_{p-1}, then its own factorisation.  So a workgroup gives a wave to every panel and runs them as
+// before it at the same boundary and on itself at the boundary before: Z_p = T_c Q_p, then Z_p made orthogonal to
+// Q_0 .. Q_{p-1}, then its own factorisation.  So a workgroup gives a wave to every panel and runs them as
 // stages of a pipeline, wave p at chunk s - p in stage s; the chain's pace is the last wave's stage and not the whole
 // factorisation.  Finished panels pass through LDS: panel q of a chunk is read up to KT - 1 - q stages after it was written, so a
 // ring of KT of them serves (one for the last panel, which only its own wave reads).
 //
-// Contraction indices of Z = T Q are dealt out as 4 g + v, so that a lane reads its part of a row of T_c (straight from
-// memory, one chunk ahead, no LDS tile) as 32 consecutive bytes.  Rows and columns past d are zero throughout: a zero pivot
-// leaves a zero column, and nothing of it reaches the others.
+// The arithmetic is reset_carry_kernel's, operation for operation: a late column of 128 steps can be 10^-8 of its norm off the
+// others, and what rounding leaves of it then moves the spectrum's tenth digit (both are 9e-10 off sequential QR
+// there), so results stay the same only if every bit does.  That includes when a state is factored a second time, which its worst column
+// decides and which replaces all panels: known only when the last wave is done with the chunk, KT - 1 stages after
+// the first.  The pipeline goes on as if there were none; when there is one, what was begun since is dropped, the chunk
+// goes through the waves a second time (each has its panel of the first in the ring) and those after it follow.  Growth is
+// booked once the decision is there.
 //
-// Bound by the last wave's chain of dependent instructions and double matrix instructions (64 cycles each).  d = 32, per chunk: 10 000
-// cycles (product 1100, two projections 2700, Gram matrix and rows 750, sixteen pivots 2950, scaling 600); one wave with a
-// whole state, four pivots per LDS round trip, took 20 400.  Carries of 512 chunks of 32 x 32: 4.34 -> 2.10 ms; of 110 chunks of
-// 64 x 64: 11.9 -> 1.45 ms (complex128, d = 50: 11.7 -> 2.2 ms).
-template <int DP> constexpr size_t staged_lds() { return ((size_t)((DP / 16 - 1) * (DP / 16) + 1) * DP + DP) * kPanelLd * sizeof(double); }
+// Rows and columns past d are zero throughout: a zero pivot leaves a zero column, and nothing of it reaches the others.
+//
+// Bound by the last wave's chain of dependent instructions and double matrix instructions (64 cycles each): product, two projections,
+// Gram matrix and rows, sixteen pivots, scaling.
+// Carries of 512 chunks of 32 x 32: 4.34 -> 2.55 ms (0.2 of it second factorisations), one wave with a whole state having
+// taken 20 400 cycles a chunk.  Whole spectra: 14 000 steps of 64 x 64 12.1 -> 1.89 ms, complex128 50 x 50 12.1 -> 2.03, complex128
+// 65 536 of 32 x 32, where nearly every chunk is factored twice (three stages a chunk instead of one), 7.5 -> 5.9.
+template <int DP> constexpr size_t staged_lds()
+{
+    constexpr int KT = DP / 16;
+    return (((size_t)((KT - 1) * KT + 1) * DP + DP) * kPanelLd + KT * DP * 2 + 4) * sizeof(double);
+}
 
 template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_carry_staged_kernel(ResetArgs a)
 {
@@ -818,13 +841,16 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
     const size_t car_mant = (size_t)DP * a.car_cols * sizeof(double);
     auto slot = [&](int q, long long i) { return reinterpret_cast<double *>(smem) + (size_t)(q * KT + (q + 1 < KT ? (int)(i & (KT - 1)) : 0)) * PANEL; };
     double *gram = reinterpret_cast<double *>(smem) + (size_t)((KT - 1) * KT + 1) * PANEL + p * 16 * kPanelLd;
+    // of the chunks that are not decided yet: a column's pivot and the exponents taken out of it
+    d2 *undecided = reinterpret_cast<d2 *>(reinterpret_cast<double *>(smem) + (size_t)((KT - 1) * KT + 1) * PANEL + DP * kPanelLd);
+    int *worst = reinterpret_cast<int *>(undecided + KT * DP); // [2][KT]: does a chunk's state have to be factored again, so far as waves 0 .. p know
 
-    d4 Y[KT]; // Y[mt][v] = entry (row 16 mt + 4 g + v, column 16 p + c), columns scaled by 2^yexp
+    d4 Y[KT]; // Y[mt][v] = entry (row 16 mt + 4 v + g, column 16 p + c), columns scaled by 2^yexp
     double yexp = 0.0, pprod = 1.0, pexp = 0.0; // product of all pivots so far = pprod 2^pexp (column exponents counted twice)
 #pragma unroll
     for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) Y[mt][v] = (16 * mt + 4 * g + v == col && col < d) ? 1.0 : 0.0;
+        for (int v = 0; v < 4; ++v) Y[mt][v] = (16 * mt + 4 * v + g == col && col < d) ? 1.0 : 0.0;
     if (a.s0 && col < d) {
         const IO *gp = reinterpret_cast<const IO *>(a.s0) + (size_t)b * d * d * 2;
         double cmax = -__builtin_huge_val();
@@ -834,7 +860,7 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
         for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int row = 16 * mt + 4 * g + v;
+                const int row = 16 * mt + 4 * v + g;
                 double val = 0.0;
                 if (row < d) {
                     const IO *e = gp + ((size_t)row * d + col) * 2;
@@ -852,7 +878,7 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
 #pragma unroll
             for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) mp[(size_t)(16 * mt + 4 * g + v) * a.car_cols + col] = Y[mt][v];
+                for (int v = 0; v < 4; ++v) mp[(size_t)(16 * mt + 4 * v + g) * a.car_cols + col] = Y[mt][v];
             if (g == 0) reinterpret_cast<double *>(carry(0) + car_mant)[col] = yexp;
         }
     }
@@ -868,12 +894,12 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
         }
     };
 
-    // the next chunk product.  d <= 32: as operands, row 16 mt + c, columns 16 kt + 4 g .. + 3.  d <= 64: a row's 128 bytes by eight
+    // The next chunk product.  d <= 32: as operands, row 16 mt + c, columns 16 kt + 4 v + g.  d <= 64: a row's 128 bytes by eight
     // lanes (as operands each load touches sixteen lines, and four waves' loads kept the memory pipe busy for half a stage).
     constexpr bool SLICES = DP > 32;
-    d2 tq[KT][KT][2];
+    double tq[KT][KT][4];
     double tex;
-    const unsigned lane_at = (unsigned)((SLICES ? (lane >> 3) * a.tot_cols + 2 * (lane & 7) : c * a.tot_cols + 4 * g) * sizeof(double));
+    const unsigned lane_at = (unsigned)((SLICES ? (lane >> 3) * a.tot_cols + 2 * (lane & 7) : c * a.tot_cols + g) * sizeof(double));
     auto load_total = [&](long long i) {
         const unsigned char *tp = a.totals + (b * a.C + i) * a.tot_stride;
         tex = *reinterpret_cast<const double *>(tp + tot_mant);
@@ -882,10 +908,17 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
             const int at = 16 * kt < a.tot_cols ? 16 * kt : 0;
 #pragma unroll
             for (int mt = 0; mt < KT; ++mt)
+                if constexpr (SLICES) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) { // (one base for the wave, one offset for the lane)
-                    const unsigned char *base = tp + (size_t)((16 * mt + (SLICES ? 8 * h : 0)) * a.tot_cols + at) * sizeof(double);
-                    tq[mt][kt][h] = *reinterpret_cast<const d2 *>(base + lane_at + (SLICES ? 0 : 16 * h));
+                    for (int h = 0; h < 2; ++h) { // (one base for the wave, one offset for the lane)
+                        const d2 x = *reinterpret_cast<const d2 *>(tp + (size_t)((16 * mt + 8 * h) * a.tot_cols + at) * sizeof(double) + lane_at);
+                        tq[mt][kt][2 * h] = x[0];
+                        tq[mt][kt][2 * h + 1] = x[1];
+                    }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        tq[mt][kt][v] = *reinterpret_cast<const double *>(tp + (size_t)(16 * mt * a.tot_cols + at + 4 * v) * sizeof(double) + lane_at);
                 }
         }
     };
@@ -896,12 +929,10 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const int row = SLICES ? 16 * mt + 8 * h + (lane >> 3) : 16 * mt + c, k = 16 * kt + (SLICES ? 2 * (lane & 7) : 4 * g + 2 * h) + e;
-                            if (row >= d || k >= d) tq[mt][kt][h][e] = 0.0;
-                        }
+                    for (int v = 0; v < 4; ++v) {
+                        const int row = SLICES ? 16 * mt + 8 * (v >> 1) + (lane >> 3) : 16 * mt + c, k = 16 * kt + (SLICES ? 2 * (lane & 7) + (v & 1) : 4 * v + g);
+                        if (row >= d || k >= d) tq[mt][kt][v] = 0.0;
+                    }
         }
     };
 
@@ -916,13 +947,9 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
 #pragma unroll
             for (int h = 0; h < 2; ++h) qa[mt][h] = -*reinterpret_cast<const d2 *>(&pq[(16 * mt + c) * kPanelLd + 4 * g + 2 * h]);
     };
-    // Q of Z (in the matrix instruction's layout) to `out` and, as rows, to `rows`; the product of its pivots and the exponents taken
-    // out of its columns.  A panel whose columns lose much of their norm is factored a second time: each on its own account, hence
-    // from a loss on that lies below the one the other kernels take over all panels (a column's largest entry is near 1 here).
-    const double again = sizeof(IO) == 4 ? 1.0e-9 : 0.5;
-    auto factor = [&](d4 (&Z)[KT], long long i, double *out, double (&rows)[1][16], double &prod, double &expo) {
-        prod = 1.0;
-        expo = 0.0;
+    // Q of Z (in the matrix instruction's layout) to `out` and, as rows, to `rows`; the columns' pivots and exponents.  Returns whether
+    // one of the columns asks for a second factorisation (see qr_panels_d and its callers).
+    auto factor = [&](d4 (&Z)[KT], long long i, double *out, double (&rows)[1][16], double &piv, double &expo, bool second) {
         auto project = [&]() {
             d4 R = {0., 0., 0., 0.};
 #pragma unroll
@@ -934,107 +961,139 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
 #pragma unroll
                 for (int mt = 0; mt < KT; ++mt) Z[mt] = mfma8(qa[mt][v >> 1][v & 1], R[v], Z[mt]);
         };
-#pragma unroll 1
-        for (int pass = 0; pass < 2; ++pass) {
-            const int ex = column_exponent(Z);
-            expo += (double)ex;
+        const int ex = column_exponent(Z);
+        expo = (double)ex;
+        double norm2 = 0.0;
 #pragma unroll
-            for (int mt = 0; mt < KT; ++mt)
+        for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) Z[mt][v] = ldexp(Z[mt][v], -ex);
-            // orthogonal to the finished panels, twice (see qr_panels_d; a panel that is so already, once)
+            for (int v = 0; v < 4; ++v) {
+                Z[mt][v] = ldexp(Z[mt][v], -ex);
+                norm2 = fma(Z[mt][v], Z[mt][v], norm2);
+            }
+        norm2 = column_sum(norm2);
+        // orthogonal to the finished panels, twice (see qr_panels_d)
 #pragma unroll 1
-            for (int rep = pass; rep < 2; ++rep)
+        for (int rep = 0; rep < 2; ++rep)
 #pragma unroll 1
-                for (int q = 0; q < p; ++q) {
-                    if (KT > 2) load_panel(q, i);
-                    project();
-                }
-            double piv;
-            const bool open = factor_panel_rows<DP>(Z, piv, out, gram, rows, lane, pass == 1);
-            prod *= piv > 1.0e-280 ? piv : 0.0;
-            if (pass == 1 || (!open && __builtin_amdgcn_ballot_w64(piv > 1.0e-280 && piv < again) == 0)) break;
-            panel_tiles<DP>(Z, out, g, c);
-        }
+            for (int q = 0; q < p; ++q) {
+                if (KT > 2) load_panel(q, i);
+                project();
+            }
+        const bool open = factor_panel_rows<DP>(Z, piv, out, gram, rows, lane, second);
+        return open || __builtin_amdgcn_ballot_w64(piv > 1.0e-280 && norm2 > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3) * piv) != 0;
     };
     // growth as in reset_carry_kernel (a column that is zero has none)
-    auto grow = [&](double prod, double expo) {
-        if (prod > 0.0) {
+    auto grow = [&](double first, double second, double expo) {
+        if (first > 1.0e-280 && second > 1.0e-280) {
             int e;
-            pprod = frexp(pprod * prod, &e);
+            pprod = frexp(pprod * first * second, &e);
             pexp += 2.0 * expo + (double)e;
         }
     };
 
-    if (a.C > 0) load_total(0);
+    load_total(0);
     const long long items = a.C + (a.growth ? 1 : 0); // (the last one: growth of the final state, factorised, not replaced)
-    for (long long s = 0; s < items + KT - 1; ++s) {
-        const long long i = s - p;
-        if (i >= 0 && i < items) { // (the same for the whole wave)
+    // wave p is at chunk from + n - p in stage n since the last (re)start, which begins with the second factorisation of chunk `from` if `redo`
+    long long from = 0, n = 0;
+    bool redo = false;
+    double redo_piv = 1.0, redo_expo = 0.0; // pivots and exponents of that chunk's first factorisation
+    d2 own; // what this wave has left in `undecided` last
+    bool hit = false;
+    for (int stage = 0;; stage ^= 1, ++n) {
+        const long long i = from + n - p;
+        const bool second = redo && i == from;
+        if (n >= p && i < items) { // (the same for the whole wave)
             double *out = slot(p, i);
-            double rows[1][16], prod, expo;
+            double rows[1][16], piv, expo, zexp = yexp;
             d4 Z[KT];
+            hit = false;
+            const bool boundary = i == a.C || (i + 1) * a.L <= a.T; // (a last, shorter chunk ends at no boundary)
             if (KT == 2 && p > 0) load_panel(0, i); // (it is there since the stage before)
-            if (i < a.C) {
-                const double zexp = yexp + tex;
+            if (second) {
+                panel_tiles<DP>(Z, out, g, c);
+            } else if (i < a.C) {
+                zexp = yexp + tex;
                 clear_past_d();
 #pragma unroll
                 for (int mt = 0; mt < KT; ++mt) Z[mt] = d4{0., 0., 0., 0.};
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt) {
-                    d2 ta[KT][2];
-                    if constexpr (SLICES) { // (sixteen columns at a time through this panel's own place)
+                    double ta[KT][4];
+                    if constexpr (SLICES) { // (sixteen columns at a time through this panel's own place, column j at position perm16(j))
+                        const int j = 2 * (lane & 7), pj = ((j & 3) << 2) | (j >> 2); // (column j + 1: four places on)
                         wave_sync();
 #pragma unroll
                         for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
-                            for (int h = 0; h < 2; ++h) *reinterpret_cast<d2 *>(&out[(16 * mt + 8 * h + (lane >> 3)) * kPanelLd + 2 * (lane & 7)]) = tq[mt][kt][h];
+                            for (int v = 0; v < 4; ++v) out[(16 * mt + 8 * (v >> 1) + (lane >> 3)) * kPanelLd + pj + 4 * (v & 1)] = tq[mt][kt][v];
                         wave_sync();
                     }
 #pragma unroll
                     for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
-                        for (int h = 0; h < 2; ++h) ta[mt][h] = SLICES ? *reinterpret_cast<const d2 *>(&out[(16 * mt + c) * kPanelLd + 4 * g + 2 * h]) : tq[mt][kt][h];
+                        for (int h = 0; h < 2; ++h) {
+                            const d2 x = SLICES ? *reinterpret_cast<const d2 *>(&out[(16 * mt + c) * kPanelLd + 4 * g + 2 * h]) : d2{tq[mt][kt][2 * h], tq[mt][kt][2 * h + 1]};
+                            ta[mt][2 * h] = x[0];
+                            ta[mt][2 * h + 1] = x[1];
+                        }
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
 #pragma unroll
-                        for (int mt = 0; mt < KT; ++mt) Z[mt] = mfma8(ta[mt][v >> 1][v & 1], Y[kt][v], Z[mt]);
+                        for (int mt = 0; mt < KT; ++mt) Z[mt] = mfma8(ta[mt][v], Y[kt][v], Z[mt]);
                 }
-                load_total(i + 1 < a.C ? i + 1 : i);
-                const bool boundary = (i + 1) * a.L <= a.T; // (a last, shorter chunk ends at no boundary)
-                if (boundary)
-                    factor(Z, i, out, rows, prod, expo);
-                else { // columns renormalised by a power of two
-                    const int ex = column_exponent(Z);
-                    yexp = col < d ? zexp + (double)ex : 0.0;
-#pragma unroll
-                    for (int mt = 0; mt < KT; ++mt)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) out[(16 * mt + 4 * v + g) * kPanelLd + pc] = ldexp(Z[mt][v], -ex);
-                    wave_sync();
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) rows[0][j] = out[(lane & (DP - 1)) * kPanelLd + (((j & 3) << 2) | (j >> 2))];
+            } else {
+                panel_tiles<DP>(Z, slot(p, i - 1), g, c);
+            }
+            load_total(i + 1 < a.C ? i + 1 : a.C - 1); // (in one place: loads in several would be copied together, and waited for, where they meet)
+            if (boundary) {
+                hit = factor(Z, i, out, rows, piv, expo, second);
+                if (second) {
+                    grow(redo_piv, piv, redo_expo + expo);
+                } else {
+                    own = d2{piv, zexp + expo};
+                    if (KT > 1 && g == 0) undecided[(i & (KT - 1)) * DP + col] = own;
                 }
+                if (i < a.C) yexp = 0.0;
+            } else { // columns renormalised by a power of two
+                const int ex = column_exponent(Z);
+                yexp = col < d ? zexp + (double)ex : 0.0;
 #pragma unroll
                 for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) Y[mt][v] = out[(16 * mt + 4 * g + v) * kPanelLd + pc];
-                if (boundary) {
-                    grow(prod, zexp + expo);
-                    yexp = 0.0;
-                }
+                    for (int v = 0; v < 4; ++v) out[(16 * mt + 4 * v + g) * kPanelLd + pc] = ldexp(Z[mt][v], -ex);
+                wave_sync();
+#pragma unroll
+                for (int j = 0; j < 16; ++j) rows[0][j] = out[(lane & (DP - 1)) * kPanelLd + (((j & 3) << 2) | (j >> 2))];
+            }
+            if (i < a.C) {
+                panel_tiles<DP>(Y, out, g, c);
                 if (a.carries) store_carry(i + 1, rows);
                 if (tid == 0) a.chunk_flags[b * a.C + i] = boundary ? 1 : 0;
-            } else {
-                panel_tiles<DP>(Z, slot(p, i - 1), g, c);
-                factor(Z, i, out, rows, prod, expo);
-                grow(prod, yexp + expo);
             }
+            if (KT > 1 && lane == 0) worst[stage * KT + p] = (hit && !second) || (p > 0 && !second && worst[(stage ^ 1) * KT + p - 1]);
         }
         // (LDS only: the loads of the next chunk product and the stores of carries stay in flight)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        // the chunk that the last wave has finished (all waves come to the same answer)
+        if (n < KT - 1) continue;
+        const long long done = from + n - (KT - 1);
+        if (!(redo && done == from) && (done == a.C || (done + 1) * a.L <= a.T)) {
+            const d2 first = KT > 1 ? undecided[(done & (KT - 1)) * DP + col] : own;
+            if (KT > 1 ? __builtin_amdgcn_readfirstlane(worst[stage * KT + KT - 1]) != 0 : hit) {
+                from = done;
+                n = -1;
+                redo = true;
+                redo_piv = first[0];
+                redo_expo = first[1];
+                yexp = 0.0;
+                continue;
+            }
+            grow(first[0], 1.0, first[1]);
+        }
+        if (done + 1 == items) break;
     }
     if (a.growth && g == 0 && col < d) a.growth[b * d + col] = 0.5 * (log(pprod) + pexp * kLn2) * a.growth_scale;
 }

@@ -76,3 +76,25 @@ def test_column_of_rounding_keeps_its_growth(G, oracle, T, d, every, thr, seed):
     _, _, oflag, ogrowth = oracle.reset_scan(Jz, S0, check_every=every, policy=0, cos_threshold=thr)
     assert np.array_equal(flags, oflag)
     assert np.abs(growth - ogrowth).max() < 1e-3 * T
+
+
+# One state, two kernels: a wave per panel where every boundary is reset, a wave with the whole state where a boundary is examined first.  With
+# a threshold of zero the second resets every boundary too, and the two take the same operations in the same order: every bit is the same,
+# also where some boundaries need a second factorisation (products of Gaussian matrices: some, nearly all and none of them).
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("d", [2, 16, 17, 32, 33, 48, 64])
+def test_same_bits_as_the_kernel_that_examines(G, oracle, d, ctype):  # noqa: F811
+    from paper_2510_03426_amd import RESET_COLINEAR
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    rng = np.random.default_rng(d)
+    for T, every, gain, start in ((60, 1, 1.0, False), (61, 2, 1.0, True), (62, 3, 1.0, True), (41, 4, 0.5, False), (40, 8, 0.2, True)):
+        J = rng.standard_normal((2, T, d, d)) / np.sqrt(d)
+        J = oracle.to_goom(((1.0 - gain) * np.eye(d) + gain * J).astype(comp))
+        S = oracle.to_goom(rng.standard_normal((2, d, d)).astype(comp)) if start else None
+        say(f"always against examined T={T} d={d} every={every} gain={gain} {np.dtype(ctype).name}")
+        put = dev(S) if start else None
+        a = [host(v) for v in G.scan_reset(dev(J), put, chunk_len=every)]
+        b = [host(v) for v in G.scan_reset(dev(J), put, chunk_len=every, policy=RESET_COLINEAR, cos_threshold=0.0)]
+        assert np.array_equal(a[1], b[1])
+        assert np.array_equal(a[2], b[2]), np.abs(a[2] - b[2]).max()
+        assert np.array_equal(a[0], b[0])

@@ -102,7 +102,12 @@ template <typename R, int DP> struct Tiles {
     static constexpr int kM = sizeof(R) == 4 ? DP + 4 : DP % 32 == 16 ? DP : DP + 16;
     static constexpr int kAll = kOne ? DP * (kLam > kM ? kLam : kM) : DP * (kLam + kM);
     static constexpr size_t kBytes = (size_t)kAll * sizeof(R) + 2 * DP * sizeof(int);
+    static_assert(kLam * sizeof(R) % 16 == 0, "rows of Lam are read in pieces of 16 bytes");
 };
+// four entries of a row of Lam: rows of an odd number lie 16 bytes from a multiple of 32 in double
+template <typename R> struct RowPiece;
+template <> struct RowPiece<float> { typedef f4 type; };
+template <> struct RowPiece<double> { typedef double type __attribute__((ext_vector_type(4), aligned(16))); };
 
 template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, sizeof(R) == 4 || DP > 64 ? 2 : 1) void scan_adjoint_kernel(AdjointArgs<R> a)
 {
@@ -396,7 +401,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                     R big = 0;
 #pragma unroll
                     for (int kt = 0; kt < KT; ++kt) {
-                        la[kt] = *reinterpret_cast<const vec4 *>(&lam[(16 * it + c) * TL::kLam + 16 * kt + 4 * g]);
+                        la[kt] = *reinterpret_cast<const typename RowPiece<R>::type *>(&lam[(16 * it + c) * TL::kLam + 16 * kt + 4 * g]);
 #pragma unroll
                         for (int v = 0; v < 4; ++v) big = X2::larger(big, N::abs_(la[kt][v]));
                     }

@@ -420,8 +420,8 @@ size_t goom_lmme_backward_workspace_bytes(int64_t batch, int n, int d, int m, in
  * (m = d without S0); grad_P: [batch, T, d, m], grad_M: [batch, T, d, d], grad_S0: NULL or [batch, d, m] (needs
  * S0) reals of the component type; device, caller-owned, outputs overwritten.  d + m <= GOOM_MAX_DIM_LMME.
  * opts: as for goom_scan (chunk length of the reverse scan); flags must be 0.  workspace:
- * goom_scan_backward_workspace_bytes(..., with_init = S0 != NULL) bytes, required: about
- * (d + m)(d + 2 m) GOOMs per step.  Errors: GOOM_EINVAL, GOOM_EUNSUPPORTED (sizes), GOOM_EWORKSPACE. */
+ * goom_scan_backward_workspace_bytes(..., with_init = S0 != NULL) bytes, required: up to d = m = 128 two real matrices
+ * (d x d and d x m, padded) per chunk, beyond about (d + m)(d + 2 m) GOOMs per step.  Errors: GOOM_EINVAL, GOOM_EUNSUPPORTED (sizes), GOOM_EWORKSPACE. */
 int goom_scan_backward(goom_ctx *ctx, const void *M, const void *S0, const void *P, const void *grad_P, void *grad_M,
                        void *grad_S0, int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts,
                        void *workspace, size_t workspace_bytes);

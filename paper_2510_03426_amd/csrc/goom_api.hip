@@ -1541,8 +1541,26 @@ static int64_t scan_adjoint_chunk(int64_t T, int d, int m, int64_t batch, const 
     return L < T ? L : T;
 }
 
+// Its workspace: a chunk product and a chunk vector for every chunk, none where a chain is one chunk (65 536 steps of complex64 64 x 64:
+// 17 MB; the scan of stacked factors above these sizes holds all of its factors and states, 13 GB there).
+struct ScanAdjointPlan {
+    int64_t L, C;
+    FactLayout tot, vec;
+    size_t bytes;
+};
+static ScanAdjointPlan plan_scan_adjoint(int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts)
+{
+    ScanAdjointPlan p;
+    p.L = scan_adjoint_chunk(T, d, m, batch, opts);
+    p.C = (T + p.L - 1) / p.L;
+    p.tot = fact_layout(padded_dim(d), d, dtype);
+    p.vec = fact_layout(padded_dim(d > m ? d : m), m, dtype);
+    p.bytes = p.C > 1 ? (size_t)batch * p.C * (p.tot.stride + p.vec.stride) : 0;
+    return p;
+}
+
 static int run_scan_adjoint(goom_ctx *ctx, const void *M, const void *S0, const void *P, const void *grad_P, void *grad_M, void *grad_S0, int64_t T, int d, int m,
-                            int64_t batch, int dtype, const goom_scan_opts *opts, unsigned char *ws, size_t ws_bytes)
+                            int64_t batch, int dtype, const ScanAdjointPlan &p, unsigned char *ws)
 {
     ScanAdjointLaunch a;
     a.M = M;
@@ -1556,14 +1574,10 @@ static int run_scan_adjoint(goom_ctx *ctx, const void *M, const void *S0, const 
     a.d = d;
     a.m = m;
     a.dtype = dtype;
-    a.tot = fact_layout(padded_dim(d), d, dtype);
-    a.vec = fact_layout(padded_dim(d > m ? d : m), m, dtype);
-    a.L = scan_adjoint_chunk(T, d, m, batch, opts);
-    a.C = (T + a.L - 1) / a.L;
-    if ((size_t)batch * a.C * (a.tot.stride + a.vec.stride) > ws_bytes) { // (a few small steps whose matrices are mostly padding)
-        a.L = T;
-        a.C = 1;
-    }
+    a.tot = p.tot;
+    a.vec = p.vec;
+    a.L = p.L;
+    a.C = p.C;
     a.totals = ws;
     a.vecs = ws + (size_t)batch * a.C * a.tot.stride;
     if (a.C > 1) {
@@ -1593,6 +1607,11 @@ size_t goom_scan_backward_workspace_bytes(int64_t T, int d, int m, int64_t batch
     if (T <= 0 || d <= 0 || m <= 0 || batch <= 0 || d + m > GOOM_MAX_DIM_LMME) return 0;
     if (dtype != GOOM_C64 && dtype != GOOM_C128) return 0;
     if (!with_init && m != d) return 0;
+    // (in pieces of 256 KiB: a program that keeps one workspace for calls of nearby sizes allocates it once)
+    if (d <= GOOM_MAX_DIM && m <= GOOM_MAX_DIM) {
+        const size_t need = plan_scan_adjoint(T, d, m, batch, dtype, opts).bytes;
+        return align_up(need ? need : 1, (size_t)256 << 10);
+    }
     return plan_scan_backward(T, d, m, batch, dtype, opts, with_init != 0).total();
 }
 
@@ -1608,11 +1627,16 @@ int goom_scan_backward(goom_ctx *ctx, const void *M, const void *S0, const void 
     if (S0 && !aligned(S0, 16)) return fail(ctx, GOOM_EINVAL, "complex data must be 16-byte aligned");
     const size_t rb = comp_bytes(dtype);
     if (!aligned(grad_P, rb) || !aligned(grad_M, rb) || (grad_S0 && !aligned(grad_S0, rb))) return fail(ctx, GOOM_EINVAL, "misaligned data pointer");
+    unsigned char *w = static_cast<unsigned char *>(ws);
+    if (d <= GOOM_MAX_DIM && m <= GOOM_MAX_DIM) {
+        const ScanAdjointPlan q = plan_scan_adjoint(T, d, m, batch, dtype, opts);
+        if (int s = check_workspace(ctx, ws, ws_bytes, q.bytes)) return s;
+        if (int s = need_ctx(ctx)) return s;
+        return run_scan_adjoint(ctx, M, S0, P, grad_P, grad_M, grad_S0, T, d, m, batch, dtype, q, w);
+    }
     const ScanBackwardPlan p = plan_scan_backward(T, d, m, batch, dtype, opts, S0 != nullptr);
     if (int s = check_workspace(ctx, ws, ws_bytes, p.total())) return s;
     if (int s = need_ctx(ctx)) return s;
-    unsigned char *w = static_cast<unsigned char *>(ws);
-    if (d <= GOOM_MAX_DIM && m <= GOOM_MAX_DIM) return run_scan_adjoint(ctx, M, S0, P, grad_P, grad_M, grad_S0, T, d, m, batch, dtype, opts, w, p.total());
     void *c = w;
     unsigned char *F = w + p.c_bytes;
     void *init = F + p.f_bytes;

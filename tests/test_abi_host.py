@@ -132,6 +132,20 @@ def test_argument_validation_without_device(lib):
     assert lib.goom_status_name(-3).decode() == "GOOM_EWORKSPACE"
 
 
+def test_scan_backward_workspace_follows_its_plan(lib):
+    from paper_2510_03426_amd.binding import ScanOpts
+    need = lambda T, d, m, code, chunk=0: lib.goom_scan_backward_workspace_bytes(T, d, m, 1, code, C.byref(ScanOpts(chunk, 0)), 1)
+    # up to 128 a chunk product and a chunk vector for every chunk: no more than 1/32 of the factors here, with room for both paddings
+    assert need(65536, 64, 64, 0) <= 65536 * 64 * 64 * 8 // 32
+    # and all chunks that the call plans for fit, also where a padded matrix is larger than eight steps of what it is for
+    for d, m, code, chunk, chunks in ((1, 1, 0, 0, 128), (1, 1, 1, 0, 128), (2, 2, 0, 32, 128), (2, 1, 1, 32, 128), (64, 64, 0, 64, 64)):
+        size = 8 if code else 4
+        dp = (max(d, m) + 15) // 16 * 16
+        assert need(4096, d, m, code, chunk) >= chunks * dp * size * ((d + 15) // 16 * 16 + (m + 15) // 16 * 16)
+    # beyond, the stacked factors and states as before
+    assert need(64, 200, 8, 0) >= 65 * 208 * (208 + 8) * 8
+
+
 def test_workspace_queries(lib):
     from paper_2510_03426_amd.binding import ScanOpts
     # one chunk needs no workspace; more chunks need room for chunk products and prefixes

@@ -70,3 +70,13 @@ def test_rows_in_units_of_their_own(G, oracle, d, ctype):  # noqa: F811
     units = np.rint(np.linspace(-1.0, 1.0, d) * (20.0 if ctype == np.complex64 else 200.0))
     run(G, oracle, 20, d, d, 1, 8, ctype, True, units)
     run(G, oracle, 20, d, d, 1, 0, ctype, True, np.random.default_rng(d).permutation(units))
+
+
+# matrices that are mostly padding, in many chunks: the workspace that the query names holds them all
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("d", [1, 2])
+def test_tiny_matrices_in_many_chunks(G, oracle, d, ctype):  # noqa: F811
+    G.profile_enable(True)
+    run(G, oracle, 1500, d, d, 1, 0, ctype, True)
+    assert "scan_adjoint_carries" in [label for label, _ in G.profile_records()]
+    G.profile_enable(False)

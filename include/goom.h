@@ -415,13 +415,15 @@ size_t goom_lmme_backward_workspace_bytes(int64_t batch, int n, int d, int m, in
  * block of a prefix scan of stacked (d + m) x (d + m) matrices [[M_{t+1}^T, grad_P_t / P_t], [0, I]] in reverse
  * time, run by goom_scan itself on log-magnitudes shifted to ordinary size, and
  *     grad_M[b, t, i, j] = M_t[i, j] sum_k Lam_t[i, k] P_{t-1}[j, k],    grad_S0[b, j, k] = S0[j, k] (M_0^T Lam_0)[j, k]
- * (there one batched LMME).  A state entry that is exactly zero passes no gradient.
+ * (there one batched LMME).  A state entry that is exactly zero passes no gradient.  Up to d = m = 128 magnitudes may lie as
+ * far apart as they like; a batch item that a column's mantissas cannot hold is walked again with an exponent for every entry
+ * (some thirty times as long).  Log-magnitudes up to 2^52.
  * M: [batch, T, d, d], S0: NULL or [batch, d, m], P: [batch, T, d, m] GOOMs as given to and returned by goom_scan
  * (m = d without S0); grad_P: [batch, T, d, m], grad_M: [batch, T, d, d], grad_S0: NULL or [batch, d, m] (needs
  * S0) reals of the component type; device, caller-owned, outputs overwritten.  d + m <= GOOM_MAX_DIM_LMME.
  * opts: as for goom_scan (chunk length of the reverse scan); flags must be 0.  workspace:
  * goom_scan_backward_workspace_bytes(..., with_init = S0 != NULL) bytes, required: up to d = m = 128 two real matrices
- * (d x d and d x m, padded) per chunk, beyond about (d + m)(d + 2 m) GOOMs per step.  Errors: GOOM_EINVAL, GOOM_EUNSUPPORTED (sizes), GOOM_EWORKSPACE. */
+ * (d x d and d x m) per chunk with a double beside every entry, beyond about (d + m)(d + 2 m) GOOMs per step.  Errors: GOOM_EINVAL, GOOM_EUNSUPPORTED (sizes), GOOM_EWORKSPACE. */
 int goom_scan_backward(goom_ctx *ctx, const void *M, const void *S0, const void *P, const void *grad_P, void *grad_M,
                        void *grad_S0, int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts,
                        void *workspace, size_t workspace_bytes);

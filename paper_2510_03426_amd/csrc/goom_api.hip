@@ -1541,12 +1541,13 @@ static int64_t scan_adjoint_chunk(int64_t T, int d, int m, int64_t batch, const 
     return L < T ? L : T;
 }
 
-// Its workspace: a chunk product and a chunk vector for every chunk, none where a chain is one chunk (65 536 steps of complex64 64 x 64:
-// 17 MB; the scan of stacked factors above these sizes holds all of its factors and states, 13 GB there).
+// Its workspace: for every chunk two flags, a chunk product and a chunk vector, in the walk and, in their place once it
+// is done, with an exponent an entry (65 536 steps of complex64 64 x 64: 17 and 50 MB; the scan of stacked factors above these sizes
+// holds all of its factors and states, 13 GB there).
 struct ScanAdjointPlan {
     int64_t L, C;
     FactLayout tot, vec;
-    size_t bytes;
+    size_t flags, slot, bytes;
 };
 static ScanAdjointPlan plan_scan_adjoint(int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts)
 {
@@ -1555,7 +1556,10 @@ static ScanAdjointPlan plan_scan_adjoint(int64_t T, int d, int m, int64_t batch,
     p.C = (T + p.L - 1) / p.L;
     p.tot = fact_layout(padded_dim(d), d, dtype);
     p.vec = fact_layout(padded_dim(d > m ? d : m), m, dtype);
-    p.bytes = p.C > 1 ? (size_t)batch * p.C * (p.tot.stride + p.vec.stride) : 0;
+    p.flags = align_up((size_t)batch * p.C * 2 * sizeof(int), 256);
+    p.slot = scan_adjoint_slot_bytes(p.C, d, m, dtype);
+    const size_t walk = p.C > 1 ? p.tot.stride + p.vec.stride : 0;
+    p.bytes = p.flags + (size_t)batch * p.C * (walk > p.slot ? walk : p.slot);
     return p;
 }
 
@@ -1578,8 +1582,12 @@ static int run_scan_adjoint(goom_ctx *ctx, const void *M, const void *S0, const 
     a.vec = p.vec;
     a.L = p.L;
     a.C = p.C;
+    a.wide = reinterpret_cast<int *>(ws);
+    ws += p.flags;
     a.totals = ws;
     a.vecs = ws + (size_t)batch * a.C * a.tot.stride;
+    a.slots = ws;
+    a.slot_stride = p.slot;
     if (a.C > 1) {
         ChainLaunch l;
         std::memset(&l, 0, sizeof l);
@@ -1599,7 +1607,8 @@ static int run_scan_adjoint(goom_ctx *ctx, const void *M, const void *S0, const 
         if (int s = launch_chain(ctx, l)) return s;
         if (int s = launch_scan_adjoint(ctx, a, 0)) return s;
     }
-    return launch_scan_adjoint(ctx, a, 1);
+    if (int s = launch_scan_adjoint(ctx, a, 1)) return s;
+    return launch_scan_adjoint_wide(ctx, a);
 }
 
 size_t goom_scan_backward_workspace_bytes(int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts, int with_init)
@@ -1610,7 +1619,7 @@ size_t goom_scan_backward_workspace_bytes(int64_t T, int d, int m, int64_t batch
     // (in pieces of 256 KiB: a program that keeps one workspace for calls of nearby sizes allocates it once)
     if (d <= GOOM_MAX_DIM && m <= GOOM_MAX_DIM) {
         const size_t need = plan_scan_adjoint(T, d, m, batch, dtype, opts).bytes;
-        return align_up(need ? need : 1, (size_t)256 << 10);
+        return align_up(need, (size_t)256 << 10);
     }
     return plan_scan_backward(T, d, m, batch, dtype, opts, with_init != 0).total();
 }

@@ -192,12 +192,18 @@ struct ScanAdjointLaunch {
     void *gM, *gS0;             // gS0: NULL or [batch][d][m]
     const void *totals;         // factored chunk products [batch][C], layout tot
     void *vecs;                 // factored d x m matrices [batch][C], layout vec
+    int *wide;                  // [batch][C][2]: whether magnitudes lie too far apart for these
+    void *slots;                // for them, instead: [batch][C], slot_stride bytes each (may lie where totals and vecs do)
+    size_t slot_stride;
     FactLayout tot, vec;
     long long T, L, C, batch;
     int d, m, dtype;
 };
 // phase 0: chunk vectors and carries (C > 1); phase 1: gradients
 int launch_scan_adjoint(goom_ctx *ctx, const ScanAdjointLaunch &l, int phase);
+// goom_scan_adjoint_wide.hip: such items' gradients written again; bytes of a slot
+int launch_scan_adjoint_wide(goom_ctx *ctx, const ScanAdjointLaunch &l);
+size_t scan_adjoint_slot_bytes(long long C, int d, int m, int dtype);
 int launch_scan_backward_prepare(goom_ctx *ctx, const void *M, const void *S0, const void *P, const void *G, void *c, void *F, void *init, long long T, int d,
                                  int m, long long batch, int dtype);
 int launch_scan_backward_operands(goom_ctx *ctx, const void *states, const void *P, const void *S0, const void *c, void *Lam, void *Pt, long long T, int d, int m,

@@ -8,18 +8,20 @@
 // A chain that fills the chip by its batch alone is one chunk.
 //
 // A workgroup owns a chunk, wave w the columns 16 w .. of the state in the matrix instruction's layout (goom_chain_kernel.h) as
-// mantissas with one power of two a column: so K and Lam need no range of their own, however far the states have grown.
+// mantissas with one power of two a column, however far the states have grown.  Rows have none: entries of a column that lie further
+// apart than a mantissa reaches, entries that a chunk product has no room for (in float all of its columns are on one power of two)
+// and log-magnitudes past the whole numbers used here are looked for on the way (2 to 8 % of a pass); an item in which any are found is
+// left to goom_scan_adjoint_wide.hip.
 //   Lam:  G_t / P_t joins a column on the larger power of two of the two; Lam goes to LDS for the other waves.
 //   K:    M_t column by column on powers of two of its own (they are rows of M_t^T), through LDS; Lam is the B operand as it stands.
 //   sum:  wave w takes the columns j = 16 w .. of M_t; row j of P_{t-1}, straight from memory, on the largest of its entries times
-//         Lam's column's power of two; a row of Lam that lies far below 1 on its own power of two, so that only a term that is
-//         2^-100 of the row's largest is lost.
+//         Lam's column's power of two; a row of Lam that lies far below 1 on its own power of two.
 //
 // Bound by instruction issue: at 64 x 64 a step's two products are 4096 cycles of matrix instructions a wave, and the conversions of
 // M, P and G and the exponents of G / P, K and the gradients some 1300 vector instructions (which do not overlap with them on this
-// chip).  64 chains of 128 complex64 64 x 64: 1735 -> 498 us against the scan of the stacked 128 x 128 factors, whose operands alone were
-// written and read as 2 GB (products 59, vectors 136, carries 25, gradients 237); 65 536 steps in one chain 14.3 -> 5.0 ms; 16 x 60 of 100 x 100
-// 1465 -> 709 us; complex128, 16 x 128 of 64 x 64: 1444 -> 388 us.  Row exponents of Lam: 3 % of a step.  Loads behind a branch, which
+// chip).  64 chains of 128 complex64 64 x 64: 1759 -> 569 us against the scan of the stacked 128 x 128 factors, whose operands alone were
+// written and read as 2 GB (products 69, vectors 168, carries 33, gradients 318); 65 536 steps in one chain 13.1 -> 5.6 ms; 16 x 60 of 100 x 100
+// 1476 -> 688 us; complex128, 16 x 128 of 64 x 64: 1459 -> 453 us.  Row exponents of Lam: 3 % of a step.  Loads behind a branch, which
 // the optimiser makes of any selection around one, cost threefold: hence entries that are loaded first and selected afterwards.
 #include "goom_chain_kernel.h"
 
@@ -44,6 +46,7 @@ template <typename R> struct AdjointArgs {
     long long vec_stride;
     int vec_cols;
     size_t vec_mant;
+    int *wide;                   // [batch][C][2]: whether magnitudes lie too far apart for the walk (see Reach)
     long long T, L, C;
     int d, m;
 };
@@ -54,6 +57,21 @@ enum { kVectors, kCarries, kGradients };
 // held within +-3.4e8, so that sums of three exponents stay whole numbers: a zero then needs no comparison of its own, it is an
 // entry times 2^kNone.
 constexpr int kNone = -500000000;
+
+// What the walk's mantissas hold for certain.  A product of two matrices loses nothing as long as the non-zero entries of Lam (and K) lie within
+// 2^kLam of their column's largest and those of M, P and the chunk products within 1 / kOtherLeast (every term is then a normal number), and exponents stay
+// inside +-kFar.  A workgroup that meets what leaves that says so, and goom_scan_adjoint_wide.hip writes that item's gradients again.
+template <typename R> struct Reach;
+template <> struct Reach<float> {
+    static constexpr int kLam = 80;
+    static constexpr float kLamLeast = 0x1p-80f, kOtherLeast = 0x1p-40f;
+};
+template <> struct Reach<double> {
+    static constexpr int kLam = 700;
+    static constexpr double kLamLeast = 0x1p-700, kOtherLeast = 0x1p-300;
+};
+constexpr int kFar = 450000000, kNothing = 1000000000; // kNothing: the least exponent of no entry at all
+constexpr double kFarLog = 3.1e8;                      // kFar, of a log-magnitude
 
 template <typename R> struct Num;
 template <> struct Num<float> {
@@ -92,6 +110,7 @@ template <> struct Num<double> {
     }
 };
 __device__ inline int imax(int x, int y) { return x > y ? x : y; }
+__device__ inline int imin(int x, int y) { return x < y ? x : y; }
 __device__ inline int column_max(int x) { return Comp<float>::xor32_imax(Comp<float>::xor16_imax(x)); } // over the four lanes of a column
 
 // DP: rows and columns in whole tiles of sixteen
@@ -131,6 +150,14 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
 
     vec4 S[KT];               // K, then Lam: entry (16 it + row_of(g, v), col), times 2^e
     int e = kNone;            // (a column of zeros)
+    int low = kNothing;       // least exponent of K's non-zero entries that this lane holds
+    unsigned long long lost = 0; // lanes in which something may not have fitted
+    // (noted at once: the scheduler otherwise puts it off and keeps what it is formed from)
+    auto note = [&](bool c) {
+        lost |= __builtin_amdgcn_ballot_w64(c);
+        asm volatile("" : "+s"(lost));
+    };
+    typedef Reach<R> Rc;
 #pragma unroll
     for (int it = 0; it < KT; ++it) S[it] = vec4{0, 0, 0, 0};
 
@@ -147,6 +174,8 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
         asm volatile("" : "+s"(x));
         return x;
     };
+    // both formed here, entry by entry (the scheduler otherwise puts one of them off and keeps what it is formed from)
+    auto now = [](int &x, int &y) { asm volatile("" : "+v"(x), "+v"(y)); };
     auto at_byte = [](const auto *base, unsigned byte) { return *reinterpret_cast<decltype(base)>(reinterpret_cast<const unsigned char *>(base) + byte); };
 
     auto vec_at = [&](long long q) { return a.vecs + (b * a.C + q) * a.vec_stride; };
@@ -176,13 +205,26 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
             if (g == 0) reinterpret_cast<double *>(dst + a.vec_mant)[col] = (double)e;
         }
     };
-    // S 2^e + V 2^ev, on the larger of the two
-    auto add_scaled = [&](const vec4 (&V)[KT], int ev) {
-        const int top = imax(e, ev);
+    auto least = [&](const vec4 (&V)[KT], int ev) {
+        int l = kNothing;
 #pragma unroll
         for (int it = 0; it < KT; ++it)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) S[it][v] = N::ldexp_(S[it][v], e - top) + N::ldexp_(V[it][v], ev - top);
+            for (int v = 0; v < 4; ++v) l = imin(l, V[it][v] != (R)0 ? X2::exponent(V[it][v]) + ev : kNothing);
+        return l;
+    };
+    // S 2^e + V 2^ev, on the larger of the two
+    auto add_scaled = [&](const vec4 (&V)[KT], int ev) {
+        const int top = imax(e, ev);
+        note((low < imax(top - Rc::kLam, -kFar)) || (top > kFar));
+#pragma unroll
+        for (int it = 0; it < KT; ++it)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const R x = N::ldexp_(V[it][v], ev - top);
+                note((N::abs_(x) < Rc::kLamLeast) && (V[it][v] != (R)0));
+                S[it][v] = N::ldexp_(S[it][v], e - top) + x;
+            }
         e = top;
     };
     // K = (matrix in mt)^T Lam
@@ -200,6 +242,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                 for (int jt = 0; jt < KT; ++jt) acc[jt] = N::mfma(row[16 * jt], s, acc[jt]);
             }
         int top = 2 * kNone;
+        low = kNothing;
 #pragma unroll
         for (int jt = 0; jt < KT; ++jt)
 #pragma unroll
@@ -207,8 +250,11 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                 const R x = acc[jt][v];
                 const int ex = X2::exponent(x) + mexp[row_at(jt, v)];
                 top = imax(top, x != (R)0 ? ex : 2 * kNone);
+                low = imin(low, x != (R)0 ? ex : kNothing); // (kept until K has its gradient's other part)
+                now(top, low);
             }
         top = column_max(top);
+        low = low < kNothing ? low + e : kNothing;
 #pragma unroll
         for (int jt = 0; jt < KT; ++jt)
 #pragma unroll
@@ -222,7 +268,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
             int ev;
             if (q > 0) {
                 const unsigned char *tp = a.totals + (b * a.C + q) * a.tot_stride;
-                const double cex = reinterpret_cast<const double *>(tp + a.tot_mant)[col < d ? col : 0]; // (every column on its own power of two)
+                const double cex = reinterpret_cast<const double *>(tp + a.tot_mant)[col < d ? col : 0]; // (in double every column on its own power of two, in float all on one)
                 vec4 A[KT];
 #pragma unroll
                 for (int it = 0; it < KT; ++it)
@@ -246,7 +292,18 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
         }
     } else {
         const long long lo = chunk * a.L, hi = lo + a.L < a.T ? lo + a.L : a.T;
-        if (MODE == kGradients && a.C > 1) load_vec(chunk, S, e);
+        if (MODE == kVectors) {
+            // the carries' other operand (a zero may be an entry that the product's common exponent had no room for)
+            const R *tp = reinterpret_cast<const R *>(a.totals + (b * a.C + chunk) * a.tot_stride);
+#pragma unroll
+            for (int it = 0; it < KT; ++it)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) note((row_at(it, v) < lim_d) && !(N::abs_(tp[row_at(it, v) < lim_d ? (unsigned)(row_at(it, v) * a.tot_cols + col) : 0u]) >= Rc::kOtherLeast));
+        }
+        if (MODE == kGradients && a.C > 1) {
+            load_vec(chunk, S, e);
+            low = least(S, e);
+        }
         for (long long t = hi - 1; t >= lo; --t) {
             const size_t step = (size_t)(b * a.T + t);
             const bool onward = MODE != kGradients || t > lo || (chunk == 0 && a.gS0); // is K_{t-1} of any use
@@ -279,13 +336,16 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                         pv[it][v].x = re;
                         gv[it][v] = in ? x : (R)0;
                         nb = imax(nb, in ? up : kNone);
+                        if (MODE == kGradients) note((row_at(it, v) < rows) && __builtin_isfinite(p.x) && (N::abs_(re) > (R)kFarLog));
                     }
                 const int top = imax(e, column_max(nb));
+                note((low < imax(top - Rc::kLam, -kFar)) || (top > kFar));
 #pragma unroll
                 for (int it = 0; it < KT; ++it)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const R x = gv[it][v], f = X2::mantissa(x) * X2::exp2(pv[it][v].x, top - X2::exponent(x));
+                        note((N::abs_(f) < Rc::kLamLeast) && (x != (R)0));
                         S[it][v] = N::ldexp_(S[it][v], e - top) + (x != (R)0 ? f : (R)0);
                     }
                 e = top;
@@ -319,20 +379,29 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                     for (int v = 0; v < 4; ++v) x[it][v] = fetch_m(it, v);
                 __builtin_amdgcn_sched_barrier(0);
                 int sh = kNone;
+                // a column's power of two: none for a column of zeros, whose entries would come out as ones
+                auto column_shift = [](int x) {
+                    x = column_max(x);
+                    return x > -kFar ? x : 0;
+                };
                 if constexpr (TL::kReload) {
                     R most = -3.4e8;
 #pragma unroll
                     for (int it = 0; it < KT; ++it)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            x[it][v].x = X2::bound(row_at(it, v) < mrows ? x[it][v].x : N::neg_inf());
-                            most = X2::larger(most, x[it][v].x);
+                            x[it][v].x = row_at(it, v) < mrows ? x[it][v].x : N::neg_inf();
+                            most = X2::larger(most, X2::bound(x[it][v].x));
                         }
-                    sh = column_max(X2::whole(most));
+                    sh = column_shift(X2::whole(most));
 #pragma unroll
                     for (int it = 0; it < KT; ++it)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) mt[row_at(it, v) * TL::kM + col] = N::apply_sign(X2::exp2(x[it][v].x, sh), x[it][v].y);
+                        for (int v = 0; v < 4; ++v) {
+                            const R y = X2::exp2(X2::bound(x[it][v].x), sh);
+                            note(onward && (x[it][v].x > N::neg_inf()) && (y < Rc::kOtherLeast));
+                            mt[row_at(it, v) * TL::kM + col] = N::apply_sign(y, x[it][v].y);
+                        }
                 } else {
 #pragma unroll
                     for (int it = 0; it < KT; ++it)
@@ -341,13 +410,18 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                             split(x[it][v], row_at(it, v) < mrows, my[it][v], mn[it][v]);
                             sh = imax(sh, mn[it][v]);
                         }
-                    sh = column_max(sh);
+                    sh = column_shift(sh);
 #pragma unroll
                     for (int it = 0; it < KT; ++it)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) mt[row_at(it, v) * TL::kM + col] = N::ldexp_(my[it][v], mn[it][v] - sh);
+                        for (int v = 0; v < 4; ++v) {
+                            const R y = N::ldexp_(my[it][v], mn[it][v] - sh);
+                            note(onward && (row_at(it, v) < mrows) && (x[it][v].x > N::neg_inf()) && (N::abs_(y) < Rc::kOtherLeast));
+                            mt[row_at(it, v) * TL::kM + col] = y;
+                        }
                 }
                 if (g == 0) mexp[col] = sh;
+                note(onward && (sh > kFar));
             };
             if (!TL::kOne) put_m();
             __syncthreads();
@@ -382,7 +456,13 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) pb[kt][v] = X2::with_sign(X2::exp2(pb[kt][v], nj - lexp[16 * kt + 4 * g + v]), pneg, 4 * kt + v);
+                    for (int v = 0; v < 4; ++v) {
+                        // (a zero, or a column of Lam without entries, is half a billion powers of two away; P itself was looked at as P_t)
+                        const int far = nj - lexp[16 * kt + 4 * g + v];
+                        const R y = X2::exp2(pb[kt][v], far);
+                        note((y < Rc::kOtherLeast) && (pb[kt][v] > (R)-kFarLog) && (far < kFar));
+                        pb[kt][v] = X2::with_sign(y, pneg, 4 * kt + v);
+                    }
                 R *out = a.gM + step * d * d;
 #pragma unroll
                 for (int it = 0; it < KT; ++it) {
@@ -439,20 +519,32 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
             __syncthreads();
         }
         if (MODE == kVectors) store_vec(chunk);
-        if (MODE == kGradients && chunk == 0 && a.gS0) {
+        if (MODE == kGradients && chunk == 0 && a.S0) {
             const c2 *S0 = a.S0 + (size_t)b * d * m;
-            R *out = a.gS0 + (size_t)b * d * m;
+            R *out = a.gS0 ? a.gS0 + (size_t)b * d * m : nullptr;
 #pragma unroll
             for (int it = 0; it < KT; ++it)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (row_at(it, v) < lim_m) {
-                        const c2 x = S0[(unsigned)(row_at(it, v) * m + col)];
-                        const R re = X2::bound(x.x);
-                        const int n0 = X2::whole(re);
-                        out[(unsigned)(row_at(it, v) * m + col)] = N::apply_sign(N::ldexp_(S[it][v] * X2::exp2(re, n0), n0 + e), x.y);
-                    }
+                for (int v = 0; v < 4; ++v) {
+                    const bool in = row_at(it, v) < lim_m;
+                    const c2 x = S0[in ? (unsigned)(row_at(it, v) * m + col) : 0u];
+                    const R re = X2::bound(x.x);
+                    const int n0 = X2::whole(re);
+                    note(in && __builtin_isfinite(x.x) && N::abs_(re) > (R)kFarLog);
+                    if (in && out) out[(unsigned)(row_at(it, v) * m + col)] = N::apply_sign(N::ldexp_(S[it][v] * X2::exp2(re, n0), n0 + e), x.y);
+                }
         }
+    }
+    // a word a workgroup (the carries' where the first chunk's vector would have been)
+    __syncthreads();
+    if (threadIdx.x == 0) lexp[0] = 0;
+    __syncthreads();
+    if (lost) lexp[0] = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int *out = a.wide + (b * a.C + (MODE == kCarries ? 0 : chunk)) * 2;
+        if (MODE != kGradients || a.C == 1) out[0] = lexp[0];
+        if (MODE == kGradients) out[1] = lexp[0];
     }
 }
 
@@ -494,6 +586,7 @@ template <typename R> int launch_t(goom_ctx *ctx, const goom::ScanAdjointLaunch 
     a.vec_stride = (long long)l.vec.stride;
     a.vec_cols = l.vec.cols_padded;
     a.vec_mant = l.vec.mant_bytes;
+    a.wide = l.wide;
     a.T = l.T;
     a.L = l.L;
     a.C = l.C;

@@ -80,3 +80,107 @@ def test_tiny_matrices_in_many_chunks(G, oracle, d, ctype):  # noqa: F811
     run(G, oracle, 1500, d, d, 1, 0, ctype, True)
     assert "scan_adjoint_carries" in [label for label, _ in G.profile_records()]
     G.profile_enable(False)
+
+
+# Magnitudes further apart than a mantissa reaches: what the walk cannot hold is written again with an exponent an entry.
+def reals(ctype):
+    return np.float32 if ctype == np.complex64 else np.float64
+
+
+def states(oracle, Z, S0):
+    re, sg = oracle.scan(Z, S0)
+    return (re + 1j * np.pi * sg).astype(Z.dtype)
+
+
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+def test_one_step_of_rows_far_apart(G, oracle, ctype):  # noqa: F811
+    say(f"scan adjoint, one diagonal step, {np.dtype(ctype).name}")
+    far = 60.0 if ctype == np.complex64 else 500.0
+    Z = np.full((1, 1, 2, 2), -np.inf, dtype=ctype)
+    Z[0, 0, 0, 0], Z[0, 0, 1, 1] = far, -far
+    S0 = np.zeros((1, 2, 1), dtype=ctype)
+    gm, gi = G.scan_backward(dev(Z), G.scan(dev(Z), dev(S0)), dev(np.ones((1, 1, 2, 1), dtype=reals(ctype))), dev(S0))
+    # one term an entry, with one rounding of each of its three factors' exponentials
+    assert np.allclose(host(gm)[0, 0], np.eye(2), rtol=0, atol=16 * np.finfo(reals(ctype)).eps)
+    assert np.allclose(host(gi)[0, :, 0], 1.0, rtol=0, atol=16 * np.finfo(reals(ctype)).eps)
+
+
+# rows e^120 (in double e^1000) apart, every row of every gradient against its own terms; of three chains one, so that the others keep the walk's
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("d,m,chunk", [(3, 2, 0), (12, 12, 8), (33, 20, 8), (64, 64, 0), (100, 17, 7), (128, 128, 8)])
+def test_rows_beyond_a_mantissa(G, oracle, d, m, chunk, ctype):  # noqa: F811
+    say(f"scan adjoint, rows far apart, d={d} m={m} {np.dtype(ctype).name}")
+    comp, T, batch, far = reals(ctype), 20, 3, 60.0 if ctype == np.complex64 else 500.0
+    rng = np.random.default_rng(17 * d + m)
+    Z = oracle.to_goom((np.eye(d) + 0.5 / np.sqrt(d) * rng.standard_normal((batch, T, d, d))).astype(comp))
+    S0 = oracle.to_goom(rng.standard_normal((batch, d, m)).astype(comp))
+    Gp = rng.standard_normal((batch, T, d, m)).astype(comp)
+    units = rng.permutation(np.rint(np.linspace(-far, far, d)))
+    Z[1] = (Z[1] + (units[:, None] - units[None, :])).astype(ctype)
+    S0[1] = (S0[1] + units[:, None]).astype(ctype)
+    P = np.stack([states(oracle, Z[b], S0[b]) for b in range(batch)])
+    gm, gi = G.scan_backward(dev(Z), dev(P), dev(Gp), dev(S0), chunk_len=chunk)
+    gm, gi = host(gm).astype(np.float64), host(gi).astype(np.float64)
+    eta = np.finfo(comp).eps / 2
+    # as in run() above, of the terms: |M_ij| sum_k |Lam_ik| |P_jk|, the largest of a row (log-magnitudes of up to 2 far are good to that times eta)
+    bound = 50 * eta * (math.sqrt(T * (d + m)) + 4 * far)
+    for b in range(batch):
+        wm, wi, (lre, _) = oracle.scan_backward(Z[b], Gp[b], init=S0[b], p=P[b])
+        prev = np.concatenate([S0[b][None], P[b][:-1]]).real
+        for t in range(T):
+            a = lre[t].reshape(d, m)[:, None, :] + prev[t][None, :, :]
+            terms = np.exp(Z[b, t].real[..., None] + a).sum(-1).max(1)
+            err = np.abs(gm[b, t] - wm[t]).max(1) / terms
+            assert err.max() <= bound, (b, t, int(err.argmax()), err.max(), bound)
+        e0 = np.abs(gi[b] - wi).max() / np.abs(wi).max()
+        assert e0 <= bound, (b, e0, bound)
+
+
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+def test_diagonal_chain_in_chunks(G, oracle, ctype):  # noqa: F811
+    say(f"scan adjoint, diagonal chain, {np.dtype(ctype).name}")
+    T, d, m = 40, 5, 3
+    Z = np.full((1, T, d, d), -np.inf, dtype=ctype)
+    for i, s in enumerate((30.0, 0.0, -30.0, 7.0, -200.0)):
+        Z[0, :, i, i] = s
+    S0 = np.zeros((1, d, m), dtype=ctype)
+    Gp = np.random.default_rng(3).integers(-8, 9, (1, T, d, m)).astype(reals(ctype))
+    gm, gi = G.scan_backward(dev(Z), dev(states(oracle, Z[0], S0[0])[None]), dev(Gp), dev(S0), chunk_len=8)
+    want = np.cumsum(Gp[0, ::-1].sum(-1), 0)[::-1]  # whole numbers; a state's log-magnitude is at most 8000, good to 8000 eps
+    err = 8000 * np.finfo(reals(ctype)).eps * np.abs(Gp).sum() / d
+    assert np.abs(host(gm)[0] - want[:, :, None] * np.eye(d)).max() <= err
+    assert np.abs(host(gi)[0] - Gp[0].sum(0)).max() <= err
+
+
+# log-magnitudes where whole numbers are all that is left of them (a state's is their exact sum)
+@pytest.mark.parametrize("ctype,at,step", [(np.complex64, 1.0e9, 64.0), (np.complex64, -1.0e9, 128.0), (np.complex128, 1.0e9, 1.0), (np.complex128, -4.0e14, 2.0),
+                                           (np.complex128, 5.0e8, 1.0e5)])
+@pytest.mark.parametrize("T,chunk", [(2, 0), (24, 8)])
+def test_far_log_magnitudes(G, oracle, T, chunk, ctype, at, step):  # noqa: F811
+    say(f"scan adjoint, log-magnitudes about {at}, T={T}, {np.dtype(ctype).name}")
+    Z = np.full((1, T, 1, 1), step, dtype=ctype)
+    S0 = np.full((1, 1, 1), at, dtype=ctype)
+    P = (at + step * np.arange(1, T + 1)).astype(ctype).reshape(1, T, 1, 1)
+    gm, gi = G.scan_backward(dev(Z), dev(P), dev(np.ones((1, T, 1, 1), dtype=reals(ctype))), dev(S0), chunk_len=chunk)
+    # (every ratio is exactly one: a rounding or two a step of what is left of an exponent)
+    assert np.allclose(host(gm).ravel(), np.arange(T, 0, -1), rtol=64 * np.finfo(reals(ctype)).eps)
+    assert np.allclose(host(gi).ravel(), T, rtol=64 * np.finfo(reals(ctype)).eps)
+
+
+@pytest.mark.parametrize("d,m", [(4, 4), (30, 30)])
+def test_states_far_out_in_double(G, oracle, d, m):  # noqa: F811
+    say(f"scan adjoint, states about e^5e8, d={d}")
+    ctype, T, at = np.complex128, 20, 5.0e8
+    rng = np.random.default_rng(d)
+    Z = oracle.to_goom(np.eye(d) + 0.5 / np.sqrt(d) * rng.standard_normal((1, T, d, d)))
+    S0 = oracle.to_goom(rng.standard_normal((1, d, m)))
+    Gp = rng.standard_normal((1, T, d, m))
+    # whole log-magnitudes are exact out there: the same chain, moved
+    Z, S0 = (np.rint(Z.real) + 1j * Z.imag).astype(ctype), (np.rint(S0.real) + 1j * S0.imag).astype(ctype)
+    far = states(oracle, Z[0], S0[0])[None] + at  # (rounded to 2^-24: what the gradients are of)
+    near = (far - at).astype(ctype)
+    gm, gi = G.scan_backward(dev(Z), dev(far), dev(Gp), dev((S0 + at).astype(ctype)), chunk_len=8)
+    wm, wi, _ = oracle.scan_backward(Z[0], Gp[0], init=S0[0], p=near[0])
+    bound = 1000 * 2.0 ** -53 * math.sqrt(T * (d + m))  # as in run(), of sums that are down to a thousandth of their terms here
+    assert np.abs(host(gm)[0] - wm).max() <= bound * np.abs(wm).max()
+    assert np.abs(host(gi)[0] - wi).max() <= bound * np.abs(wi).max()

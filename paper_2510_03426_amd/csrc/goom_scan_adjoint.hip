@@ -19,9 +19,9 @@
 //
 // Bound by instruction issue: at 64 x 64 a step's two products are 4096 cycles of matrix instructions a wave, and the conversions of
 // M, P and G and the exponents of G / P, K and the gradients some 1300 vector instructions (which do not overlap with them on this
-// chip).  64 chains of 128 complex64 64 x 64: 1759 -> 569 us against the scan of the stacked 128 x 128 factors, whose operands alone were
-// written and read as 2 GB (products 69, vectors 168, carries 33, gradients 318); 65 536 steps in one chain 13.1 -> 5.6 ms; 16 x 60 of 100 x 100
-// 1476 -> 688 us; complex128, 16 x 128 of 64 x 64: 1459 -> 453 us.  Row exponents of Lam: 3 % of a step.  Loads behind a branch, which
+// chip).  64 chains of 128 complex64 64 x 64: 1759 -> 545 us against the scan of the stacked 128 x 128 factors, whose operands alone were
+// written and read as 2 GB (products 68, vectors 162, carries 30, gradients 301, 10 for three launches that find no flag); 65 536 steps in one chain 13.1 -> 5.5 ms;
+// 16 x 60 of 100 x 100 1476 -> 704 us; complex128, 16 x 128 of 64 x 64: 1459 -> 439 us.  Row exponents of Lam: 3 % of a step.  Loads behind a branch, which
 // the optimiser makes of any selection around one, cost threefold: hence entries that are loaded first and selected afterwards.
 #include "goom_chain_kernel.h"
 
@@ -155,7 +155,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
     // (noted at once: the scheduler otherwise puts it off and keeps what it is formed from)
     auto note = [&](bool c) {
         lost |= __builtin_amdgcn_ballot_w64(c);
-        asm volatile("" : "+s"(lost));
+        asm("" : "+s"(lost));
     };
     typedef Reach<R> Rc;
 #pragma unroll
@@ -175,7 +175,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
         return x;
     };
     // both formed here, entry by entry (the scheduler otherwise puts one of them off and keeps what it is formed from)
-    auto now = [](int &x, int &y) { asm volatile("" : "+v"(x), "+v"(y)); };
+    auto now = [](int &x, int &y) { asm("" : "+v"(x), "+v"(y)); };
     auto at_byte = [](const auto *base, unsigned byte) { return *reinterpret_cast<decltype(base)>(reinterpret_cast<const unsigned char *>(base) + byte); };
 
     auto vec_at = [&](long long q) { return a.vecs + (b * a.C + q) * a.vec_stride; };

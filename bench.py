@@ -596,9 +596,9 @@ def recurrence(g, torch, dev, si):
     fn = lambda: g.affine_scan_backward(az, bz, h, gh)
     sec = timed(torch, fn, 2)
     kms = kernel_times(g, fn)
-    # algorithmic bytes: A read by the adjoint recurrence (transposed, in place; twice where that runs as a chunked scan), read
-    # again for its gradient (reals), which is written
-    reads = 2 if "affine_sequential_walk" in kms else 3
+    # algorithmic bytes: A read by the adjoint recurrence, once where sequences are walked whole and its gradient (reals) is written on the
+    # way; twice as a chunked scan, and then again for the gradient
+    reads = 1 if "affine_sequential_adjoint" in kms else 3
     bbytes = az.numel() * (8 * reads + 4)
     res["recurrence_backward_128seq_T65536_d32"] = {
         "ms": round(sec * 1e3, 3), "tokens_per_s": round(nseq * T / sec, 1), "hbm_gbs_algorithmic": round(bbytes / sec / 1e9, 1),

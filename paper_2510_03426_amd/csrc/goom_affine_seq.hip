@@ -22,7 +22,7 @@
 // gradients: while the chain applies A_t^T to lam_t, the matrix waves that still hold A_t's entries form
 // lam_t[i] A_t[i, j] h_{t-1}[j] from them and store it, others scale the next matrix, and two more waves bring h_{t-1} to LDS and write the
 // bias's gradient.  A pass of its own over the matrices for the gradients took almost as long as the walk: 128 x 4096 x 32,
-// 1336 + 1212 us, in one walk 1570 to 1630.
+// 1336 + 1212 us, in one walk 1567 to 1633.
 //
 // One workgroup barrier ends a step (285 ns, adjoint 380: the chain's dependent instructions and LDS reads; longer rings and contiguous loads
 // change nothing): scaled matrices, mantissas and exponents alternate between two sets of LDS words.

@@ -281,7 +281,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                 for (int it = 0; it < KT; ++it)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) mt[row_at(it, v) * TL::kM + col] = row_at(it, v) < lim_d ? A[it][v] : (R)0;
-                if (g == 0) mexp[col] = col < d ? (int)cex : 0;
+                if (g == 0) mexp[col] = col < d ? (int)__builtin_fmin(__builtin_fmax(cex, -1.0e9), 1.0e9) : 0; // (past kFar: noted with the vectors)
                 __syncthreads();
                 store_vec(q); // K as it enters this chunk, in its vector's place (each lane in the places it read)
                 propagate();
@@ -294,7 +294,9 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
         const long long lo = chunk * a.L, hi = lo + a.L < a.T ? lo + a.L : a.T;
         if (MODE == kVectors) {
             // the carries' other operand (a zero may be an entry that the product's common exponent had no room for)
-            const R *tp = reinterpret_cast<const R *>(a.totals + (b * a.C + chunk) * a.tot_stride);
+            const unsigned char *total = a.totals + (b * a.C + chunk) * a.tot_stride;
+            const R *tp = reinterpret_cast<const R *>(total);
+            note(!(__builtin_fabs(reinterpret_cast<const double *>(total + a.tot_mant)[col < d ? col : 0]) <= (double)kFar));
 #pragma unroll
             for (int it = 0; it < KT; ++it)
 #pragma unroll

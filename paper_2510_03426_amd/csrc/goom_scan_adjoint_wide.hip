@@ -6,8 +6,10 @@
 // The walk sets an item's flag where something may not have fitted; only then does a workgroup here do anything, and it overwrites that item's
 // gradients.  Same chunks, three kernels: chunk products and vectors (A_c^T column by column beside the vectors: columns of one adjoint
 // recurrence, the former without gradients), carries, gradients.  K and Lam lie in the workspace, where the walk had its own chunk products.
-// Vector instructions only, bound by their number: a dozen per term in double.  A column is as good as another, so a workgroup has
-// sixteen of them (gradients: all), a thread four of one row, which share the conversion of the matrix's entries.
+// Vector instructions only, bound by their number: a sum's exponent first, then its terms on it, nine instructions in double a term and the
+// loads; with an exponent carried along instead, 17 and 8.4 ms where now 16 and 5.3 (64 x 128 steps of complex64 64 x 64; 16 x 128 of complex128).
+// A column is as good as another, so a workgroup has sixteen of them (gradients: all), a thread four of one row, which share the
+// conversion of the matrix's entries.  Four times the waves a workgroup, with spills: 21 to 25 ms.
 #include "goom_chain_kernel.h"
 
 namespace {
@@ -21,7 +23,7 @@ template <> struct C2<double> { typedef double2 type; };
 constexpr double kZeroExp = -1.0e300; // exponent of a zero
 constexpr int kCols = 16, kPer = 4;   // columns of a group, of a thread
 constexpr int kThreads = 256;
-constexpr int kItems = GOOM_MAX_DIM * (kCols / kPer) / kThreads; // (row, four columns) pairs of a group that a thread has
+constexpr int kItems = GOOM_MAX_DIM / 64; // rows that a thread has, four columns each
 
 struct Entry { // m 2^e
     double m, e;
@@ -59,8 +61,38 @@ template <typename R> __device__ inline Entry entry_of(typename C2<R>::type x, b
     const double n = __builtin_rint(re * kLog2e);
     double f = __builtin_fma(re, kLog2e, -n);
     f = __builtin_fma(re, 2.0355273740931033e-17, f); // log2(e) - kLog2e
-    const double y = f > -0.6 && f < 0.6 ? Comp<double>::exp2_small(f) : exp2(f);
+    const double y = Comp<double>::exp2_small(f); // (|f| is 1/2 and what the product with log2(e) was rounded by)
     return Entry{Comp<R>::is_negative(x.y) ? -y : y, n};
+}
+// sum over i < n of x(i) l(u, i) for four u: the exponent first, then the terms on it
+template <class X, class L> __device__ inline void sums(int n, X &&x, L &&l, Entry (&out)[kPer])
+{
+    double top[kPer], m[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        top[u] = -1.0e290; // (above what a zero's can be)
+        m[u] = 0.0;
+    }
+#pragma unroll 4
+    for (int i = 0; i < n; ++i) {
+        const double e = x(i).e;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) top[u] = __builtin_fmax(top[u], e + l(u, i).e);
+    }
+#pragma unroll 2
+    for (int i = 0; i < n; ++i) {
+        const Entry a = x(i);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const Entry b = l(u, i);
+            // 2^t for a whole t from -1000 to 0: t + 1023 in the last bits of a double between 2^52 and 2^53, moved to an exponent's place
+            const double t = __builtin_fmax(a.e + (b.e - top[u]), -1000.0) + 4503599627371519.0;
+            const double scale = __builtin_bit_cast(double, (unsigned long long)((unsigned)__builtin_bit_cast(unsigned long long, t) << 20) << 32);
+            m[u] = __builtin_fma(a.m * b.m, scale, m[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) out[u] = Entry{m[u], top[u]};
 }
 template <typename R> __device__ inline R value_of(Entry s)
 {
@@ -100,7 +132,7 @@ template <typename R> struct Slot {
 
 // item q of a thread: row j and columns k .. k + 3 of a group of sixteen that begins at k0 and ends before k1
 #define GOOM_WIDE_ITEM(q, k0, k1)                                                                                                                            \
-    const int at_ = (q) * kThreads + (int)threadIdx.x, j = at_ / (kCols / kPer), k = (k0) + kPer * (at_ % (kCols / kPer));                                      \
+    const int j = 64 * (q) + (int)threadIdx.x % 64, k = (k0) + kPer * ((int)threadIdx.x / 64);                                                                  \
     const bool mine = j < a.d && k < (k1);
 
 // columns k0 .. of the slot, Lam, become K = M^T Lam (all threads of the workgroup come here)
@@ -114,14 +146,7 @@ template <typename R> __device__ void propagate(const WideArgs<R> &a, const Slot
 #pragma unroll
         for (int u = 0; u < kPer; ++u) out[q][u] = zero_entry();
         if (!mine) continue;
-        for (int i = 0; i < d; ++i) {
-            const Entry x = entry_of<R>(Mt[i * d + j]);
-#pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                const Entry l = s.get((k + u < k1 ? k + u : k) * d + i);
-                add_term(out[q][u], x.m * l.m, x.e + l.e);
-            }
-        }
+        sums(d, [&](int i) { return entry_of<R>(Mt[i * d + j]); }, [&](int u, int i) { return s.get((k + u < k1 ? k + u : k) * d + i); }, out[q]);
     }
     __syncthreads();
 #pragma unroll
@@ -206,16 +231,13 @@ template <typename R> __global__ __launch_bounds__(kThreads) void wide_carries_k
         for (int q = 0; q < kItems; ++q) {
             GOOM_WIDE_ITEM(q, k0, k1)
             if (!mine) continue;
-            for (int i = 0; i < d; ++i) {
-                const Entry x = s.get(i * d + j); // A_c[i, j]
+            Entry sum[kPer]; // of A_c[i, j] K[i, k]
+            sums(d, [&](int i) { return s.get(i * d + j); }, [&](int u, int i) { return s.get((d + (k + u < k1 ? k + u : k)) * d + i); }, sum);
 #pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    const Entry l = s.get((d + (k + u < k1 ? k + u : k)) * d + i);
-                    add_term(V[q][u], x.m * l.m, x.e + l.e);
-                }
+            for (int u = 0; u < kPer; ++u) {
+                add_term(V[q][u], sum[u].m, sum[u].e);
+                K[q][u] = normal(V[q][u]);
             }
-#pragma unroll
-            for (int u = 0; u < kPer; ++u) K[q][u] = normal(V[q][u]);
         }
     }
 }
@@ -242,16 +264,8 @@ template <typename R> __global__ __launch_bounds__(kThreads) void wide_gradients
         for (int at = threadIdx.x; at < rows4 * d; at += kThreads) {
             const int j = at % d, i = kPer * (at / d);
             Entry sum[kPer];
-#pragma unroll
-            for (int u = 0; u < kPer; ++u) sum[u] = zero_entry();
-            for (int k = 0; k < m; ++k) {
-                const Entry p = prev ? entry_of<R>(prev[j * m + k]) : j == k ? Entry{1.0, 0.0} : zero_entry();
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    const Entry l = s.get((first + k) * d + (i + u < d ? i + u : i));
-                    add_term(sum[u], p.m * l.m, p.e + l.e);
-                }
-            }
+            sums(m, [&](int k) { return prev ? entry_of<R>(prev[j * m + k]) : j == k ? Entry{1.0, 0.0} : zero_entry(); },
+                 [&](int u, int k) { return s.get((first + k) * d + (i + u < d ? i + u : i)); }, sum);
 #pragma unroll
             for (int u = 0; u < kPer; ++u) {
                 if (i + u >= d) continue;

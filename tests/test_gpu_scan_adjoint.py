@@ -184,3 +184,19 @@ def test_states_far_out_in_double(G, oracle, d, m):  # noqa: F811
     bound = 1000 * 2.0 ** -53 * math.sqrt(T * (d + m))  # as in run(), of sums that are down to a thousandth of their terms here
     assert np.abs(host(gm)[0] - wm).max() <= bound * np.abs(wm).max()
     assert np.abs(host(gi)[0] - wi).max() <= bound * np.abs(wi).max()
+
+
+# a chunk's product beyond the exponents that the walk carries, in a direction that the states never take
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+def test_product_out_of_range(G, oracle, ctype):  # noqa: F811
+    say(f"scan adjoint, a direction out of range, {np.dtype(ctype).name}")
+    T, step = 32, 1.0e8
+    Z = np.full((1, T, 2, 2), -np.inf, dtype=ctype)
+    Z[0, :, 0, 0], Z[0, :, 1, 1], Z[0, :, 1, 0] = step, 0.0, 0.0
+    S0 = np.array([[[-np.inf], [0.0]]], dtype=ctype)
+    P = np.broadcast_to(S0, (1, T, 2, 1)).copy()
+    gm, gi = G.scan_backward(dev(Z), dev(P), dev(np.ones((1, T, 2, 1), dtype=reals(ctype))), dev(S0), chunk_len=8)
+    want = np.zeros((T, 2, 2))
+    want[:, 1, 1] = np.arange(T, 0, -1)
+    assert np.abs(host(gm)[0] - want).max() <= 64 * np.finfo(reals(ctype)).eps * T
+    assert np.abs(host(gi)[0, :, 0] - [0.0, T]).max() <= 64 * np.finfo(reals(ctype)).eps * T

@@ -1,5 +1,5 @@
 """Backward pass of the recurrence over many sequences of d = 32, walked whole: lengths around the rounds in which steps are loaded
-(eight and ten), zeros among the entries, steps that change every magnitude at once, an initial state or none; against the oracle on
+(sixteen for the matrices, eight for the chain), zeros among the entries, steps that change every magnitude at once, an initial state or none; against the oracle on
 the device's forward states."""
 import numpy as np
 import pytest

@@ -10,7 +10,7 @@
 // A workgroup owns a chunk, wave w the columns 16 w .. of the state in the matrix instruction's layout (goom_chain_kernel.h) as
 // mantissas with one power of two a column, however far the states have grown.  Rows have none: entries of a column that lie further
 // apart than a mantissa reaches, entries that a chunk product has no room for (in float all of its columns are on one power of two)
-// and log-magnitudes past the whole numbers used here are looked for on the way (2 to 8 % of a pass); an item in which any are found is
+// and log-magnitudes past the whole numbers used here are looked for on the way (8 to 12 % of a pass); an item in which any are found is
 // left to goom_scan_adjoint_wide.hip.
 //   Lam:  G_t / P_t joins a column on the larger power of two of the two; Lam goes to LDS for the other waves.
 //   K:    M_t column by column on powers of two of its own (they are rows of M_t^T), through LDS; Lam is the B operand as it stands.

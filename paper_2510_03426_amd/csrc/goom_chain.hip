@@ -98,6 +98,7 @@ int launch_chain(goom_ctx *ctx, const ChainLaunch &l)
     if (l.m == 1 && !l.left_shift && !l.left_real && !l.acc_f64 && !l.io_c64 &&
         !(l.dtype == GOOM_C64 && !l.left_fact && !l.left_prepared && goom_chain::affine_walk_applies(a, dp)))
         return goom_chain::dispatch_vec(ctx, a, dp, l.dtype == GOOM_C128, l.left_fact, grid, l.label);
+    if (l.left_fact) return goom_chain::launch_carry(ctx, a, dp, l.dtype == GOOM_C128, grid, l.label);
     if (l.left_real && (l.dtype != GOOM_C64 || l.left_fact))
         return fail(ctx, GOOM_EUNSUPPORTED, "real left factors are read by the hot float kernel only");
     if (l.io_c64) {
@@ -106,8 +107,8 @@ int launch_chain(goom_ctx *ctx, const ChainLaunch &l)
         return goom_chain::dispatch_f64_goom_io32(ctx, a, dp, nw, grid, l.label);
     }
     if (l.dtype == GOOM_C64)
-        return l.left_fact ? goom_chain::dispatch_f32_fact(ctx, a, dp, nw, grid, l.label) : goom_chain::dispatch_f32_goom(ctx, a, dp, nw, grid, l.label);
-    return l.left_fact ? goom_chain::dispatch_f64_fact(ctx, a, dp, nw, grid, l.label) : goom_chain::dispatch_f64_goom(ctx, a, dp, nw, grid, l.label);
+        return goom_chain::dispatch_f32_goom(ctx, a, dp, nw, grid, l.label);
+    return goom_chain::dispatch_f64_goom(ctx, a, dp, nw, grid, l.label);
 }
 
 } // namespace goom

@@ -12,6 +12,6 @@ int dispatch_f32_goom(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long
     if (args.left_real) return goom::fail(ctx, GOOM_EUNSUPPORTED, "real left factors are read by the hot float kernel only (d = 32, 64 or 128, square state)");
     if (affine_chunk_applies(args, dp)) return dispatch_affine_chunk(ctx, args, dp, grid, label);
     if (affine_walk_applies(args, dp)) return dispatch_affine_walk(ctx, args, dp, grid, label);
-    return dispatch<float, 0>(ctx, args, dp, nw, grid, label);
+    return dispatch<float>(ctx, args, dp, nw, grid, label);
 }
 } // namespace goom_chain

@@ -4,6 +4,6 @@
 namespace goom_chain {
 int dispatch_f64_goom(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label)
 {
-    return dispatch<double, 0>(ctx, args, dp, nw, grid, label);
+    return dispatch<double>(ctx, args, dp, nw, grid, label);
 }
 } // namespace goom_chain

@@ -78,6 +78,8 @@ struct ChainArgs {
 
 // chains of one state column (goom_vec.hip): GOOM or factored left factors, n, d <= dp
 int dispatch_vec(goom_ctx *ctx, const ChainArgs &args, int dp, int f64, int left_fact, long long grid, const char *label);
+// chains over factored left factors with more than one state column (goom_carry.hip)
+int launch_carry(goom_ctx *ctx, const ChainArgs &args, int dp, int f64, long long grid, const char *label);
 // the float matrix-vector walk (goom_affine.hip)
 bool affine_walk_applies(const ChainArgs &args, int dp);
 
@@ -339,7 +341,7 @@ constexpr int waves_per_simd(int comp_bytes, int dp, int nw)
 // IO: component type of the GOOM arrays in memory (left factors, initial state, bias, outputs).  It differs
 // from R in one combination only, IO = float with R = double: complex64 data walked with a double running
 // product (every load widened, every output rounded once when it is stored).
-template <typename R, int DP, int NW, int LEFT_FACT, bool FAST, typename IO = R>
+template <typename R, int DP, int NW, bool FAST, typename IO = R>
 __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void chain_kernel(ChainArgs a)
 {
     constexpr int KT = DP / 16;
@@ -392,64 +394,40 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
         const unsigned char *src = left0 + t * a.left_step_stride;
         // row strides: the template's size where it is known, else opaque to the optimiser, so that the
         // items' offsets are not carried in registers across the chain's loop
-        int ld = FAST ? DP : d, lfc = a.left_fact_cols;
+        int ld = FAST ? DP : d;
         if (!FAST) asm volatile("" : "+s"(ld));
-        asm volatile("" : "+s"(lfc));
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
             const int p = tid + (q0 + q) * NT;
             const int row = p / LPR, cj = 2 * (p % LPR);
             const bool v0 = FAST || ((p < NITEMS) && row < n_rows && cj < d);
             const bool v1 = FAST || (v0 && (cj + 1 < d));
-            if (LEFT_FACT) {
-                // factored left factor: mantissas [DP][left_fact_cols], leading columns on one exponent
-                const R *mp = reinterpret_cast<const R *>(src) + (size_t)(row * lfc + cj);
-                it[q].re0 = v0 ? mp[0] : (R)0;
-                it[q].re1 = v1 ? mp[1] : (R)0;
-                it[q].im0 = it[q].im1 = (R)0;
-            } else {
-                const IO *gp = reinterpret_cast<const IO *>(src) + (size_t)(row * ld + cj) * 2;
-                if (FAST || (v1 && vec_ok)) {
-                    if (sizeof(IO) == 4) {
-                        const f4 w = *reinterpret_cast<const f4 *>(gp);
-                        it[q].re0 = w[0]; it[q].im0 = w[1]; it[q].re1 = w[2]; it[q].im1 = w[3];
-                    } else {
-                        const d4 w = *reinterpret_cast<const d4 *>(gp);
-                        it[q].re0 = w[0]; it[q].im0 = w[1]; it[q].re1 = w[2]; it[q].im1 = w[3];
-                    }
+            const IO *gp = reinterpret_cast<const IO *>(src) + (size_t)(row * ld + cj) * 2;
+            if (FAST || (v1 && vec_ok)) {
+                if (sizeof(IO) == 4) {
+                    const f4 w = *reinterpret_cast<const f4 *>(gp);
+                    it[q].re0 = w[0]; it[q].im0 = w[1]; it[q].re1 = w[2]; it[q].im1 = w[3];
                 } else {
-                    it[q].re0 = v0 ? gp[0] : kNegInf; it[q].im0 = v0 ? gp[1] : (R)0;
-                    it[q].re1 = v1 ? gp[2] : kNegInf; it[q].im1 = v1 ? gp[3] : (R)0;
+                    const d4 w = *reinterpret_cast<const d4 *>(gp);
+                    it[q].re0 = w[0]; it[q].im0 = w[1]; it[q].re1 = w[2]; it[q].im1 = w[3];
                 }
+            } else {
+                it[q].re0 = v0 ? gp[0] : kNegInf; it[q].im0 = v0 ? gp[1] : (R)0;
+                it[q].re1 = v1 ? gp[2] : kNegInf; it[q].im1 = v1 ? gp[3] : (R)0;
             }
         }
     };
-    auto convert_items = [&](long long t, int q0, const Item<R> (&it)[QB], int buf) {
+    auto convert_items = [&](int q0, const Item<R> (&it)[QB], int buf) {
         R *tile = tile_of(buf);
         R *nsh = nsh_of(buf);
-        R common = (R)0;
-        if (LEFT_FACT) {
-            const unsigned char *src = left0 + t * a.left_step_stride;
-            common = (R) * reinterpret_cast<const double *>(src + (size_t)DP * a.left_fact_cols * sizeof(R));
-        }
 #pragma unroll
         for (int q = 0; q < QB; ++q) {
             const int p = tid + (q0 + q) * NT;
             const int row = p / LPR, cj = 2 * (p % LPR);
-            R x0, x1, n;
-            if (LEFT_FACT) {
-                const R a0 = Comp<R>::abs_(it[q].re0), a1 = Comp<R>::abs_(it[q].re1);
-                const R r = Comp<R>::template group_allmax<LPR>(a0, a1);
-                const int e = (r > (R)0 && r < -kNegInf) ? Comp<R>::frexp_exp(r) : 0;
-                x0 = Comp<R>::ldexp_(it[q].re0, -e);
-                x1 = Comp<R>::ldexp_(it[q].re1, -e);
-                n = (R)e + common;
-            } else {
-                const R r = Comp<R>::template group_allmax<LPR>(it[q].re0, it[q].re1);
-                n = Comp<R>::row_shift(r);
-                x0 = Comp<R>::apply_sign(Comp<R>::exp2_shifted(it[q].re0, n), it[q].im0);
-                x1 = Comp<R>::apply_sign(Comp<R>::exp2_shifted(it[q].re1, n), it[q].im1);
-            }
+            const R r = Comp<R>::template group_allmax<LPR>(it[q].re0, it[q].re1);
+            const R n = Comp<R>::row_shift(r);
+            const R x0 = Comp<R>::apply_sign(Comp<R>::exp2_shifted(it[q].re0, n), it[q].im0);
+            const R x1 = Comp<R>::apply_sign(Comp<R>::exp2_shifted(it[q].re1, n), it[q].im1);
             if (FAST || p < NITEMS) {
                 tile[row * LDA + Comp<R>::phys(cj)] = x0;
                 tile[row * LDA + Comp<R>::phys(cj + 1)] = x1;
@@ -463,7 +441,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
         for (int q0 = 0; q0 < Q; q0 += QB) {
             Item<R> it[QB];
             load_items(t, q0, it);
-            convert_items(t, q0, it, buf);
+            convert_items(q0, it, buf);
         }
     };
 
@@ -531,7 +509,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
         double e_out = ecol;
         int shift = 0;
         if (common_exponent) {
-            // one exponent for the leading columns (< d when a bias column exists, all otherwise)
+            // one exponent for all columns
             R cm = (R)0;
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt)
@@ -542,8 +520,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
                 }
             cm = wave_xor_max<R>(cm, 16);
             cm = wave_xor_max<R>(cm, 32);
-            const int ncommon = a.bias_mode ? d : m;
-            double ev = (slab_active && col < ncommon && cm > (R)0) ? ecol : kNegBig;
+            double ev = (slab_active && col < m && cm > (R)0) ? ecol : kNegBig;
 #pragma unroll
             for (int s = 1; s < 16; s <<= 1) {
                 double o = shfl_xor_double(ev, s);
@@ -555,7 +532,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
             double emax = kNegBig;
             for (int w = 0; w < NW; ++w) emax = wave_red[w] > emax ? wave_red[w] : emax;
             if (emax == kNegBig) emax = 0.0;
-            if (col < ncommon) {
+            if (col < m) {
                 double dsh = ecol - emax;
                 dsh = dsh > -4000.0 ? dsh : -4000.0;
                 shift = (cm > (R)0) ? (int)dsh : 0;
@@ -600,7 +577,6 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
             // scheduling region and the matrix instructions are interleaved with the
             // vector work.  Past the end of the chain the last factor is converted and
             // loaded again (clamped index) instead of branching; nobody reads the result.
-            const long long tn = t + 1 < len ? t + 1 : len - 1;
             const long long tl = t + 2 < len ? t + 2 : len - 1;
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt) {
@@ -614,7 +590,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
                     for (int mt = 0; mt < KT; ++mt) acc[mt] = Comp<R>::mfma(av[mt][v], st[kt][v], acc[mt]);
             }
             if (PREFETCH && NBUF == 2) {
-                convert_items(tn, 0, pre, cur ^ 1);
+                convert_items(0, pre, cur ^ 1);
                 load_items(tl, 0, pre);
             }
         } else if (slab_active) {
@@ -637,23 +613,6 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
         // type on whole numbers: differences that matter are between numbers of like size
         // and therefore exact; a reference exponent that is a few units off only moves the
         // mantissas' scale, never the represented value.
-        //
-        // bias column (carries of the linear recurrence): b_i, a column of the factored left factor, is added to entry
-        // (i, bias_col) in the log2 domain.  (Biases given as GOOMs belong to vector chains and to the chunk products' bias wave.)
-        const bool bias_lane = !FAST && LEFT_FACT && a.bias_mode != 0 && slab_active && col == a.bias_col;
-        auto bias_term = [&](int i, double &blog, bool &bneg) { // blog = log2|b_i| - ecol
-            blog = kNegBig;
-            bneg = false;
-            if (i >= n_rows) return;
-            const unsigned char *src = left0 + t * a.left_step_stride;
-            const R *mp = reinterpret_cast<const R *>(src);
-            const double *ex = reinterpret_cast<const double *>(src + (size_t)DP * a.left_fact_cols * sizeof(R));
-            int lfc = a.left_fact_cols; // opaque, as in load_items
-            asm volatile("" : "+s"(lfc));
-            R bv = mp[(size_t)(i * lfc + d)];
-            if (bv != (R)0) blog = (double)Comp<R>::log2_abs(bv) + ex[d] - ecol;
-            bneg = bv < (R)0;
-        };
 
         // column reference: cm = max_i of (binary exponent of the entry) + n_i
         R cm = kNegInf;
@@ -667,20 +626,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
                 cm = Comp<R>::max_(lg, cm);
             }
         }
-        if (bias_lane) {
-#pragma unroll
-            for (int mt = 0; mt < KT; ++mt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    double blog;
-                    bool bneg;
-                    bias_term(16 * mt + Comp<R>::row_of(g, v), blog, bneg);
-                    const R lb = blog > kNegBig ? (R)__builtin_ceil(blog) : kNegInf;
-                    cm = lb > cm ? lb : cm;
-                }
-        }
         cm = Comp<R>::xor16_32_max(cm);
-        if (bias_lane) cm += (R)2; // room for the sum of two terms
         const bool col_nonzero = cm > kNegInf;
         const R cms = col_nonzero ? cm : (R)0;
 
@@ -732,7 +678,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
                     for (int v = 0; v < 4; ++v) st[mt][v] = rescale(acc[mt][v], nv[v]);
                 }
             }
-        } else if (!bias_lane) {
+        } else {
 #pragma unroll
             for (int mt = 0; mt < KT; ++mt) {
                 const vec4 nv = *reinterpret_cast<const vec4 *>(&nsh[16 * mt + 4 * g]);
@@ -753,31 +699,6 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
                     st[mt][v] = rescale(x, nv[v]);
                 }
             }
-        } else {
-#pragma unroll
-            for (int mt = 0; mt < KT; ++mt) {
-                const vec4 nv = *reinterpret_cast<const vec4 *>(&nsh[16 * mt + 4 * g]);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int i = 16 * mt + Comp<R>::row_of(g, v);
-                    const R x = acc[mt][v];
-                    double blog;
-                    bool bneg;
-                    bias_term(i, blog, bneg);
-                    // entry = x 2^(n_i - cm) + (+-) 2^(blog - cm), in units of 2^(ecol + cm)
-                    const R xa = rescale(x, nv[v]);
-                    const R xb = (col_nonzero && blog > kNegBig) ? exp2_of<R>(blog - (double)cm) : (R)0;
-                    const R xs = xa + (bneg ? -xb : xb);
-                    if (want_out && i < n_rows) {
-                        const R re = Comp<R>::out_re(xs, cms, ecol);
-                        const IO im = xs < (R)0 ? Comp<IO>::pi() : (IO)0;
-                        IO *o = outp + (size_t)(i * mo + col) * 2;
-                        o[0] = (IO)re;
-                        o[1] = im;
-                    }
-                    st[mt][v] = xs;
-                }
-            }
         }
         if (col_nonzero) ecol += (double)cm;
 
@@ -788,7 +709,7 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
         } else if (t + 1 < len) {
             const int nxt = NBUF == 2 ? (cur ^ 1) : 0;
             if (PREFETCH) {
-                convert_items(t + 1, 0, pre, nxt);
+                convert_items(0, pre, nxt);
                 if (t + 2 < len) load_items(t + 2, 0, pre);
             } else {
                 produce_now(t + 1, nxt);
@@ -801,13 +722,13 @@ __global__ __launch_bounds__(NW * 64, waves_per_simd(sizeof(R), DP, NW)) void ch
     if (a.out_fact_final) store_fact(a.out_fact_final + chain_global * a.fact_stride, a.final_common_exponent != 0);
 }
 
-template <typename R, int DP, int NW, int LEFT_FACT, bool FAST, typename IO = R> int launch_one(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
+template <typename R, int DP, int NW, bool FAST, typename IO = R> int launch_one(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
 {
     constexpr int LDA = DP + Comp<R>::kPad;
     const size_t buf = (size_t)DP * LDA * sizeof(R) + (size_t)DP * sizeof(double);
     const int nbuf = (2 * buf + 128 <= 160 * 1024) ? 2 : 1;
     size_t lds = nbuf * buf + 128;
-    auto kern = chain_kernel<R, DP, NW, LEFT_FACT, FAST, IO>;
+    auto kern = chain_kernel<R, DP, NW, FAST, IO>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return goom::check_hip(ctx, e, "hipFuncSetAttribute(chain_kernel)");
@@ -820,14 +741,14 @@ template <typename R, int DP, int NW, int LEFT_FACT, bool FAST, typename IO = R>
     return goom::check_hip(ctx, hipGetLastError(), "launch chain_kernel");
 }
 
-template <typename R, int LEFT_FACT, typename IO = R> int dispatch(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label)
+template <typename R, typename IO = R> int dispatch(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label)
 {
-    const bool fast = args.n == dp && args.d == dp && args.m == 16 * nw && args.bias_mode == 0;
-    if (!LEFT_FACT && args.bias_mode) return goom::fail(ctx, GOOM_EUNSUPPORTED, "a bias given as GOOMs: vector chains and chunk products of float d = 64 only");
+    const bool fast = args.n == dp && args.d == dp && args.m == 16 * nw;
+    if (args.bias_mode) return goom::fail(ctx, GOOM_EUNSUPPORTED, "a bias given as GOOMs: vector chains and chunk products of float d = 64 only");
 #define GOOM_CASE(DPV, NWV)                                                                           \
     if (dp == DPV && nw == NWV)                                                                       \
-        return fast ? launch_one<R, DPV, NWV, LEFT_FACT, true, IO>(ctx, args, grid, label)            \
-                    : launch_one<R, DPV, NWV, LEFT_FACT, false, IO>(ctx, args, grid, label);
+        return fast ? launch_one<R, DPV, NWV, true, IO>(ctx, args, grid, label)            \
+                    : launch_one<R, DPV, NWV, false, IO>(ctx, args, grid, label);
     GOOM_CASE(16, 1)
     GOOM_CASE(16, 2)
     GOOM_CASE(32, 1)
@@ -846,9 +767,7 @@ template <typename R, int LEFT_FACT, typename IO = R> int dispatch(goom_ctx *ctx
 
 // one explicit instantiation per translation unit (they compile in parallel)
 int dispatch_f32_goom(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label);
-int dispatch_f32_fact(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label);
 int dispatch_f64_goom(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label);
-int dispatch_f64_fact(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label);
 // double running product over complex64 GOOMs (left factors, initial state, bias, outputs)
 int dispatch_f64_goom_io32(goom_ctx *ctx, const ChainArgs &args, int dp, int nw, long long grid, const char *label);
 

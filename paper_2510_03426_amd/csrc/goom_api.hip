@@ -373,9 +373,14 @@ static int run_scan(goom_ctx *ctx, const void *M, const void *init, void *P, lon
         // the state no longer fits a workgroup: chains advance step by step through a tiled GEMM
         const long long req = opts ? opts->chunk_len : 0;
         const bool f32 = dtype == GOOM_C64;
-        const size_t need = f32 ? scan_large_workspace_bytes(T, d, m, batch, req, final_only) : scan_large_f64_workspace_bytes(T, d, m, batch, req, final_only);
+        // (a workspace too small for the products in parts may do for those in floats: goom_scan_static's does)
+        const bool split = f32 && scan_split_applies(T, d, m, batch) && ws_bytes >= scan_split_workspace_bytes(T, d, m, batch, req, final_only);
+        const size_t need = split ? scan_split_workspace_bytes(T, d, m, batch, req, final_only)
+                            : f32 ? scan_large_workspace_bytes(T, d, m, batch, req, final_only)
+                                  : scan_large_f64_workspace_bytes(T, d, m, batch, req, final_only);
         if (int s = check_workspace(ctx, ws, ws_bytes, need)) return s;
         if (int s = need_ctx(ctx)) return s;
+        if (split) return run_scan_split(ctx, M, init, P, T, d, m, batch, req, ws, final_only);
         return f32 ? run_scan_large(ctx, M, init, P, T, d, m, batch, req, ws, final_only)
                    : run_scan_large_f64(ctx, M, init, P, T, d, m, batch, req, ws, final_only);
     }
@@ -776,7 +781,7 @@ size_t goom_lmme_workspace_bytes(int64_t batch, int n, int d, int m, int dtype, 
     if (lmme_tall_applies(n, d, m, dtype)) return 0;
     if (!lmme_is_large(n, d, m)) return 0;
     if (n > GOOM_MAX_DIM_LMME || d > GOOM_MAX_DIM_LMME || m > GOOM_MAX_DIM_LMME) return 0;
-    return dtype == GOOM_C64 ? lmme_large_workspace_bytes(batch, n, d, m) : lmme_large_f64_workspace_bytes(batch, n, d, m);
+    return dtype == GOOM_C64 ? lmme_split_workspace_bytes(batch, n, d, m) : lmme_large_f64_workspace_bytes(batch, n, d, m);
 }
 
 int goom_lmme(goom_ctx *ctx, const void *A, const void *B, void *C, int64_t batch, int n, int d, int m, int dtype,
@@ -799,10 +804,10 @@ int goom_lmme(goom_ctx *ctx, const void *A, const void *B, void *C, int64_t batc
     if (lmme_is_large(n, d, m)) {
         // beyond the register-resident kernels: scaled operands, a tiled GEMM and a store pass, through the workspace
         const bool f32 = dtype == GOOM_C64;
-        const size_t need = f32 ? lmme_large_workspace_bytes(batch, n, d, m) : lmme_large_f64_workspace_bytes(batch, n, d, m);
+        const size_t need = f32 ? lmme_split_workspace_bytes(batch, n, d, m) : lmme_large_f64_workspace_bytes(batch, n, d, m);
         if (int s = check_workspace(ctx, workspace, workspace_bytes, need)) return s;
         if (int s = need_ctx(ctx)) return s;
-        if (int s = f32 ? launch_lmme_large(ctx, A, B, C, batch, n, d, m, workspace) : launch_lmme_large_f64(ctx, A, B, C, batch, n, d, m, workspace))
+        if (int s = f32 ? launch_lmme_split(ctx, A, B, C, batch, n, d, m, workspace) : launch_lmme_large_f64(ctx, A, B, C, batch, n, d, m, workspace))
             return s;
         if (flags & GOOM_LMME_EXACT) return launch_lmme_exact(ctx, A, B, C, batch, n, d, m, dtype);
         return GOOM_OK;
@@ -841,13 +846,19 @@ int goom_lmme(goom_ctx *ctx, const void *A, const void *B, void *C, int64_t batc
     return GOOM_OK;
 }
 
+static size_t large_scan_bytes(int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts, bool final_only)
+{
+    const long long chunk = opts ? opts->chunk_len : 0;
+    if (dtype == GOOM_C128) return scan_large_f64_workspace_bytes(T, d, m, batch, chunk, final_only);
+    return scan_split_applies(T, d, m, batch) ? scan_split_workspace_bytes(T, d, m, batch, chunk, final_only) : scan_large_workspace_bytes(T, d, m, batch, chunk, final_only);
+}
+
 size_t goom_scan_workspace_bytes(int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts)
 {
     if (T <= 0 || d <= 0 || m <= 0 || batch <= 0 || d > GOOM_MAX_DIM_LMME || m > GOOM_MAX_DIM_LMME) return 0;
     if (dtype != GOOM_C64 && dtype != GOOM_C128) return 0;
     if (d > GOOM_MAX_DIM || m > GOOM_MAX_DIM)
-        return dtype == GOOM_C64 ? scan_large_workspace_bytes(T, d, m, batch, opts ? opts->chunk_len : 0, false)
-                                 : scan_large_f64_workspace_bytes(T, d, m, batch, opts ? opts->chunk_len : 0, false);
+        return large_scan_bytes(T, d, m, batch, dtype, opts, false);
     ScanPlan p = plan_scan(T, d, d, m, batch, dtype, opts ? opts->chunk_len : 0, false);
     return p.total();
 }
@@ -857,8 +868,7 @@ size_t goom_reduce_workspace_bytes(int64_t T, int d, int m, int64_t batch, int d
     if (T <= 0 || d <= 0 || m <= 0 || batch <= 0 || d > GOOM_MAX_DIM_LMME || m > GOOM_MAX_DIM_LMME) return 0;
     if (dtype != GOOM_C64 && dtype != GOOM_C128) return 0;
     if (d > GOOM_MAX_DIM || m > GOOM_MAX_DIM)
-        return dtype == GOOM_C64 ? scan_large_workspace_bytes(T, d, m, batch, opts ? opts->chunk_len : 0, true)
-                                 : scan_large_f64_workspace_bytes(T, d, m, batch, opts ? opts->chunk_len : 0, true);
+        return large_scan_bytes(T, d, m, batch, dtype, opts, true);
     ScanPlan p = plan_scan(T, d, d, m, batch, dtype, opts ? opts->chunk_len : 0, true);
     return p.total();
 }
@@ -875,14 +885,19 @@ int goom_scan_static(goom_ctx *ctx, const void *M, const void *init, void *P, in
     // argument errors first (reported without a device); the size check uses the same plan as goom_scan
     if (int s = check_scan_args(ctx, M, P, T, d, m, batch, dtype, opts, GOOM_MAX_DIM_LMME)) return s;
     goom_scan_opts eff = opts ? *opts : goom_scan_opts{0, 0};
-    size_t need = goom_scan_workspace_bytes(T, d, m, batch, dtype, &eff);
+    // (the least that run_scan takes)
+    auto least = [&](const goom_scan_opts &o) {
+        return dtype == GOOM_C64 && (d > GOOM_MAX_DIM || m > GOOM_MAX_DIM) ? scan_large_workspace_bytes(T, d, m, batch, o.chunk_len, false)
+                                                                            : goom_scan_workspace_bytes(T, d, m, batch, dtype, &o);
+    };
+    size_t need = least(eff);
     if (need > (size_t)GOOM_STATIC_SCRATCH_BYTES && eff.chunk_len == 0) {
         // the default plan has more chunks than the array holds products of: the shortest chunks, by powers of two,
         // that fit (fewer chunks, a smaller workspace; the result is the same scan)
         for (long long L = 8; L < T; L *= 2) {
             goom_scan_opts longer = eff;
             longer.chunk_len = L;
-            const size_t n = goom_scan_workspace_bytes(T, d, m, batch, dtype, &longer);
+            const size_t n = least(longer);
             if (n > 0 && n <= (size_t)GOOM_STATIC_SCRATCH_BYTES) {
                 eff = longer;
                 need = n;

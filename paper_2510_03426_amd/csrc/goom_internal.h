@@ -137,8 +137,13 @@ size_t lyap_steps_partial_bytes(long long batch, int d);
 int launch_lle_epilogue(goom_ctx *ctx, const void *v, double *lle, long long batch, int d, int dtype, double scale);
 int launch_uniform_u0(goom_ctx *ctx, void *u, long long batch, int d, int dtype);
 
-size_t lmme_large_workspace_bytes(long long batch, int n, int d, int m);
-int launch_lmme_large(goom_ctx *ctx, const void *A, const void *B, void *C, long long batch, int n, int d, int m, void *ws);
+// goom_large_split.hip: LMME of shapes above 128 and scans of large matrices, float components in three parts on the bf16 matrix instruction
+size_t lmme_split_workspace_bytes(long long batch, int n, int d, int m);
+int launch_lmme_split(goom_ctx *ctx, const void *A, const void *B, void *C, long long batch, int n, int d, int m, void *ws);
+bool scan_split_applies(long long T, int d, int m, long long batch);
+size_t scan_split_workspace_bytes(long long T, int d, int m, long long batch, long long requested_chunk, bool final_only);
+int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long long T, int d, int m, long long batch, long long requested_chunk, void *ws,
+                   bool final_only);
 // the same for complex128 operands (double components, double-precision matrix instruction)
 size_t lmme_large_f64_workspace_bytes(long long batch, int n, int d, int m);
 int launch_lmme_large_f64(goom_ctx *ctx, const void *A, const void *B, void *C, long long batch, int n, int d, int m, void *ws);

@@ -1,0 +1,71 @@
+"""Float products and scans of large matrices in three bf16 parts: sizes around the tiles of both kernels and the inner step, entries whose lower parts lie far
+below a row's largest, chunks of every kind, and the workspace that is too small for it."""
+import numpy as np
+import pytest
+
+import synthetic_inputs as si
+from test_gpu_parity import G, compare, dev, host, run_scan_case, tolerance, with_sensitivity  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def operands(oracle, shape, seed, spread):
+    batch, n, d, m = shape
+    out = []
+    for k, s in ((1, (batch, n, d)), (2, (batch, d, m))):
+        z = oracle.to_goom(si.normal_f32(si.BASE_SEED + seed, k, int(np.prod(s))).reshape(s))
+        z.real += (np.random.default_rng(seed + k).standard_normal(s) * spread).astype(np.float32)
+        out.append(z)
+    return out
+
+
+# inner sizes of one step, odd numbers of steps, a part of one; rows and columns at the edges of 32 and 128; both kernels (few tiles, many)
+@pytest.mark.parametrize("shape,spread", [((1, 129, 7, 3), 0), ((2, 1, 300, 1), 0), ((1, 130, 16, 129), 0), ((1, 31, 129, 33), 0), ((1, 257, 145, 65), 0),
+                                          ((64, 129, 47, 20), 0), ((40, 150, 33, 131), 0), ((1, 1024, 80, 1024), 0), ((1, 256, 1024, 40), 0),
+                                          ((3, 140, 150, 60), 15), ((70, 132, 80, 17), 15), ((1, 129, 200, 33), 20)])
+def test_products(G, oracle, shape, spread):  # noqa: F811
+    A, B = operands(oracle, shape, 1200 + shape[1] + shape[2], spread)
+    if spread:
+        A[:, 3] = -np.inf
+        B[:, :, 1] = -np.inf
+        A[:, 5, 1:] = -np.inf  # a row with one entry
+    got = host(G.lmme(dev(A), dev(B)))
+    for i in range(min(shape[0], 3)):
+        re, sg, kap, well = with_sensitivity(lambda a, b: oracle.lmme(a, b, return_kappa=True), [A[i], B[i]], np.float32, nprobe=1)
+        compare(got[i], re, sg, kap, name=f"product {shape}", max_ill_fraction=0.5 if spread else 0.05, well=well)
+        # these outputs are one float sum and one logarithm away from exact: sqrt(d) / 2 units of 2^-24 of a sum kappa times its result, the
+        # exponentials' (2^-22) and the logarithm's last place
+        plain = (kap < 16) & np.isfinite(re) & np.isfinite(got[i].real) & (spread == 0)
+        bound = kap * (np.sqrt(shape[2]) * 2.0 ** -24 + 2.0 ** -22) + np.abs(re) * 2.0 ** -22 + 2.0 ** -22
+        err = np.abs(got[i].real - re)
+        assert np.all(err[plain] <= bound[plain])
+
+
+# chunks of one step, of two, uneven ones (the last shorter: identities), a single one; states of their own width; several items
+@pytest.mark.parametrize("T,d,chunk,m,batch", [(5, 257, 1, None, 1), (7, 300, 2, None, 2), (8, 260, 3, 20, 1), (6, 130, 6, None, 2), (9, 200, 4, 300, 1), (5, 100, 2, 140, 1),
+                                               (11, 140, 0, None, 1), (1, 270, 0, None, 1), (2, 384, 0, 1, 3)])
+def test_scans(G, oracle, T, d, chunk, m, batch):  # noqa: F811
+    run_scan_case(G, oracle, T, d, chunk, m=m, batch=batch, seed=1300 + d, name=f"in parts d={d} m={m}")
+
+
+def test_scan_of_rows_far_apart(G, oracle):  # noqa: F811
+    T, d = 6, 264
+    Z = oracle.to_goom(si.normal_chain(si.BASE_SEED + 1400, T, d))
+    Z.real += (np.linspace(-40, 40, d)[:, None] - np.linspace(-40, 40, d)[None, :]).astype(np.float32)  # units of their own: D A D^-1
+    Z[2] += np.float32(2000.0)
+    Z[3, 7] = -np.inf
+    re, sg, kap, well = with_sensitivity(lambda z: oracle.scan(z, return_kappa=True), [Z], np.float32, nprobe=2)
+    for chunk in (2, 6):
+        compare(host(G.scan(dev(Z), chunk_len=chunk)), re, sg, kap, name=f"far apart chunk={chunk}", max_ill_fraction=0.05, well=well)
+
+
+def test_static_scratch(G, oracle):  # noqa: F811
+    import torch
+    for T, d in ((4, 300), (24, 300), (12, 520)):  # beside the room for it, and too large for that
+        z = dev(oracle.to_goom(si.normal_chain(si.BASE_SEED + 1500 + d, T, d)))
+        out = torch.empty_like(z)
+        G.scan_static(z, out)
+        ref = G.scan(z)
+        torch.cuda.synchronize()
+        a, b = host(out), host(ref)
+        assert np.quantile(np.abs(a.real - b.real), 0.99) < 1e-3

@@ -22,7 +22,9 @@
 // phase is latency bound: what counts is the length of the dependent instruction chain per
 // chunk.  One wave per batch item holds the whole state in registers (policies that look at a
 // state first), or one wave per panel of it, the panels' waves a chunk apart (policy "always").
+#include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "goom_internal.h"
 
@@ -47,6 +49,11 @@ struct ResetArgs {
     int d;
     int policy;
     float cos_threshold;
+    const int *only_if;          // staged kernel: NULL, or [batch]: items for which it has work
+    // spectra in segments (see reset_carry_staged_kernel): room for their results, [batch][segments] of SegmentRoom doubles
+    double *segments_room;
+    int segments, warm;
+    long long per_segment;
 };
 
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -339,8 +346,11 @@ constexpr int kPanelLd = 18; // row stride of a 16-column panel (or of its Gram 
 // One pivot of the elimination below (by recursion, so that every index is a constant).  neg: minus the multipliers of step K.
 // The order is the source's: the next pivot's row is updated first, and its reciprocal (rcp_d, step by step), a chain of dependent
 // instructions, is formed between the updates that nothing waits for.
-template <int K, int NR> __device__ inline void eliminate_from(double (&G)[16], double (&z)[NR][16], double neg, double &piv, int c)
+// KEEP: the multipliers stay in u: row K of the panel's unit triangular factor, lane c its column.
+template <int K, int NR, bool KEEP>
+__device__ inline void eliminate_from(double (&G)[16], double (&z)[NR][16], double neg, double &piv, int c, double (&u)[KEEP ? 16 : 1])
 {
+    if constexpr (KEEP) u[K] = -neg;
     if constexpr (K < 15) {
         // (with two rows a lane the second row's updates are filler enough, and fewer pieces leave the registers alone)
         constexpr int Z1 = NR > 1 ? 16 : K + 1 + (17 - K) / 3, Z2 = Z1 + (17 - Z1) / 2, G1 = NR > 1 ? 16 : K + 2 + (15 - K) / 2;
@@ -372,7 +382,7 @@ template <int K, int NR> __device__ inline void eliminate_from(double (&G)[16], 
         __builtin_amdgcn_sched_barrier(0);
         piv = c == K + 1 ? G[K + 1] : piv;
         const double inv = r1 * (2.0 - pivot * r1);
-        eliminate_from<K + 1, NR>(G, z, -(G[K + 1] * (pivot > 1.0e-280 ? inv : 0.0)), piv, c);
+        eliminate_from<K + 1, NR, KEEP>(G, z, -(G[K + 1] * (pivot > 1.0e-280 ? inv : 0.0)), piv, c, u);
     }
 }
 
@@ -390,8 +400,10 @@ template <int K, int NR> __device__ inline void eliminate_from(double (&G)[16], 
 // A pivot that comes out negative is a column that is nothing but rounding beside its norm: in a first pass it stays as it is,
 // its residual, with a pivot of 1, and the caller (told so) factors once more, where the residual stands for itself; in the
 // `last` one it is dropped, like a column that is zero.
-template <int DP> __device__ inline bool factor_panel_rows(const d4 (&Zp)[DP / 16], double &piv, double *panel, double *gram,
-                                                           double (&z)[DP > 64 ? 2 : 1][16], int lane, bool last)
+//
+// tri: (KEEP) receives the triangular factor, [16][18].
+template <int DP, bool KEEP = false> __device__ inline bool factor_panel_rows(const d4 (&Zp)[DP / 16], double &piv, double *panel, double *gram,
+                                                                              double (&z)[DP > 64 ? 2 : 1][16], int lane, bool last, double *tri = nullptr)
 {
     constexpr int KT = DP / 16, NR = DP > 64 ? 2 : 1;
     const int g = lane >> 4, c = lane & 15;
@@ -428,9 +440,18 @@ template <int DP> __device__ inline bool factor_panel_rows(const d4 (&Zp)[DP / 1
     }
     const double first = row_bcast<0>(G[0]);
     piv = G[0];
-    eliminate_from<0, NR>(G, z, -(G[0] * (first > 1.0e-280 ? rcp_d(first) : 0.0)), piv, c);
+    double u[KEEP ? 16 : 1];
+    eliminate_from<0, NR, KEEP>(G, z, -(G[0] * (first > 1.0e-280 ? rcp_d(first) : 0.0)), piv, c, u);
     const bool live = piv > 1.0e-280, open = !live && !last && piv != 0.0;
     const double sc = live ? rsqrt_d(piv) : open ? 1.0 : 0.0;
+    if constexpr (KEEP) {
+        gram[c] = live ? piv * sc : sc; // (the Gram matrix has been read) the factor's diagonal
+        wave_sync();
+        if (g == 0) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) tri[k * kPanelLd + c] = c < k ? 0.0 : c == k ? gram[k] : gram[k] * u[k];
+        }
+    }
     piv = open ? 1.0 : piv;
     const double cols[16] = {row_bcast<0>(sc),  row_bcast<1>(sc),  row_bcast<2>(sc),  row_bcast<3>(sc), row_bcast<4>(sc),  row_bcast<5>(sc),
                              row_bcast<6>(sc),  row_bcast<7>(sc),  row_bcast<8>(sc),  row_bcast<9>(sc), row_bcast<10>(sc), row_bcast<11>(sc),
@@ -821,14 +842,28 @@ template <int DP, typename IO> __global__ __launch_bounds__(64) void reset_carry
 // Carries of 512 chunks of 32 x 32: 4.34 -> 2.55 ms (0.2 of it second factorisations), one wave with a whole state having
 // taken 20 400 cycles a chunk.  Whole spectra: 14 000 steps of 64 x 64 12.1 -> 1.89 ms, complex128 50 x 50 12.1 -> 2.03, complex128
 // 65 536 of 32 x 32, where nearly every chunk is factored twice (three stages a chunk instead of one), 7.5 -> 5.9.
-template <int DP> constexpr size_t staged_lds()
+//
+// SEG: the spectrum of a long chain.  Its stages are a serial chain, but the growth is the diagonal of one triangular factor: that of
+// the whole chain's product times the initial state, and this can be put together from pieces.  Each segment of the chunks is walked by a workgroup of its
+// own, from the identity (`warm` chunks early, so that its state is close to the chain's when the segment begins), and what it keeps is its product
+// as Q_e R Q_s^T: the states at its ends and the product of its triangular factors, R = diag(2^E) N, on exponents of its rows (R's entries
+// lie e^+-1000 apart).  segment_join_kernel makes one of two.  R is put together by a wave beside the panels' waves, a
+// stage behind the decision about a chunk, from the projections' coefficients and the panels' triangles that they leave in LDS.
+// 512 chunks of 32 x 32: 2532 -> 360 us (189 in segments of 16 chunks, 5 x 33 to join 32 of them); whole spectra, T = 65 536: 2.83 -> 0.64 ms, complex128
+// (nearly every chunk factored twice) 5.93 -> 0.82.  Error against sequential QR, geometric means over 8 to 14 chains, in order -> in segments:
+// 16 x 16 1.6e-13 -> 1.5e-13, 20 x 20 1.9e-13 -> 2.4e-13, 32 x 32 7.1e-13 -> 4.6e-13, complex128 7.3e-13 -> 5.0e-13 (`warm` 0: ten times as much, and up to 1e6 in L).
+constexpr int kTriSlots = 5; // four chunks, and a second factorisation
+template <int DP, bool SEG = false> constexpr size_t staged_lds()
 {
     constexpr int KT = DP / 16;
-    return (((size_t)((KT - 1) * KT + 1) * DP + DP) * kPanelLd + KT * DP * 2 + 4) * sizeof(double);
+    return (((size_t)((KT - 1) * KT + 1) * DP + DP) * kPanelLd + KT * DP * 2 + 4 + (SEG ? kTriSlots * (3 * 16 * kPanelLd + DP) + DP : 0)) * sizeof(double);
 }
+// a segment's results: Q_s, N, Q_e (DP x DP), E, its growth (of the first one, from its true start), whether it can be used
+template <int DP> constexpr int segment_room() { return 3 * DP * DP + 2 * DP + 2; }
 
-template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_carry_staged_kernel(ResetArgs a)
+template <int DP, typename IO, bool SEG = false> __global__ __launch_bounds__(DP * 4 + (SEG ? 64 : 0)) void reset_carry_staged_kernel(ResetArgs a)
 {
+    static_assert(!SEG || DP <= 32, "two panels at most");
     constexpr int KT = DP / 16, PANEL = DP * kPanelLd;
     extern __shared__ __align__(32) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -836,7 +871,12 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
     const int g = lane >> 4, c = lane & 15;
     const int pc = ((c & 3) << 2) | (c >> 2);
     const int d = a.d, col = 16 * p + c;
-    const long long b = blockIdx.x;
+    const long long b = SEG ? blockIdx.x / a.segments : blockIdx.x;
+    if (a.only_if && !a.only_if[b]) return; // the whole workgroup
+    const int segment = SEG ? (int)(blockIdx.x % a.segments) : 0;
+    const bool last_segment = !SEG || segment + 1 == a.segments;
+    const long long kept_from = SEG ? segment * a.per_segment : 0;                          // chunks whose factors count
+    const long long begin = SEG && segment > 0 ? (kept_from > a.warm ? kept_from - a.warm : 0) : 0;
     const size_t tot_mant = (size_t)DP * a.tot_cols * sizeof(double);
     const size_t car_mant = (size_t)DP * a.car_cols * sizeof(double);
     auto slot = [&](int q, long long i) { return reinterpret_cast<double *>(smem) + (size_t)(q * KT + (q + 1 < KT ? (int)(i & (KT - 1)) : 0)) * PANEL; };
@@ -844,6 +884,12 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
     // of the chunks that are not decided yet: a column's pivot and the exponents taken out of it
     d2 *undecided = reinterpret_cast<d2 *>(reinterpret_cast<double *>(smem) + (size_t)((KT - 1) * KT + 1) * PANEL + DP * kPanelLd);
     int *worst = reinterpret_cast<int *>(undecided + KT * DP); // [2][KT]: does a chunk's state have to be factored again, so far as waves 0 .. p know
+    // SEG: per slot the triangular factor's blocks (0, 0), (1, 1), (0, 1) and its columns' exponents; E
+    [[maybe_unused]] double *tri = reinterpret_cast<double *>(worst) + 4;
+    auto tri_block = [&](int sl, int q) { return tri + (size_t)(sl * 3 + q) * 16 * kPanelLd; };
+    [[maybe_unused]] double *tri_exp = tri + (size_t)kTriSlots * 3 * 16 * kPanelLd; // [slot][DP]
+    [[maybe_unused]] double *row_exp = tri_exp + kTriSlots * DP;
+    [[maybe_unused]] double *room = SEG ? a.segments_room + (size_t)blockIdx.x * segment_room<DP>() : nullptr;
 
     d4 Y[KT]; // Y[mt][v] = entry (row 16 mt + 4 v + g, column 16 p + c), columns scaled by 2^yexp
     double yexp = 0.0, pprod = 1.0, pexp = 0.0; // product of all pivots so far = pprod 2^pexp (column exponents counted twice)
@@ -851,7 +897,7 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
     for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
         for (int v = 0; v < 4; ++v) Y[mt][v] = (16 * mt + 4 * v + g == col && col < d) ? 1.0 : 0.0;
-    if (a.s0 && col < d) {
+    if (a.s0 && col < d && segment == 0) {
         const IO *gp = reinterpret_cast<const IO *>(a.s0) + (size_t)b * d * d * 2;
         double cmax = -__builtin_huge_val();
         for (int i = 0; i < d; ++i) cmax = fmax(cmax, (double)gp[((size_t)i * d + col) * 2]);
@@ -950,12 +996,14 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
     // Q of Z (in the matrix instruction's layout) to `out` and, as rows, to `rows`; the columns' pivots and exponents.  Returns whether
     // one of the columns asks for a second factorisation (see qr_panels_d and its callers).
     auto factor = [&](d4 (&Z)[KT], long long i, double *out, double (&rows)[1][16], double &piv, double &expo, bool second) {
+        [[maybe_unused]] d4 coefficients = {0., 0., 0., 0.};
         auto project = [&]() {
             d4 R = {0., 0., 0., 0.};
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) R = mfma8(qt[kt][v], Z[kt][v], R);
+            if constexpr (SEG) coefficients += R;
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -980,7 +1028,15 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
                 if (KT > 2) load_panel(q, i);
                 project();
             }
-        const bool open = factor_panel_rows<DP>(Z, piv, out, gram, rows, lane, second);
+        const int sl = second ? kTriSlots - 1 : (int)(i & 3);
+        if constexpr (SEG) {
+            if (p > 0) {
+                double *t = tri_block(sl, 2);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) t[(4 * v + g) * kPanelLd + c] = coefficients[v];
+            }
+        }
+        const bool open = factor_panel_rows<DP, SEG>(Z, piv, out, gram, rows, lane, second, SEG ? tri_block(sl, p) : nullptr);
         return open || __builtin_amdgcn_ballot_w64(piv > 1.0e-280 && norm2 > (sizeof(IO) == 4 ? 1.0e10 : 1.0e3) * piv) != 0;
     };
     // growth as in reset_carry_kernel (a column that is zero has none)
@@ -992,18 +1048,94 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
         }
     };
 
-    load_total(0);
-    const long long items = a.C + (a.growth ? 1 : 0); // (the last one: growth of the final state, factorised, not replaced)
+    load_total(begin);
+    // (the last one: growth of the final state, factorised, not replaced)
+    const long long items = last_segment ? a.C + (a.growth ? 1 : 0) : (segment + 1) * a.per_segment;
+    // SEG: N in the matrix instruction's layout, E in LDS
+    [[maybe_unused]] d4 N[KT][KT];
+    [[maybe_unused]] bool lost = false;
+    if constexpr (SEG) {
+        if (p == KT) {
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int nt = 0; nt < KT; ++nt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) N[kt][nt][v] = kt == nt && 4 * v + g == c ? 1.0 : 0.0;
+            if (lane < DP) row_exp[lane] = 0.0;
+            wave_sync();
+        }
+    }
+    // N <- R N, rows on exponents of their own
+    auto accumulate = [&](int sl) {
+        double rv[KT][KT][4], ek[KT][4], top[KT];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) ek[kt][v] = row_exp[16 * kt + 4 * v + g] + tri_exp[sl * DP + 16 * kt + 4 * v + g];
+#pragma unroll
+        for (int mt = 0; mt < KT; ++mt) {
+            top[mt] = -1.0e300;
+#pragma unroll
+            for (int kt = mt; kt < KT; ++kt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    rv[mt][kt][v] = tri_block(sl, mt == kt ? mt : 2)[c * kPanelLd + 4 * v + g];
+                    if (rv[mt][kt][v] != 0.0) {
+                        int e;
+                        (void)frexp(rv[mt][kt][v], &e);
+                        top[mt] = fmax(top[mt], (double)e + ek[kt][v]);
+                    }
+                }
+            top[mt] = fmax(top[mt], __shfl_xor(top[mt], 16, 64));
+            top[mt] = fmax(top[mt], __shfl_xor(top[mt], 32, 64));
+            const bool empty = !(top[mt] > -1.0e299);
+            lost = lost || (empty && 16 * mt + c < d);
+            if (empty) top[mt] = 0.0;
+        }
+        wave_sync();
+#pragma unroll
+        for (int mt = 0; mt < KT; ++mt) {
+            if (g == 0) row_exp[16 * mt + c] = top[mt];
+#pragma unroll
+            for (int kt = mt; kt < KT; ++kt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) rv[mt][kt][v] = ldexp(rv[mt][kt][v], (int)fmax(ek[kt][v] - top[mt], -4000.0));
+        }
+#pragma unroll
+        for (int mt = 0; mt < KT; ++mt) // (upper triangular: the rows below a row's block are the old ones still)
+#pragma unroll
+            for (int nt = mt; nt < KT; ++nt) {
+                d4 sum = {0., 0., 0., 0.};
+#pragma unroll
+                for (int kt = mt; kt <= nt; ++kt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) sum = mfma8(rv[mt][kt][v], N[kt][nt][v], sum);
+                N[mt][nt] = sum;
+            }
+        wave_sync();
+    };
     // wave p is at chunk from + n - p in stage n since the last (re)start, which begins with the second factorisation of chunk `from` if `redo`
-    long long from = 0, n = 0;
+    long long from = begin, n = 0;
     bool redo = false;
+    int pending = -1; // SEG: the slot of a factor that has been decided
     double redo_piv = 1.0, redo_expo = 0.0; // pivots and exponents of that chunk's first factorisation
     d2 own; // what this wave has left in `undecided` last
     bool hit = false;
     for (int stage = 0;; stage ^= 1, ++n) {
         const long long i = from + n - p;
         const bool second = redo && i == from;
-        if (n >= p && i < items) { // (the same for the whole wave)
+        if constexpr (SEG) {
+            if (p == KT && pending >= 0) accumulate(pending);
+            pending = -1;
+            if (p < KT && n >= p && i == kept_from && !second && segment > 0) { // (written again should the chunk before be factored again)
+#pragma unroll
+                for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) room[(16 * mt + 4 * v + g) * DP + col] = Y[mt][v];
+            }
+        }
+        if ((!SEG || p < KT) && n >= p && i < items) { // (the same for the whole wave)
             double *out = slot(p, i);
             double rows[1][16], piv, expo, zexp = yexp;
             d4 Z[KT];
@@ -1048,6 +1180,9 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
             load_total(i + 1 < a.C ? i + 1 : a.C - 1); // (in one place: loads in several would be copied together, and waited for, where they meet)
             if (boundary) {
                 hit = factor(Z, i, out, rows, piv, expo, second);
+                if constexpr (SEG) {
+                    if (g == 0) tri_exp[(second ? kTriSlots - 1 : (int)(i & 3)) * DP + col] = second ? expo : zexp + expo;
+                }
                 if (second) {
                     grow(redo_piv, piv, redo_expo + expo);
                 } else {
@@ -1071,7 +1206,7 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
                 if (a.carries) store_carry(i + 1, rows);
                 if (tid == 0) a.chunk_flags[b * a.C + i] = boundary ? 1 : 0;
             }
-            if (KT > 1 && lane == 0) worst[stage * KT + p] = (hit && !second) || (p > 0 && !second && worst[(stage ^ 1) * KT + p - 1]);
+            if ((KT > 1 || SEG) && lane == 0) worst[stage * KT + p] = (hit && !second) || (p > 0 && !second && worst[(stage ^ 1) * KT + p - 1]);
         }
         // (LDS only: the loads of the next chunk product and the stores of carries stay in flight)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -1080,9 +1215,11 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
         // the chunk that the last wave has finished (all waves come to the same answer)
         if (n < KT - 1) continue;
         const long long done = from + n - (KT - 1);
+        if (SEG && redo && done == from && done >= kept_from && segment > 0) pending = kTriSlots - 1;
         if (!(redo && done == from) && (done == a.C || (done + 1) * a.L <= a.T)) {
-            const d2 first = KT > 1 ? undecided[(done & (KT - 1)) * DP + col] : own;
-            if (KT > 1 ? __builtin_amdgcn_readfirstlane(worst[stage * KT + KT - 1]) != 0 : hit) {
+            if (SEG && done >= kept_from && segment > 0) pending = (int)(done & 3);
+            const d2 first = KT > 1 ? (!SEG || p < KT ? undecided[(done & (KT - 1)) * DP + col] : d2{1.0, 0.0}) : own;
+            if (KT > 1 || SEG ? __builtin_amdgcn_readfirstlane(worst[stage * KT + KT - 1]) != 0 : hit) {
                 from = done;
                 n = -1;
                 redo = true;
@@ -1095,7 +1232,221 @@ template <int DP, typename IO> __global__ __launch_bounds__(DP * 4) void reset_c
         }
         if (done + 1 == items) break;
     }
-    if (a.growth && g == 0 && col < d) a.growth[b * d + col] = 0.5 * (log(pprod) + pexp * kLn2) * a.growth_scale;
+    if constexpr (SEG) {
+        if (p == KT) {
+            if (pending >= 0) accumulate(pending);
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < KT; ++nt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) room[DP * DP + (16 * mt + 4 * v + g) * DP + 16 * nt + c] = N[mt][nt][v];
+            if (lane < DP) room[3 * DP * DP + lane] = row_exp[lane];
+            const bool any = __builtin_amdgcn_ballot_w64(lost) != 0;
+            if (lane < 2) room[3 * DP * DP + 2 * DP + lane] = any ? 1.0 : 0.0; // (the first segment's own mark is the second)
+        } else {
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) room[2 * DP * DP + (16 * mt + 4 * v + g) * DP + col] = Y[mt][v];
+            if (g == 0) room[3 * DP * DP + DP + col] = col < d ? 0.5 * (log(pprod) + pexp * kLn2) : 0.0;
+        }
+    } else if (a.growth && g == 0 && col < d) {
+        a.growth[b * d + col] = 0.5 * (log(pprod) + pexp * kLn2) * a.growth_scale;
+    }
+}
+
+// sum over the eight lanes that share a row (column) below
+__device__ inline double eight_sum(double x)
+{
+    auto moved = [](double v, auto ctrl) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u & 0xffffffffull), decltype(ctrl)::value, 0xf, 0xf, true);
+        const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+    };
+    x += moved(x, std::integral_constant<int, 0xB1>{});  // quad_perm [1,0,3,2]
+    x += moved(x, std::integral_constant<int, 0x4E>{});  // quad_perm [2,3,0,1]
+    x += moved(x, std::integral_constant<int, 0x141>{}); // row_half_mirror
+    return x;
+}
+__device__ inline double eight_max(double x)
+{
+#pragma unroll
+    for (int s = 1; s < 8; s <<= 1) x = fmax(x, __shfl_xor(x, s, 64));
+    return x;
+}
+
+// Two neighbouring segments of reset_carry_staged_kernel<., ., true> become one (a tree of launches makes one of all).  With Q_s, E, N, Q_e of the first (1) and
+// of the second (2),
+//     Q_e2 diag(2^E2) N2 W diag(2^E1) N1 Q_s1^-1,  Q_s2 W = Q_e1,
+// and what is needed is the triangular factorisation of diag(2^E2) N2 W, whose rows lie e^+-1000 apart: from the columns as they are, everything
+// below the largest rows would be rounding.  N2 W = L U without exchanges first; then
+//     diag(2^E2) L U = (diag(2^E2) L diag(2^-E2)) diag(2^E2) U,
+// where the bracket is 1 on the diagonal, small below it where the exponents are in order (they are, but for directions of nearly equal
+// growth), and is factored by columns, Q' R'.  L is small when Q_s2 is close to Q_e1.  Should it not be, or a segment have lost a row (singular
+// chunks), the chain is walked in order after all.  For the chain's first segment only the growth counts: the diagonals' logarithms.
+// One workgroup a pair, eight threads a row.  Bound by the 2 d dependent steps of the two factorisations.
+template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(ResetArgs a, int stride, int *again)
+{
+    constexpr int LD = DP + 1, W = DP / 8, KT = DP / 16;
+    __shared__ double X[DP * LD], Y[DP * LD], Z[DP * LD], low[DP * LD], rest[DP * LD];
+    __shared__ double E1[DP], E2[DP];
+    __shared__ int bad;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid >> 3, s = tid & 7, d = a.d;
+    const int g = lane >> 4, c = lane & 15;
+    const int pairs = (a.segments - stride + 2 * stride - 1) / (2 * stride);
+    const long long b = blockIdx.x / pairs;
+    const int first = (int)(blockIdx.x % pairs) * 2 * stride;
+    double *room1 = a.segments_room + ((size_t)b * a.segments + first) * segment_room<DP>();
+    const double *room2 = room1 + (size_t)stride * segment_room<DP>();
+    auto fetch = [&](double *to, const double *from) {
+        for (int m = 0; m < W; ++m) to[r * LD + s + 8 * m] = from[r * DP + s + 8 * m];
+    };
+    // C <- base + sign * A B (or A^T B); a wave a tile
+    auto multiply = [&](double *C, const double *base, double sign, const double *A, bool transposed, const double *B) {
+        if (wave < KT * KT) {
+            const int mt = wave / KT, nt = wave % KT;
+            d4 sum = {0., 0., 0., 0.};
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int k = 16 * kt + 4 * v + g, i = 16 * mt + c;
+                    sum = mfma8(transposed ? A[k * LD + i] : A[i * LD + k], B[k * LD + 16 * nt + c], sum);
+                }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int at = (16 * mt + 4 * v + g) * LD + 16 * nt + c;
+                C[at] = base ? base[at] + sign * sum[v] : sum[v];
+            }
+        }
+        __syncthreads();
+    };
+    fetch(Y, room2);                   // Q_s2
+    fetch(Z, room1 + 2 * DP * DP);     // Q_e1
+    fetch(low, room2 + DP * DP);       // N2
+    if (tid < DP) {
+        E2[tid] = room2[3 * DP * DP + tid];
+        E1[tid] = room1[3 * DP * DP + tid];
+    }
+    if (tid == 0) bad = room2[3 * DP * DP + 2 * DP] != 0.0 || (first > 0 && room1[3 * DP * DP + 2 * DP] != 0.0) || (first == 0 && room1[3 * DP * DP + 2 * DP + 1] != 0.0);
+    __syncthreads();
+    // W: Q_s2^T Q_e1, and corrected twice (states of complex64 chains are orthonormal to 1e-6 only, where a chunk was not factored twice)
+    multiply(X, nullptr, 1.0, Y, true, Z);
+    for (int turn = 0; turn < 2; ++turn) {
+        multiply(rest, Z, -1.0, Y, false, X);
+        multiply(X, X, 1.0, Y, true, rest);
+    }
+    multiply(Z, nullptr, 1.0, low, false, X); // N2 W
+    for (int m = 0; m < W; ++m) low[r * LD + s + 8 * m] = 0.0;
+    __syncthreads();
+    // Z = L U, U in place; the bracket in `low`
+    bool wrong = false;
+    for (int k = 0; k < d; ++k) {
+        const double pivot = Z[k * LD + k];
+        if (r > k && r < d) {
+            const double l = Z[r * LD + k] / pivot;
+#pragma unroll
+            for (int m = 0; m < W; ++m)
+                if (s + 8 * m > k) Z[r * LD + s + 8 * m] = fma(-l, Z[k * LD + s + 8 * m], Z[r * LD + s + 8 * m]);
+            wrong = wrong || !(fabs(l) <= 1.0e6); // (also a pivot of zero)
+            if (s == 0) {
+                const double x = ldexp(l, (int)fmin(fmax(E2[r] - E2[k], -4000.0), 1000.0));
+                wrong = wrong || !(fabs(x) <= 1.0e6);
+                low[r * LD + k] = x;
+            }
+        }
+        __syncthreads();
+    }
+    if (s == 0) low[r * LD + r] = r < d ? 1.0 : 0.0;
+    for (int m = 0; m < W; ++m) {
+        const int j = s + 8 * m;
+        if (j < r || r >= d) Z[r * LD + j] = 0.0;
+        rest[r * LD + j] = 0.0;
+    }
+    if (tid < d) wrong = wrong || !(fabs(Z[tid * LD + tid]) > 0.0);
+    __syncthreads();
+    // the bracket's columns one after the other: Q' to X, R' to rest.  r is a column here
+    for (int k = 0; k < d; ++k) {
+        double n2 = 0.0, dot = 0.0, ck[W], cr[W];
+#pragma unroll
+        for (int m = 0; m < W; ++m) {
+            ck[m] = low[(s + 8 * m) * LD + k];
+            cr[m] = low[(s + 8 * m) * LD + r];
+            n2 = fma(ck[m], ck[m], n2);
+            dot = fma(ck[m], cr[m], dot);
+        }
+        n2 = eight_sum(n2);
+        dot = eight_sum(dot);
+        if (r >= k && r < d) {
+            const double norm = sqrt(n2), f = dot / n2;
+            if (s == 0) rest[k * LD + r] = f * norm;
+            if (r > k) {
+#pragma unroll
+                for (int m = 0; m < W; ++m) low[(s + 8 * m) * LD + r] = fma(-f, ck[m], cr[m]);
+            } else {
+                const double inv = 1.0 / norm;
+#pragma unroll
+                for (int m = 0; m < W; ++m) X[(s + 8 * m) * LD + k] = ck[m] * inv;
+            }
+        }
+        __syncthreads();
+    }
+    for (int m = 0; m < W; ++m)
+        if (r >= d || s + 8 * m >= d) X[r * LD + s + 8 * m] = 0.0;
+    if (first == 0) {
+        if (tid < d) {
+            double &growth = room1[3 * DP * DP + DP + tid];
+            growth += log(fabs(Z[tid * LD + tid])) + log(rest[tid * LD + tid]) + E2[tid] * kLn2;
+            if (2 * stride >= a.segments) { // the last pair
+                const double x = growth * a.growth_scale;
+                if (!(fabs(x) < 1.0e300)) bad = 1;
+                a.growth[b * d + tid] = x;
+            }
+        }
+    } else {
+        // N1 <- R' diag(2^E2) U diag(2^E1) N1, rows on exponents of their own
+        fetch(Y, room1 + DP * DP);
+        for (int turn = 0; turn < 2; ++turn) {
+            double *A = turn ? rest : Z;
+            __syncthreads();
+            double top = -1.0e300;
+            for (int m = 0; m < W; ++m) {
+                const int j = s + 8 * m;
+                const double x = A[r * LD + j];
+                if (x != 0.0) {
+                    int e;
+                    (void)frexp(x, &e);
+                    top = fmax(top, (double)e + E1[j]);
+                }
+            }
+            top = eight_max(top);
+            const bool empty = !(top > -1.0e299);
+            wrong = wrong || (empty && r < d);
+            if (empty) top = 0.0;
+            for (int m = 0; m < W; ++m) {
+                const int j = s + 8 * m;
+                A[r * LD + j] = ldexp(A[r * LD + j], (int)fmax(E1[j] - top, -4000.0));
+            }
+            __syncthreads();
+            if (s == 0) E1[r] = top + (turn == 0 ? E2[r] : 0.0);
+            multiply(turn ? Y : low, nullptr, 1.0, A, false, turn ? low : Y);
+        }
+        for (int m = 0; m < W; ++m) room1[DP * DP + r * DP + s + 8 * m] = Y[r * LD + s + 8 * m];
+        if (tid < DP) room1[3 * DP * DP + tid] = E1[tid];
+    }
+    if (wrong) bad = 1;
+    __syncthreads();
+    // Q_e1 <- Q_e2 Q'
+    fetch(Z, room2 + 2 * DP * DP);
+    __syncthreads();
+    multiply(Y, nullptr, 1.0, Z, false, X);
+    for (int m = 0; m < W; ++m) room1[2 * DP * DP + r * DP + s + 8 * m] = Y[r * LD + s + 8 * m];
+    if (tid == 0) {
+        room1[3 * DP * DP + 2 * DP + (first == 0 ? 1 : 0)] = bad ? 1.0 : 0.0;
+        if (first == 0 && 2 * stride >= a.segments) again[b] = bad;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -2394,7 +2745,12 @@ int launch_reset_carry(goom_ctx *ctx, const ResetLaunch &l)
     a.d = l.d;
     a.policy = l.policy;
     a.cos_threshold = l.cos_threshold;
+    a.only_if = nullptr;
+    a.segments_room = nullptr;
+    a.segments = a.warm = 0;
+    a.per_segment = 0;
     const int dp = padded_dim(l.d);
+    unsigned char *const carries = static_cast<unsigned char *>(l.carries);
     if (l.policy == GOOM_RESET_ALWAYS && dp <= 64 && !l.post_states) a.carries = nullptr; // (without states nobody reads them)
     if (l.d > 128) return fail(ctx, GOOM_EUNSUPPORTED, "the reset scan supports d <= 128 (d=%d)", l.d);
     if (dp == 128) { // four waves per batch item, the state's columns divided among them
@@ -2408,6 +2764,42 @@ int launch_reset_carry(goom_ctx *ctx, const ResetLaunch &l)
             hipLaunchKernelGGL(reset_carry_wide_kernel<double>, dim3((unsigned)l.batch), dim3(256), lds, ctx->stream, a);
         prof_end(ctx);
         return check_hip(ctx, hipGetLastError(), "launch reset_carry_wide_kernel");
+    }
+    // The spectrum alone of a long chain: in segments of sixteen chunks and more, whose results lie where the carries would.
+    const long long warm = 8;
+    long long segments = l.C / 16;
+    if (segments > 256 / l.batch) segments = 256 / l.batch; // a compute unit each
+    if (!a.carries && l.policy == GOOM_RESET_ALWAYS && dp <= 32 && l.growth && segments >= 4) {
+        a.per_segment = (l.C + segments - 1) / segments;
+        a.segments = (int)((l.C + a.per_segment - 1) / a.per_segment);
+        a.warm = (int)warm;
+        a.segments_room = reinterpret_cast<double *>(carries);
+        int *again = reinterpret_cast<int *>(a.segments_room + (size_t)l.batch * a.segments * (dp == 16 ? segment_room<16>() : segment_room<32>()));
+        prof_begin(ctx, "reset_phase2_segments_qr");
+        const dim3 grid((unsigned)(l.batch * a.segments));
+#define GOOM_SEGMENT_CASE(DPV, IO)                                                                                                                        \
+    {                                                                                                                                                      \
+        if (int st = check_hip(ctx,                                                                                                                        \
+                               hipFuncSetAttribute(reinterpret_cast<const void *>(reset_carry_staged_kernel<DPV, IO, true>),                               \
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)staged_lds<DPV, true>()),                              \
+                               "hipFuncSetAttribute(reset_carry_staged_kernel)"))                                                                          \
+            return st;                                                                                                                                     \
+        hipLaunchKernelGGL((reset_carry_staged_kernel<DPV, IO, true>), grid, dim3(4 * DPV + 64), (staged_lds<DPV, true>()), ctx->stream, a);               \
+    }
+        if (dp == 16) {
+            if (l.dtype == GOOM_C64) GOOM_SEGMENT_CASE(16, float) else GOOM_SEGMENT_CASE(16, double)
+        } else {
+            if (l.dtype == GOOM_C64) GOOM_SEGMENT_CASE(32, float) else GOOM_SEGMENT_CASE(32, double)
+        }
+        for (int stride = 1; stride < a.segments; stride *= 2) {
+            const unsigned pairs = (unsigned)((a.segments - stride + 2 * stride - 1) / (2 * stride) * l.batch);
+            if (dp == 16) hipLaunchKernelGGL(segment_join_kernel<16>, dim3(pairs), dim3(128), 0, ctx->stream, a, stride, again);
+            else hipLaunchKernelGGL(segment_join_kernel<32>, dim3(pairs), dim3(256), 0, ctx->stream, a, stride, again);
+        }
+#undef GOOM_SEGMENT_CASE
+        prof_end(ctx);
+        if (int st = check_hip(ctx, hipGetLastError(), "launch reset_carry_staged_kernel in segments")) return st;
+        a.only_if = again; // and in order those that did not come out
     }
     prof_begin(ctx, "reset_phase2_carries_qr");
 #define GOOM_STAGED_CASE(DPV)                                                                                                  \

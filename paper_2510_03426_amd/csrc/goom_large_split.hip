@@ -415,12 +415,13 @@ template <bool RAW> __global__ __launch_bounds__(256, 2) void gemm_split_few_ker
 
 // Do products of n x m (any sizes) fill the chip in 128 x 128 tiles?  512 x 512 x 512, one after the other (16 tiles): 18 us in 64 x 64 tiles of the large kernel's
 // kind, 9.4 in the other's; from 64 tiles on the large kernel's sharing of operands counts.
-bool split_in_tiles(int n, int m, long long products) { return (unsigned long long)(pad_to(n, 128) / 128) * (pad_to(m, 128) / 128) * products >= 64; }
+// (Tiles' worth of entries: 64 products of 64 x 1000 x 64 are 64 tiles that are three quarters padding, 49 us, and 20 in the other's.)
+bool split_in_tiles(int n, int m, long long products) { return (double)n * m * (double)products >= 64.0 * 128 * 128; }
 
 // products: of M x N x K (padded: K to 16, M and N to 128, or to 32 if they are too few)
-template <bool RAW> void launch_gemm_split(hipStream_t st, const SplitGemm &a, unsigned products)
+template <bool RAW> void launch_gemm_split(hipStream_t st, const SplitGemm &a, unsigned products, bool in_tiles)
 {
-    if (split_in_tiles(a.M, a.N, products))
+    if (in_tiles)
         hipLaunchKernelGGL(gemm_split_kernel<RAW>, dim3(a.N / 128, a.M / 128, products), dim3(256), 0, st, a);
     else
         hipLaunchKernelGGL(gemm_split_few_kernel<RAW>, dim3(a.N / 32, a.M / 32, products), dim3(256), 0, st, a);
@@ -804,7 +805,7 @@ int launch_lmme_split(goom_ctx *ctx, const void *A, const void *B, void *C, long
     a.step = 0;
     a.n = n;
     a.m = m;
-    launch_gemm_split<false>(st, a, nb);
+    launch_gemm_split<false>(st, a, nb, split_in_tiles(n, m, batch));
     prof_end(ctx);
     return check_hip(ctx, hipGetLastError(), "launch gemm_split_kernel");
 }
@@ -991,7 +992,7 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
                 a.key1 = {key_tot, C * dp, dp};
                 a.e_out = {e_tot, C * dp, dp};
             }
-            launch_gemm_split<true>(st, a, nchains);
+            launch_gemm_split<true>(st, a, nchains, split_in_tiles(dp, dp, nchains));
         }
         prof_end(ctx);
         if (int e = ok("scan_large phase 1")) return e;
@@ -1048,7 +1049,7 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
             a.n = d;
             a.m = m;
         }
-        launch_gemm_split<true>(st, a, (unsigned)batch);
+        launch_gemm_split<true>(st, a, (unsigned)batch, split_in_tiles(dp, mp, batch));
     }
     prof_end(ctx);
     if (int e = ok("scan_large phase 2")) return e;
@@ -1091,7 +1092,7 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
             a.L = final_only ? 1 : L;
             a.step = final_only ? 0 : s;
         }
-        launch_gemm_split<true>(st, a, (unsigned)chains);
+        launch_gemm_split<true>(st, a, (unsigned)chains, split_in_tiles(dp, mp, chains));
     }
     prof_end(ctx);
     return ok("scan_large phase 3");

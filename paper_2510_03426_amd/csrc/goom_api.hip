@@ -992,13 +992,32 @@ static bool affine_walk_whole(int d, long long batch, int dtype, const goom_scan
     return batch >= (d <= 16 ? 384 : d <= 32 ? 96 : 48);
 }
 
+// One matrix for all steps: sixteen chunks a workgroup (goom_one_matrix.hip) where there are enough of them.  At 32 rows a chain of its own wave
+// is as fast up to some thousand chains (forward pass, a wave a chain / sixteen chains a workgroup: 8 x 511 x 24 72 / 81 us, complex128 75 / 93;
+// 512 x 100 x 32 80 / 75, 193 / 77; 128 x 4096 x 32 296 / 265, 1361 / 369), at 64 it never is (1 x 60 x 64 100 / 60; 64 x 1000 x 64 179 / 135).
+static bool one_matrix_tiles(int dp, long long T, long long batch, int dtype)
+{
+    return goom_chain::one_matrix_walk_applies(dp, dtype) && (dp > 32 || batch * T >= 32768);
+}
+
 // One matrix for all steps: chunks of a power of two (their product is a few squarings).  A chunk is walked twice, its carry once, each
 // about a step's time, so 2 L + T / L is least near L = sqrt(T / 2); longer where that makes more chains than the chip holds at once
 // (the walks' time is then that of all their steps, whatever L), and never more chunks than the scan's own plan has room for.
-static long long one_matrix_chunk(long long T, int d, long long batch, int dtype)
+//
+// Walks of sixteen chunks a workgroup (goom_one_matrix.hip): a step takes its latency whatever else runs, so the chunks are short, longer only
+// where there are more than the chip holds at once, and again where their totals' room outgrows the input.  In us a forward pass, chunks of 8 / 16
+// / 32 / 64: 64 x 1000 x 64 176 / 133 / 145 / 202; 256 x 512 x 64 209 / 150 / 140 / 201; 4 x 8192 x 64 192 / 212 / 213 / 284; 300 x 100 (one
+// sequence) 184 / 217 / 298 / 458.  Sequences of up to 48 steps are walked in one: 40 x 32 31 us, in chunks of eight 45; 60 x 64 53, 60.
+static long long one_matrix_chunk(long long T, int d, long long batch, int dtype, bool least)
 {
     const ScanPlan p = plan_scan(T, d, d + 1, 1, batch, dtype, 0, false);
     long long L = 8;
+    if (!least && one_matrix_tiles(p.dp, T, batch, dtype)) {
+        if (T <= 48) return T;
+        if (T >= 512) L = batch * (T / 16) > 4096 ? 32 : 16;
+        while (batch * (T / L) > 65536) L *= 2;
+        return L < T ? L : T;
+    }
     while (2 * L * L < T || (L < T && batch * (T / L) > 4096)) L *= 2;
     while (L < p.L) L *= 2;
     return L < T ? L : T;
@@ -1009,17 +1028,28 @@ static long long one_matrix_chunk(long long T, int d, long long batch, int dtype
 // of d = 100 285 / 354, of d = 48 162 / 138; 249 carries of d = 100 394 / 332, of d = 8 (complex128) 173 / 84; 4095 carries of d = 24 3165 / 245.
 constexpr long long kOneMatrixCarries = 192;
 
-static AffinePlan plan_affine(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts)
+// least: in the room that a plan of one-column walks asks for.
+static AffinePlan plan_affine(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts, bool least = false)
 {
     AffinePlan ap;
     const bool one_matrix = opts && opts->chunk_len == 0 && (opts->flags & GOOM_AFFINE_TIME_INVARIANT);
-    const long long req = affine_walk_whole(d, batch, dtype, opts) ? T : one_matrix ? one_matrix_chunk(T, d, batch, dtype) : opts ? opts->chunk_len : 0;
+    const long long req = affine_walk_whole(d, batch, dtype, opts) ? T : one_matrix ? one_matrix_chunk(T, d, batch, dtype, least) : opts ? opts->chunk_len : 0;
     ap.p = plan_scan(T, d, d + 1, 1, batch, dtype, req, false);
     ap.f64 = dtype == GOOM_C64 && (d == 16 || d == 32) && ap.p.dp == d && ap.p.C > 1;
     ap.h0_bytes = 0;
     if (ap.f64) {
         ap.p = plan_scan(T, d, d + 1, 1, batch, dtype, req, false, GOOM_C128);
         ap.h0_bytes = align_up((size_t)batch * d * 16, 256);
+    }
+    if (one_matrix && !least && ap.p.S) { // groups of a power of two: their product is then squarings alone
+        ScanPlan &p = ap.p;
+        long long S = 16;
+        while (S < p.S) S *= 2;
+        p.S = S;
+        p.G = (p.nt + S - 1) / S;
+        p.gtot_bytes = (size_t)batch * p.G * p.tot.stride;
+        p.gcar_bytes = (size_t)batch * p.G * p.car.stride;
+        p.car_bytes = (size_t)batch * p.G * (S + 1) * p.car.stride;
     }
     return ap;
 }
@@ -1077,9 +1107,13 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
     if (d > GOOM_MAX_DIM) return fail(ctx, GOOM_EUNSUPPORTED, "the recurrence with bias needs d <= %d", GOOM_MAX_DIM);
     if (!aligned(bias, 16) || (h0 && !aligned(h0, 16))) return fail(ctx, GOOM_EINVAL, "complex data must be 16-byte aligned");
     if (logscale && !aligned(logscale, comp_bytes(dtype))) return fail(ctx, GOOM_EINVAL, "misaligned data pointer");
-    const AffinePlan ap = plan_affine(T, d, batch, dtype, opts);
+    AffinePlan ap = plan_affine(T, d, batch, dtype, opts);
+    auto needed = [&] {
+        return want_scaled ? align_up(ap.total(), 256) + (affine_scaled_needs_no_states(ap.p, d, dtype) ? 0 : affine_states_bytes(T, d, batch, dtype)) : ap.total();
+    };
+    if (ti && needed() > ws_bytes) ap = plan_affine(T, d, batch, dtype, opts, true);
+    const size_t need = needed();
     ScanPlan p = ap.p;
-    const size_t need = want_scaled ? align_up(ap.total(), 256) + (affine_scaled_needs_no_states(p, d, dtype) ? 0 : affine_states_bytes(T, d, batch, dtype)) : ap.total();
     if (int s = check_workspace(ctx, ws, ws_bytes, need)) return s;
     if (int s = need_ctx(ctx)) return s;
     if (affine_sequential_applies(T, d, batch, dtype, opts) && !io_shift && !adjoint_shift)
@@ -1130,22 +1164,24 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
     // are one power again, in the first group's slot.
     if (ti && p.nt <= kOneMatrixCarries) p.S = p.G = 0;
     const unsigned char *prepared = ti ? totals + (p.C - 1) * p.tot.stride : nullptr;
+    const bool tiles = ti && one_matrix_tiles(p.dp, T, batch, dtype);
     auto with_prepared = [&](ChainLaunch &l) {
-        // (float d = 16, 32 and 64 have a walk of one wave a chain that converts the matrix itself: more chains at once, and faster where
-        // many run; 64 x 1000 x 64: 63 us a pass against 74)
-        if (dtype == GOOM_C64 && (d == 16 || d == 32 || d == 64)) return;
+        if (!tiles && dtype == GOOM_C64 && (d == 16 || d == 32)) return; // (their walk of one wave a chain converts the matrix itself)
         l.left_prepared = prepared;
         l.prepared_stride = (long long)p.C * p.tot.stride;
         l.prepared_cols = p.tot.cols_padded;
         l.prepared_f64 = f64 || dtype == GOOM_C128;
     };
     if (ti) {
+        int squarings = 0; // from a chunk's product to a group's, where the group is a power of two
+        while ((1LL << squarings) < p.S) ++squarings;
+        const bool onward = p.S && (1LL << squarings) == p.S;
+        const long long group_stride = (long long)p.G * p.tot.stride;
         if (int s = goom_chain::launch_matrix_power(ctx, A, d, batch, dtype, f64, p.dp, p.L, totals, totals + (p.C - 1) * p.tot.stride,
-                                                    (long long)p.C * p.tot.stride, p.tot.cols_padded))
+                                                    (long long)p.C * p.tot.stride, squarings, onward ? gtot : nullptr, group_stride, p.tot.cols_padded))
             return s;
-        if (p.S)
-            if (int s = goom_chain::launch_matrix_power(ctx, A, d, batch, dtype, f64, p.dp, p.L * p.S, gtot, nullptr, (long long)p.G * p.tot.stride,
-                                                        p.tot.cols_padded))
+        if (p.S && !onward)
+            if (int s = goom_chain::launch_matrix_power(ctx, A, d, batch, dtype, f64, p.dp, p.L * p.S, gtot, nullptr, group_stride, 0, nullptr, 0, p.tot.cols_padded))
                 return s;
         ChainLaunch w = base;
         w.m = 1;
@@ -1159,7 +1195,7 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         w.fact_f64 = f64;
         with_prepared(w);
         w.label = "affine_phase1_chunk_vectors";
-        if (int s = launch_chain(ctx, w)) return s;
+        if (int s = tiles ? goom_chain::launch_one_matrix_walk(ctx, w, p.dp) : launch_chain(ctx, w)) return s;
     } else if (!f64 && !(dtype == GOOM_C64 && d == 64)) {
         // Phase 1 in two passes: the products A* by the chain kernels of plain chains, the vectors b* by a walk of every chunk from
         // zero.  The second read costs less than the bias wave did: with nine waves the general kernel has no registers left at d > 64
@@ -1241,7 +1277,7 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
         l.fact_f64 = f64;
         if (ti) with_prepared(l);
         l.label = "affine_phase3_outputs";
-        return launch_chain(ctx, l);
+        return tiles ? goom_chain::launch_one_matrix_walk(ctx, l, p.dp) : launch_chain(ctx, l);
     }
 }
 
@@ -1274,7 +1310,7 @@ struct AffineBackwardPlan {
     size_t total() const { return at_bytes + 2 * vec_bytes + scan_bytes + uv_bytes + partial_bytes; }
 };
 
-static AffineBackwardPlan plan_affine_backward(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts)
+static AffineBackwardPlan plan_affine_backward(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts, bool least = false)
 {
     AffineBackwardPlan p;
     const size_t cb = 2 * comp_bytes(dtype);
@@ -1290,7 +1326,7 @@ static AffineBackwardPlan plan_affine_backward(long long T, int d, long long bat
         p.direct = false;
         p.at_bytes = align_up((size_t)batch * d * d * cb, 256) + align_up((size_t)batch * (size_t)T * sizeof(float), 256);
         p.vec_bytes = align_up((size_t)batch * (size_t)T * d * cb, 256);
-        p.scan_bytes = align_up(goom_affine_scan_workspace_bytes(T, d, batch, dtype, &inv), 256);
+        p.scan_bytes = align_up(plan_affine(T, d, batch, dtype, &inv, least).total(), 256);
     } else {
         // the transposed, reversed and rescaled copy of A, or only the shifts of its log-magnitudes, one per step
         p.at_bytes = p.direct ? align_up((size_t)batch * (size_t)T * sizeof(float), 256) : align_up((size_t)batch * (size_t)T * d * d * cb, 256);
@@ -1331,7 +1367,8 @@ int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, co
     const size_t rb = comp_bytes(dtype);
     if (!aligned(grad_H, rb) || !aligned(grad_A, rb) || (grad_bias && !aligned(grad_bias, rb)) || (grad_h0 && !aligned(grad_h0, rb)))
         return fail(ctx, GOOM_EINVAL, "misaligned data pointer");
-    const AffineBackwardPlan p = plan_affine_backward(T, d, batch, dtype, opts);
+    AffineBackwardPlan p = plan_affine_backward(T, d, batch, dtype, opts);
+    if (p.one_matrix && p.total() > ws_bytes) p = plan_affine_backward(T, d, batch, dtype, opts, true);
     if (int s = check_workspace(ctx, ws, ws_bytes, p.total())) return s;
     if (int s = need_ctx(ctx)) return s;
     unsigned char *w = static_cast<unsigned char *>(ws);

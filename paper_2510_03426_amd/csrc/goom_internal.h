@@ -236,7 +236,10 @@ int launch_affine_seq_adjoint(goom_ctx *ctx, const void *A, const void *bias, co
 // A^exponent of one matrix per batch item, factored (component double if fact_f64 or GOOM_C128, else float; consecutive items `stride`
 // bytes apart), and, if prepared is given, the converted matrix for the vector chains (goom_power.hip)
 int launch_matrix_power(goom_ctx *ctx, const void *A, int d, long long batch, int dtype, int fact_f64, int dp, long long exponent, void *power, void *prepared,
-                        long long stride, int fact_cols);
+                        long long stride, int squarings, void *group, long long group_stride, int fact_cols);
+// the walks of the recurrence's chunks over one matrix, converted beforehand (goom_one_matrix.hip)
+bool one_matrix_walk_applies(int dp, int dtype);
+int launch_one_matrix_walk(goom_ctx *ctx, const goom::ChainLaunch &l, int dp);
 // adjoint of the recurrence and its gradients, every size and type (goom_vec_adjoint.hip)
 size_t adjoint_vec_stride(int dp, int dtype);
 int launch_affine_adjoint(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *G, void *gA, void *gb, void *gh0,

@@ -1336,8 +1336,8 @@ static AffineBackwardPlan plan_affine_backward(long long T, int d, long long bat
     p.nsplit = 1;
     p.uv_bytes = p.partial_bytes = 0;
     if (p.one_matrix) {
-        // several thousand workgroups (each step's loads depend on one another: many waves in flight hide them), at least 64 steps each
-        long long want = (8192 + batch - 1) / batch, most = (T + 63) / 64;
+        // two workgroups a compute unit, at least 64 steps each: every one writes a matrix of sums
+        long long want = (512 + batch - 1) / batch, most = (T + 63) / 64;
         p.nsplit = (int)(want < 1 ? 1 : want > most ? most : want);
         const int dp = d <= 16 ? 16 : d <= 32 ? 32 : d <= 64 ? 64 : 128;
         p.uv_bytes = align_up((size_t)batch * 2 * d * sizeof(double), 256); // u and v of step 0, for the initial state's gradient

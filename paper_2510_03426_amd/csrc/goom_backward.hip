@@ -17,7 +17,7 @@
 // nearest the largest log-magnitude of h_t: lamhat_t = G_t / (h_t e^(-c_t)) + (e^(c_t - c_{t+1}) A_{t+1}^T) lamhat_{t+1},
 // whose operands all have log-magnitudes of ordinary size (h'_t - c_t is exact in the component type; the matrices
 // move by the whole number c_t - c_{t+1}).  The shift is undone, in double, where the gradients are formed.
-#include "goom_internal.h"
+#include "goom_vec.h"
 
 namespace {
 
@@ -230,10 +230,29 @@ template <typename R> __global__ __launch_bounds__(128) void bwd_h0_kernel(const
 
 // One matrix for all steps: its gradient is A[i, j] sum_t lam_t[i] h_{t-1}[j].  partial[b, q] = sum over the steps of span q of
 // u_t v_t^T, DP x DP doubles (rows and columns beyond d are zero), with u_t[i] = lam_t[i] e^r and v_t[j] = h_{t-1}[j] e^(-r), r the
-// largest log-magnitude of h_{t-1} (|v| <= 1; u is of the size of the gradient's terms).  Eight steps at a time: each of the four
-// waves forms u and v of two steps in LDS (side by side in its two halves when d <= 32) (and writes those steps' bias gradients lam_t[i] b_t[i]), then every thread adds the
-// eight products to its DP * DP / 256 neighbouring entries of one row.  u and v of step 0 are kept for the initial state's gradient.
-constexpr int kOuterSteps = 8;
+// largest log-magnitude of h_{t-1} (|v| <= 1; u is of the size of the gradient's terms).  u and v of step 0 are kept for the initial state's
+// gradient.
+//
+// Sixteen steps at a time.  Each of the four waves forms u and v of four of them in LDS (side by side where DP <= 32) and writes those steps'
+// bias gradients lam_t[i] b_t[i]; their operands were loaded a turn before.  The sum over the sixteen steps is then a matrix product on the double
+// matrix instruction, 16 x 16 x 4: a wave owns a row of tiles and reads five doubles a lane for every four steps of DP = 64.  As a sum in
+// registers, sixteen neighbouring entries a thread, each step read sixteen doubles a lane, and the 64 x 1000 steps of d = 64 took 75 us with 64
+// steps a workgroup, now 38 with 125 (and the sums over workgroups 14, now 8); bound by the loads of 115 MB and the conversions on them.
+constexpr int kOuterSteps = 16;
+
+typedef double outer_d4 __attribute__((ext_vector_type(4)));
+
+// the largest of a group of lanes (16, 32 or 64 of them; none of the values NaN)
+template <typename R, int GROUP> __device__ inline R group_max(R x)
+{
+    x = goom_chain::max16(x);
+    if (GROUP == 64) return goom_chain::Comp<R>::xor16_32_max(x);
+    if (GROUP == 32) {
+        const R o = __shfl_xor(x, 16, 64);
+        x = o > x ? o : x;
+    }
+    return x;
+}
 
 template <typename R, int DP> __global__ __launch_bounds__(256) void bwd_outer_kernel(const typename C2<R>::type *__restrict__ bias,
                                                                                      const typename C2<R>::type *__restrict__ h0,
@@ -243,82 +262,120 @@ template <typename R, int DP> __global__ __launch_bounds__(256) void bwd_outer_k
                                                                                      int nsplit)
 {
     typedef typename C2<R>::type c2;
-    constexpr int EPT = DP * DP / 256;
-    constexpr int GROUP = DP <= 32 ? 32 : 64; // lanes that serve one step: short vectors share a wave two by two
-    constexpr int SPW = 64 / GROUP;
-    __shared__ double u[kOuterSteps][DP], v[kOuterSteps][DP];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane % GROUP;
+    constexpr int GROUP = DP < 64 ? DP : 64; // lanes that serve one step
+    constexpr int NE = DP / GROUP;           // entries a lane
+    constexpr int SPW = 64 / GROUP;          // steps of a wave at once
+    constexpr int ROUNDS = kOuterSteps / 4 / SPW;
+    constexpr int NT = DP / 16;              // tiles in a row
+    constexpr int TPW = NT >= 4 ? NT / 4 : 1; // rows of tiles a wave
+    constexpr int LD = DP + 2;
+    __shared__ double u[kOuterSteps][LD], v[kOuterSteps][LD];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), sub = lane % GROUP;
+    const int g = lane >> 4, c = lane & 15;
     const long long b = blockIdx.x / nsplit;
     const int q = (int)(blockIdx.x - b * nsplit);
     const long long per = (T + nsplit - 1) / nsplit, t0 = q * per, t1 = t0 + per < T ? t0 + per : T;
-    const int e0 = threadIdx.x * EPT, row = e0 / DP, j0 = e0 - row * DP;
-    const double ninf = -__builtin_huge_val();
-    double acc[EPT];
+    const R ninf = sizeof(R) == 4 ? (R)-__builtin_huge_valf() : (R)-__builtin_huge_val();
+    const c2 none = {ninf, (R)0};
+
+    struct Operands {
+        c2 h[NE], p[NE], l[NE], b[NE];
+    };
+    Operands ring[ROUNDS];
+    auto load = [&](long long tb, int round, Operands &o) {
+        const long long t = tb + 4 * wave + round * SPW + lane / GROUP;
+        const bool in = t < t1;
+        const size_t at = (size_t)(b * T + (in ? t : t0)) * d;
+        const c2 *prev = t > 0 ? H + at - d : h0 ? h0 + (size_t)b * d : nullptr;
 #pragma unroll
-    for (int k = 0; k < EPT; ++k) acc[k] = 0.0;
-    for (long long tb = t0; tb < t1; tb += kOuterSteps) {
-        for (int kb0 = wave * SPW; kb0 < kOuterSteps; kb0 += 4 * SPW) {
-            const int kb = kb0 + lane / GROUP;
-            const long long t = tb + kb;
-            const bool in = t < t1; // the same in all lanes of a group
-            // c_t: the whole number nearest the largest log-magnitude of h_t; r: the largest log-magnitude of h_{t-1}
-            double top = ninf, r = ninf;
-            const c2 *prev = !in ? nullptr : t > 0 ? H + (size_t)(b * T + t - 1) * d : h0 ? h0 + (size_t)b * d : nullptr;
-            for (int i = sub; i < d && in; i += GROUP) {
-                const double hv = (double)H[(size_t)(b * T + t) * d + i].x;
-                top = hv > top ? hv : top;
-                if (prev) {
-                    const double pv = (double)prev[i].x;
-                    r = pv > r ? pv : r;
-                }
-            }
-            for (int sft = GROUP / 2; sft > 0; sft >>= 1) {
-                const double o1 = __shfl_xor(top, sft, 64), o2 = __shfl_xor(r, sft, 64);
-                top = o1 > top ? o1 : top;
-                r = o2 > r ? o2 : r;
-            }
-            const double ct = (top > ninf && top < -ninf) ? __builtin_rint(top) : 0.0;
-            const bool any = r > ninf && r < -ninf;
-            for (int i = sub; i < DP; i += GROUP) {
-                double uu = 0.0, vv = 0.0;
-                if (in && i < d) {
-                    const c2 l = mu[(size_t)(b * T + (T - 1 - t)) * d + i];
-                    const double lre = (double)l.x - ct; // log-magnitude of lam_t[i]; -inf stays -inf
-                    const bool lneg = odd_phase<R>(l.y);
-                    if (any && lre > ninf) uu = exp_for<R>(lre + r); // (float GOOMs: the hardware exponential of the small double sum)
-                    if (lneg) uu = -uu;
-                    if (prev) {
-                        const c2 p = prev[i];
-                        if (any && (double)p.x > ninf) vv = exp_for<R>((double)p.x - r);
-                        if (odd_phase<R>(p.y)) vv = -vv;
-                    }
-                    if (gb) {
-                        const c2 bb = bias[(size_t)(b * T + t) * d + i];
-                        const bool live = lre > ninf && (double)bb.x > ninf;
-                        const double g = live ? exp_for<R>(lre + (double)bb.x) : 0.0;
-                        gb[(size_t)(b * T + t) * d + i] = (R)(lneg != odd_phase<R>(bb.y) ? -g : g);
-                    }
-                    if (t == 0) {
-                        uv0[((size_t)b * 2) * d + i] = uu;
-                        uv0[((size_t)b * 2 + 1) * d + i] = vv;
-                    }
-                }
-                u[kb][i] = uu;
-                v[kb][i] = vv;
+        for (int e = 0; e < NE; ++e) {
+            const int i = sub + GROUP * e;
+            const bool live = in && i < d;
+            o.h[e] = o.p[e] = o.l[e] = o.b[e] = none;
+            if (live) {
+                o.h[e] = H[at + i];
+                o.l[e] = mu[(size_t)(b * T + (T - 1 - t)) * d + i];
+                if (prev) o.p[e] = prev[i];
+                if (gb) o.b[e] = bias[at + i];
             }
         }
+    };
+    auto form = [&](long long tb, int round, const Operands &o) {
+        const int kb = 4 * wave + round * SPW + lane / GROUP;
+        const long long t = tb + kb;
+        // c_t: the whole number nearest the largest log-magnitude of h_t; r: the largest log-magnitude of h_{t-1}
+        R top = ninf, big = ninf;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            top = o.h[e].x > top ? o.h[e].x : top;
+            big = o.p[e].x > big ? o.p[e].x : big;
+        }
+        top = group_max<R, GROUP>(top);
+        big = group_max<R, GROUP>(big);
+        const double ct = (top > ninf && top < -ninf) ? __builtin_rint((double)top) : 0.0;
+        const double r = (double)big;
+        const bool any = big > ninf && big < -ninf;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int i = sub + GROUP * e;
+            const double lre = (double)o.l[e].x - ct; // log-magnitude of lam_t[i]; -inf stays -inf
+            const bool lneg = odd_phase<R>(o.l[e].y);
+            double uu = (any && lre > (double)ninf) ? exp_for<R>(lre + r) : 0.0; // (float GOOMs: the hardware exponential of the small double sum)
+            double vv = (any && o.p[e].x > ninf) ? exp_for<R>((double)o.p[e].x - r) : 0.0;
+            uu = lneg ? -uu : uu;
+            vv = odd_phase<R>(o.p[e].y) ? -vv : vv;
+            if (gb && t < t1 && i < d) {
+                const bool live = lre > (double)ninf && o.b[e].x > ninf;
+                const double w = live ? exp_for<R>(lre + (double)o.b[e].x) : 0.0;
+                gb[(size_t)(b * T + t) * d + i] = (R)(lneg != odd_phase<R>(o.b[e].y) ? -w : w);
+            }
+            if (t == 0 && i < d) {
+                uv0[((size_t)b * 2) * d + i] = uu;
+                uv0[((size_t)b * 2 + 1) * d + i] = vv;
+            }
+            u[kb][i] = uu;
+            v[kb][i] = vv;
+        }
+    };
+
+    outer_d4 acc[TPW][NT];
+#pragma unroll
+    for (int w = 0; w < TPW; ++w)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[w][n] = outer_d4{0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) load(t0, k, ring[k]);
+    for (long long tb = t0; tb < t1; tb += kOuterSteps) {
+#pragma unroll
+        for (int k = 0; k < ROUNDS; ++k) {
+            form(tb, k, ring[k]);
+            load(tb + kOuterSteps, k, ring[k]);
+        }
         __syncthreads();
+        if (wave * TPW < NT) {
 #pragma unroll
-        for (int kb = 0; kb < kOuterSteps; ++kb) {
-            const double ui = u[kb][row];
+            for (int k = 0; k < kOuterSteps; k += 4) {
+                double y[NT];
 #pragma unroll
-            for (int k = 0; k < EPT; ++k) acc[k] += ui * v[kb][j0 + k];
+                for (int n = 0; n < NT; ++n) y[n] = v[k + g][16 * n + c];
+#pragma unroll
+                for (int w = 0; w < TPW; ++w) {
+                    const double x = u[k + g][16 * (wave * TPW + w) + c];
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) acc[w][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y[n], acc[w][n], 0, 0, 0);
+                }
+            }
         }
         __syncthreads();
     }
-    double *out = partial + (size_t)blockIdx.x * DP * DP + e0;
+    if (wave * TPW >= NT) return;
+    double *out = partial + (size_t)blockIdx.x * DP * DP;
 #pragma unroll
-    for (int k = 0; k < EPT; ++k) out[k] = acc[k];
+    for (int w = 0; w < TPW; ++w)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) out[(size_t)(16 * (wave * TPW + w) + 4 * x + g) * DP + 16 * n + c] = acc[w][n][x];
 }
 
 // gA[b, i, j] = A[b, i, j] sum_q partial[b, q, i, j] (in the order of q);  gh0[b, j] = v_0[j] sum_i u_0[i] A[b, i, j]  (uv0[b] = u_0, v_0)
@@ -328,7 +385,7 @@ template <typename R> __global__ __launch_bounds__(256) void bwd_outer_finish_ke
 {
     typedef typename C2<R>::type c2;
     // A workgroup an item summed the spans and took an exponential and a logarithm in double for every entry, and for every entry once more for
-    // gh0: 104 us for 64 items of d = 64 (16 spans).  Now 256 entries a workgroup and gh0 in one of its own: 15 us.
+    // gh0: 104 us for 64 items of d = 64 (16 spans).  Now 256 entries a workgroup, and gh0 in workgroups of its own.
     const long long b = blockIdx.x;
     const double ninf = -__builtin_huge_val();
     const int e = (int)blockIdx.y * 256 + threadIdx.x;
@@ -343,22 +400,25 @@ template <typename R> __global__ __launch_bounds__(256) void bwd_outer_finish_ke
         gA[(size_t)b * d * d + e] = (R)((acc < 0.0) != odd_phase<R>(a.y) ? -mag : mag);
         return;
     }
-    // the last workgroup of the item, where there is one: gh0, four threads a column
-    __shared__ double part[4][64];
-    const int c = threadIdx.x & 63, p = threadIdx.x >> 6;
-    for (int j0 = 0; j0 < d; j0 += 64) {
-        const int j = j0 + c;
-        double acc = 0.0;
-        for (int i = p; i < d && j < d; i += 4) {
-            const c2 a = A[(size_t)b * d * d + (size_t)i * d + j];
-            const double ui = uv0[((size_t)b * 2) * d + i];
-            const double mag = (ui != 0.0 && (double)a.x > ninf) ? exp((double)a.x + log(__builtin_fabs(ui))) : 0.0;
-            acc += (ui < 0.0) != odd_phase<R>(a.y) ? -mag : mag;
-        }
-        part[p][c] = acc;
-        __syncthreads();
-        if (p == 0 && j < d) gh0[(size_t)b * d + j] = (R)(((part[0][c] + part[1][c]) + (part[2][c] + part[3][c])) * uv0[((size_t)b * 2 + 1) * d + j]);
-        __syncthreads();
+    // the item's workgroups after those, where there are any: gh0, sixteen columns each, sixteen threads a column (four threads a column in one
+    // workgroup took sixteen exponentials and logarithms one after the other, and the launch 14 us for d = 64)
+    __shared__ double part[16][17];
+    const int c = threadIdx.x & 15, p = threadIdx.x >> 4;
+    const int j = ((int)blockIdx.y - (d * d + 255) / 256) * 16 + c;
+    double acc = 0.0;
+    for (int i = p; i < d && j < d; i += 16) {
+        const c2 a = A[(size_t)b * d * d + (size_t)i * d + j];
+        const double ui = uv0[((size_t)b * 2) * d + i];
+        const double mag = (ui != 0.0 && (double)a.x > ninf) ? exp((double)a.x + log(__builtin_fabs(ui))) : 0.0;
+        acc += (ui < 0.0) != odd_phase<R>(a.y) ? -mag : mag;
+    }
+    part[p][c] = acc;
+    __syncthreads();
+    if (p == 0 && j < d) {
+        double sum = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) sum += part[k][c];
+        gh0[(size_t)b * d + j] = (R)(sum * uv0[((size_t)b * 2 + 1) * d + j]);
     }
 }
 
@@ -495,7 +555,7 @@ template <typename R> static int bwd_grad_ti_t(goom_ctx *ctx, const void *A, con
     else if (dp == 32) hipLaunchKernelGGL((bwd_outer_kernel<R, 32>), grid, dim3(256), 0, ctx->stream, bp, hp, Hp, mp, gbp, partial, uv0, T, d, nsplit);
     else if (dp == 64) hipLaunchKernelGGL((bwd_outer_kernel<R, 64>), grid, dim3(256), 0, ctx->stream, bp, hp, Hp, mp, gbp, partial, uv0, T, d, nsplit);
     else hipLaunchKernelGGL((bwd_outer_kernel<R, 128>), grid, dim3(256), 0, ctx->stream, bp, hp, Hp, mp, gbp, partial, uv0, T, d, nsplit);
-    hipLaunchKernelGGL(bwd_outer_finish_kernel<R>, dim3((unsigned)batch, (unsigned)((d * d + 255) / 256 + (gh0 ? 1 : 0))), dim3(256), 0, ctx->stream, static_cast<const c2 *>(A), partial, uv0, static_cast<R *>(gA),
+    hipLaunchKernelGGL(bwd_outer_finish_kernel<R>, dim3((unsigned)batch, (unsigned)((d * d + 255) / 256 + (gh0 ? (d + 15) / 16 : 0))), dim3(256), 0, ctx->stream, static_cast<const c2 *>(A), partial, uv0, static_cast<R *>(gA),
                        static_cast<R *>(gh0), d, dp, nsplit);
     prof_end(ctx);
     return check_hip(ctx, hipGetLastError(), "launch bwd_outer_kernel");

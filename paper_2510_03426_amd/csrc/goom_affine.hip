@@ -682,22 +682,18 @@ template <int DP, bool TI, bool ADJ = false, bool IOS = false> int launch_walk(g
 
 } // namespace
 
-// chunk products with the bias wave: the factor fills its tile, the state is [A* | b*] with the
+// chunk products with the bias column: the factor fills its tile, the state is [A* | b*] with the
 // bias in column d, starting from the identity, and only the chunk's factored product is wanted
 bool affine_chunk_applies(const ChainArgs &args, int dp)
 {
-    return (dp == 16 || dp == 32 || dp == 64) && args.n == dp && args.d == dp && args.m == dp + 1 && args.bias_mode == 1 &&
+    return dp == 64 && args.n == dp && args.d == dp && args.m == dp + 1 && args.bias_mode == 1 &&
            args.bias_col == dp && args.init_mode == 0 && args.out_goom == nullptr && args.out_fact_steps == nullptr &&
            args.out_fact_final != nullptr && args.fact_cols == dp + 16 && args.io_shift == nullptr;
 }
 
-int dispatch_affine_chunk(goom_ctx *ctx, const ChainArgs &args, int dp, long long grid, const char *label)
+int dispatch_affine_chunk(goom_ctx *ctx, const ChainArgs &args, int, long long grid, const char *label)
 {
-    switch (dp) {
-    case 16: return launch_fast<16, 1, true>(ctx, args, grid, label);
-    case 32: return launch_fast<32, 2, true>(ctx, args, grid, label);
-    default: return launch_fast<64, 4, true>(ctx, args, grid, label);
-    }
+    return launch_fast<64, 4, true>(ctx, args, grid, label);
 }
 
 // the walk: a single state column that receives the bias, started from factored carries (or from

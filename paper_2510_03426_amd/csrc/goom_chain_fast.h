@@ -3,10 +3,12 @@
 // also, with the padding left out of the product, square sizes in between that are multiples of four.
 // This is the kernel the long scans spend their time in (phase 1 and phase 3 of the
 // three-phase scan; paper Section 4.1), and LMME on such shapes (Section 3.2).
-// With BIAS one more wave carries column d of the augmented state [A* | b*] of a linear
-// recurrence with bias (Section 4.3): it takes no part in converting the factor; its column is
-// a matrix-vector product of the same LDS tile on the vector ALU (one row per lane, or per
-// two or four lanes), to which it adds the step's bias vector.
+// With BIAS the state has column d of the augmented [A* | b*] of a linear recurrence with bias
+// (Section 4.3) besides.  Its product is a matrix-vector product of the same LDS tile on the vector
+// ALU, to which the step's bias is added; every wave takes sixteen of its rows, four lanes a row, on
+// a power of two of the wave's own, so that nothing but the column itself and those exponents passes
+// between the waves, at the step's one barrier.  (A fifth wave for the column alone held up the
+// barrier, and its SIMD's other waves: 16 x 4096 matrices of 64 x 64 720 us, 510 so; the whole pass 1139, 927.)
 //
 // On this chip the float matrix instructions run at the rate of the vector ALU and do
 // not overlap with it, so a step costs (matrix cycles) + 4 x (vector instructions) and
@@ -82,11 +84,11 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
 {
     typedef Comp<float> C;
     static_assert(!RAG || (!BIAS && !REAL && KD <= DP / 16), "ragged sizes: GOOM factors, no bias column");
+    static_assert(!BIAS || (DP == 64 && NW == 4 && !REAL), "a bias column: sixteen rows to each of four waves");
     constexpr int KT = KD;
     constexpr int LDA = DP + 4;
-    constexpr int NWT = NW + (BIAS ? 1 : 0); // waves, one per 16-column slab of the state
-    constexpr int M = 16 * NWT;  // state columns
-    constexpr int NT = NW * 64;  // threads that convert the factor
+    constexpr int M = 16 * NW;   // state columns, a wave per sixteen
+    constexpr int NT = NW * 64;
     constexpr int LPR = DP / 4;  // lanes per row of the factor
     constexpr int NITEMS = DP * LPR;
     constexpr int Q = NITEMS / NT; // items per thread
@@ -104,7 +106,9 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
     auto tile_of = [&](int b) { return reinterpret_cast<float *>(smem + (size_t)b * kBufBytes); };
     auto nsh_of = [&](int b) { return reinterpret_cast<float *>(smem + (size_t)b * kBufBytes + kTileBytes); };
     double *wave_red = reinterpret_cast<double *>(smem + 2 * kBufBytes);
-    float *wvec = reinterpret_cast<float *>(smem + 2 * kBufBytes + 128); // the bias wave's column (BIAS only)
+    // (BIAS) the bias column, for the step in hand and the next: mantissas, and an exponent for every sixteen rows
+    double *wexp = reinterpret_cast<double *>(smem + 2 * kBufBytes + 128); // [2][4]
+    float *wvec = reinterpret_cast<float *>(wexp + 8);                     // [2][DP]
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -113,8 +117,6 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
     const int c = lane & 15;
     const int col = wave * 16 + c;
     const int c4 = 4 * (tid % LPR); // first of this lane's four factor columns
-    const bool converter = !BIAS || wave < NW;
-    const bool bias_wave = BIAS && wave == NW;
     const int dd = RAG ? a.d : DP;        // size of the matrices in memory
     // this wave owns sixteen columns of the state (KD may exceed ceil(d / 16) when a wider state elsewhere in
     // the same scan has fixed the tile size; the factored product stored at the end has ceil(d / 16) slabs)
@@ -122,11 +124,8 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
     const bool owner = !RAG || (RAG == 2 ? 16 * wave < mm : (wave < KD && 16 * wave < dd));
     // RAG = 2: first of the four columns this lane loads, and how far beyond them its own four begin
     const int cl = c4 < dd - 4 ? c4 : dd - 4, cmove = RAG == 2 && c4 < dd ? c4 - cl : 0;
-    // bias wave: lane -> row and part of the contraction index
-    constexpr int LPRB = DP >= 64 ? 1 : 64 / DP; // lanes per row
-    constexpr int CPLB = DP / LPRB;              // contraction indices per lane
-    const int brow = lane / LPRB;
-    const int bc0 = CPLB * (lane % LPRB);
+    // bias column: this lane's row and the sixteen inner indices of it (those that wave `bpart` has written)
+    const int brow = 16 * wave + (lane >> 2), bpart = lane & 3;
 
     const long long chain = blockIdx.x;
     const long long item = chain / a.chunks_launched;
@@ -324,19 +323,23 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
     if (RAG) {
         for (int i = 16 * KD + tid; i < DP; i += NT) nsh_of(0)[i] = nsh_of(1)[i] = -1.0e30f;
     }
-    if (len > 0 && converter) {
+    if (len > 0) {
         load_items(0, pre);
         convert_items(pre, 0, nullptr);
         if (len > 1) load_items(1, pre);
     }
-    // bias wave: entry brow of a step's bias vector, and its column of the state (also kept in LDS,
-    // where the lanes read the entries they contract over); the column starts at zero
+    // entry brow of a step's bias vector; the column starts at zero
     float2 bpre = {0.0f, 0.0f};
     auto load_bias = [&](long long t) {
         bpre = *reinterpret_cast<const float2 *>(a.bias + ((size_t)(item * a.steps + t0 + t) * DP + brow) * 8);
     };
-    if (BIAS && bias_wave && lane < DP) wvec[lane] = 0.0f;
-    if (BIAS && bias_wave && len > 0) load_bias(0);
+    float accb = 0.0f;
+    double becol = kNegBig; // the wave's rows of the column are accb 2^(n_i + becol); kNegBig: all of them zero
+    if (BIAS) {
+        if (bpart == 0) wvec[brow] = 0.0f;
+        if (lane == 0) wexp[wave] = kNegBig;
+        if (len > 0) load_bias(0);
+    }
     __syncthreads();
 
     for (long long t = 0; t < len; ++t) {
@@ -347,19 +350,7 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
 
         // ------------------------------------------------------------ product, and next factor beside it
         f4 acc[KT];
-        float accb = 0.0f;
-        if (BIAS && bias_wave) {
-            // column d of the product: row brow of the tile times the column, on the vector ALU
-#pragma unroll
-            for (int k = 0; k < CPLB / 4; ++k) {
-                const f4 av = *reinterpret_cast<const f4 *>(&tile[brow * LDA + bc0 + 4 * k]);
-                const f4 wv = *reinterpret_cast<const f4 *>(&wvec[bc0 + 4 * k]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) accb = __builtin_fmaf(av[e], wv[e], accb);
-            }
-            if (LPRB >= 2) accb = add_dpp<0xB1>(accb);
-            if (LPRB >= 4) accb = add_dpp<0x4E>(accb);
-        } else if (owner) {
+        if (owner) {
 #pragma unroll
             for (int mt = 0; mt < KT; ++mt) acc[mt] = f4{0, 0, 0, 0};
 #pragma unroll
@@ -374,42 +365,79 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
                     for (int mt = 0; mt < KT; ++mt) acc[mt] = C::mfma(av[mt][v], st[kt][v], acc[mt]);
             }
         }
+        if (BIAS) {
+            // row brow of the tile times the column: sixteen terms a lane on their writer's power of two, then the row's four lanes
+            // on the largest
+            const double *we = wexp + 4 * cur;
+            double top = we[0];
+#pragma unroll
+            for (int p = 1; p < 4; ++p) top = we[p] > top ? we[p] : top;
+            const int down = (int)Comp<double>::clamp_shift(we[bpart] - top);
+            f4 part = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const f4 av = *reinterpret_cast<const f4 *>(&tile[brow * LDA + 16 * bpart + 4 * k]);
+                const f4 wv = *reinterpret_cast<const f4 *>(&wvec[DP * cur + 16 * bpart + 4 * k]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) part[e] = __builtin_fmaf(av[e], wv[e], part[e]);
+            }
+            accb = __builtin_ldexpf((part[0] + part[1]) + (part[2] + part[3]), down);
+            accb = add_dpp<0xB1>(accb);
+            accb = add_dpp<0x4E>(accb);
+            becol = top;
+        }
         // (after the last product there is nothing to convert: a single product, as in a
         // batched LMME, would otherwise pay for its left factor twice)
-        if (converter && !last) {
+        if (!last) {
             convert_items(pre, cur ^ 1, nsh);
             load_items(t + 2 < len ? t + 2 : len - 1, pre);
         }
         float nrb = 0.0f;
-        if (BIAS && bias_wave) {
-            // b_i enters entry (i, d) of the product, which is held as accb 2^(n_i + ecol): add
-            // (+-) 2^(log2|b_i| - n_i - ecol).  Should the column have shrunk so far below the bias
-            // that this would overflow, the column is first scaled down (to nothing, if need be).
+        if (BIAS) {
+            // b_i enters entry (i, d) of the product, which is held as accb 2^(n_i + becol): add
+            // (+-) 2^(log2|b_i| - n_i - becol).  Should the wave's rows have shrunk so far below the bias
+            // that this would overflow, they are first scaled down (to nothing, if need be).
             const float kHi = 1.44269502162933349609375f;
             const float kLo = 1.925963033500011e-8f;
             nrb = nsh[brow];
             if (__builtin_amdgcn_ballot_w64(accb != 0.0f) == 0) {
-                // a zero column has no scale of its own: it takes the bias's, whatever its magnitude
+                // rows of zeros have no scale of their own: they take the bias's, whatever its magnitude
                 float m = __builtin_fmaf(bpre.x, kHi, -nrb);
                 m = C::template group_allmax<64>(m, m);
-                ecol = (m > -1.0e30f && m < 1.0e30f) ? (double)__builtin_ceilf(m) : 0.0;
+                becol = (m > -1.0e30f && m < 1.0e30f) ? (double)__builtin_ceilf(m) : 0.0;
             }
-            float x = __builtin_fmaf(bpre.x, kHi, -(nrb + (float)ecol));
+            float x = __builtin_fmaf(bpre.x, kHi, -(nrb + (float)becol));
             x = __builtin_fmaf(bpre.x, kLo, x);
             float down = 0.0f;
             if (__builtin_amdgcn_ballot_w64(x > 64.0f) != 0) {
                 const float amax = C::template group_allmax<64>(x, x);
                 down = C::max_(0.0f, __builtin_ceilf(amax) - 64.0f);
                 accb = __builtin_ldexpf(accb, -(int)C::clamp_shift(down));
-                ecol += (double)down;
+                becol += (double)down;
             }
             accb += C::apply_sign(__builtin_amdgcn_exp2f(x - down), bpre.y);
             load_bias(t + 1 < len ? t + 1 : len - 1);
+            if (!last) { // raw between steps, renormalised now and then
+                if ((t % kRenormEvery) == kRenormEvery - 1) {
+                    float cm = C::max_(-300.0f, C::exponent_of(accb));
+                    cm = C::template group_allmax<64>(cm, cm);
+                    accb = __builtin_ldexpf(accb, -(int)cm);
+                    becol += (double)cm;
+                }
+            } else { // row exponents folded in
+                float cm = C::exponent_of(accb) + nrb;
+                cm = C::template group_allmax<64>(cm, cm);
+                accb = __builtin_ldexpf(accb, (int)C::clamp_shift(nrb - cm));
+                becol += (double)cm;
+            }
+            if (__builtin_amdgcn_ballot_w64(accb != 0.0f) == 0) becol = kNegBig;
+            if (bpart == 0) wvec[DP * (cur ^ 1) + brow] = accb;
+            if (lane == 0) wexp[4 * (cur ^ 1) + wave] = becol;
         }
 
         // ------------------------------------------------------------ outputs
         // entry (i = 16 mt + 4 g + v, col) of the product is acc 2^(n_i + ecol)
-        const bool want_out = a.out_goom && (!a.out_goom_last_only || last) && !bias_wave && owner;
+        const bool want_out = a.out_goom && (!a.out_goom_last_only || last) && owner;
         if (want_out && !RAG) {
             const long long o_idx = a.out_goom_last_only ? chain_global : (item * a.steps + t0 + t);
             float *outp = reinterpret_cast<float *>(a.out_goom) + ((size_t)o_idx * DP * M + (size_t)(4 * g) * M + col) * 2;
@@ -466,24 +494,7 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
         }
 
         // ------------------------------------------------------------ state for the next step
-        if (BIAS && bias_wave) {
-            // the same bookkeeping for the one column: raw between steps, renormalised now and then,
-            // row exponents folded in at the end
-            if (!last) {
-                if ((t % kRenormEvery) == kRenormEvery - 1) {
-                    float cm = C::max_(-300.0f, C::exponent_of(accb));
-                    cm = C::template group_allmax<64>(cm, cm);
-                    accb = __builtin_ldexpf(accb, -(int)cm);
-                    ecol += (double)cm;
-                }
-            } else {
-                float cm = C::exponent_of(accb) + nrb;
-                cm = C::template group_allmax<64>(cm, cm);
-                accb = __builtin_ldexpf(accb, (int)C::clamp_shift(nrb - cm));
-                ecol += (double)cm;
-            }
-            if (lane % LPRB == 0) wvec[brow] = accb;
-        } else if (!owner) {
+        if (!owner) {
             // (no state columns)
         } else if (!last) {
             // keep the raw product; its row exponents n_i go to the next factor's columns
@@ -540,7 +551,7 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
         cm = C::xor16_32_max(cm);
         // (the bias column is not contracted over when the product serves as a left factor: it
         // keeps an exponent of its own, so a bias far above or below A* costs neither any bits)
-        double ev = (cm > 0.0f && !bias_wave && owner) ? ecol : kNegBig;
+        double ev = (cm > 0.0f && owner) ? ecol : kNegBig;
 #pragma unroll
         for (int s = 1; s < 16; s <<= 1) {
             const double o = shfl_xor_double(ev, s);
@@ -549,29 +560,35 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
         if (lane == 0) wave_red[wave] = ev;
         __syncthreads();
         double emax = kNegBig;
-        for (int w = 0; w < NWT; ++w) emax = wave_red[w] > emax ? wave_red[w] : emax;
+        for (int w = 0; w < NW; ++w) emax = wave_red[w] > emax ? wave_red[w] : emax;
         if (emax == kNegBig) emax = 0.0;
         double dsh = ecol - emax;
         dsh = dsh > -4000.0 ? dsh : -4000.0;
-        const int shift = (cm > 0.0f && !bias_wave) ? (int)dsh : 0;
-        if (BIAS && bias_wave) {
-            // column d from the lanes that own its rows; the padding columns behind it are zero
-            if (lane % LPRB == 0) mp[(size_t)brow * a.fact_cols + DP] = wvec[brow];
-            for (int idx = lane; idx < DP * 15; idx += 64) mp[(size_t)(idx / 15) * a.fact_cols + DP + 1 + idx % 15] = 0.0f;
-        } else if (owner) {
+        const int shift = cm > 0.0f ? (int)dsh : 0;
+        if (BIAS) {
+            // column d, on the largest of the waves' exponents; the padding columns behind it are zero
+            const double *we = wexp + 4 * (int)(len & 1);
+            double top = we[0];
+#pragma unroll
+            for (int p = 1; p < 4; ++p) top = we[p] > top ? we[p] : top;
+            if (bpart == 0) mp[(size_t)brow * a.fact_cols + DP] = __builtin_ldexpf(accb, (int)Comp<double>::clamp_shift(becol - top));
+            for (int idx = lane; idx < 16 * 15; idx += 64) mp[(size_t)(16 * wave + idx / 15) * a.fact_cols + DP + 1 + idx % 15] = 0.0f;
+            if (threadIdx.x < 16) ep[DP + threadIdx.x] = top > kNegBig ? top : 0.0;
+        }
+        if (owner) {
 #pragma unroll
             for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     mp[(size_t)(16 * kt + 4 * g + v) * a.fact_cols + col] = __builtin_ldexpf(st[kt][v], shift);
         }
-        if (g == 0 && owner) ep[col] = bias_wave ? ecol : emax;
+        if (g == 0 && owner) ep[col] = emax;
     }
 }
 
 // (second launch bound: waves per SIMD the register allocation has to leave room for)
 template <int DP, int NW, bool BIAS>
-__global__ __launch_bounds__((NW + (BIAS ? 1 : 0)) * 64, (DP <= 16 ? 8 : DP == 32 ? (BIAS ? 5 : 6) : DP == 64 ? (BIAS ? 3 : 4) : 2)) void chain_kernel_fast(ChainArgs a)
+__global__ __launch_bounds__(NW * 64, (DP <= 16 ? 8 : DP == 32 ? 6 : DP == 64 ? 4 : 2)) void chain_kernel_fast(ChainArgs a)
 {
     chain_body<DP, NW, BIAS, false>(a);
 }
@@ -592,7 +609,7 @@ __global__ __launch_bounds__(NW * 64, (DP == 32 ? 6 : DP == 64 ? 4 : 2)) void ch
 template <int DP, int NW, bool BIAS, bool REAL = false> int launch_fast(goom_ctx *ctx, const ChainArgs &args, long long grid, const char *label)
 {
     constexpr int LDA = DP + 4;
-    const size_t lds = 2 * ((size_t)DP * LDA * sizeof(float) + (size_t)DP * sizeof(float)) + 128 + (BIAS ? DP * sizeof(float) : 0);
+    const size_t lds = 2 * ((size_t)DP * LDA * sizeof(float) + (size_t)DP * sizeof(float)) + 128 + (BIAS ? 8 * sizeof(double) + 2 * DP * sizeof(float) : 0);
     void (*kern)(ChainArgs);
     if constexpr (REAL) kern = chain_kernel_fast_real<DP, NW>;
     else kern = chain_kernel_fast<DP, NW, BIAS>;
@@ -603,7 +620,7 @@ template <int DP, int NW, bool BIAS, bool REAL = false> int launch_fast(goom_ctx
     if (grid <= 0) return GOOM_OK;
     if (grid > 0x7fffffffLL) return goom::fail(ctx, GOOM_EUNSUPPORTED, "too many chains for one launch (%lld)", grid);
     goom::prof_begin(ctx, label);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((NW + (BIAS ? 1 : 0)) * 64), lds, ctx->stream, args);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), lds, ctx->stream, args);
     goom::prof_end(ctx);
     return goom::check_hip(ctx, hipGetLastError(), "launch chain_kernel_fast");
 }
@@ -618,7 +635,7 @@ inline bool fast_applies(const ChainArgs &args, int dp, int nw)
 }
 
 // Kernels of the linear recurrence with bias (separate translation unit): chunk products of
-// the augmented matrices with the extra bias wave, and the matrix-vector walk that produces
+// the augmented matrices, bias column included, and the matrix-vector walk that produces
 // the states from the carried vectors.
 bool affine_chunk_applies(const ChainArgs &args, int dp);
 int dispatch_affine_chunk(goom_ctx *ctx, const ChainArgs &args, int dp, long long grid, const char *label);

@@ -19,8 +19,8 @@
 //
 // Bound by instruction issue: at 64 x 64 a step's two products are 4096 cycles of matrix instructions a wave, and the conversions of
 // M, P and G and the exponents of G / P, K and the gradients some 1300 vector instructions (which do not overlap with them on this
-// chip).  64 chains of 128 complex64 64 x 64: 1759 -> 545 us against the scan of the stacked 128 x 128 factors, whose operands alone were
-// written and read as 2 GB (products 68, vectors 162, carries 30, gradients 301, 10 for three launches that find no flag); 65 536 steps in one chain 13.1 -> 5.5 ms;
+// chip).  64 chains of 128 complex64 64 x 64: 1759 -> 444 us against the scan of the stacked 128 x 128 factors, whose operands alone were
+// written and read as 2 GB (products 68, vectors 145, carries 27, gradients 265, 10 for three launches that find no flag); 65 536 steps in one chain 13.1 -> 5.5 ms;
 // 16 x 60 of 100 x 100 1476 -> 704 us; complex128, 16 x 128 of 64 x 64: 1459 -> 439 us.  Row exponents of Lam: 3 % of a step.  Loads behind a branch, which
 // the optimiser makes of any selection around one, cost threefold: hence entries that are loaded first and selected afterwards.
 #include "goom_chain_kernel.h"
@@ -128,7 +128,10 @@ template <typename R> struct RowPiece;
 template <> struct RowPiece<float> { typedef f4 type; };
 template <> struct RowPiece<double> { typedef double type __attribute__((ext_vector_type(4), aligned(16))); };
 
-template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, sizeof(R) == 4 || DP > 64 ? 2 : 1) void scan_adjoint_kernel(AdjointArgs<R> a)
+// FULL: d = m = DP, no entry to leave out.  Comparisons, selections and addresses are a seventh of a step's vector instructions then, and registers that
+// are short at 128.  Before / now: 64 x 128 of 64 x 64 499 -> 444 us, of 32 x 32 143 -> 128; 64 x 40 of 128 x 128 1268 -> 947; complex128, 16 x 30 of 128 x
+// 128 2199 -> 1572.  (Loading a step ahead instead of at its start took no more off.)
+template <typename R, int DP, int MODE, bool FULL> __global__ __launch_bounds__(DP * 4, sizeof(R) == 4 || DP > 64 ? 2 : 1) void scan_adjoint_kernel(AdjointArgs<R> a)
 {
     typedef Comp<R> N;
     typedef typename N::vec4 vec4;
@@ -136,6 +139,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
     typedef Num<R> X2;
     typedef Tiles<R, DP> TL;
     constexpr int KT = DP / 16;
+    constexpr bool EARLY = FULL && sizeof(R) == 4 && DP <= 64; // all that a step reads is loaded at its start: as far as the registers go
     extern __shared__ __align__(32) unsigned char smem[];
     R *lam = reinterpret_cast<R *>(smem);                // [DP][kLam] Lam_t's mantissas
     R *mt = TL::kOne ? lam : lam + DP * TL::kLam;        // [DP][kM] M_t, column j times 2^-mexp[j]
@@ -144,7 +148,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, c = lane & 15, col = 16 * w + c;
-    const int d = a.d, m = a.m;
+    const int d = FULL ? DP : a.d, m = FULL ? DP : a.m;
     const long long per = MODE == kVectors ? a.C - 1 : MODE == kCarries ? 1 : a.C;
     const long long b = blockIdx.x / per, chunk = MODE == kVectors ? blockIdx.x % per + 1 : MODE == kCarries ? a.C - 1 : blockIdx.x % per;
 
@@ -166,12 +170,13 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
     // and the first entry where there is none, so that no load is behind a branch.
     auto row_at = [&](int it, int v) { return 16 * it + N::row_of(g, v); };
     const int lim_m = col < m ? d : 0, lim_d = col < d ? d : 0; // rows of a d x m, of a d x d matrix that this lane's column has
+    auto inside = [](int i, int lim) { return FULL || i < lim; };
     auto opaque = [](unsigned x) {
         asm volatile("" : "+v"(x));
         return x;
     };
     auto opaque_int = [](int x) {
-        asm volatile("" : "+s"(x));
+        if (!FULL) asm volatile("" : "+s"(x));
         return x;
     };
     // both formed here, entry by entry (the scheduler otherwise puts one of them off and keeps what it is formed from)
@@ -180,7 +185,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
 
     auto vec_at = [&](long long q) { return a.vecs + (b * a.C + q) * a.vec_stride; };
     // (written and read whole, by the same lanes: what lies past the matrix is zero)
-    const bool owns = 16 * w < a.vec_cols;
+    const bool owns = FULL || 16 * w < a.vec_cols;
     auto load_vec = [&](long long q, vec4 (&V)[KT], int &ev) {
         const unsigned char *src = vec_at(q);
         const int at = owns ? col : 0;
@@ -274,13 +279,13 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                 for (int it = 0; it < KT; ++it)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        A[it][v] = reinterpret_cast<const R *>(tp)[row_at(it, v) < lim_d ? (unsigned)(row_at(it, v) * a.tot_cols + col) : 0u];
+                        A[it][v] = reinterpret_cast<const R *>(tp)[inside(row_at(it, v), lim_d) ? (unsigned)(row_at(it, v) * a.tot_cols + col) : 0u];
                 load_vec(q, V, ev);
                 __syncthreads();
 #pragma unroll
                 for (int it = 0; it < KT; ++it)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) mt[row_at(it, v) * TL::kM + col] = row_at(it, v) < lim_d ? A[it][v] : (R)0;
+                    for (int v = 0; v < 4; ++v) mt[row_at(it, v) * TL::kM + col] = inside(row_at(it, v), lim_d) ? A[it][v] : (R)0;
                 if (g == 0) mexp[col] = col < d ? (int)__builtin_fmin(__builtin_fmax(cex, -1.0e9), 1.0e9) : 0; // (past kFar: noted with the vectors)
                 __syncthreads();
                 store_vec(q); // K as it enters this chunk, in its vector's place (each lane in the places it read)
@@ -300,7 +305,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
 #pragma unroll
             for (int it = 0; it < KT; ++it)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) note((row_at(it, v) < lim_d) && !(N::abs_(tp[row_at(it, v) < lim_d ? (unsigned)(row_at(it, v) * a.tot_cols + col) : 0u]) >= Rc::kOtherLeast));
+                for (int v = 0; v < 4; ++v) note((inside(row_at(it, v), lim_d)) && !(N::abs_(tp[inside(row_at(it, v), lim_d) ? (unsigned)(row_at(it, v) * a.tot_cols + col) : 0u]) >= Rc::kOtherLeast));
         }
         if (MODE == kGradients && a.C > 1) {
             load_vec(chunk, S, e);
@@ -309,6 +314,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
         for (long long t = hi - 1; t >= lo; --t) {
             const size_t step = (size_t)(b * a.T + t);
             const bool onward = MODE != kGradients || t > lo || (chunk == 0 && a.gS0); // is K_{t-1} of any use
+            [[maybe_unused]] c2 mraw[EARLY ? KT : 1][4], praw[EARLY ? KT : 1][4]; // EARLY: M_t, and row col of P_{t-1}
             // ---- Lam = K + G / P
             {
                 const c2 *Pt = a.P + step * d * m;
@@ -317,15 +323,29 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                 R gv[KT][4];
                 int nb = kNone;
                 const unsigned first = opaque((unsigned)(N::row_of(g, 0) * m + col));
-                const int rows = (int)opaque((unsigned)lim_m), cols = opaque_int(m);
+                const int rows = FULL ? DP : (int)opaque((unsigned)lim_m), cols = opaque_int(m);
 #pragma unroll
                 for (int it = 0; it < KT; ++it)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const unsigned at = row_at(it, v) < rows ? first + (unsigned)((row_at(it, v) - N::row_of(g, 0)) * cols) : 0u;
+                        const unsigned at = inside(row_at(it, v), rows) ? first + (unsigned)((row_at(it, v) - N::row_of(g, 0)) * cols) : 0u;
                         pv[it][v] = at_byte(Pt, at * (unsigned)sizeof(c2));
                         gv[it][v] = at_byte(Gt, at * (unsigned)sizeof(R));
                     }
+                if constexpr (EARLY) {
+                    const c2 *Mt = a.M + step * DP * DP + N::row_of(g, 0) * DP + col;
+                    const c2 *prev = (t > 0 ? Pt - (size_t)DP * DP : a.S0 ? a.S0 + (size_t)b * DP * DP : Pt) + col * DP + 4 * g;
+#pragma unroll
+                    for (int it = 0; it < KT; ++it)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) mraw[it][v] = Mt[(row_at(it, v) - N::row_of(g, 0)) * DP];
+                    if (MODE == kGradients) {
+#pragma unroll
+                        for (int it = 0; it < KT; ++it)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) praw[it][v] = prev[16 * it + v];
+                    }
+                }
                 __builtin_amdgcn_sched_barrier(0); // (all loads of a matrix in flight at once)
 #pragma unroll
                 for (int it = 0; it < KT; ++it)
@@ -333,12 +353,12 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                     for (int v = 0; v < 4; ++v) {
                         const c2 p = pv[it][v];
                         const R x = N::apply_sign(gv[it][v], p.y), re = X2::bound(-p.x);
-                        const bool in = (row_at(it, v) < rows) & __builtin_isfinite(p.x) & (x != (R)0);
+                        const bool in = (inside(row_at(it, v), rows)) & __builtin_isfinite(p.x) & (x != (R)0);
                         const int up = X2::whole(re) + X2::exponent(x);
                         pv[it][v].x = re;
                         gv[it][v] = in ? x : (R)0;
                         nb = imax(nb, in ? up : kNone);
-                        if (MODE == kGradients) note((row_at(it, v) < rows) && __builtin_isfinite(p.x) && (N::abs_(re) > (R)kFarLog));
+                        if (MODE == kGradients) note((inside(row_at(it, v), rows)) && __builtin_isfinite(p.x) && (N::abs_(re) > (R)kFarLog));
                     }
                 const int top = imax(e, column_max(nb));
                 note((low < imax(top - Rc::kLam, -kFar)) || (top > kFar));
@@ -362,9 +382,9 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
             // ---- M_t, entry (16 it + row_of(g, v), col) = my 2^mn
             const c2 *Mt = a.M + step * d * d;
             const unsigned mfirst = opaque((unsigned)(N::row_of(g, 0) * d + col));
-            const int dd = opaque_int(d), mrows = (int)opaque((unsigned)lim_d);
+            const int dd = opaque_int(d), mrows = FULL ? DP : (int)opaque((unsigned)lim_d);
             auto fetch_m = [&](int it, int v) {
-                return at_byte(Mt, (row_at(it, v) < mrows ? mfirst + (unsigned)((row_at(it, v) - N::row_of(g, 0)) * dd) : 0u) * (unsigned)sizeof(c2));
+                return at_byte(Mt, (inside(row_at(it, v), mrows) ? mfirst + (unsigned)((row_at(it, v) - N::row_of(g, 0)) * dd) : 0u) * (unsigned)sizeof(c2));
             };
             R my[KT][4];
             int mn[KT][4];
@@ -378,8 +398,13 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
 #pragma unroll
                 for (int it = 0; it < KT; ++it)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) x[it][v] = fetch_m(it, v);
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int v = 0; v < 4; ++v) {
+                        if constexpr (EARLY)
+                            x[it][v] = mraw[it][v];
+                        else
+                            x[it][v] = fetch_m(it, v);
+                    }
+                if (!EARLY) __builtin_amdgcn_sched_barrier(0);
                 int sh = kNone;
                 // a column's power of two: none for a column of zeros, whose entries would come out as ones
                 auto column_shift = [](int x) {
@@ -392,7 +417,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                     for (int it = 0; it < KT; ++it)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            x[it][v].x = row_at(it, v) < mrows ? x[it][v].x : N::neg_inf();
+                            x[it][v].x = inside(row_at(it, v), mrows) ? x[it][v].x : N::neg_inf();
                             most = X2::larger(most, X2::bound(x[it][v].x));
                         }
                     sh = column_shift(X2::whole(most));
@@ -409,7 +434,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                     for (int it = 0; it < KT; ++it)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            split(x[it][v], row_at(it, v) < mrows, my[it][v], mn[it][v]);
+                            split(x[it][v], inside(row_at(it, v), mrows), my[it][v], mn[it][v]);
                             sh = imax(sh, mn[it][v]);
                         }
                     sh = column_shift(sh);
@@ -418,7 +443,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             const R y = N::ldexp_(my[it][v], mn[it][v] - sh);
-                            note(onward && (row_at(it, v) < mrows) && (x[it][v].x > N::neg_inf()) && (N::abs_(y) < Rc::kOtherLeast));
+                            note(onward && (inside(row_at(it, v), mrows)) && (x[it][v].x > N::neg_inf()) && (N::abs_(y) < Rc::kOtherLeast));
                             mt[row_at(it, v) * TL::kM + col] = y;
                         }
                 }
@@ -436,13 +461,18 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                 const unsigned pfirst = opaque((unsigned)(col * m + 4 * g));
                 unsigned pneg = 0; // signs, a bit an entry
                 const bool have = prev != nullptr;
-                const int klim = (int)opaque((unsigned)(col < d ? m : 0));
+                const int klim = FULL ? DP : (int)opaque((unsigned)(col < d ? m : 0));
                 c2 raw[KT][4];
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) raw[kt][v] = at_byte(src, (16 * kt + 4 * g + v < klim ? pfirst + (unsigned)(16 * kt + v) : 0u) * (unsigned)sizeof(c2));
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int v = 0; v < 4; ++v) {
+                        if constexpr (EARLY)
+                            raw[kt][v] = praw[kt][v];
+                        else
+                            raw[kt][v] = at_byte(src, (inside(16 * kt + 4 * g + v, klim) ? pfirst + (unsigned)(16 * kt + v) : 0u) * (unsigned)sizeof(c2));
+                    }
+                if (!EARLY) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
@@ -450,7 +480,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                         const int k = 16 * kt + 4 * g + v;
                         const c2 x = raw[kt][v];
                         const R re = have ? x.x : k == col ? (R)0 : N::neg_inf();
-                        pb[kt][v] = X2::bound(k < klim ? re : N::neg_inf());
+                        pb[kt][v] = X2::bound(inside(k, klim) ? re : N::neg_inf());
                         pneg |= (unsigned)(have & N::is_negative(x.y)) << (4 * kt + v);
                         nj = imax(nj, X2::whole(pb[kt][v]) + lexp[k]);
                     }
@@ -507,7 +537,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
                     for (int v = 0; v < 4; ++v) {
                         const int ri = far ? __shfl(r, N::row_of(g, v), 64) : 0;
                         const R val = N::ldexp_(X[v] * y[v], n0[v] + nj + ri);
-                        if (row_at(it, v) < mrows)
+                        if (inside(row_at(it, v), mrows))
                             *reinterpret_cast<R *>(reinterpret_cast<unsigned char *>(out) + (mfirst + (unsigned)((row_at(it, v) - N::row_of(g, 0)) * dd)) * (unsigned)sizeof(R)) = val;
                     }
                 }
@@ -528,7 +558,7 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
             for (int it = 0; it < KT; ++it)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const bool in = row_at(it, v) < lim_m;
+                    const bool in = inside(row_at(it, v), lim_m);
                     const c2 x = S0[in ? (unsigned)(row_at(it, v) * m + col) : 0u];
                     const R re = X2::bound(x.x);
                     const int n0 = X2::whole(re);
@@ -550,24 +580,32 @@ template <typename R, int DP, int MODE> __global__ __launch_bounds__(DP * 4, siz
     }
 }
 
-template <typename R, int DP, int MODE> int launch_mode(goom_ctx *ctx, const AdjointArgs<R> &a, long long grid, const char *label)
+template <typename R, int DP, int MODE, bool FULL> int launch_mode(goom_ctx *ctx, const AdjointArgs<R> &a, long long grid, const char *label)
 {
-    const void *kern = reinterpret_cast<const void *>(scan_adjoint_kernel<R, DP, MODE>);
+    const void *kern = reinterpret_cast<const void *>(scan_adjoint_kernel<R, DP, MODE, FULL>);
     const size_t lds = Tiles<R, DP>::kBytes;
     if (int st = goom::check_hip(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds), "hipFuncSetAttribute(scan_adjoint_kernel)")) return st;
     goom::prof_begin(ctx, label);
-    hipLaunchKernelGGL((scan_adjoint_kernel<R, DP, MODE>), dim3((unsigned)grid), dim3(DP * 4), lds, ctx->stream, a);
+    hipLaunchKernelGGL((scan_adjoint_kernel<R, DP, MODE, FULL>), dim3((unsigned)grid), dim3(DP * 4), lds, ctx->stream, a);
     goom::prof_end(ctx);
     return goom::check_hip(ctx, hipGetLastError(), "launch scan_adjoint_kernel");
 }
 
-template <typename R, int DP> int launch_dp(goom_ctx *ctx, const AdjointArgs<R> &a, long long batch, int phase)
+template <typename R, int DP, bool FULL> int launch_phase(goom_ctx *ctx, const AdjointArgs<R> &a, long long batch, int phase)
 {
     if (phase == 0) {
-        if (int st = launch_mode<R, DP, kVectors>(ctx, a, batch * (a.C - 1), "scan_adjoint_chunk_vectors")) return st;
-        return launch_mode<R, DP, kCarries>(ctx, a, batch, "scan_adjoint_carries");
+        if (int st = launch_mode<R, DP, kVectors, FULL>(ctx, a, batch * (a.C - 1), "scan_adjoint_chunk_vectors")) return st;
+        return launch_mode<R, DP, kCarries, FULL>(ctx, a, batch, "scan_adjoint_carries");
     }
-    return launch_mode<R, DP, kGradients>(ctx, a, batch * a.C, "scan_adjoint_gradients");
+    return launch_mode<R, DP, kGradients, FULL>(ctx, a, batch * a.C, "scan_adjoint_gradients");
+}
+
+template <typename R, int DP> int launch_dp(goom_ctx *ctx, const AdjointArgs<R> &a, long long batch, int phase)
+{
+    if constexpr (DP == 16 || DP == 32 || DP == 64 || DP == 128) { // (the sizes that are common)
+        if (a.d == DP && a.m == DP) return launch_phase<R, DP, true>(ctx, a, batch, phase);
+    }
+    return launch_phase<R, DP, false>(ctx, a, batch, phase);
 }
 
 template <typename R> int launch_t(goom_ctx *ctx, const goom::ScanAdjointLaunch &l, int phase)

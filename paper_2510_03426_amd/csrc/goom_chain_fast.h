@@ -8,7 +8,8 @@
 // ALU, to which the step's bias is added; every wave takes sixteen of its rows, four lanes a row, on
 // a power of two of the wave's own, so that nothing but the column itself and those exponents passes
 // between the waves, at the step's one barrier.  (A fifth wave for the column alone held up the
-// barrier, and its SIMD's other waves: 16 x 4096 matrices of 64 x 64 720 us, 510 so; the whole pass 1139, 927.)
+// barrier, and its SIMD's other waves: 16 x 4096 matrices of 64 x 64 720 us, 500 so; the whole pass 1139, 910.  With
+// fewer workgroups than compute units it is the other way round, 41 and 47 us for 20 steps, which is why such scans take shorter chunks.)
 //
 // On this chip the float matrix instructions run at the rate of the vector ALU and do
 // not overlap with it, so a step costs (matrix cycles) + 4 x (vector instructions) and
@@ -349,30 +350,13 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
         const bool last = t == len - 1;
 
         // ------------------------------------------------------------ product, and next factor beside it
-        f4 acc[KT];
-        if (owner) {
-#pragma unroll
-            for (int mt = 0; mt < KT; ++mt) acc[mt] = f4{0, 0, 0, 0};
-#pragma unroll
-            for (int kt = 0; kt < KT; ++kt) {
-                f4 av[KT];
-#pragma unroll
-                for (int mt = 0; mt < KT; ++mt)
-                    av[mt] = *reinterpret_cast<const f4 *>(&tile[(16 * mt + c) * LDA + 16 * kt + 4 * g]);
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                    for (int mt = 0; mt < KT; ++mt) acc[mt] = C::mfma(av[mt][v], st[kt][v], acc[mt]);
-            }
-        }
         if (BIAS) {
             // row brow of the tile times the column: sixteen terms a lane on their writer's power of two, then the row's four lanes
             // on the largest
             const double *we = wexp + 4 * cur;
-            double top = we[0];
-#pragma unroll
-            for (int p = 1; p < 4; ++p) top = we[p] > top ? we[p] : top;
-            const int down = (int)Comp<double>::clamp_shift(we[bpart] - top);
+            const double top = __builtin_fmax(__builtin_fmax(we[0], we[1]), __builtin_fmax(we[2], we[3]));
+            const int fall = (int)__builtin_fmax(we[bpart] - top, -4000.0);
+            const float nrb = nsh[brow];
             f4 part = {0, 0, 0, 0};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -381,39 +365,33 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) part[e] = __builtin_fmaf(av[e], wv[e], part[e]);
             }
-            accb = __builtin_ldexpf((part[0] + part[1]) + (part[2] + part[3]), down);
+            accb = __builtin_ldexpf((part[0] + part[1]) + (part[2] + part[3]), fall);
             accb = add_dpp<0xB1>(accb);
             accb = add_dpp<0x4E>(accb);
             becol = top;
-        }
-        // (after the last product there is nothing to convert: a single product, as in a
-        // batched LMME, would otherwise pay for its left factor twice)
-        if (!last) {
-            convert_items(pre, cur ^ 1, nsh);
-            load_items(t + 2 < len ? t + 2 : len - 1, pre);
-        }
-        float nrb = 0.0f;
-        if (BIAS) {
-            // b_i enters entry (i, d) of the product, which is held as accb 2^(n_i + becol): add
-            // (+-) 2^(log2|b_i| - n_i - becol).  Should the wave's rows have shrunk so far below the bias
-            // that this would overflow, they are first scaled down (to nothing, if need be).
+            // b_i enters entry (i, d) of the product, which is held as accb 2^(n_i + becol): add (+-) 2^(log2|b_i| - n_i - becol)
             const float kHi = 1.44269502162933349609375f;
             const float kLo = 1.925963033500011e-8f;
-            nrb = nsh[brow];
-            if (__builtin_amdgcn_ballot_w64(accb != 0.0f) == 0) {
-                // rows of zeros have no scale of their own: they take the bias's, whatever its magnitude
-                float m = __builtin_fmaf(bpre.x, kHi, -nrb);
-                m = C::template group_allmax<64>(m, m);
-                becol = (m > -1.0e30f && m < 1.0e30f) ? (double)__builtin_ceilf(m) : 0.0;
-            }
             float x = __builtin_fmaf(bpre.x, kHi, -(nrb + (float)becol));
             x = __builtin_fmaf(bpre.x, kLo, x);
             float down = 0.0f;
-            if (__builtin_amdgcn_ballot_w64(x > 64.0f) != 0) {
+            const bool none = __builtin_amdgcn_ballot_w64(accb != 0.0f) == 0;
+            if (none || __builtin_amdgcn_ballot_w64(x > 64.0f) != 0) {
+                if (none) { // rows of zeros have no scale of their own: they take the bias's, whatever its magnitude
+                    float m = __builtin_fmaf(bpre.x, kHi, -nrb);
+                    m = C::template group_allmax<64>(m, m);
+                    becol = (m > -1.0e30f && m < 1.0e30f) ? (double)__builtin_ceilf(m) : 0.0;
+                    x = __builtin_fmaf(bpre.x, kHi, -(nrb + (float)becol));
+                    x = __builtin_fmaf(bpre.x, kLo, x);
+                }
+                // should the wave's rows have shrunk so far below the bias that this would overflow, they are first scaled down (to
+                // nothing, if need be)
                 const float amax = C::template group_allmax<64>(x, x);
-                down = C::max_(0.0f, __builtin_ceilf(amax) - 64.0f);
-                accb = __builtin_ldexpf(accb, -(int)C::clamp_shift(down));
-                becol += (double)down;
+                if (amax > 64.0f) {
+                    down = __builtin_ceilf(amax) - 64.0f;
+                    accb = __builtin_ldexpf(accb, -(int)C::clamp_shift(down));
+                    becol += (double)down;
+                }
             }
             accb += C::apply_sign(__builtin_amdgcn_exp2f(x - down), bpre.y);
             load_bias(t + 1 < len ? t + 1 : len - 1);
@@ -434,7 +412,28 @@ __device__ __forceinline__ void chain_body(const ChainArgs &a)
             if (bpart == 0) wvec[DP * (cur ^ 1) + brow] = accb;
             if (lane == 0) wexp[4 * (cur ^ 1) + wave] = becol;
         }
-
+        f4 acc[KT];
+        if (owner) {
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt) acc[mt] = f4{0, 0, 0, 0};
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
+                f4 av[KT];
+#pragma unroll
+                for (int mt = 0; mt < KT; ++mt)
+                    av[mt] = *reinterpret_cast<const f4 *>(&tile[(16 * mt + c) * LDA + 16 * kt + 4 * g]);
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int mt = 0; mt < KT; ++mt) acc[mt] = C::mfma(av[mt][v], st[kt][v], acc[mt]);
+            }
+        }
+        // (after the last product there is nothing to convert: a single product, as in a
+        // batched LMME, would otherwise pay for its left factor twice)
+        if (!last) {
+            convert_items(pre, cur ^ 1, nsh);
+            load_items(t + 2 < len ? t + 2 : len - 1, pre);
+        }
         // ------------------------------------------------------------ outputs
         // entry (i = 16 mt + 4 g + v, col) of the product is acc 2^(n_i + ecol)
         const bool want_out = a.out_goom && (!a.out_goom_last_only || last) && owner;

@@ -1028,13 +1028,42 @@ static long long one_matrix_chunk(long long T, int d, long long batch, int dtype
 // of d = 100 285 / 354, of d = 48 162 / 138; 249 carries of d = 100 394 / 332, of d = 8 (complex128) 173 / 84; 4095 carries of d = 24 3165 / 245.
 constexpr long long kOneMatrixCarries = 192;
 
-// least: in the room that a plan of one-column walks asks for.
-static AffinePlan plan_affine(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts, bool least = false)
+// Adjoint of the recurrence: carries that one chain an item takes; more go in groups.  (A carry of the adjoint takes 1.3 us at d = 24 and 2 us at
+// d = 64, so the line could lie lower - 93 carries of d = 64: 328 us in one chain, 220 in groups - but a group's float product rounds once more,
+// which up to here nothing has to.  255 carries of d = 48: 681 / 277 us; 511 of d = 64: 1860 / 945 us; 8191 of d = 8: 7400 / 391 us.)
+constexpr long long kAdjointCarries = 128;
+
+// A matrix a step, fewer tokens than fill the chip: chunks shorter than a plain scan's.  While a compute unit has no more than one chunk a step takes
+// its latency, twice (product and walk), and a carry a vector's, so r L + T / L is least near sqrt(T / r), r a chunk's step over a carry's; from 590 steps
+// on the carries go in groups and six steps a chunk are best or near it.  In us, former chunks / these (the best of ten lengths): complex64
+// 1 x 60 x 64 91 / 43 (43), 1 x 300 x 64 99 / 80 (79), 1 x 1000 x 64 137 / 111 (111), 8 x 300 x 64 105 / 90 (84), 1 x 60 x 8 52 / 29 (29), 1 x 300 x 16 43 / 40 (40), 1 x
+// 60 x 128 330 / 97 (97), 1 x 1000 x 128 377 / 264 (264); complex128 1 x 60 x 64 135 / 81 (80), 1 x 300 x 24 97 / 88 (81), 1 x 30 x 100 448 / 148 (148).  Up to
+// two dozen steps one chunk takes less than three launches.
+//
+// The backward pass is a recurrence as well, over as many carries and with groups above kAdjointCarries of them (float d = 16 and 32: as forward).  The former
+// chunks / these: complex64 1 x 60 x 64 131 / 68, 1 x 600 x 64 197 / 157, 1 x 1000 x 64 248 / 170, 1 x 60 x 128 388 / 135; complex128 1 x 30 x 100 698 / 223, 1 x 1000 x
+// 24 246 / 142.
+static long long affine_short_chunk(long long T, int d, long long batch, int dtype, bool adjoint, long long former)
+{
+    if (T < (dtype == GOOM_C64 && d <= 64 ? 28 : 24)) return former;
+    const long long r = dtype == GOOM_C64 ? (d == 16 || d == 32 ? 2 : d <= 16 ? 3 : d <= 64 ? 4 : 8) : (d <= 64 ? 8 : 12);
+    const long long carries = adjoint && !(dtype == GOOM_C64 && (d == 16 || d == 32)) ? kAdjointCarries : dtype == GOOM_C64 && d == 16 ? 130 : 97; // (plan_scan's groups: from 98 chunks on)
+    long long L = T > 6 * (carries + 1) ? 6 : T > 4 * (carries + 1) && carries == kAdjointCarries ? 4 : 2;
+    if (L == 2)
+        while (r * L * L < T) ++L;
+    const long long fill = (T * batch + 255) / 256; // a chunk for every compute unit
+    if (L < fill) L = fill;
+    return L < former ? L : former;
+}
+
+// least: in the room that a plan of one-column walks asks for; a matrix a step: in a plain scan's chunks.
+static AffinePlan plan_affine(long long T, int d, long long batch, int dtype, const goom_scan_opts *opts, bool least = false, bool adjoint = false)
 {
     AffinePlan ap;
     const bool one_matrix = opts && opts->chunk_len == 0 && (opts->flags & GOOM_AFFINE_TIME_INVARIANT);
-    const long long req = affine_walk_whole(d, batch, dtype, opts) ? T : one_matrix ? one_matrix_chunk(T, d, batch, dtype, least) : opts ? opts->chunk_len : 0;
+    long long req = affine_walk_whole(d, batch, dtype, opts) ? T : one_matrix ? one_matrix_chunk(T, d, batch, dtype, least) : opts ? opts->chunk_len : 0;
     ap.p = plan_scan(T, d, d + 1, 1, batch, dtype, req, false);
+    if (req == 0 && !least) ap.p = plan_scan(T, d, d + 1, 1, batch, dtype, req = affine_short_chunk(T, d, batch, dtype, adjoint, ap.p.L), false);
     ap.f64 = dtype == GOOM_C64 && (d == 16 || d == 32) && ap.p.dp == d && ap.p.C > 1;
     ap.h0_bytes = 0;
     if (ap.f64) {
@@ -1107,11 +1136,11 @@ static int run_affine(goom_ctx *ctx, const void *A, const void *bias, const void
     if (d > GOOM_MAX_DIM) return fail(ctx, GOOM_EUNSUPPORTED, "the recurrence with bias needs d <= %d", GOOM_MAX_DIM);
     if (!aligned(bias, 16) || (h0 && !aligned(h0, 16))) return fail(ctx, GOOM_EINVAL, "complex data must be 16-byte aligned");
     if (logscale && !aligned(logscale, comp_bytes(dtype))) return fail(ctx, GOOM_EINVAL, "misaligned data pointer");
-    AffinePlan ap = plan_affine(T, d, batch, dtype, opts);
+    AffinePlan ap = plan_affine(T, d, batch, dtype, opts, false, adjoint_shift != nullptr);
     auto needed = [&] {
         return want_scaled ? align_up(ap.total(), 256) + (affine_scaled_needs_no_states(ap.p, d, dtype) ? 0 : affine_states_bytes(T, d, batch, dtype)) : ap.total();
     };
-    if (ti && needed() > ws_bytes) ap = plan_affine(T, d, batch, dtype, opts, true);
+    if (needed() > ws_bytes) ap = plan_affine(T, d, batch, dtype, opts, true, adjoint_shift != nullptr);
     const size_t need = needed();
     ScanPlan p = ap.p;
     if (int s = check_workspace(ctx, ws, ws_bytes, need)) return s;
@@ -1296,11 +1325,6 @@ int goom_affine_scan_scaled(goom_ctx *ctx, const void *A, const void *bias, cons
 }
 
 // ---- backward passes ---------------------------------------------------------------------------------------
-// Adjoint of the recurrence: carries that one chain an item takes; more go in groups.  (A carry of the adjoint takes 1.3 us at d = 24 and 2 us at
-// d = 64, so the line could lie lower - 93 carries of d = 64: 328 us in one chain, 220 in groups - but a group's float product rounds once more,
-// which up to here nothing has to.  255 carries of d = 48: 681 / 277 us; 511 of d = 64: 1860 / 945 us; 8191 of d = 8: 7400 / 391 us.)
-constexpr long long kAdjointCarries = 128;
-
 struct AffineBackwardPlan {
     bool direct; // the adjoint scan reads the forward pass's matrices itself (transposed, in reverse order)
     bool one_matrix; // GOOM_AFFINE_TIME_INVARIANT: A is [batch, d, d] and so is its gradient
@@ -1318,7 +1342,7 @@ static AffineBackwardPlan plan_affine_backward(long long T, int d, long long bat
     goom_scan_opts plain = opts ? *opts : goom_scan_opts{0, 0};
     p.one_matrix = (plain.flags & GOOM_AFFINE_TIME_INVARIANT) != 0;
     plain.flags &= ~GOOM_AFFINE_TIME_INVARIANT;
-    p.direct = plan_affine(T, d, batch, dtype, &plain).f64;
+    p.direct = plan_affine(T, d, batch, dtype, &plain, least, true).f64;
     p.same_factor = p.one_matrix;
     if (p.same_factor) {
         goom_scan_opts inv = plain;
@@ -1331,7 +1355,7 @@ static AffineBackwardPlan plan_affine_backward(long long T, int d, long long bat
         // the transposed, reversed and rescaled copy of A, or only the shifts of its log-magnitudes, one per step
         p.at_bytes = p.direct ? align_up((size_t)batch * (size_t)T * sizeof(float), 256) : align_up((size_t)batch * (size_t)T * d * d * cb, 256);
         p.vec_bytes = align_up((size_t)batch * (size_t)T * d * cb, 256);
-        p.scan_bytes = align_up(goom_affine_scan_workspace_bytes(T, d, batch, dtype, &plain), 256);
+        p.scan_bytes = align_up(plan_affine(T, d, batch, dtype, &plain, least, true).total(), 256);
     }
     p.nsplit = 1;
     p.uv_bytes = p.partial_bytes = 0;
@@ -1368,7 +1392,8 @@ int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, co
     if (!aligned(grad_H, rb) || !aligned(grad_A, rb) || (grad_bias && !aligned(grad_bias, rb)) || (grad_h0 && !aligned(grad_h0, rb)))
         return fail(ctx, GOOM_EINVAL, "misaligned data pointer");
     AffineBackwardPlan p = plan_affine_backward(T, d, batch, dtype, opts);
-    if (p.one_matrix && p.total() > ws_bytes) p = plan_affine_backward(T, d, batch, dtype, opts, true);
+    const bool least = p.total() > ws_bytes;
+    if (least) p = plan_affine_backward(T, d, batch, dtype, opts, true);
     if (int s = check_workspace(ctx, ws, ws_bytes, p.total())) return s;
     if (int s = need_ctx(ctx)) return s;
     unsigned char *w = static_cast<unsigned char *>(ws);
@@ -1394,7 +1419,7 @@ int goom_affine_scan_backward(goom_ctx *ctx, const void *A, const void *bias, co
     if (!p.direct) {
         // Every size but float d = 16 and 32: the adjoints walked backwards, gradients written on the way (goom_vec_adjoint.hip), over
         // the forward chunks.  One chain an item carries the adjoint from chunk to chunk, up to kAdjointCarries of them, more in groups.
-        const ScanPlan q = plan_affine(T, d, batch, dtype, &plain).p;
+        const ScanPlan q = plan_affine(T, d, batch, dtype, &plain, least, true).p;
         const size_t vec = goom_chain::adjoint_vec_stride(q.dp, dtype);
         unsigned char *totals = static_cast<unsigned char *>(w), *vecs = totals + align_up((size_t)batch * q.C * q.tot.stride, 256);
         unsigned char *gtot = vecs + (size_t)batch * q.C * vec, *gvecs = nullptr;

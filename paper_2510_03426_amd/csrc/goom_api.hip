@@ -224,6 +224,30 @@ static ScanPlan plan_scan(long long T, int d, int m_tot, int m_state, long long 
     return p;
 }
 
+// Scans and reductions of few matrices: shorter chunks than default_chunk_len's, which are made for chains that fill the chip.  While a compute unit
+// has no more than one chunk a step takes its latency, in two phases, and a carry a product's, so r L + T / L is least near sqrt(T / r), r the
+// two phases' steps over a carry; with more than 96 chunks the carries go in groups, and a few steps a chunk are best.  In us, a scan in the former chunks
+// / in these (the best of ten lengths): complex64 1 x 60 x 64 90 / 42 (42), 1 x 300 x 64 96 / 82 (80), 1 x 1000 x 64 138 / 104 (104), 1 x 60 x 128 441 /
+// 137 (137), 1 x 2000 x 100 448 / 356 (356), 8 x 300 x 64 103 / 87 (87), 1 x 60 x 8 27 / 19 (19); complex128 1 x 24 x 64 140 / 71 (71), 1 x 300 x 128 791 / 470 (470), 1 x
+// 1000 x 16 94 / 67 (67).  Reductions, with one phase of steps: 1 x 60 x 64 45 / 30, 1 x 600 x 64 75 / 61.  States narrower than half the matrices keep the former.
+// least: the former chunks.
+static ScanPlan plan_prefix(long long T, int d, int m, long long batch, int dtype, long long requested, bool final_only, bool least = false)
+{
+    const ScanPlan p = plan_scan(T, d, d, m, batch, dtype, requested, final_only);
+    const bool heavy = dtype == GOOM_C128 || d > 64;
+    if (requested > 0 || least || d > GOOM_MAX_DIM || 2 * m < d || T < (heavy || d > 16 ? 24 : 40)) return p;
+    if (final_only && !heavy && T > 1500) return p;
+    const long long grouped = heavy ? 3 : final_only && T >= 98 * 8 ? 8 : 6;
+    long long r = heavy ? 8 : d > 32 ? 4 : d > 16 ? 2 : 1;
+    if (final_only && r > 1) r = heavy && d <= 32 ? 2 : r / 2; // (one phase of steps)
+    long long L = T >= 98 * grouped ? grouped : 2;
+    if (L == 2)
+        while (r * L * L < T) ++L;
+    const long long fill = (T * batch + 255) / 256; // a chunk for every compute unit
+    if (L < fill) L = fill;
+    return L < p.L ? plan_scan(T, d, d, m, batch, dtype, L, final_only) : p;
+}
+
 static int check_scan_args(goom_ctx *ctx, const void *M, const void *out, long long T, int d, int m, long long batch,
                            int dtype, const goom_scan_opts *opts, int max_dim = GOOM_MAX_DIM)
 {
@@ -384,7 +408,8 @@ static int run_scan(goom_ctx *ctx, const void *M, const void *init, void *P, lon
         return f32 ? run_scan_large(ctx, M, init, P, T, d, m, batch, req, ws, final_only)
                    : run_scan_large_f64(ctx, M, init, P, T, d, m, batch, req, ws, final_only);
     }
-    const ScanPlan p = plan_scan(T, d, d, m, batch, dtype, opts ? opts->chunk_len : 0, final_only);
+    ScanPlan p = plan_prefix(T, d, m, batch, dtype, opts ? opts->chunk_len : 0, final_only);
+    if (p.total() > ws_bytes) p = plan_prefix(T, d, m, batch, dtype, opts ? opts->chunk_len : 0, final_only, true);
     if (int s = check_workspace(ctx, ws, ws_bytes, p.total())) return s;
     const size_t cb = 2 * comp_bytes(dtype);
     if (int s = need_ctx(ctx)) return s;
@@ -859,7 +884,7 @@ size_t goom_scan_workspace_bytes(int64_t T, int d, int m, int64_t batch, int dty
     if (dtype != GOOM_C64 && dtype != GOOM_C128) return 0;
     if (d > GOOM_MAX_DIM || m > GOOM_MAX_DIM)
         return large_scan_bytes(T, d, m, batch, dtype, opts, false);
-    ScanPlan p = plan_scan(T, d, d, m, batch, dtype, opts ? opts->chunk_len : 0, false);
+    ScanPlan p = plan_prefix(T, d, m, batch, dtype, opts ? opts->chunk_len : 0, false);
     return p.total();
 }
 
@@ -869,7 +894,7 @@ size_t goom_reduce_workspace_bytes(int64_t T, int d, int m, int64_t batch, int d
     if (dtype != GOOM_C64 && dtype != GOOM_C128) return 0;
     if (d > GOOM_MAX_DIM || m > GOOM_MAX_DIM)
         return large_scan_bytes(T, d, m, batch, dtype, opts, true);
-    ScanPlan p = plan_scan(T, d, d, m, batch, dtype, opts ? opts->chunk_len : 0, true);
+    ScanPlan p = plan_prefix(T, d, m, batch, dtype, opts ? opts->chunk_len : 0, true);
     return p.total();
 }
 
@@ -937,9 +962,17 @@ static int run_scan_real(goom_ctx *ctx, const void *X, const void *init, void *P
 {
     if (int s = check_scan_args(ctx, X, P, T, d, m, batch, dtype, opts, GOOM_MAX_DIM_LMME)) return s;
     if (real_input_native(d, m, dtype)) return run_scan(ctx, X, init, P, T, d, m, batch, dtype, opts, ws, ws_bytes, final_only, true);
-    const size_t base = final_only ? goom_reduce_workspace_bytes(T, d, m, batch, dtype, opts) : goom_scan_workspace_bytes(T, d, m, batch, dtype, opts);
+    size_t base = final_only ? goom_reduce_workspace_bytes(T, d, m, batch, dtype, opts) : goom_scan_workspace_bytes(T, d, m, batch, dtype, opts);
+    const size_t encoded = align_up((size_t)batch * (size_t)T * d * d * 2 * comp_bytes(dtype), 256);
+    if (align_up(base, 256) + encoded > ws_bytes) { // (what run_scan does with less room)
+        const long long req = opts ? opts->chunk_len : 0;
+        const size_t least = d <= GOOM_MAX_DIM && m <= GOOM_MAX_DIM ? plan_prefix(T, d, m, batch, dtype, req, final_only, true).total()
+                             : dtype == GOOM_C64                    ? scan_large_workspace_bytes(T, d, m, batch, req, final_only)
+                                                                    : base;
+        if (align_up(least, 256) + encoded <= ws_bytes) base = least;
+    }
     const size_t zoff = align_up(base, 256);
-    const size_t need = zoff + align_up((size_t)batch * (size_t)T * d * d * 2 * comp_bytes(dtype), 256);
+    const size_t need = zoff + encoded;
     if (int s = check_workspace(ctx, ws, ws_bytes, need)) return s;
     if (int s = need_ctx(ctx)) return s;
     void *Z = static_cast<unsigned char *>(ws) + zoff;

@@ -245,7 +245,8 @@ static ScanPlan plan_prefix(long long T, int d, int m, long long batch, int dtyp
         while (r * L * L < T) ++L;
     const long long fill = (T * batch + 255) / 256; // a chunk for every compute unit
     if (L < fill) L = fill;
-    return L < p.L ? plan_scan(T, d, d, m, batch, dtype, L, final_only) : p;
+    // (a reduction gains little from chunks a little shorter, and its carries take it back: 60 of 32 x 32 in chunks of 8 19.1 us, of 9 17.6)
+    return L < p.L && !(final_only && 3 * L > 2 * p.L) ? plan_scan(T, d, d, m, batch, dtype, L, final_only) : p;
 }
 
 static int check_scan_args(goom_ctx *ctx, const void *M, const void *out, long long T, int d, int m, long long batch,

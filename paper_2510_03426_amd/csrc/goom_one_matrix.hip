@@ -111,14 +111,17 @@ template <typename R, int DP, bool FULL, bool SHIFT, int PD> __global__ __launch
         }
         const unsigned char *ip = a.init + idx * a.init_stride;
         const bool f64 = sizeof(R) == 8 || a.fact_f64;
+        R some = (R)0;
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             if (row0 + v * dr < d) {
                 const size_t at = (size_t)(row0 + v * dr) * a.fact_cols;
                 own[v] = f64 ? (R) reinterpret_cast<const double *>(ip)[at] : (R) reinterpret_cast<const float *>(ip)[at];
+                some = own[v] != (R)0 ? (R)1 : some;
             }
         E = *reinterpret_cast<const double *>(ip + (size_t)DP * a.fact_cols * (f64 ? 8 : 4));
-        if (!(__builtin_fabs(E) < 1.0e15)) E = 0.0; // (a zero vector's exponent says nothing)
+        // (a zero vector's exponent says nothing: without rows that are not zero the column has none, see combine)
+        if (!(Comp<R>::xor16_32_max(some) > (R)0)) ownx = kNegInf;
     }
     auto publish = [&](int buf) {
         if (sizeof(R) == 4) {

@@ -66,6 +66,26 @@ def test_one_matrix_zeros_and_lone_biases(G, d, ctype):  # noqa: F811
     assert np.all(H[:, 37:300, d - 1].real == none) and np.abs(H[:, 300:, d - 1].real - above).max() <= 1e-6 * abs(above)
 
 
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("d", [33, 48, 100])
+@pytest.mark.parametrize("ctype", [np.complex64, np.complex128])
+def test_one_matrix_carries_of_any_exponent(G, d, ctype, sign):  # noqa: F811
+    """States that grow (shrink) by e^(3e14) a step, so that the carried vectors' exponents pass 1e15: every chunk starts where the one before ended."""
+    comp = np.float32 if ctype == np.complex64 else np.float64
+    T, batch, step = 60, 2, float(comp(sign * 3e14))
+    A = np.full((batch, d, d), -np.inf, dtype=ctype)
+    A[:, range(d), range(d)] = step
+    b = np.full((batch, T, d), -np.inf, dtype=ctype)
+    h0 = np.zeros((batch, d), dtype=ctype)
+    h0[1, ::2] = -np.inf  # (zeros among them stay zeros)
+    H = host(G.affine_scan(dev(A), dev(b), dev(h0), time_invariant=True))
+    want = np.arange(1, T + 1)[:, None] * step + h0[:, None, :].real
+    ok = np.isfinite(want)
+    assert np.array_equal(np.isfinite(H.real), ok) and not H.imag.any()
+    # a rounding of the matrix's entry and of the state's logarithm a step
+    assert np.abs(H.real[ok] / want[ok] - 1).max() <= 4 * T * np.finfo(comp).eps
+
+
 def test_one_matrix_in_the_room_of_one_column_walks(G, oracle):  # noqa: F811
     """A workspace too small for the short chunks: longer ones, and the same states and gradients; nothing at all is refused."""
     T, d, batch = 1000, 64, 4

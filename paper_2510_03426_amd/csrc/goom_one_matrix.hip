@@ -148,16 +148,16 @@ template <typename R, int DP, bool FULL, bool SHIFT, int PD> __global__ __launch
         brow[v] = (unsigned)(past[v] ? d - 1 : row0 + v * dr);
     }
     auto load = [&](int t, Rest &r) {
-        const unsigned tt = (unsigned)(t < len ? t : len - 1);
+        const size_t tt = (size_t)(t < len ? t : len - 1); // (a chunk may be longer than 2^32 entries)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             if constexpr (FULL && sizeof(R) == 4) { // four entries side by side
                 if (v & 1) continue;
-                const vec4 w = *reinterpret_cast<const vec4 *>(bias0 + tt * (unsigned)DP + row0 + v);
+                const vec4 w = *reinterpret_cast<const vec4 *>(bias0 + tt * DP + row0 + v);
                 r.b[v] = R2{w[0], w[1]};
                 r.b[v + 1] = R2{w[2], w[3]};
             } else {
-                r.b[v] = bias0[tt * (unsigned)d + brow[v]];
+                r.b[v] = bias0[tt * (size_t)d + brow[v]];
             }
         }
         if (SHIFT) r.shift = shift0[tt];

@@ -16,7 +16,8 @@
 // with X, the left factor, as three planes of bf16 with K contiguous, and Y either the same (LMME) or the running state of a
 // chain as the last product left it: plain floats Ct[n][k].  A state is never rescaled by a pass of its own: the kernel that
 // writes it finds every column's largest exponent (an integer maximum by atomics), and the kernel that reads it applies the factor's row shifts
-// and that exponent, and splits into parts, on the way into LDS.
+// and that exponent, and splits into parts, on the way into LDS.  Row shifts are taken relative to the factor's largest there (whole numbers of
+// any size themselves, the differences that matter are small and exact); the largest joins the columns' exponents, in double.
 #include <climits>
 #include <cmath>
 
@@ -97,7 +98,11 @@ template <typename T> struct Pieces {
     __device__ __host__ T *at(long long i, long long c) const { return p + i * item + c * chunk; }
 };
 
-__device__ inline int exponent_key(float e) { return (int)__builtin_amdgcn_fmed3f(e, -2.0e9f, 2.0e9f); }
+__device__ inline int exponent_key(float e) { return (int)e; }
+
+// A row this far below its factor's largest (in powers of two) counts as no farther: such shifts, two of them and a float's exponent add up
+// exactly in float.  (No sum in float reaches so far down; a column that has entries in such rows alone is kept, on a wrong exponent.)
+constexpr double kFarRow = -4.0e6;
 
 struct SplitGemm {
     int chunks;                            // products: blockIdx.z = item * chunks + chunk
@@ -107,12 +112,12 @@ struct SplitGemm {
     // Y as planes [3][K / 16][N][16], columns times 2^col_shift[n] (LMME) ...
     Pieces<const __bf16> Yp;
     Pieces<const float> col_shift;
-    // ... or as the raw product Yr [K / 16][N][16] of the step before: entry k times 2^fold[k], column n's largest exponent with these key[n],
-    // exponent of the column outside of these e_in[n] + extra
+    // ... or as the raw product Yr [K / 16][N][16] of the step before: entry k times 2^fold[k] (no more than 1), column n's largest exponent with
+    // these key[n], exponent of the column outside of these e_in[n] + extra
     Pieces<const float> Yr, fold;
     Pieces<const int> key;
     Pieces<const double> e_in;
-    Pieces<const double> extra;            // p NULL: 0
+    Pieces<const double> extra;
     Pieces<double> e_out;                  // of the product's columns
     // outputs
     Pieces<float> Ct, C;                   // p NULL or the product as [M / 16][N][16] / [M][N]
@@ -135,7 +140,7 @@ __device__ inline void finish(const SplitGemm &a, long long item, long long chun
         const int col = col0 + 32 * j;
         if constexpr (RAW) {
             const int key = a.key.at(item, chunk)[col];
-            eo[j] = a.e_in.at(item, chunk)[col] + (a.extra.p ? *a.extra.at(item, chunk) : 0.0) + ((key > INT_MIN ? (double)key : 0.0) - (double)kLift);
+            eo[j] = a.e_in.at(item, chunk)[col] + *a.extra.at(item, chunk) + ((key > INT_MIN ? (double)key : 0.0) - (double)kLift);
             if (once && h == 0 && a.e_out.p) a.e_out.at(item, chunk)[col] = eo[j];
         } else {
             eo[j] = (double)a.col_shift.at(item, chunk)[col];
@@ -428,7 +433,8 @@ template <bool RAW> void launch_gemm_split(hipStream_t st, const SplitGemm &a, u
 }
 
 // ---- rows of GOOM matrices into planes.  Row r of matrix b: 2^(log2|x| - shift), shift = the row's whole power of two less kLift.  One wave a
-// row (up to 1024 entries, sixteen a lane, in pairs), four rows a workgroup: grid (rows_padded / 4, matrices), 256 threads.
+// row (up to 1024 entries, sixteen a lane, in pairs), four rows a workgroup: grid (rows_padded / 4, matrices), 256 threads.  A row without entries
+// has the shift -inf.
 // A chain of matrices (L > 0): matrix b is step s = s0 + b % per_chain of chain b / per_chain = item * C + chunk, and goes to place
 // chain * places + s % places; beyond the chunk or T it is the identity.
 struct RowsArgs {
@@ -476,7 +482,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(RowsArgs a)
         const float one = !active && row < a.n ? 1.0f : 0.0f; // (a power of two: 2^kLift with the shift -kLift)
         for (int j = 2 * lane; j < a.k_padded; j += 128)
             put(j, j == row ? one * 1099511627776.0f : 0.f, j + 1 == row ? one * 1099511627776.0f : 0.f);
-        if (lane == 0) *shift = !active && row < a.n ? -kLift : 0.0f;
+        if (lane == 0) *shift = !active && row < a.n ? -kLift : CF::neg_inf();
         write_out();
         return;
     }
@@ -502,7 +508,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(RowsArgs a)
     }
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
-    const float sh = (mx > CF::neg_inf() ? ceilf(mx * kLog2eF) : 0.0f) - kLift;
+    const float sh = ceilf(mx * kLog2eF) - kLift;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         const int j = 2 * lane + 128 * r;
@@ -511,6 +517,42 @@ __global__ __launch_bounds__(256) void split_rows_kernel(RowsArgs a)
     }
     if (lane == 0) *shift = sh;
     write_out();
+}
+
+// The row shifts of the matrices that split_rows_kernel has converted, relative to each one's largest, and these (infinite: a row is).
+// grid (matrices), 256 threads; places as there.
+struct RelativeArgs {
+    const float *shifts;
+    float *rel;
+    double *top;
+    int dp;
+    long long per_chain, s0, places;
+};
+__global__ __launch_bounds__(256) void relative_shifts_kernel(RelativeArgs a)
+{
+    __shared__ float red[4];
+    const long long b = blockIdx.x, place = b / a.per_chain * a.places + (a.s0 + b % a.per_chain) % a.places;
+    const float *sh = a.shifts + (size_t)place * a.dp;
+    float x[GOOM_MAX_DIM_LMME / 256], mx = CF::neg_inf();
+#pragma unroll
+    for (int r = 0; r < GOOM_MAX_DIM_LMME / 256; ++r) {
+        const int k = threadIdx.x + 256 * r;
+        x[r] = k < a.dp ? sh[k] : CF::neg_inf();
+        mx = fmaxf(mx, x[r]);
+    }
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const double top = mx > CF::neg_inf() ? (double)mx : 0.0;
+#pragma unroll
+    for (int r = 0; r < GOOM_MAX_DIM_LMME / 256; ++r) {
+        const int k = threadIdx.x + 256 * r;
+        const double rel = (double)x[r] - top; // (NaN: such a row)
+        if (k < a.dp) a.rel[(size_t)place * a.dp + k] = (float)(rel > kFarRow ? rel : kFarRow);
+    }
+    if (threadIdx.x == 0) a.top[place] = top;
 }
 
 // ---- columns of a GOOM matrix [d][m]: their shifts (less kLift); grid (cols_padded / 64 rounded up, matrices), block 64 x 4
@@ -587,11 +629,11 @@ __global__ __launch_bounds__(256) void split_columns_kernel(const float2 *__rest
 }
 
 // ---- the chunks' first matrices as the states after their first step: Ct[chain][i / 16][n][i % 16] = row i, column n of A scaled as in split_rows_kernel (whose
-// shifts these are), and the columns' keys under those shifts.
+// shifts these are), and the columns' keys under those shifts, relative to their largest.
 // grid (dp / 32, dp / 32, chains), 256 threads.
 struct FirstArgs {
     const float2 *A;
-    Pieces<const float> shifts;
+    Pieces<const float> shifts, rel;
     Pieces<float> Ct;
     Pieces<int> key;
     int d, dp, chunks;
@@ -604,15 +646,16 @@ __global__ __launch_bounds__(256) void first_state_kernel(FirstArgs a)
     const int n0 = blockIdx.x * 32, i0 = blockIdx.y * 32;
     const long long item = blockIdx.z / a.chunks, chunk = blockIdx.z % a.chunks;
     const float2 *A = a.A + ((size_t)item * a.T + chunk * a.L) * a.d * a.d;
-    const float *sh = a.shifts.at(item, chunk);
+    const float *sh = a.shifts.at(item, chunk), *rel = a.rel.at(item, chunk);
     float mx = CF::neg_inf();
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int i = i0 + ty + 8 * r, n = n0 + tx;
+        const float ri = rel[i];
         float v = 0.0f;
         if (i < a.d && n < a.d) {
             v = lifted(A[(size_t)i * a.d + n], sh[i]);
-            if (v != 0.f) mx = fmaxf(mx, CF::exponent_of(v) + sh[i]);
+            if (v != 0.f) mx = fmaxf(mx, CF::exponent_of(v) + ri);
         }
         tile[ty + 8 * r][tx] = v; // [i][n]
     }
@@ -653,15 +696,16 @@ __global__ __launch_bounds__(256) void totals_planes_kernel(TotalsArgs a)
         *reinterpret_cast<unsigned *>(o + 2 * plane) = lo;
     }
 }
-// What the carries' entries have to be multiplied by.  The carry into chunk c still lacks the row shifts of total c - 1 (fold2; none for
-// c = 0); as the operand of the next product it takes the exponents of total c's columns too, g(c)[k] relative to the largest of them, gmax
-// (fold1).  grid (chunks, items), 256 threads.
+// What the carries' entries have to be multiplied by.  The carry into chunk c still lacks the row shifts of total c - 1 (fold2, and their largest,
+// top2; none for c = 0); as the operand of the next product it takes the exponents of total c's columns too, g(c)[k] relative to the largest of
+// them, which joins gmax (fold1).  grid (chunks, items), 256 threads.
 struct FoldArgs {
     const int *key;             // as above; NULL: the totals are the matrices themselves, g = 0
     const double *e;
-    Pieces<const float> shifts; // rows of total c
+    Pieces<const float> rel;    // rows of total c
+    Pieces<const double> top;
     float *fold1, *fold2;       // [item][chunk][dp]
-    double *gmax;               // [item][chunk]
+    double *gmax, *top2;        // [item][chunk]
     int dp, d;
     long long chunks, totals;
 };
@@ -669,7 +713,9 @@ __global__ __launch_bounds__(256) void totals_fold_kernel(FoldArgs a)
 {
     __shared__ double red[4];
     const long long chunk = blockIdx.x, item = blockIdx.y, at = item * a.chunks + chunk;
-    const float *before = chunk > 0 ? a.shifts.at(item, chunk - 1) : nullptr;
+    const float *before = chunk > 0 ? a.rel.at(item, chunk - 1) : nullptr;
+    const double top2 = chunk > 0 ? *a.top.at(item, chunk - 1) : 0.0;
+    if (threadIdx.x == 0) a.top2[at] = top2;
     double g[4], mx = -1.0e300;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -696,10 +742,10 @@ __global__ __launch_bounds__(256) void totals_fold_kernel(FoldArgs a)
         const int k = threadIdx.x + 256 * r;
         if (k < a.dp) {
             const double rel = g[r] - mx;
-            a.fold1[at * a.dp + k] = (rel > -1.0e6 ? (float)rel : -1.0e6f) + (before ? before[k] : 0.0f);
+            a.fold1[at * a.dp + k] = (float)(rel > kFarRow ? rel : kFarRow) + (before ? before[k] : 0.0f);
         }
     }
-    if (threadIdx.x == 0) a.gmax[at] = mx;
+    if (threadIdx.x == 0) a.gmax[at] = mx + top2;
 }
 
 // the initial state (identity, or a converted one that lies there already): its entries, its keys under the first total's fold and without.
@@ -740,9 +786,13 @@ __global__ __launch_bounds__(256) void start_state_kernel(StartArgs a)
     }
 }
 
-__global__ __launch_bounds__(256) void fill_keys_kernel(int *p, size_t n)
+// n keys; nz zeros (no more than keys)
+__global__ __launch_bounds__(256) void fill_keys_kernel(int *p, size_t n, double *z, size_t nz)
 {
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = INT_MIN;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+        p[i] = INT_MIN;
+        if (i < nz) z[i] = 0.0;
+    }
 }
 
 struct LmmeSplitPlan {
@@ -821,7 +871,7 @@ struct SplitPlan {
     long long L, C, C1;  // chunk length, chunks per item, chunks whose products phase 1 forms
     long long places;    // of converted matrices a chain: all of them, converted once, or two, converted step by step in both phases
     int dp, mp;
-    size_t x, shifts, xt, raw, tot, fold1, fold2, gmax, car, start_shifts, keys, keys_count, e, total;
+    size_t x, shifts, rel, top, xt, raw, tot, fold1, fold2, gmax, top2, car, start_shifts, keys, keys_count, e, total;
     size_t key_round, key_tot, key_car1, key_car2, e_round, e_tot, e_car; // offsets in elements within keys, e
 };
 
@@ -873,6 +923,8 @@ SplitPlan plan_split(long long T, int d, int m, long long batch, long long reque
     auto take = [&](size_t bytes) { size_t o = off; off += goom::align_up(bytes, 256); return o; };
     p.x = take(slots * mat * 6);
     p.shifts = take(slots * p.dp * 4);
+    p.rel = take(slots * p.dp * 4);
+    p.top = take(slots * 8);
     const bool products = p.C1 > 0 && p.L > 1;
     p.xt = take(products ? chains * mat * 6 : 0);
     p.tot = take(products ? chains * mat * 4 : 0);
@@ -880,6 +932,7 @@ SplitPlan plan_split(long long T, int d, int m, long long batch, long long reque
     p.fold1 = take(chains * p.dp * 4);
     p.fold2 = take(chains * p.dp * 4);
     p.gmax = take(chains * 8);
+    p.top2 = take(chains * 8);
     p.car = take((size_t)batch * (p.C + 1) * p.mp * p.dp * 4);
     p.start_shifts = take((size_t)batch * p.mp * 4);
     size_t k = 0;
@@ -896,11 +949,6 @@ SplitPlan plan_split(long long T, int d, int m, long long batch, long long reque
     p.e = take(k * 8);
     p.total = off;
     return p;
-}
-
-__global__ __launch_bounds__(256) void fill_zero_kernel(double *p, size_t n)
-{
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0.0;
 }
 
 } // namespace
@@ -928,7 +976,8 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
     const int rows = mp > dp ? mp : dp;
     const float2 *Mg = static_cast<const float2 *>(M);
     __bf16 *X = reinterpret_cast<__bf16 *>(w + p.x);
-    float *shifts = reinterpret_cast<float *>(w + p.shifts);
+    float *shifts = reinterpret_cast<float *>(w + p.shifts), *rel = reinterpret_cast<float *>(w + p.rel);
+    double *top = reinterpret_cast<double *>(w + p.top), *top2 = reinterpret_cast<double *>(w + p.top2);
     float *raw[2] = {reinterpret_cast<float *>(w + p.raw), reinterpret_cast<float *>(w + p.raw) + chains * rows * dp};
     float *car = reinterpret_cast<float *>(w + p.car);
     float *fold1 = reinterpret_cast<float *>(w + p.fold1), *fold2 = reinterpret_cast<float *>(w + p.fold2);
@@ -948,16 +997,20 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
     auto convert = [&](long long s0, long long per_chain) {
         RowsArgs r{Mg, X, shifts, d, d, dp, dp, T, L, C, per_chain, s0, p.places};
         hipLaunchKernelGGL(split_rows_kernel, dim3(dp / 4, (unsigned)(chains * per_chain)), dim3(256), 0, st, r);
+        RelativeArgs q{shifts, rel, top, dp, per_chain, s0, p.places};
+        hipLaunchKernelGGL(relative_shifts_kernel, dim3((unsigned)(chains * per_chain)), dim3(256), 0, st, q);
     };
     auto planes = [&](long long s) { return Pieces<const __bf16>{X + s % p.places * 3 * mat, C * p.places * 3 * mat, p.places * 3 * mat}; };
     auto row_shifts = [&](long long s) { return Pieces<const float>{shifts + s % p.places * dp, C * p.places * dp, p.places * dp}; };
-    auto fill_keys = [&](int *k, size_t n) {
+    auto relative = [&](long long s) { return Pieces<const float>{rel + s % p.places * dp, C * p.places * dp, p.places * dp}; };
+    auto tops = [&](long long s) { return Pieces<const double>{top + s % p.places, C * p.places, p.places}; };
+    auto fill_keys = [&](int *k, size_t n, double *z, size_t nz) {
         const unsigned g = (unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
-        hipLaunchKernelGGL(fill_keys_kernel, dim3(g), dim3(256), 0, st, k, n);
+        hipLaunchKernelGGL(fill_keys_kernel, dim3(g), dim3(256), 0, st, k, n, z, nz);
     };
 
     prof_begin(ctx, "scan_large_convert");
-    fill_keys(keys, p.keys_count);
+    fill_keys(keys, p.keys_count, e_round[0], (size_t)chains * rows); // (the exponents outside of the chunks' first matrices)
     if (all) convert(0, L);
     prof_end(ctx);
 
@@ -967,9 +1020,8 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
         prof_begin(ctx, "scan_large_phase1_chunk_products");
         const unsigned nchains = (unsigned)(batch * p.C1);
         if (!all) convert(0, 1);
-        FirstArgs f{Mg, row_shifts(0), {raw[0], C * rows * dp, (long long)rows * dp}, {key_round[0], C * rows, rows}, d, dp, (int)p.C1, T, L};
+        FirstArgs f{Mg, row_shifts(0), relative(0), {raw[0], C * rows * dp, (long long)rows * dp}, {key_round[0], C * rows, rows}, d, dp, (int)p.C1, T, L};
         hipLaunchKernelGGL(first_state_kernel, dim3(dp / 32, dp / 32, nchains), dim3(256), 0, st, f);
-        hipLaunchKernelGGL(fill_zero_kernel, dim3(64), dim3(256), 0, st, e_round[0], (size_t)chains * rows);
         for (long long s = 1; s < L; ++s) {
             if (!all) convert(s, 1);
             SplitGemm a{};
@@ -978,12 +1030,13 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
             a.X = planes(s);
             a.row_shift = row_shifts(s);
             a.Yr = {raw[(s - 1) & 1], C * rows * dp, (long long)rows * dp};
-            a.fold = row_shifts(s - 1);
+            a.fold = relative(s - 1);
+            a.extra = tops(s - 1);
             a.key = {key_round[(s - 1) % 3], C * rows, rows};
             a.e_in = {e_round[(s - 1) & 1], C * rows, rows};
             if (s + 1 < L) {
                 a.Ct = {raw[s & 1], C * rows * dp, (long long)rows * dp};
-                a.fold1 = row_shifts(s);
+                a.fold1 = relative(s);
                 a.key1 = {key_round[s % 3], C * rows, rows};
                 a.clear = {key_round[(s + 1) % 3], C * rows, rows};
                 a.e_out = {e_round[s & 1], C * rows, rows};
@@ -1001,14 +1054,15 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
     // ---- phase 2: prefixes at the chunk boundaries (and, for a reduction, the final product)
     prof_begin(ctx, "scan_large_phase2_carries");
     Pieces<const __bf16> xt = planes(0); // (chunks of one step are their own products)
-    const Pieces<const float> tot_shifts = row_shifts(L - 1);
+    const Pieces<const float> tot_shifts = row_shifts(L - 1), tot_rel = relative(L - 1);
+    const Pieces<const double> tot_top = tops(L - 1);
     if (products) {
         __bf16 *xtp = reinterpret_cast<__bf16 *>(w + p.xt);
         TotalsArgs t{reinterpret_cast<const float *>(w + p.tot), key_tot, e_tot, xtp, dp, C};
         hipLaunchKernelGGL(totals_planes_kernel, dim3(dp / 4, (unsigned)p.C1, (unsigned)batch), dim3(256), 0, st, t);
         xt = {xtp, C * 3 * mat, 3 * mat};
     }
-    FoldArgs f{products ? key_tot : nullptr, e_tot, tot_shifts, fold1, fold2, gmax, dp, d, C, p.C1};
+    FoldArgs f{products ? key_tot : nullptr, e_tot, tot_rel, tot_top, fold1, fold2, gmax, top2, dp, d, C, p.C1};
     hipLaunchKernelGGL(totals_fold_kernel, dim3((unsigned)C, (unsigned)batch), dim3(256), 0, st, f);
     float *start_shifts = reinterpret_cast<float *>(w + p.start_shifts);
     if (init) {
@@ -1041,7 +1095,7 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
             a.key1 = {key_car1 + (c + 1) * mp, carm, 0};
         }
         if (!final_only) { // as chunk c + 1 reads it
-            a.fold2 = a.row_shift;
+            a.fold2 = {tot_rel.p + c * tot_rel.chunk, tot_rel.item, 0};
             a.key2 = {key_car2 + (c + 1) * mp, carm, 0};
         } else if (last) {
             a.P = static_cast<float2 *>(P);
@@ -1057,7 +1111,7 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
 
     // ---- phase 3: every chunk from its incoming prefix, all prefixes stored (a reduction of a single chunk stores the last)
     prof_begin(ctx, final_only ? "scan_large_single_chunk" : "scan_large_phase3_outputs");
-    fill_keys(keys + p.key_round, 3 * chains * rows);
+    fill_keys(keys + p.key_round, 3 * chains * rows, nullptr, 0);
     for (long long s = 0; s < L; ++s) {
         if (!all) convert(s, 1);
         SplitGemm a{};
@@ -1069,17 +1123,19 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
         if (s == 0) {
             a.Yr = {car, car_item, state};
             a.fold = {fold2, C * dp, dp};
+            a.extra = {top2, C, 1};
             a.key = {key_car2, carm, mp};
             a.e_in = {e_car, carm, mp};
         } else {
             a.Yr = {raw[(s - 1) & 1], C * rows * dp, (long long)rows * dp};
-            a.fold = row_shifts(s - 1);
+            a.fold = relative(s - 1);
+            a.extra = tops(s - 1);
             a.key = {key_round[(s - 1) % 3], C * rows, rows};
             a.e_in = {e_round[(s - 1) & 1], C * rows, rows};
         }
         if (s + 1 < L) {
             a.Ct = {raw[s & 1], C * rows * dp, (long long)rows * dp};
-            a.fold1 = row_shifts(s);
+            a.fold1 = relative(s);
             a.key1 = {key_round[s % 3], C * rows, rows};
             a.clear = {key_round[(s + 1) % 3], C * rows, rows};
             a.e_out = {e_round[s & 1], C * rows, rows};

@@ -59,6 +59,39 @@ def test_scan_of_rows_far_apart(G, oracle):  # noqa: F811
         compare(host(G.scan(dev(Z), chunk_len=chunk)), re, sg, kap, name=f"far apart chunk={chunk}", max_ill_fraction=0.05, well=well)
 
 
+def whole_power(x):
+    """The first float from x on that is a float's power of two to a quarter (the conversion corrects the product with log2(e) by no more than a few units)."""
+    x = np.float32(x)
+    while abs(float(x) * np.log2(np.e) - float(np.float32(float(x) * np.log2(np.e)))) > 0.25:
+        x = np.nextafter(x, np.float32(np.inf))
+    return float(x)
+
+
+# (log-magnitudes whose last place is 128 and more: the factors' entries are all alike, and so are the states', whose sums are of one sign)
+@pytest.mark.parametrize("reduce", [False, True])
+@pytest.mark.parametrize("T,d,m,chunk", [(6, 140, None, 2), (5, 300, 3, 1), (7, 270, None, 7), (9, 260, None, 0)])
+@pytest.mark.parametrize("magnitude", [2.0e9, -2.0e9, 3.0e12])
+def test_magnitudes_of_any_size(G, T, d, m, chunk, magnitude, reduce):  # noqa: F811
+    step = whole_power(magnitude)
+    Z = np.full((1, T, d, d), step, dtype=np.complex64)
+    Z[0, 1, 5] = -np.inf
+    init = None if m is None else dev(np.full((1, d, m), -step, dtype=np.complex64))
+    if reduce:
+        got = host(G.reduce(dev(Z), init, chunk_len=chunk))[:, None]
+    else:
+        got = host(G.scan(dev(Z), init, chunk_len=chunk))
+    first = T if reduce else 1
+    want = np.arange(first, T + 1) * step - (0.0 if m is None else step)
+    assert not got[got.real > -np.inf].imag.any()
+    for i, w in enumerate(want):
+        z = got[0, i].real
+        if first + i == 2:  # the empty row's own step
+            assert np.all(z[5] == -np.inf)
+            z = np.delete(z, 5, axis=0)
+        # a rounding of each factor's shift and of the state's logarithm
+        assert np.abs(z - w).max() <= 2.0 ** -22 * T * abs(step), (first + i, z.min(), z.max(), w)
+
+
 def test_static_scratch(G, oracle):  # noqa: F811
     import torch
     for T, d in ((4, 300), (24, 300), (12, 520)):  # beside the room for it, and too large for that

@@ -199,9 +199,10 @@ __device__ inline void finish(const SplitGemm &a, long long item, long long chun
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     const float x = v[i][j][r];
+                    const float zero = RAW && w[r] == -CF::neg_inf() ? w[r] : CF::neg_inf(); // (a chain's row that is not finite)
                     if (row[i] + r < a.n && col0 + 32 * j < a.m)
                         o[(size_t)(row[i] + r) * a.m + col0 + 32 * j] =
-                            float2{x != 0.0f ? log_of(x, eo[j] + (double)w[r]) : CF::neg_inf(), x < 0.0f ? CF::pi() : 0.0f};
+                            float2{x != 0.0f ? log_of(x, eo[j] + (double)w[r]) : zero, x < 0.0f ? CF::pi() : 0.0f};
                 }
         }
     }
@@ -434,7 +435,8 @@ template <bool RAW> void launch_gemm_split(hipStream_t st, const SplitGemm &a, u
 
 // ---- rows of GOOM matrices into planes.  Row r of matrix b: 2^(log2|x| - shift), shift = the row's whole power of two less kLift.  One wave a
 // row (up to 1024 entries, sixteen a lane, in pairs), four rows a workgroup: grid (rows_padded / 4, matrices), 256 threads.  A row without entries
-// has the shift -inf.
+// has the shift -inf; of a chain's matrices a row with an infinite entry or a NaN has inf, and no entries: the product's row is infinite
+// then, and so are all states after it.
 // A chain of matrices (L > 0): matrix b is step s = s0 + b % per_chain of chain b / per_chain = item * C + chunk, and goes to place
 // chain * places + s % places; beyond the chunk or T it is the identity.
 struct RowsArgs {
@@ -490,6 +492,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(RowsArgs a)
     const bool pairs = (a.d & 1) == 0;
     float2 e[8][2];
     float mx = CF::neg_inf();
+    bool bad = false;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         const int j = 2 * lane + 128 * r;
@@ -505,7 +508,9 @@ __global__ __launch_bounds__(256) void split_rows_kernel(RowsArgs a)
             }
         }
         mx = fmaxf(mx, fmaxf(e[r][0].x, e[r][1].x));
+        bad = bad || e[r][0].x != e[r][0].x || e[r][1].x != e[r][1].x;
     }
+    if (a.L > 0 && bad) mx = -CF::neg_inf();
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
     const float sh = ceilf(mx * kLog2eF) - kLift;

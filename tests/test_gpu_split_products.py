@@ -92,6 +92,18 @@ def test_magnitudes_of_any_size(G, T, d, m, chunk, magnitude, reduce):  # noqa: 
         assert np.abs(z - w).max() <= 2.0 ** -22 * T * abs(step), (first + i, z.min(), z.max(), w)
 
 
+@pytest.mark.parametrize("chunk", [2, 6, 1])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("d", [200, 300])
+def test_entries_that_are_not_finite_show(G, oracle, d, value, chunk):  # noqa: F811
+    """In the row that they lie in, and in every state from the next step on."""
+    T = 6
+    Z = oracle.to_goom(si.normal_chain(si.BASE_SEED + 1450, T, d))
+    Z.real[2, 3, 4] = value
+    failed = [(z != z) | (z == np.inf) for z in host(G.scan(dev(Z[None]), chunk_len=chunk))[0].real]
+    assert not np.any(failed[:2]) and np.all(failed[2][3]) and not np.any(np.delete(failed[2], 3, axis=0)) and np.all(failed[3:])
+
+
 def test_static_scratch(G, oracle):  # noqa: F811
     import torch
     for T, d in ((4, 300), (24, 300), (12, 520)):  # beside the room for it, and too large for that

@@ -8,7 +8,8 @@
 //   * a lane converts four adjacent entries of a row (four lanes share a row: two lane exchanges for the
 //     row's maximum); pointers advance by a constant per step;
 //   * 8 x 8 chains travel in pairs: the tile is block diagonal, chain 2 w in rows and columns 0..7 and
-//     chain 2 w + 1 in 8..15, and so is the state, so one wave's instructions serve both;
+//     chain 2 w + 1 in 8..15, and so is the state, so one wave's instructions serve both.  Outside of the blocks neither
+//     the one's row exponents nor what a NaN leaves there reaches the other;
 //   * as in the larger kernel the product is not rescaled after a step: the row exponents go into the
 //     next factor's exponent arguments, columns are renormalised every fourth step.
 //   * other sizes below 16 are padded to the next of the two with zero rows and columns (their entries come one by
@@ -30,7 +31,7 @@ template <int D, bool OUT, bool RAG> __global__ __launch_bounds__(64, 6) void sm
     typedef Comp<float> C;
     constexpr int PACK = D == 8 ? 2 : 1;
     __shared__ __align__(16) float tile[16 * kSmallLDA];
-    __shared__ __align__(16) float nsh[16];
+    __shared__ __align__(16) float nsh[PACK == 2 ? 20 : 16]; // (PACK 2: the last four for the lanes outside of the blocks)
 
     const int dd = RAG ? a.d : D, mm = RAG ? a.m : D;
     const int lane = threadIdx.x;
@@ -76,6 +77,8 @@ template <int D, bool OUT, bool RAG> __global__ __launch_bounds__(64, 6) void sm
         len = o > len ? o : len;
     }
     if (len <= 0) return;
+    if (PACK == 2 && lane < 4) nsh[16 + lane] = 0.0f;
+    const int rj_at = cvalid ? c4 : 16;
 
     // ---- initial state
     float st[4];
@@ -201,7 +204,7 @@ template <int D, bool OUT, bool RAG> __global__ __launch_bounds__(64, 6) void sm
         // ---------------------------------------------------------------- product
         const f4 av = *reinterpret_cast<const f4 *>(&tile[c * kSmallLDA + 4 * g]);
         nv = *reinterpret_cast<const f4 *>(&nsh[4 * g]);
-        rj = *reinterpret_cast<const f4 *>(&nsh[c4]);
+        rj = *reinterpret_cast<const f4 *>(&nsh[rj_at]);
         acc = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc = C::mfma(av[v], st[v], acc);
@@ -219,7 +222,7 @@ template <int D, bool OUT, bool RAG> __global__ __launch_bounds__(64, 6) void sm
         }
         // ---------------------------------------------------------------- state: raw; columns renormalised now and then
 #pragma unroll
-        for (int v = 0; v < 4; ++v) st[v] = acc[v];
+        for (int v = 0; v < 4; ++v) st[v] = svalid ? acc[v] : 0.0f;
         if (slot == kAhead - 1 && t + 1 < len) {
             float cm = -300.0f;
 #pragma unroll
@@ -238,7 +241,7 @@ template <int D, bool OUT, bool RAG> __global__ __launch_bounds__(64, 6) void sm
         // becomes a left factor); the padding of the chain's 16 x 16 slot is written as zeros
         float cm = C::neg_inf();
 #pragma unroll
-        for (int v = 0; v < 4; ++v) cm = C::max_(cm, C::exponent_of(st[v]) + nv[v]);
+        for (int v = 0; v < 4; ++v) cm = C::max_(cm, svalid ? C::exponent_of(st[v]) + nv[v] : C::neg_inf());
         cm = C::xor16_32_max(cm);
         float amax = 0.0f;
 #pragma unroll

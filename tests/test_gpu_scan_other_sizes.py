@@ -35,3 +35,26 @@ def test_zeros_and_wide_entries(G, oracle, d):  # noqa: F811
     re, sg, kap, well = with_sensitivity(lambda z: oracle.scan(z, return_kappa=True), [Z], np.float32, nprobe=2)
     for chunk in (24, 5):
         compare(host(G.scan(dev(Z), chunk_len=chunk)), re, sg, kap, name=f"zeros d={d} chunk={chunk}", max_ill_fraction=0.05, well=well)
+
+
+# (chunks of one sequence, and of neighbouring sequences, share a wave up to 8 rows)
+@pytest.mark.parametrize("value", ["large", "small", "nan", "inf"])
+@pytest.mark.parametrize("d", [3, 5, 8, 16])
+@pytest.mark.parametrize("chunk", [2, 4, 6, 16])
+def test_chains_of_a_wave_do_not_meet(G, oracle, d, chunk, value):  # noqa: F811
+    """One factor's magnitude, NaN or infinity changes no bit of what comes before it, or of another sequence."""
+    T, at = 34, 21
+    z = np.stack([oracle.to_goom(si.normal_chain(si.BASE_SEED + 4100 + d + i, T, d)) for i in range(3)])
+    b = np.stack([oracle.to_goom(si.normal_f32(si.BASE_SEED + 4200 + i, 3, T * d).reshape(T, d)) for i in range(3)])
+    w = z.copy()
+    if value in ("large", "small"):
+        w.real[1, at] += 1e6 if value == "large" else -1e6
+    else:
+        w.real[1, at, 1, d - 1] = np.nan if value == "nan" else np.inf
+    for run in (lambda x: G.scan(dev(x), chunk_len=chunk), lambda x: G.affine_scan(dev(x), dev(b), chunk_len=chunk)):
+        plain, other = host(run(z)), host(run(w))
+        for i in range(3):
+            t = at if i == 1 else T
+            assert np.array_equal(plain[i, :t].view(np.int64), other[i, :t].view(np.int64)), (i, np.argwhere(plain[i, :t] != other[i, :t])[:4])
+    plain, other = host(G.reduce(dev(z), chunk_len=chunk)), host(G.reduce(dev(w), chunk_len=chunk))
+    assert np.array_equal(plain[[0, 2]], other[[0, 2]])

@@ -28,6 +28,15 @@ def test_short_sequences(G, oracle, d, ctype):  # noqa: F811
         compare(got, re, sg, kap, name=f"T{T}d{d}", max_ill_fraction=0.25, well=well)
 
 
+@pytest.mark.parametrize("T", [28, 31])
+def test_logarithms_of_16_rows(G, oracle, T):  # noqa: F811
+    """One chunk, whose logarithms are taken of mantissas below 1: a last place of 2^-24 there, and one of the result's (the chunks' own walk: 2^-20)."""
+    Az, bz, h0 = inputs(oracle, 1460, 8, T, 16, np.complex64, False)
+    re = oracle.affine_scan(Az, bz, h0=h0, return_kappa=True)[0]
+    got = host(G.affine_scan(dev(Az), dev(bz), dev(h0)))
+    assert np.median(np.abs(got.real - re)) <= 2.0 ** -22 * max(1.0, np.median(np.abs(re)))
+
+
 @pytest.mark.parametrize("d,former", [(64, 20), (24, 9)])
 def test_in_the_room_of_longer_chunks(G, oracle, d, former):  # noqa: F811
     T, batch = 60, 3

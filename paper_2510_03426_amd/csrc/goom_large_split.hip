@@ -591,11 +591,11 @@ __global__ __launch_bounds__(256) void split_column_shift_kernel(const float2 *_
     }
 }
 
-// transposed, as planes Y[3][k_padded / 16][cols_padded][16] (FLOATS: as floats, one of them).  grid (cols_padded / 32, k_padded / 32 rounded
-// up, matrices), 256 threads.
+// transposed, as planes Y[3][k_padded / 16][cols_padded][16] (FLOATS: as floats, one of them), a matrix every `stride` values.  grid (cols_padded /
+// 32, k_padded / 32 rounded up, matrices), 256 threads.
 template <bool FLOATS>
-__global__ __launch_bounds__(256) void split_columns_kernel(const float2 *__restrict__ B, const float *__restrict__ shifts, void *__restrict__ Yv, int d, int m,
-                                                            int cols_padded, int k_padded)
+__global__ __launch_bounds__(256) void split_columns_kernel(const float2 *__restrict__ B, const float *__restrict__ shifts, void *__restrict__ Yv, long long stride,
+                                                            int d, int m, int cols_padded, int k_padded)
 {
     __shared__ float tile[32][33];
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
@@ -614,12 +614,12 @@ __global__ __launch_bounds__(256) void split_columns_kernel(const float2 *__rest
     }
     __syncthreads();
     if constexpr (FLOATS) {
-        float *Y = static_cast<float *>(Yv) + (size_t)b * cols_padded * k_padded;
+        float *Y = static_cast<float *>(Yv) + b * stride;
 #pragma unroll
         for (int r = 0; r < 4; ++r) Y[((size_t)((j0 + tx) >> 4) * cols_padded + c0 + ty + 8 * r) * 16 + (tx & 15)] = tile[tx][ty + 8 * r];
     } else {
         const size_t plane = (size_t)cols_padded * k_padded;
-        __bf16 *Y = static_cast<__bf16 *>(Yv) + (size_t)b * 3 * plane;
+        __bf16 *Y = static_cast<__bf16 *>(Yv) + b * stride;
         const int jj = 2 * (threadIdx.x & 15), cc = threadIdx.x >> 4;
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
@@ -841,7 +841,8 @@ int launch_lmme_split(goom_ctx *ctx, const void *A, const void *B, void *C, long
     RowsArgs r{static_cast<const float2 *>(A), X, rs, n, d, p.Np, p.Kp, 0, 0, 0, 0, 0, 0};
     hipLaunchKernelGGL(split_rows_kernel, dim3(p.Np / 4, nb), dim3(256), 0, st, r);
     hipLaunchKernelGGL(split_column_shift_kernel, dim3((p.Mp + 63) / 64, nb), dim3(256), 0, st, static_cast<const float2 *>(B), cs, d, m, p.Mp);
-    hipLaunchKernelGGL(split_columns_kernel<false>, dim3(p.Mp / 32, (p.Kp + 31) / 32, nb), dim3(256), 0, st, static_cast<const float2 *>(B), cs, Y, d, m, p.Mp, p.Kp);
+    hipLaunchKernelGGL(split_columns_kernel<false>, dim3(p.Mp / 32, (p.Kp + 31) / 32, nb), dim3(256), 0, st, static_cast<const float2 *>(B), cs, Y,
+                       3LL * p.Mp * p.Kp, d, m, p.Mp, p.Kp);
     prof_end(ctx);
     if (int s = check_hip(ctx, hipGetLastError(), "launch LMME operand kernels")) return s;
     prof_begin(ctx, "lmme_large_gemm");
@@ -1073,9 +1074,8 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
     if (init) {
         hipLaunchKernelGGL(split_column_shift_kernel, dim3(mp / 64, (unsigned)batch), dim3(256), 0, st, static_cast<const float2 *>(init), start_shifts, d, m, mp);
         // (into the first carry's place, which lies a whole item of carries from the next item's)
-        for (long long b = 0; b < batch; ++b)
-            hipLaunchKernelGGL(split_columns_kernel<true>, dim3(mp / 32, dp / 32, 1), dim3(256), 0, st, static_cast<const float2 *>(init) + b * d * m,
-                               start_shifts + b * mp, static_cast<void *>(car + b * car_item), d, m, mp, dp);
+        hipLaunchKernelGGL(split_columns_kernel<true>, dim3(mp / 32, dp / 32, (unsigned)batch), dim3(256), 0, st, static_cast<const float2 *>(init), start_shifts,
+                           static_cast<void *>(car), car_item, d, m, mp, dp);
     }
     StartArgs s0{{car, car_item, state}, {p.C1 > 0 ? key_car1 : nullptr, carm, mp}, {key_car2, carm, mp}, {e_car, carm, mp}, {fold1, C * dp, dp},
                  init ? start_shifts : nullptr, d, dp, mp};

@@ -104,6 +104,33 @@ def test_entries_that_are_not_finite_show(G, oracle, d, value, chunk):  # noqa: 
     assert not np.any(failed[:2]) and np.all(failed[2][3]) and not np.any(np.delete(failed[2], 3, axis=0)) and np.all(failed[3:])
 
 
+def launches_of(G, run):  # noqa: F811
+    """How much a call enqueues: the nodes of the graph that it is captured into."""
+    import ctypes as C
+    import torch
+    run()  # (sizes the workspace)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        G.set_stream(torch.cuda.current_stream())
+        run()
+    G.set_stream(torch.cuda.default_stream())
+    n = C.c_size_t()
+    assert G.lib.hipGraphGetNodes(C.c_void_p(graph.raw_cuda_graph()), None, C.byref(n)) == 0
+    return n.value
+
+
+def test_items_share_launches(G, oracle):  # noqa: F811
+    T, d, m = 3, 130, 4
+    count = []
+    for batch in (2, 20):
+        z = dev(np.stack([oracle.to_goom(si.normal_chain(si.BASE_SEED + 1480 + i, T, d)) for i in range(batch)]))
+        init = dev(oracle.to_goom(si.normal_f32(si.BASE_SEED + 1490, 1, batch * d * m).reshape(batch, d, m)))
+        out = dev(np.zeros((batch, T, d, m), dtype=np.complex64))
+        count.append(launches_of(G, lambda: G.scan(z, init, chunk_len=T, out=out)))
+    assert count[0] == count[1] > 0
+
+
 def test_static_scratch(G, oracle):  # noqa: F811
     import torch
     for T, d in ((4, 300), (24, 300), (12, 520)):  # beside the room for it, and too large for that

@@ -419,10 +419,16 @@ template <bool RAW> __global__ __launch_bounds__(256, 2) void gemm_split_few_ker
     finish<1, 1, RAW>(a, item, chunk, v, row, bx * 32 + c, by == 0 && wave == 0, h);
 }
 
-// Do products of n x m (any sizes) fill the chip in 128 x 128 tiles?  512 x 512 x 512, one after the other (16 tiles): 18 us in 64 x 64 tiles of the large kernel's
-// kind, 9.4 in the other's; from 64 tiles on the large kernel's sharing of operands counts.
-// (Tiles' worth of entries: 64 products of 64 x 1000 x 64 are 64 tiles that are three quarters padding, 49 us, and 20 in the other's.)
-bool split_in_tiles(int n, int m, long long products) { return (double)n * m * (double)products >= 64.0 * 128 * 128; }
+// Do products of n x m (any sizes) fill the chip in 128 x 128 tiles, and the tiles?  Before, the large kernel's sharing of operands does not count for its
+// latency, and tiles that are more than two thirds padding cost more than it saves.  In us, an LMME in these tiles / in the other kernel's of 32 x 32 (which
+// have `few` entries in all, padding included): 64 tiles, 4 x 512^3 52 / 37, 64 x 128 x 1024 x 128 101 / 97; 80 and more, 32 x 200^3 44 / 46, 64 x 200^3
+// 51 / 74, 128 x 128 x 1024 x 128 174 / 204, 64 x 160 x 1000 x 160 149 / 163; mostly padding, 256 x 64 x 1000 x 64 282 / 171, 1024 of them 1114 /
+// 673, 1000 x 130 x 300 x 20 448 / 248.
+bool split_in_tiles(int n, int m, long long products)
+{
+    const double few = (double)pad_to(n, 32) * pad_to(m, 32) * (double)products, tiles = (double)pad_to(n, 128) * pad_to(m, 128) * (double)products;
+    return few >= 80.0 * 128 * 128 && tiles <= 3.0 * few;
+}
 
 // products: of M x N x K (padded: K to 16, M and N to 128, or to 32 if they are too few)
 template <bool RAW> void launch_gemm_split(hipStream_t st, const SplitGemm &a, unsigned products, bool in_tiles)

@@ -182,6 +182,14 @@ def test_workspace_queries(lib):
     assert w32 == 2 * (3 * 1024 * 1024 + 2 * 1024) * 4 and w64 == 2 * w32
 
 
+def test_products_that_tiles_would_pad_threefold_are_not_padded(lib):
+    """However many there are: their operands' rows are padded to 32, and the room for them grows as their number."""
+    for n, d, m in ((64, 1000, 64), (130, 300, 20), (40, 1000, 40)):
+        few = lib.goom_lmme_workspace_bytes(32, n, d, m, 0, 0)
+        for batch in (256, 1024, 4096):
+            assert lib.goom_lmme_workspace_bytes(batch, n, d, m, 0, 0) == batch // 32 * few
+
+
 def test_product_path_has_no_cpu_fallback():
     # the package never imports the oracle, and the binding refuses to run without the library
     import paper_2510_03426_amd.binding as b

@@ -151,7 +151,10 @@ int goom_count_nonfinite(goom_ctx *ctx, const void *z, size_t n, int dtype, uint
  * workspace: goom_lmme_workspace_bytes(...) bytes (may be 0 -> NULL allowed).  For n = d = m = 128 with
  * GOOM_LMME_EXACT the query asks for 256 components per pair, in which the product hands its row and
  * column shifts to the repair pass; there the workspace is optional (NULL or a smaller one: the repair
- * pass takes the maxima of the operands itself, more slowly, with the same results within tolerance). */
+ * pass takes the maxima of the operands itself, more slowly, with the same results within tolerance).  For
+ * GOOM_C64 above GOOM_MAX_DIM a long inner dimension makes the query ask for more than operands, shifts and
+ * product take as floats (rows padded to 128); a workspace of that size does too (the product is then
+ * taken on the float matrix instruction). */
 int goom_lmme(goom_ctx *ctx, const void *A, const void *B, void *C, int64_t batch, int n, int d,
               int m, int dtype, uint32_t flags, void *workspace, size_t workspace_bytes);
 size_t goom_lmme_workspace_bytes(int64_t batch, int n, int d, int m, int dtype, uint32_t flags);

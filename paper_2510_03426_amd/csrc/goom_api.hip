@@ -830,10 +830,15 @@ int goom_lmme(goom_ctx *ctx, const void *A, const void *B, void *C, int64_t batc
     if (lmme_is_large(n, d, m)) {
         // beyond the register-resident kernels: scaled operands, a tiled GEMM and a store pass, through the workspace
         const bool f32 = dtype == GOOM_C64;
-        const size_t need = f32 ? lmme_split_workspace_bytes(batch, n, d, m) : lmme_large_f64_workspace_bytes(batch, n, d, m);
+        size_t need = f32 ? lmme_split_workspace_bytes(batch, n, d, m) : lmme_large_f64_workspace_bytes(batch, n, d, m);
+        // (a workspace too small for the products in parts may do for those in floats, where the inner dimension is long)
+        const bool floats = f32 && workspace_bytes < need && workspace_bytes >= lmme_large_workspace_bytes(batch, n, d, m);
+        if (floats) need = lmme_large_workspace_bytes(batch, n, d, m);
         if (int s = check_workspace(ctx, workspace, workspace_bytes, need)) return s;
         if (int s = need_ctx(ctx)) return s;
-        if (int s = f32 ? launch_lmme_split(ctx, A, B, C, batch, n, d, m, workspace) : launch_lmme_large_f64(ctx, A, B, C, batch, n, d, m, workspace))
+        if (int s = floats ? launch_lmme_large(ctx, A, B, C, batch, n, d, m, workspace)
+                    : f32  ? launch_lmme_split(ctx, A, B, C, batch, n, d, m, workspace)
+                           : launch_lmme_large_f64(ctx, A, B, C, batch, n, d, m, workspace))
             return s;
         if (flags & GOOM_LMME_EXACT) return launch_lmme_exact(ctx, A, B, C, batch, n, d, m, dtype);
         return GOOM_OK;

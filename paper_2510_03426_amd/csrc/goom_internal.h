@@ -137,6 +137,9 @@ size_t lyap_steps_partial_bytes(long long batch, int d);
 int launch_lle_epilogue(goom_ctx *ctx, const void *v, double *lle, long long batch, int d, int dtype, double scale);
 int launch_uniform_u0(goom_ctx *ctx, void *u, long long batch, int d, int dtype);
 
+// goom_large.hip: LMME of shapes above 128 with float components, in less room than the products in parts want of a long inner dimension
+size_t lmme_large_workspace_bytes(long long batch, int n, int d, int m);
+int launch_lmme_large(goom_ctx *ctx, const void *A, const void *B, void *C, long long batch, int n, int d, int m, void *ws);
 // goom_large_split.hip: LMME of shapes above 128 and scans of large matrices, float components in three parts on the bf16 matrix instruction
 size_t lmme_split_workspace_bytes(long long batch, int n, int d, int m);
 int launch_lmme_split(goom_ctx *ctx, const void *A, const void *B, void *C, long long batch, int n, int d, int m, void *ws);

@@ -1,7 +1,8 @@
-// Scans and reductions of large float matrices with the float matrix instruction: the shared driver's GEMM (128 x 128 tile per workgroup, 64 x 64
-// per wave, K in steps of 16 through double-buffered LDS), the conversion of an initial state, and the register-resident kernels for
-// 128 < d <= 256.  These serve long chains of that range (goom_large_split.hip says where the line lies) and workspaces too small for the products
-// in parts that other calls take.
+// Products (LMME), scans and reductions of large float matrices with the float matrix instruction: a GEMM (128 x 128 tile per workgroup, 64 x 64
+// per wave, K in steps of 16 through double-buffered LDS) between passes that scale its operands, transpose the right one and take the
+// logarithm; for scans the shared driver's, and the register-resident kernels for 128 < d <= 256.  These serve long chains of that range
+// (goom_large_split.hip says where the line lies) and workspaces too small for the products in parts that other calls take, which want six bytes an
+// entry of the operands, and of a scan's matrices, where these want four of the operands and of the product.
 #include <cmath>
 
 #include "goom_large_scan.h"
@@ -19,8 +20,44 @@ __device__ inline float signed_scaled(float re, float im, float shift)
     return CF::apply_sign(CF::exp2_shifted(re, shift), im);
 }
 
-// ---- column maxima of an initial state.  grid (ceil(m / 64), batch), block 64 x 4.
-__global__ __launch_bounds__(256) void column_shift_kernel(const float2 *__restrict__ B, double *__restrict__ shifts, int d, int m, int cols_padded)
+// ---- rows of the left operand of a product (LMME).  grid (rows_padded, batch), 256 threads.
+__global__ __launch_bounds__(256) void convert_left_kernel(const float2 *__restrict__ A, float *__restrict__ X, float *__restrict__ shifts,
+                                                           int n, int d, int rows_padded, int k_padded)
+{
+    __shared__ float red[4];
+    const int row = blockIdx.x;
+    const long long b = blockIdx.y;
+    const int tid = threadIdx.x;
+    float *xrow = X + ((size_t)b * rows_padded + row) * k_padded;
+    if (row >= n) { // padding rows
+        for (int j = tid; j < k_padded; j += 256) xrow[j] = 0.0f;
+        if (tid == 0) shifts[(size_t)b * rows_padded + row] = 0.0f;
+        return;
+    }
+    const float2 *arow = A + ((size_t)b * n + row) * d;
+    float mx = -__builtin_huge_valf();
+    for (int j = tid; j < d; j += 256) mx = fmaxf(mx, arow[j].x);
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
+    if ((tid & 63) == 0) red[tid >> 6] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const bool zero_row = !(mx > -__builtin_huge_valf());
+    const float sh = zero_row ? 0.0f : ceilf(mx * kLog2eF);
+    for (int j = tid; j < k_padded; j += 256) {
+        float v = 0.0f;
+        if (j < d && !zero_row) {
+            const float2 e = arow[j];
+            v = signed_scaled(e.x, e.y, sh);
+        }
+        xrow[j] = v;
+    }
+    if (tid == 0) shifts[(size_t)b * rows_padded + row] = sh;
+}
+
+// ---- column maxima of a right operand or an initial state.  grid (ceil(m / 64), batch), block 64 x 4.
+template <typename S>
+__global__ __launch_bounds__(256) void column_shift_kernel(const float2 *__restrict__ B, S *__restrict__ shifts, int d, int m, int cols_padded)
 {
     __shared__ float red[4][64];
     const int cx = threadIdx.x & 63, ry = threadIdx.x >> 6;
@@ -46,13 +83,14 @@ __global__ __launch_bounds__(256) void column_shift_kernel(const float2 *__restr
     __syncthreads();
     if (ry == 0 && col < cols_padded) {
         mx = fmaxf(fmaxf(red[0][cx], red[1][cx]), fmaxf(red[2][cx], red[3][cx]));
-        shifts[(size_t)b * cols_padded + col] = (col < m && mx > -__builtin_huge_valf()) ? (double)ceilf(mx * kLog2eF) : 0.0;
+        shifts[(size_t)b * cols_padded + col] = (col < m && mx > -__builtin_huge_valf()) ? (S)ceilf(mx * kLog2eF) : (S)0;
     }
 }
 
-// ---- the state scaled and transposed: Y[b][col][j] = (+-) 2^(log2|B_j,col| - shift_col).
+// ---- that operand scaled and transposed: Y[b][col][j] = (+-) 2^(log2|B_j,col| - shift_col).
 // grid (cols_padded / 32, k_padded / 32 rounded up, batch), block 32 x 8.
-__global__ __launch_bounds__(256) void convert_right_kernel(const float2 *__restrict__ B, const double *__restrict__ shifts, float *__restrict__ Y,
+template <typename S>
+__global__ __launch_bounds__(256) void convert_right_kernel(const float2 *__restrict__ B, const S *__restrict__ shifts, float *__restrict__ Y,
                                                             int d, int m, int cols_padded, int k_padded)
 {
     __shared__ float tile[32][33];
@@ -184,7 +222,85 @@ inline void launch_gemm_nt(hipStream_t st, const float *X, const float *Y, float
         hipLaunchKernelGGL(gemm_nt_kernel<4>, dim3(gx, gy, gz), dim3(256), 0, st, X, Y, C, M, N, K, sx, sy, sc);
 }
 
+// ---- C'[b][i][k] = GOOM of Ct[b][k][i] 2^(row_shift_i + col_shift_k).
+// grid (ceil(n / 32), ceil(m / 32), batch), block 32 x 8.
+__global__ __launch_bounds__(256) void lmme_store_kernel(const float *__restrict__ Ct, const float *__restrict__ row_shift,
+                                                         const float *__restrict__ col_shift, float2 *__restrict__ Cg, int n, int m,
+                                                         int rows_padded, int cols_padded)
+{
+    __shared__ float tile[32][33];
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int i0 = blockIdx.x * 32, k0 = blockIdx.y * 32;
+    const long long b = blockIdx.z;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int k = k0 + ty + 8 * r, i = i0 + tx; // k < cols_padded and i < rows_padded always (multiples of 128)
+        tile[ty + 8 * r][tx] = Ct[((size_t)b * cols_padded + k) * rows_padded + i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + ty + 8 * r, k = k0 + tx;
+        if (i < n && k < m) {
+            const float x = tile[tx][ty + 8 * r];
+            const float s = row_shift[(size_t)b * rows_padded + i] + col_shift[(size_t)b * cols_padded + k];
+            float2 o;
+            o.x = x != 0.0f ? CF::out_re_f(x, s) : -__builtin_huge_valf();
+            o.y = x < 0.0f ? CF::pi() : 0.0f;
+            Cg[((size_t)b * n + i) * m + k] = o;
+        }
+    }
+}
+
+
+using goom_large::pad_to;
+
 } // namespace
+
+namespace goom {
+
+// workspace: X [batch][Np][Kp], row shifts [batch][Np], Y [batch][Mp][Kp], column shifts [batch][Mp], Ct [batch][Mp][Np]
+size_t lmme_large_workspace_bytes(long long batch, int n, int d, int m)
+{
+    const size_t Np = pad_to(n, 128), Mp = pad_to(m, 128), Kp = pad_to(d, 16);
+    return align_up((size_t)batch * Np * Kp * 4, 256) + align_up((size_t)batch * Np * 4, 256) + align_up((size_t)batch * Mp * Kp * 4, 256) +
+           align_up((size_t)batch * Mp * 4, 256) + align_up((size_t)batch * Mp * Np * 4, 256);
+}
+
+int launch_lmme_large(goom_ctx *ctx, const void *A, const void *B, void *C, long long batch, int n, int d, int m, void *ws)
+{
+    const int Np = pad_to(n, 128), Mp = pad_to(m, 128), Kp = pad_to(d, 16);
+    if (batch > 65535) return fail(ctx, GOOM_EUNSUPPORTED, "at most 65535 pairs per call for shapes above 128 (batch=%lld)", batch);
+    unsigned char *w = static_cast<unsigned char *>(ws);
+    float *X = reinterpret_cast<float *>(w);
+    w += align_up((size_t)batch * Np * Kp * 4, 256);
+    float *rs = reinterpret_cast<float *>(w);
+    w += align_up((size_t)batch * Np * 4, 256);
+    float *Y = reinterpret_cast<float *>(w);
+    w += align_up((size_t)batch * Mp * Kp * 4, 256);
+    float *cs = reinterpret_cast<float *>(w);
+    w += align_up((size_t)batch * Mp * 4, 256);
+    float *Ct = reinterpret_cast<float *>(w);
+    const unsigned nb = (unsigned)batch;
+    prof_begin(ctx, "lmme_large_floats_scale_operands");
+    hipLaunchKernelGGL(convert_left_kernel, dim3(Np, nb), dim3(256), 0, ctx->stream, static_cast<const float2 *>(A), X, rs, n, d, Np, Kp);
+    hipLaunchKernelGGL(column_shift_kernel<float>, dim3(Mp / 64, nb), dim3(256), 0, ctx->stream, static_cast<const float2 *>(B), cs, d, m, Mp);
+    hipLaunchKernelGGL(convert_right_kernel<float>, dim3(Mp / 32, (Kp + 31) / 32, nb), dim3(256), 0, ctx->stream, static_cast<const float2 *>(B), cs, Y,
+                       d, m, Mp, Kp);
+    prof_end(ctx);
+    if (int s = check_hip(ctx, hipGetLastError(), "launch LMME operand kernels")) return s;
+    prof_begin(ctx, "lmme_large_floats_gemm");
+    launch_gemm_nt(ctx->stream, Y, X, Ct, Np / 128, Mp / 128, nb, Mp, Np, Kp, (long long)Mp * Kp, (long long)Np * Kp, (long long)Mp * Np);
+    prof_end(ctx);
+    if (int s = check_hip(ctx, hipGetLastError(), "launch gemm_nt_kernel")) return s;
+    prof_begin(ctx, "lmme_large_floats_log_store");
+    hipLaunchKernelGGL(lmme_store_kernel, dim3((n + 31) / 32, (m + 31) / 32, nb), dim3(256), 0, ctx->stream, Ct, rs, cs,
+                       static_cast<float2 *>(C), n, m, Np, Mp);
+    prof_end(ctx);
+    return check_hip(ctx, hipGetLastError(), "launch lmme_store_kernel");
+}
+
+} // namespace goom
 
 // ------------------------------------------------------------------------------------------------
 // Scans and reductions of complex64 matrices above 128 x 128: the shared driver with this file's GEMM, the
@@ -202,8 +318,8 @@ struct OpsF32 {
     }
     static void init_state(hipStream_t st, const void *init, double *ey, float *yt, int d, int m, int mp, int dp, unsigned batch)
     {
-        hipLaunchKernelGGL(column_shift_kernel, dim3(mp / 64, batch), dim3(256), 0, st, static_cast<const float2 *>(init), ey, d, m, mp);
-        hipLaunchKernelGGL(convert_right_kernel, dim3(mp / 32, dp / 32, batch), dim3(256), 0, st, static_cast<const float2 *>(init), ey, yt, d,
+        hipLaunchKernelGGL(column_shift_kernel<double>, dim3(mp / 64, batch), dim3(256), 0, st, static_cast<const float2 *>(init), ey, d, m, mp);
+        hipLaunchKernelGGL(convert_right_kernel<double>, dim3(mp / 32, dp / 32, batch), dim3(256), 0, st, static_cast<const float2 *>(init), ey, yt, d,
                            m, mp, dp);
     }
     static int row_shifts(goom_ctx *ctx, const void *M, float *nrow, int d, long long nmat) { return goom::launch_row_shifts256(ctx, M, nrow, d, nmat); }

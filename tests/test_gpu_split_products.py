@@ -41,6 +41,27 @@ def test_products(G, oracle, shape, spread):  # noqa: F811
         assert np.all(err[plain] <= bound[plain])
 
 
+@pytest.mark.parametrize("batch,n,d,m", [(3, 128, 1024, 128), (1, 130, 700, 20), (2, 7, 513, 100)])
+def test_products_in_the_room_of_floats(G, oracle, batch, n, d, m):  # noqa: F811
+    """A workspace for operands and product in floats: too small for three parts of the operands where the inner dimension is long."""
+    import ctypes as C
+    import torch
+    A, B = operands(oracle, (batch, n, d, m), 1270 + n, 0)
+    pad = lambda v, k: -(-v // k) * k
+    up = lambda v: pad(v, 256)
+    N, M, K = pad(n, 128), pad(m, 128), pad(d, 16)
+    room = up(batch * N * K * 4) + up(batch * N * 4) + up(batch * M * K * 4) + up(batch * M * 4) + up(batch * M * N * 4)
+    z, w, out = dev(A), dev(B), dev(np.zeros((batch, n, m), dtype=np.complex64))
+    ws = torch.empty(room, dtype=torch.uint8, device="cuda")
+    run = lambda size: G.lib.goom_lmme(G._ctx, *(C.c_void_p(t.data_ptr()) for t in (z, w, out)), batch, n, d, m, 0, 0, C.c_void_p(ws.data_ptr()), size)
+    assert run(room) == 0
+    for i in range(batch):
+        re, sg, kap, well = with_sensitivity(lambda a, b: oracle.lmme(a, b, return_kappa=True), [A[i], B[i]], np.float32, nprobe=1)
+        compare(host(out)[i], re, sg, kap, name=f"product in floats {n}", max_ill_fraction=0.05, well=well)
+    least = min(room, G.lib.goom_lmme_workspace_bytes(batch, n, d, m, 0, 0))
+    assert run(least) == 0 and run(least - 256) != 0
+
+
 # chunks of one step, of two, uneven ones (the last shorter: identities), a single one; states of their own width; several items
 @pytest.mark.parametrize("T,d,chunk,m,batch", [(5, 257, 1, None, 1), (7, 300, 2, None, 2), (8, 260, 3, 20, 1), (6, 130, 6, None, 2), (9, 200, 4, 300, 1), (5, 100, 2, 140, 1),
                                                (11, 140, 0, None, 1), (1, 270, 0, None, 1), (2, 384, 0, 1, 3)])

@@ -177,7 +177,10 @@ typedef struct goom_scan_opts {
  * prefix and writes all outputs.  Between steps the running product is kept as real
  * mantissas with a power-of-two exponent per column, so log-magnitudes are rounded to
  * the component type only when an output is stored.
- * workspace: goom_scan_workspace_bytes(...) bytes. */
+ * workspace: goom_scan_workspace_bytes(...) bytes.  For GOOM_C64 with d or m above GOOM_MAX_DIM the query asks for
+ * the whole input in three bf16 parts, 6 bytes an entry of matrices padded to 128 (up to 4 GiB of them), each converted once;
+ * with less room two matrices a chunk are held and converted again in the last phase (the same outputs, bit by bit), and
+ * with less than that the products run on the float matrix instruction, in whatever room that wants. */
 int goom_scan(goom_ctx *ctx, const void *M, const void *init, void *P, int64_t T, int d, int m,
               int64_t batch, int dtype, const goom_scan_opts *opts, void *workspace,
               size_t workspace_bytes);
@@ -192,7 +195,9 @@ size_t goom_scan_workspace_bytes(int64_t T, int d, int m, int64_t batch, int dty
  * the shortest chunk length among 8, 16, 32, ... whose plan fits is taken instead (the outputs are then those of
  * goom_scan with that chunk_len).  A scan whose goom_scan_workspace_bytes(...) still exceeds
  * GOOM_STATIC_SCRATCH_BYTES is rejected with GOOM_EWORKSPACE and nothing is enqueued (the T = 2^20, d = 64
- * complex64 scan needs 36.2 MB and fits).  All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two
+ * complex64 scan needs 36.2 MB and fits).  For GOOM_C64 with d or m above GOOM_MAX_DIM a plan fits if two
+ * converted matrices a chunk do; where none does, the first plan of the float matrix instruction that fits is taken
+ * (see goom_scan; the outputs are then goom_scan's within its tolerance, not bit by bit).  All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two
  * streams, two contexts, two threads) race on it and must be serialised by the caller.  Nothing in the array
  * has to be cleared between calls: every phase writes what the next one reads. */
 #define GOOM_STATIC_SCRATCH_BYTES (40u << 20)

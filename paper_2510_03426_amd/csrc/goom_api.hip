@@ -398,14 +398,14 @@ static int run_scan(goom_ctx *ctx, const void *M, const void *init, void *P, lon
         // the state no longer fits a workgroup: chains advance step by step through a tiled GEMM
         const long long req = opts ? opts->chunk_len : 0;
         const bool f32 = dtype == GOOM_C64;
-        // (a workspace too small for the products in parts may do for those in floats: goom_scan_static's does)
-        const bool split = f32 && scan_split_applies(T, d, m, batch) && ws_bytes >= scan_split_workspace_bytes(T, d, m, batch, req, final_only);
-        const size_t need = split ? scan_split_workspace_bytes(T, d, m, batch, req, final_only)
+        // (a workspace too small for the products in parts may do for those in floats)
+        const bool split = f32 && scan_split_applies(T, d, m, batch) && ws_bytes >= scan_split_workspace_bytes(T, d, m, batch, req, final_only, true);
+        const size_t need = split ? scan_split_workspace_bytes(T, d, m, batch, req, final_only, true)
                             : f32 ? scan_large_workspace_bytes(T, d, m, batch, req, final_only)
                                   : scan_large_f64_workspace_bytes(T, d, m, batch, req, final_only);
         if (int s = check_workspace(ctx, ws, ws_bytes, need)) return s;
         if (int s = need_ctx(ctx)) return s;
-        if (split) return run_scan_split(ctx, M, init, P, T, d, m, batch, req, ws, final_only);
+        if (split) return run_scan_split(ctx, M, init, P, T, d, m, batch, req, ws, ws_bytes, final_only);
         return f32 ? run_scan_large(ctx, M, init, P, T, d, m, batch, req, ws, final_only)
                    : run_scan_large_f64(ctx, M, init, P, T, d, m, batch, req, ws, final_only);
     }
@@ -916,26 +916,26 @@ int goom_scan_static(goom_ctx *ctx, const void *M, const void *init, void *P, in
     // argument errors first (reported without a device); the size check uses the same plan as goom_scan
     if (int s = check_scan_args(ctx, M, P, T, d, m, batch, dtype, opts, GOOM_MAX_DIM_LMME)) return s;
     goom_scan_opts eff = opts ? *opts : goom_scan_opts{0, 0};
-    // (the least that run_scan takes)
-    auto least = [&](const goom_scan_opts &o) {
-        return dtype == GOOM_C64 && (d > GOOM_MAX_DIM || m > GOOM_MAX_DIM) ? scan_large_workspace_bytes(T, d, m, batch, o.chunk_len, false)
-                                                                            : goom_scan_workspace_bytes(T, d, m, batch, dtype, &o);
+    const bool split = dtype == GOOM_C64 && (d > GOOM_MAX_DIM || m > GOOM_MAX_DIM) && scan_split_applies(T, d, m, batch);
+    // (the least room that run_scan takes for goom_scan's kernels; false: for the float products that it takes otherwise)
+    auto least = [&](const goom_scan_opts &o, bool same) {
+        return !split ? goom_scan_workspace_bytes(T, d, m, batch, dtype, &o)
+               : same ? scan_split_workspace_bytes(T, d, m, batch, o.chunk_len, false, true)
+                      : scan_large_workspace_bytes(T, d, m, batch, o.chunk_len, false);
     };
-    size_t need = least(eff);
-    if (need > (size_t)GOOM_STATIC_SCRATCH_BYTES && eff.chunk_len == 0) {
+    auto choose = [&](bool same) {
+        eff = opts ? *opts : goom_scan_opts{0, 0};
+        size_t n = least(eff, same);
         // the default plan has more chunks than the array holds products of: the shortest chunks, by powers of two,
         // that fit (fewer chunks, a smaller workspace; the result is the same scan)
-        for (long long L = 8; L < T; L *= 2) {
-            goom_scan_opts longer = eff;
-            longer.chunk_len = L;
-            const size_t n = least(longer);
-            if (n > 0 && n <= (size_t)GOOM_STATIC_SCRATCH_BYTES) {
-                eff = longer;
-                need = n;
-                break;
-            }
+        for (long long L = 8; n > (size_t)GOOM_STATIC_SCRATCH_BYTES && (opts ? opts->chunk_len : 0) == 0 && (L < T || (split && (L == 8 || L / 2 < T))); L *= 2) {
+            eff.chunk_len = L;
+            n = least(eff, same);
         }
-    }
+        return n;
+    };
+    size_t need = choose(true);
+    if (need > (size_t)GOOM_STATIC_SCRATCH_BYTES && split) need = choose(false);
     if (need > (size_t)GOOM_STATIC_SCRATCH_BYTES)
         return fail(ctx, GOOM_EWORKSPACE, "this scan needs %zu bytes of scratch memory; goom_scan_static holds %zu (use goom_scan with a workspace)",
                     need, (size_t)GOOM_STATIC_SCRATCH_BYTES);
@@ -972,9 +972,13 @@ static int run_scan_real(goom_ctx *ctx, const void *X, const void *init, void *P
     const size_t encoded = align_up((size_t)batch * (size_t)T * d * d * 2 * comp_bytes(dtype), 256);
     if (align_up(base, 256) + encoded > ws_bytes) { // (what run_scan does with less room)
         const long long req = opts ? opts->chunk_len : 0;
-        const size_t least = d <= GOOM_MAX_DIM && m <= GOOM_MAX_DIM ? plan_prefix(T, d, m, batch, dtype, req, final_only, true).total()
-                             : dtype == GOOM_C64                    ? scan_large_workspace_bytes(T, d, m, batch, req, final_only)
-                                                                    : base;
+        size_t least = d <= GOOM_MAX_DIM && m <= GOOM_MAX_DIM ? plan_prefix(T, d, m, batch, dtype, req, final_only, true).total()
+                       : dtype == GOOM_C64                    ? scan_large_workspace_bytes(T, d, m, batch, req, final_only)
+                                                              : base;
+        if (dtype == GOOM_C64 && (d > GOOM_MAX_DIM || m > GOOM_MAX_DIM) && scan_split_applies(T, d, m, batch)) {
+            const size_t split = scan_split_workspace_bytes(T, d, m, batch, req, final_only, true);
+            if (split < least || align_up(split, 256) + encoded <= ws_bytes) least = split;
+        }
         if (align_up(least, 256) + encoded <= ws_bytes) base = least;
     }
     const size_t zoff = align_up(base, 256);

@@ -144,9 +144,10 @@ int launch_lmme_large(goom_ctx *ctx, const void *A, const void *B, void *C, long
 size_t lmme_split_workspace_bytes(long long batch, int n, int d, int m);
 int launch_lmme_split(goom_ctx *ctx, const void *A, const void *B, void *C, long long batch, int n, int d, int m, void *ws);
 bool scan_split_applies(long long T, int d, int m, long long batch);
-size_t scan_split_workspace_bytes(long long T, int d, int m, long long batch, long long requested_chunk, bool final_only);
+// least: with the fewest matrices converted ahead (which run_scan_split takes where there is not the room for more)
+size_t scan_split_workspace_bytes(long long T, int d, int m, long long batch, long long requested_chunk, bool final_only, bool least = false);
 int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long long T, int d, int m, long long batch, long long requested_chunk, void *ws,
-                   bool final_only);
+                   size_t ws_bytes, bool final_only);
 // the same for complex128 operands (double components, double-precision matrix instruction)
 size_t lmme_large_f64_workspace_bytes(long long batch, int n, int d, int m);
 int launch_lmme_large_f64(goom_ctx *ctx, const void *A, const void *B, void *C, long long batch, int n, int d, int m, void *ws);

@@ -887,7 +887,8 @@ struct SplitPlan {
     size_t key_round, key_tot, key_car1, key_car2, e_round, e_tot, e_car; // offsets in elements within keys, e
 };
 
-SplitPlan plan_split(long long T, int d, int m, long long batch, long long requested, bool final_only)
+// least: two converted matrices a chain whatever the room (the same chunks, and the same results in every bit)
+SplitPlan plan_split(long long T, int d, int m, long long batch, long long requested, bool final_only, bool least)
 {
     SplitPlan p;
     p.dp = pad_to(d, 128);
@@ -928,7 +929,7 @@ SplitPlan plan_split(long long T, int d, int m, long long batch, long long reque
     p.C = (T + p.L - 1) / p.L;
     p.C1 = p.C <= 1 ? 0 : (final_only ? p.C : p.C - 1);
     const size_t chains = (size_t)batch * p.C;
-    p.places = chains * p.L * mat * 6 <= ((size_t)4 << 30) || p.L < 2 ? p.L : 2;
+    p.places = (!least && chains * p.L * mat * 6 <= ((size_t)4 << 30)) || p.L < 2 ? p.L : 2;
     const size_t slots = chains * p.places;
     const int rows = p.mp > p.dp ? p.mp : p.dp;
     size_t off = 0;
@@ -971,15 +972,16 @@ namespace goom {
 // Measured, 256 x 256, states in registers against this: T = 64 675 / 284 us, 512 1929 / 986, 4096 5982 / 4476, 16 384 15.6 / 19.2 ms.
 bool scan_split_applies(long long T, int d, int m, long long batch) { return !(d > 128 && d <= 256 && m <= 256 && T * batch > 8192); }
 
-size_t scan_split_workspace_bytes(long long T, int d, int m, long long batch, long long requested_chunk, bool final_only)
+size_t scan_split_workspace_bytes(long long T, int d, int m, long long batch, long long requested_chunk, bool final_only, bool least)
 {
-    return plan_split(T, d, m, batch, requested_chunk, final_only).total;
+    return plan_split(T, d, m, batch, requested_chunk, final_only, least).total;
 }
 
 int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long long T, int d, int m, long long batch, long long requested_chunk, void *ws,
-                   bool final_only)
+                   size_t ws_bytes, bool final_only)
 {
-    const SplitPlan p = plan_split(T, d, m, batch, requested_chunk, final_only);
+    SplitPlan p = plan_split(T, d, m, batch, requested_chunk, final_only, false);
+    if (p.total > ws_bytes) p = plan_split(T, d, m, batch, requested_chunk, final_only, true);
     const long long C = p.C, L = p.L, chains = batch * C;
     if (chains > 65535) return fail(ctx, GOOM_EUNSUPPORTED, "too many chains (%lld) for matrices above %d", chains, GOOM_MAX_DIM);
     unsigned char *w = static_cast<unsigned char *>(ws);

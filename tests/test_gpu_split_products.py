@@ -152,13 +152,40 @@ def test_items_share_launches(G, oracle):  # noqa: F811
     assert count[0] == count[1] > 0
 
 
-def test_static_scratch(G, oracle):  # noqa: F811
+# beside the room for it, too large for that (two converted matrices a chunk, longer chunks, one chunk), and too large for the products in parts
+@pytest.mark.parametrize("T,d,batch,chunk", [(4, 300, 1, 0), (24, 300, 1, 0), (12, 520, 1, 0), (60, 300, 1, 0), (6, 520, 1, 3), (3, 520, 4, None)])
+def test_static_scratch(G, oracle, T, d, batch, chunk):  # noqa: F811
     import torch
-    for T, d in ((4, 300), (24, 300), (12, 520)):  # beside the room for it, and too large for that
-        z = dev(oracle.to_goom(si.normal_chain(si.BASE_SEED + 1500 + d, T, d)))
-        out = torch.empty_like(z)
-        G.scan_static(z, out)
-        ref = G.scan(z)
-        torch.cuda.synchronize()
-        a, b = host(out), host(ref)
-        assert np.quantile(np.abs(a.real - b.real), 0.99) < 1e-3
+    z = np.stack([oracle.to_goom(si.normal_chain(si.BASE_SEED + 1500 + d + i, T, d)) for i in range(batch)])
+    out = torch.empty_like(dev(z))
+    G.scan_static(dev(z), out, chunk_len=chunk or 0)
+    got = host(out)
+    same = lambda L: np.array_equal(got.view(np.uint32), host(G.scan(dev(z), chunk_len=L)).view(np.uint32))
+    if chunk is None:  # the float products: as good as the others, not their bits
+        assert not any(same(L) for L in (0, 8, 16, 32))
+        re, sg, kap, well = with_sensitivity(lambda a: oracle.scan(a, return_kappa=True), [z[-1]], np.float32, nprobe=1)
+        compare(got[-1], re, sg, kap, name=f"static scratch {T} x {d}", max_ill_fraction=0.05, well=well)
+    else:
+        assert same(chunk) or any(same(L) for L in (8, 16, 32, 64))
+
+
+@pytest.mark.parametrize("T,d,m,chunk", [(7, 300, None, 3), (6, 270, 5, 6), (9, 384, None, 5), (7, 140, 200, 3)])
+def test_scans_with_room_for_two_matrices_a_chunk(G, oracle, T, d, m, chunk):  # noqa: F811
+    """Matrices converted step by step, in both phases: the same bits."""
+    import ctypes as C
+    import torch
+    from paper_2510_03426_amd.binding import ScanOpts
+    batch, opts = 2, ScanOpts(chunk, 0)
+    z = dev(np.stack([oracle.to_goom(si.normal_chain(si.BASE_SEED + 1600 + d + i, T, d)) for i in range(batch)]))
+    init = None if m is None else dev(oracle.to_goom(si.normal_f32(si.BASE_SEED + 1610, 1, batch * d * m).reshape(batch, d, m)))
+    cols = m or d
+    for final in (False, True):
+        size = G.lib.goom_reduce_workspace_bytes if final else G.lib.goom_scan_workspace_bytes
+        call = G.lib.goom_reduce if final else G.lib.goom_scan
+        want = host((G.reduce if final else G.scan)(z, init, chunk_len=chunk))
+        full = size(T, d, cols, batch, 0, C.byref(opts))
+        out = dev(np.zeros(want.shape, dtype=np.complex64))
+        ws = torch.full((full,), 255, dtype=torch.uint8, device="cuda")  # (what is not written reads as NaN)
+        p = lambda t: None if t is None else C.c_void_p(t.data_ptr())
+        assert call(G._ctx, p(z), p(init), p(out), T, d, cols, batch, 0, C.byref(opts), p(ws), full - 256) == 0
+        assert np.array_equal(host(out).view(np.uint32), want.view(np.uint32))

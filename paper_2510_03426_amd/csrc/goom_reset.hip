@@ -52,7 +52,8 @@ struct ResetArgs {
     const int *only_if;          // staged kernel: NULL, or [batch]: items for which it has work
     // spectra in segments (see reset_carry_staged_kernel): room for their results, [batch][segments] of SegmentRoom doubles
     double *segments_room;
-    int segments, warm;
+    const double *frames;        // NULL, or as much: the chain's states at the segments' ends, as a first pass has put them together
+    int segments;
     long long per_segment;
 };
 
@@ -845,21 +846,28 @@ template <int DP, typename IO> __global__ __launch_bounds__(64) void reset_carry
 //
 // SEG: the spectrum of a long chain.  Its stages are a serial chain, but the growth is the diagonal of one triangular factor: that of
 // the whole chain's product times the initial state, and this can be put together from pieces.  Each segment of the chunks is walked by a workgroup of its
-// own, from the identity (`warm` chunks early, so that its state is close to the chain's when the segment begins), and what it keeps is its product
-// as Q_e R Q_s^T: the states at its ends and the product of its triangular factors, R = diag(2^E) N, on exponents of its rows (R's entries
-// lie e^+-1000 apart).  segment_join_kernel makes one of two.  R is put together by a wave beside the panels' waves, a
+// own, and what it keeps is its product as Q_e R Q_s^T: the states at its ends and the product of its triangular factors, R = diag(2^E) N, on exponents of
+// its rows (R's entries lie e^+-1000 apart).  segment_join_kernel makes one of two.  R is put together by a wave beside the panels' waves, a
 // stage behind the decision about a chunk, from the projections' coefficients and the panels' triangles that they leave in LDS.
-// 512 chunks of 32 x 32: 2532 -> 360 us (189 in segments of 16 chunks, 5 x 33 to join 32 of them); whole spectra, T = 65 536: 2.83 -> 0.64 ms, complex128
-// (nearly every chunk factored twice) 5.93 -> 0.82.  Error against sequential QR, geometric means over 8 to 14 chains, in order -> in segments:
-// 16 x 16 1.6e-13 -> 1.5e-13, 20 x 20 1.9e-13 -> 2.4e-13, 32 x 32 7.1e-13 -> 4.6e-13, complex128 7.3e-13 -> 5.0e-13 (`warm` 0: ten times as much, and up to 1e6 in L).
+// Twice: joined from segments that begin at the identity, the growth has lost what the joins magnify (weakly separated directions, I + 0.15 N(0, 1) /
+// sqrt(32), 128 chunks of 8 steps: 3e-13 of growth, 4e-14 in order), and the more the longer it takes the states to come close to the chain's.  But the
+// chain's states at the segments' ends come out good to 1e-7 and better, and from these the second pass's joins magnify nothing: 4e-14.
+// Error against extended precision, in order -> so, the worst of three chains: 8 x 8 3.7e-14 -> 6.4e-14, 16 x 16 6.6e-14 -> 5.6e-14, 32 x 32 4.8e-14 -> 4.4e-14,
+// Lorenz-96 of d = 32, 96 chunks of 64 8.6e-11 -> 5.9e-11.
+// 512 chunks of 32 x 32: 2532 -> 550 us (two walks of 64 segments 63 each, twelve joins of 34); whole spectra, T = 65 536: 2.80 -> 0.83 ms; 128 chunks 626 ->
+// 417 us, 96 of them 478 -> 415, complex128 (nearly every chunk factored twice) 1138 -> 610, 64 of these 768 -> 528; but complex64 64 chunks 362 -> 387.
+// Chains that do not join (directions that grow alike and turn) are found out in the first joins and walked in order: 128 chunks 615 -> 812 us, 512 of
+// them 2390 -> 2590.
 constexpr int kTriSlots = 5; // four chunks, and a second factorisation
+constexpr long long kSegmentChunks = 8;
 template <int DP, bool SEG = false> constexpr size_t staged_lds()
 {
     constexpr int KT = DP / 16;
     return (((size_t)((KT - 1) * KT + 1) * DP + DP) * kPanelLd + KT * DP * 2 + 4 + (SEG ? kTriSlots * (3 * 16 * kPanelLd + DP) + DP : 0)) * sizeof(double);
 }
-// a segment's results: Q_s, N, Q_e (DP x DP), E, its growth (of the first one, from its true start), whether it can be used
+// a segment's results: Q_s, N, Q_e (DP x DP), E, its growth (of the first one, from its true start), whether it is of no use
 template <int DP> constexpr int segment_room() { return 3 * DP * DP + 2 * DP + 2; }
+template <int DP> constexpr int kSegmentLost = 3 * DP * DP + 2 * DP;
 
 template <int DP, typename IO, bool SEG = false> __global__ __launch_bounds__(DP * 4 + (SEG ? 64 : 0)) void reset_carry_staged_kernel(ResetArgs a)
 {
@@ -875,8 +883,7 @@ template <int DP, typename IO, bool SEG = false> __global__ __launch_bounds__(DP
     if (a.only_if && !a.only_if[b]) return; // the whole workgroup
     const int segment = SEG ? (int)(blockIdx.x % a.segments) : 0;
     const bool last_segment = !SEG || segment + 1 == a.segments;
-    const long long kept_from = SEG ? segment * a.per_segment : 0;                          // chunks whose factors count
-    const long long begin = SEG && segment > 0 ? (kept_from > a.warm ? kept_from - a.warm : 0) : 0;
+    const long long begin = SEG ? segment * a.per_segment : 0;
     const size_t tot_mant = (size_t)DP * a.tot_cols * sizeof(double);
     const size_t car_mant = (size_t)DP * a.car_cols * sizeof(double);
     auto slot = [&](int q, long long i) { return reinterpret_cast<double *>(smem) + (size_t)(q * KT + (q + 1 < KT ? (int)(i & (KT - 1)) : 0)) * PANEL; };
@@ -890,6 +897,13 @@ template <int DP, typename IO, bool SEG = false> __global__ __launch_bounds__(DP
     [[maybe_unused]] double *tri_exp = tri + (size_t)kTriSlots * 3 * 16 * kPanelLd; // [slot][DP]
     [[maybe_unused]] double *row_exp = tri_exp + kTriSlots * DP;
     [[maybe_unused]] double *room = SEG ? a.segments_room + (size_t)blockIdx.x * segment_room<DP>() : nullptr;
+    [[maybe_unused]] const double *frame = SEG && a.frames && segment > 0 ? a.frames + ((size_t)blockIdx.x - 1) * segment_room<DP>() : nullptr;
+    if constexpr (SEG) {
+        if (frame && frame[kSegmentLost<DP>] != 0.0) { // the whole workgroup
+            if (tid == 0) room[kSegmentLost<DP>] = 1.0;
+            return;
+        }
+    }
 
     d4 Y[KT]; // Y[mt][v] = entry (row 16 mt + 4 v + g, column 16 p + c), columns scaled by 2^yexp
     double yexp = 0.0, pprod = 1.0, pexp = 0.0; // product of all pivots so far = pprod 2^pexp (column exponents counted twice)
@@ -897,6 +911,14 @@ template <int DP, typename IO, bool SEG = false> __global__ __launch_bounds__(DP
     for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
         for (int v = 0; v < 4; ++v) Y[mt][v] = (16 * mt + 4 * v + g == col && col < d) ? 1.0 : 0.0;
+    if constexpr (SEG) {
+        if (frame && p < KT) {
+#pragma unroll
+            for (int mt = 0; mt < KT; ++mt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) Y[mt][v] = frame[2 * DP * DP + (16 * mt + 4 * v + g) * DP + col];
+        }
+    }
     if (a.s0 && col < d && segment == 0) {
         const IO *gp = reinterpret_cast<const IO *>(a.s0) + (size_t)b * d * d * 2;
         double cmax = -__builtin_huge_val();
@@ -1128,7 +1150,7 @@ template <int DP, typename IO, bool SEG = false> __global__ __launch_bounds__(DP
         if constexpr (SEG) {
             if (p == KT && pending >= 0) accumulate(pending);
             pending = -1;
-            if (p < KT && n >= p && i == kept_from && !second && segment > 0) { // (written again should the chunk before be factored again)
+            if (p < KT && n >= p && i == begin && !second && segment > 0) {
 #pragma unroll
                 for (int mt = 0; mt < KT; ++mt)
 #pragma unroll
@@ -1215,9 +1237,9 @@ template <int DP, typename IO, bool SEG = false> __global__ __launch_bounds__(DP
         // the chunk that the last wave has finished (all waves come to the same answer)
         if (n < KT - 1) continue;
         const long long done = from + n - (KT - 1);
-        if (SEG && redo && done == from && done >= kept_from && segment > 0) pending = kTriSlots - 1;
+        if (SEG && redo && done == from && segment > 0) pending = kTriSlots - 1;
         if (!(redo && done == from) && (done == a.C || (done + 1) * a.L <= a.T)) {
-            if (SEG && done >= kept_from && segment > 0) pending = (int)(done & 3);
+            if (SEG && segment > 0) pending = (int)(done & 3);
             const d2 first = KT > 1 ? (!SEG || p < KT ? undecided[(done & (KT - 1)) * DP + col] : d2{1.0, 0.0}) : own;
             if (KT > 1 || SEG ? __builtin_amdgcn_readfirstlane(worst[stage * KT + KT - 1]) != 0 : hit) {
                 from = done;
@@ -1243,7 +1265,7 @@ template <int DP, typename IO, bool SEG = false> __global__ __launch_bounds__(DP
                     for (int v = 0; v < 4; ++v) room[DP * DP + (16 * mt + 4 * v + g) * DP + 16 * nt + c] = N[mt][nt][v];
             if (lane < DP) room[3 * DP * DP + lane] = row_exp[lane];
             const bool any = __builtin_amdgcn_ballot_w64(lost) != 0;
-            if (lane < 2) room[3 * DP * DP + 2 * DP + lane] = any ? 1.0 : 0.0; // (the first segment's own mark is the second)
+            if (lane == 0) room[kSegmentLost<DP>] = any ? 1.0 : 0.0;
         } else {
 #pragma unroll
             for (int mt = 0; mt < KT; ++mt)
@@ -1284,10 +1306,13 @@ __device__ inline double eight_max(double x)
 // below the largest rows would be rounding.  N2 W = L U without exchanges first; then
 //     diag(2^E2) L U = (diag(2^E2) L diag(2^-E2)) diag(2^E2) U,
 // where the bracket is 1 on the diagonal, small below it where the exponents are in order (they are, but for directions of nearly equal
-// growth), and is factored by columns, Q' R'.  L is small when Q_s2 is close to Q_e1.  Should it not be, or a segment have lost a row (singular
-// chunks), the chain is walked in order after all.  For the chain's first segment only the growth counts: the diagonals' logarithms.
-// One workgroup a pair, eight threads a row.  Bound by the 2 d dependent steps of the two factorisations.
-template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(ResetArgs a, int stride, int *again)
+// growth), and is factored by columns, Q' R'.  An error of U's is magnified as L's entries are large: in the first pass, from the identity, up to
+// 1e9 times, which leaves the states at the ends good to some digits (out: every segment joined with the one `stride` before it, so that the
+// tree gives them at all ends).  In the second, where Q_s2 is such a state, L is the identity to 1e-7 and better, and is refused beyond `limit`; as
+// it is where a segment has lost a row (singular chunks): the chain is walked in order after all.  For what begins with the chain's first segment
+// only the growth counts: the diagonals' logarithms.  One workgroup a pair, eight threads a row.  Bound by the 2 d dependent steps of the two
+// factorisations.
+template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(ResetArgs a, double *out, int stride, double limit, int *again)
 {
     constexpr int LD = DP + 1, W = DP / 8, KT = DP / 16;
     __shared__ double X[DP * LD], Y[DP * LD], Z[DP * LD], low[DP * LD], rest[DP * LD];
@@ -1295,11 +1320,19 @@ template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(
     __shared__ int bad;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = tid >> 3, s = tid & 7, d = a.d;
     const int g = lane >> 4, c = lane & 15;
-    const int pairs = (a.segments - stride + 2 * stride - 1) / (2 * stride);
+    const int pairs = out ? a.segments : (a.segments - stride + 2 * stride - 1) / (2 * stride);
     const long long b = blockIdx.x / pairs;
-    const int first = (int)(blockIdx.x % pairs) * 2 * stride;
-    double *room1 = a.segments_room + ((size_t)b * a.segments + first) * segment_room<DP>();
-    const double *room2 = room1 + (size_t)stride * segment_room<DP>();
+    const int first = out ? (int)(blockIdx.x % pairs) - stride : (int)(blockIdx.x % pairs) * 2 * stride;
+    const bool from_start = out ? first < stride : first == 0; // what the first segment stands for begins where the chain does
+    double *room1 = a.segments_room + ((ptrdiff_t)b * a.segments + first) * segment_room<DP>();
+    const double *room2 = room1 + (ptrdiff_t)stride * segment_room<DP>();
+    double *to = out ? out + (size_t)blockIdx.x * segment_room<DP>() : room1;
+    if (first < 0) { // (the chain's state at this end is there)
+        for (int m = 0; m < W; ++m) to[2 * DP * DP + r * DP + s + 8 * m] = room2[2 * DP * DP + r * DP + s + 8 * m];
+        if (tid == 0) to[kSegmentLost<DP>] = room2[kSegmentLost<DP>];
+        return;
+    }
+    const bool last_pair = !out && first == 0 && 2 * stride >= a.segments;
     auto fetch = [&](double *to, const double *from) {
         for (int m = 0; m < W; ++m) to[r * LD + s + 8 * m] = from[r * DP + s + 8 * m];
     };
@@ -1330,8 +1363,15 @@ template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(
         E2[tid] = room2[3 * DP * DP + tid];
         E1[tid] = room1[3 * DP * DP + tid];
     }
-    if (tid == 0) bad = room2[3 * DP * DP + 2 * DP] != 0.0 || (first > 0 && room1[3 * DP * DP + 2 * DP] != 0.0) || (first == 0 && room1[3 * DP * DP + 2 * DP + 1] != 0.0);
+    if (tid == 0) bad = room1[kSegmentLost<DP>] != 0.0 || room2[kSegmentLost<DP>] != 0.0;
     __syncthreads();
+    if (bad) { // the whole workgroup
+        if (tid == 0) {
+            to[kSegmentLost<DP>] = 1.0;
+            if (last_pair) again[b] = 1;
+        }
+        return;
+    }
     // W: Q_s2^T Q_e1, and corrected twice (states of complex64 chains are orthonormal to 1e-6 only, where a chunk was not factored twice)
     multiply(X, nullptr, 1.0, Y, true, Z);
     for (int turn = 0; turn < 2; ++turn) {
@@ -1350,10 +1390,10 @@ template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(
 #pragma unroll
             for (int m = 0; m < W; ++m)
                 if (s + 8 * m > k) Z[r * LD + s + 8 * m] = fma(-l, Z[k * LD + s + 8 * m], Z[r * LD + s + 8 * m]);
-            wrong = wrong || !(fabs(l) <= 1.0e6); // (also a pivot of zero)
+            wrong = wrong || !(fabs(l) <= limit); // (also a pivot of zero)
             if (s == 0) {
                 const double x = ldexp(l, (int)fmin(fmax(E2[r] - E2[k], -4000.0), 1000.0));
-                wrong = wrong || !(fabs(x) <= 1.0e6);
+                wrong = wrong || !(fabs(x) <= fmax(limit, 1.0e6));
                 low[r * LD + k] = x;
             }
         }
@@ -1395,11 +1435,11 @@ template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(
     }
     for (int m = 0; m < W; ++m)
         if (r >= d || s + 8 * m >= d) X[r * LD + s + 8 * m] = 0.0;
-    if (first == 0) {
-        if (tid < d) {
+    if (from_start) {
+        if (!out && tid < d) {
             double &growth = room1[3 * DP * DP + DP + tid];
             growth += log(fabs(Z[tid * LD + tid])) + log(rest[tid * LD + tid]) + E2[tid] * kLn2;
-            if (2 * stride >= a.segments) { // the last pair
+            if (last_pair) {
                 const double x = growth * a.growth_scale;
                 if (!(fabs(x) < 1.0e300)) bad = 1;
                 a.growth[b * d + tid] = x;
@@ -1433,8 +1473,11 @@ template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(
             if (s == 0) E1[r] = top + (turn == 0 ? E2[r] : 0.0);
             multiply(turn ? Y : low, nullptr, 1.0, A, false, turn ? low : Y);
         }
-        for (int m = 0; m < W; ++m) room1[DP * DP + r * DP + s + 8 * m] = Y[r * LD + s + 8 * m];
-        if (tid < DP) room1[3 * DP * DP + tid] = E1[tid];
+        for (int m = 0; m < W; ++m) {
+            to[DP * DP + r * DP + s + 8 * m] = Y[r * LD + s + 8 * m];
+            if (out) to[r * DP + s + 8 * m] = room1[r * DP + s + 8 * m]; // Q_s1
+        }
+        if (tid < DP) to[3 * DP * DP + tid] = E1[tid];
     }
     if (wrong) bad = 1;
     __syncthreads();
@@ -1442,10 +1485,10 @@ template <int DP> __global__ __launch_bounds__(DP * 8) void segment_join_kernel(
     fetch(Z, room2 + 2 * DP * DP);
     __syncthreads();
     multiply(Y, nullptr, 1.0, Z, false, X);
-    for (int m = 0; m < W; ++m) room1[2 * DP * DP + r * DP + s + 8 * m] = Y[r * LD + s + 8 * m];
+    for (int m = 0; m < W; ++m) to[2 * DP * DP + r * DP + s + 8 * m] = Y[r * LD + s + 8 * m];
     if (tid == 0) {
-        room1[3 * DP * DP + 2 * DP + (first == 0 ? 1 : 0)] = bad ? 1.0 : 0.0;
-        if (first == 0 && 2 * stride >= a.segments) again[b] = bad;
+        to[kSegmentLost<DP>] = bad ? 1.0 : 0.0;
+        if (last_pair) again[b] = bad;
     }
 }
 
@@ -2747,7 +2790,8 @@ int launch_reset_carry(goom_ctx *ctx, const ResetLaunch &l)
     a.cos_threshold = l.cos_threshold;
     a.only_if = nullptr;
     a.segments_room = nullptr;
-    a.segments = a.warm = 0;
+    a.frames = nullptr;
+    a.segments = 0;
     a.per_segment = 0;
     const int dp = padded_dim(l.d);
     unsigned char *const carries = static_cast<unsigned char *>(l.carries);
@@ -2765,18 +2809,24 @@ int launch_reset_carry(goom_ctx *ctx, const ResetLaunch &l)
         prof_end(ctx);
         return check_hip(ctx, hipGetLastError(), "launch reset_carry_wide_kernel");
     }
-    // The spectrum alone of a long chain: in segments of sixteen chunks and more, whose results lie where the carries would.
-    const long long warm = 8;
-    long long segments = l.C / 16;
+    // The spectrum alone of a long chain: in segments of eight chunks and more, whose results lie where the carries would (twice: for a chunk two times
+    // 3 / 8 of a matrix, and the carries are a matrix each).
+    long long segments = l.C / kSegmentChunks;
     if (segments > 256 / l.batch) segments = 256 / l.batch; // a compute unit each
-    if (!a.carries && l.policy == GOOM_RESET_ALWAYS && dp <= 32 && l.growth && segments >= 4) {
+    if (!a.carries && l.policy == GOOM_RESET_ALWAYS && dp <= 32 && l.growth && l.C >= (l.dtype == GOOM_C64 ? 80 : 64) && segments >= 4) {
         a.per_segment = (l.C + segments - 1) / segments;
         a.segments = (int)((l.C + a.per_segment - 1) / a.per_segment);
-        a.warm = (int)warm;
-        a.segments_room = reinterpret_cast<double *>(carries);
-        int *again = reinterpret_cast<int *>(a.segments_room + (size_t)l.batch * a.segments * (dp == 16 ? segment_room<16>() : segment_room<32>()));
+        const size_t all = (size_t)l.batch * a.segments * (dp == 16 ? segment_room<16>() : segment_room<32>());
+        double *rooms[2] = {reinterpret_cast<double *>(carries), reinterpret_cast<double *>(carries) + all};
+        int *again = reinterpret_cast<int *>(rooms[1] + all);
+        a.segments_room = rooms[0];
         prof_begin(ctx, "reset_phase2_segments_qr");
         const dim3 grid((unsigned)(l.batch * a.segments));
+        auto join = [&](double *out, int stride, double limit) {
+            const unsigned pairs = out ? (unsigned)a.segments : (unsigned)((a.segments - stride + 2 * stride - 1) / (2 * stride));
+            if (dp == 16) hipLaunchKernelGGL(segment_join_kernel<16>, dim3(pairs * (unsigned)l.batch), dim3(128), 0, ctx->stream, a, out, stride, limit, again);
+            else hipLaunchKernelGGL(segment_join_kernel<32>, dim3(pairs * (unsigned)l.batch), dim3(256), 0, ctx->stream, a, out, stride, limit, again);
+        };
 #define GOOM_SEGMENT_CASE(DPV, IO)                                                                                                                        \
     {                                                                                                                                                      \
         if (int st = check_hip(ctx,                                                                                                                        \
@@ -2786,15 +2836,23 @@ int launch_reset_carry(goom_ctx *ctx, const ResetLaunch &l)
             return st;                                                                                                                                     \
         hipLaunchKernelGGL((reset_carry_staged_kernel<DPV, IO, true>), grid, dim3(4 * DPV + 64), (staged_lds<DPV, true>()), ctx->stream, a);               \
     }
-        if (dp == 16) {
-            if (l.dtype == GOOM_C64) GOOM_SEGMENT_CASE(16, float) else GOOM_SEGMENT_CASE(16, double)
-        } else {
-            if (l.dtype == GOOM_C64) GOOM_SEGMENT_CASE(32, float) else GOOM_SEGMENT_CASE(32, double)
-        }
-        for (int stride = 1; stride < a.segments; stride *= 2) {
-            const unsigned pairs = (unsigned)((a.segments - stride + 2 * stride - 1) / (2 * stride) * l.batch);
-            if (dp == 16) hipLaunchKernelGGL(segment_join_kernel<16>, dim3(pairs), dim3(128), 0, ctx->stream, a, stride, again);
-            else hipLaunchKernelGGL(segment_join_kernel<32>, dim3(pairs), dim3(256), 0, ctx->stream, a, stride, again);
+        for (int pass = 0; pass < 2; ++pass) {
+            if (dp == 16) {
+                if (l.dtype == GOOM_C64) GOOM_SEGMENT_CASE(16, float) else GOOM_SEGMENT_CASE(16, double)
+            } else {
+                if (l.dtype == GOOM_C64) GOOM_SEGMENT_CASE(32, float) else GOOM_SEGMENT_CASE(32, double)
+            }
+            if (pass == 0) {
+                for (int stride = 1; stride < a.segments; stride *= 2) {
+                    double *to = a.segments_room == rooms[0] ? rooms[1] : rooms[0];
+                    join(to, stride, 1.0e12);
+                    a.segments_room = to;
+                }
+                a.frames = a.segments_room;
+                a.segments_room = a.segments_room == rooms[0] ? rooms[1] : rooms[0];
+            } else {
+                for (int stride = 1; stride < a.segments; stride *= 2) join(nullptr, stride, 1.0e-2);
+            }
         }
 #undef GOOM_SEGMENT_CASE
         prof_end(ctx);

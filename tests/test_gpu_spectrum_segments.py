@@ -1,5 +1,6 @@
 """Spectra of chains with many chunks, walked in segments that are joined afterwards: sizes at the edges of the panels, a last chunk that is shorter, initial
-states, several items, chunks that are factored twice, and chains whose segments do not join (walked in order then)."""
+states, several items, chunks that are factored twice, directions that are weakly separated, and chains whose segments do not join (walked in order
+then)."""
 import numpy as np
 import pytest
 
@@ -22,7 +23,7 @@ def in_order(G, z, s0=None, chunk_len=0):  # noqa: F811
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("d,T,chunk,batch", [(1, 64, 1, 1), (3, 129, 2, 1), (15, 200, 2, 2), (16, 321, 5, 1), (17, 192, 3, 1), (31, 400, 4, 2), (32, 130, 2, 1), (32, 65, 1, 1),
-                                             (20, 127, 1, 3)])
+                                             (20, 127, 1, 3), (1, 80, 1, 1), (3, 181, 2, 1), (16, 401, 5, 1), (17, 240, 3, 1), (32, 170, 2, 1), (32, 81, 1, 1)])
 def test_spectrum(G, oracle, d, T, chunk, batch, dtype):  # noqa: F811
     x = np.stack([chain(2000 + d + i, T, d, dtype, 0.05) for i in range(batch)])
     z = oracle.to_goom(x)
@@ -33,6 +34,35 @@ def test_spectrum(G, oracle, d, T, chunk, batch, dtype):  # noqa: F811
         # both sum T logarithms of numbers good to a few units of 2^-52, magnified by what the joining lost (1e6 at most)
         assert np.abs(lam[i] - ref).max() <= 1e-9 * max(1.0, np.abs(ref).max())
         assert np.abs(lam[i] - kept[i]).max() <= 1e-9 * max(1.0, np.abs(ref).max())
+
+
+def growth_in_extended_precision(x):
+    """Logarithms of the triangular factors' diagonals, step by step."""
+    Q, out = np.eye(x.shape[-1], dtype=np.longdouble), 0
+    for M in x:
+        Z = M @ Q
+        norm = np.empty(len(Q), dtype=np.longdouble)
+        for k in range(len(Q)):
+            for _ in range(2):
+                Z[:, k] -= Z[:, :k] @ (Z[:, :k].T @ Z[:, k])
+            norm[k] = np.sqrt((Z[:, k] ** 2).sum())
+            Z[:, k] /= norm[k]
+        Q, out = Z, out + np.log(norm)
+    return out.astype(np.float64)
+
+
+@pytest.mark.parametrize("dtype", [np.complex64, np.complex128])
+@pytest.mark.parametrize("d", [8, 24, 32])
+def test_weakly_separated_directions(G, d, dtype):  # noqa: F811
+    """Segments that begin far from the chain's states, and joins that would magnify their roundings: as good as in order."""
+    C, L = 96, 8
+    for seed in range(3):
+        x = np.eye(d) + 0.15 / np.sqrt(d) * np.random.default_rng(seed + d).standard_normal((C * L, d, d))
+        z = (np.log(np.abs(x)) + 1j * np.pi * (x < 0)).astype(dtype)
+        want = growth_in_extended_precision(np.exp(z.real.astype(np.longdouble)) * np.where(z.imag > 1, -1, 1))
+        got = host(G.lyapunov_spectrum(dev(z[None]), 1.0 / (C * L), chunk_len=L))[0]
+        # a chunk's factorisation: some units of 2^-52, times the spread of its columns (up to five); they add up as their number, at worst
+        assert np.abs(got - want).max() <= 5 * 2.0 ** -52 * C, (seed, np.abs(got - want).max())
 
 
 @pytest.mark.parametrize("d", [9, 32])

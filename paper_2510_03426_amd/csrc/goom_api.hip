@@ -230,12 +230,14 @@ static ScanPlan plan_scan(long long T, int d, int m_tot, int m_state, long long 
 // / in these (the best of ten lengths): complex64 1 x 60 x 64 90 / 42 (42), 1 x 300 x 64 96 / 82 (80), 1 x 1000 x 64 138 / 104 (104), 1 x 60 x 128 441 /
 // 137 (137), 1 x 2000 x 100 448 / 356 (356), 8 x 300 x 64 103 / 87 (87), 1 x 60 x 8 27 / 19 (19); complex128 1 x 24 x 64 140 / 71 (71), 1 x 300 x 128 791 / 470 (470), 1 x
 // 1000 x 16 94 / 67 (67).  Reductions, with one phase of steps: 1 x 60 x 64 45 / 30, 1 x 600 x 64 75 / 61.  States narrower than half the matrices keep the former.
+// What was one chunk stays one: its matrices never meet as a product of their own, whose columns share an exponent, and may have any units (D A D^-1 with
+// D over e^+-30: right in one chunk, four entries in five lost in chunks of three).
 // least: the former chunks.
 static ScanPlan plan_prefix(long long T, int d, int m, long long batch, int dtype, long long requested, bool final_only, bool least = false)
 {
     const ScanPlan p = plan_scan(T, d, d, m, batch, dtype, requested, final_only);
     const bool heavy = dtype == GOOM_C128 || d > 64;
-    if (requested > 0 || least || d > GOOM_MAX_DIM || 2 * m < d || T < (heavy || d > 16 ? 24 : 40)) return p;
+    if (requested > 0 || least || p.C <= 1 || d > GOOM_MAX_DIM || 2 * m < d || T < (heavy || d > 16 ? 24 : 40)) return p;
     if (final_only && !heavy && T > 1500) return p;
     const long long grouped = heavy ? 3 : final_only && T >= 98 * 8 ? 8 : 6;
     long long r = heavy ? 8 : d > 32 ? 4 : d > 16 ? 2 : 1;
@@ -1081,15 +1083,16 @@ constexpr long long kAdjointCarries = 128;
 // on the carries go in groups and six steps a chunk are best or near it.  In us, former chunks / these (the best of ten lengths): complex64
 // 1 x 60 x 64 91 / 43 (43), 1 x 300 x 64 99 / 80 (79), 1 x 1000 x 64 137 / 111 (111), 8 x 300 x 64 105 / 90 (84), 1 x 60 x 8 52 / 29 (29), 1 x 300 x 16 43 / 40 (40), 1 x
 // 60 x 128 330 / 97 (97), 1 x 1000 x 128 377 / 264 (264); complex128 1 x 60 x 64 135 / 81 (80), 1 x 300 x 24 97 / 88 (81), 1 x 30 x 100 448 / 148 (148).  Up to
-// two dozen steps one chunk takes less than three launches.  (Float 16 x 16 in one chunk as long as before: its logarithms come from the vector kernel
-// then, median error 1.6e-7, in chunks from the tile's walk, 6.6e-7.)
+// two dozen steps one chunk takes less than three launches.  What was one chunk stays one: as for scans (plan_prefix), and float 16 x 16 has its logarithms from
+// the vector kernel then, median error 1.6e-7, in chunks from the tile's walk, 6.6e-7.  So do two chunks: the states from zero and the adjoints pass from one to the
+// other as vectors, and need no chunk's product either.
 //
 // The backward pass is a recurrence as well, over as many carries and with groups above kAdjointCarries of them (float d = 16 and 32: as forward).  The former
 // chunks / these: complex64 1 x 60 x 64 131 / 68, 1 x 600 x 64 197 / 157, 1 x 1000 x 64 248 / 170, 1 x 60 x 128 388 / 135; complex128 1 x 30 x 100 698 / 223, 1 x 1000 x
 // 24 246 / 142.
 static long long affine_short_chunk(long long T, int d, long long batch, int dtype, bool adjoint, long long former)
 {
-    if (T < (dtype == GOOM_C64 && d <= 64 ? 28 : 24) || (dtype == GOOM_C64 && d == 16 && T <= former)) return former;
+    if (T < (dtype == GOOM_C64 && d <= 64 ? 28 : 24) || T <= 2 * former) return former;
     const long long r = dtype == GOOM_C64 ? (d == 16 || d == 32 ? 2 : d <= 16 ? 3 : d <= 64 ? 4 : 8) : (d <= 64 ? 8 : 12);
     const long long carries = adjoint && !(dtype == GOOM_C64 && (d == 16 || d == 32)) ? kAdjointCarries : dtype == GOOM_C64 && d == 16 ? 130 : 97; // (plan_scan's groups: from 98 chunks on)
     long long L = T > 6 * (carries + 1) ? 6 : T > 4 * (carries + 1) && carries == kAdjointCarries ? 4 : 2;

@@ -28,6 +28,45 @@ def test_short_sequences(G, oracle, d, ctype):  # noqa: F811
         compare(got, re, sg, kap, name=f"T{T}d{d}", max_ill_fraction=0.25, well=well)
 
 
+@pytest.mark.parametrize("ctype,T,d,batch", [(np.complex64, 28, 8, 1), (np.complex64, 31, 64, 1), (np.complex64, 24, 100, 1), (np.complex64, 31, 128, 2),
+                                             (np.complex128, 24, 8, 1), (np.complex128, 31, 16, 2)])
+def test_units_of_their_own(G, oracle, ctype, T, d, batch):  # noqa: F811
+    """D A D^-1, D b and D h0, D over e^+-30 (e^+-250), forward and backward: one chunk, without products whose columns would have to share an exponent."""
+    comp, span = (np.float32, 30) if ctype == np.complex64 else (np.float64, 250)
+    units = np.random.default_rng(d).permutation(np.linspace(-span, span, d)).astype(comp)
+    Az, bz, h0 = inputs(oracle, 1470 + d, batch, T, d, ctype, False)
+    Az.real += units[:, None] - units[None, :]
+    bz.real += units
+    h0.real += units
+    re, sg, kap, well = with_sensitivity(lambda a_, b_, h_: oracle.affine_scan(a_, b_, h0=h_, return_kappa=True), [Az, bz, h0], comp, nprobe=2)
+    H = host(G.affine_scan(dev(Az), dev(bz), dev(h0)))
+    compare(H, re, sg, kap, name=f"units T{T}d{d}", max_ill_fraction=0.25, well=well)
+    Gh = np.random.default_rng(T + d).normal(size=H.shape).astype(comp)
+    got = [host(v).astype(np.float64) for v in G.affine_scan_backward(dev(Az), dev(bz), dev(H), dev(Gh), dev(h0))]
+    for name, g, w in zip(("A", "bias", "h0"), got, oracle.affine_scan_backward(Az, bz, Gh, h0=h0, h=H)[:3]):
+        # (as below)
+        assert np.linalg.norm(g - w) <= (1e-3 if comp == np.float32 else 1e-10) * np.linalg.norm(w), (name, np.linalg.norm(g - w) / np.linalg.norm(w))
+
+
+@pytest.mark.parametrize("ctype,T,d", [(np.complex64, 32, 64), (np.complex64, 47, 100), (np.complex64, 40, 8), (np.complex128, 47, 12)])
+def test_two_chunks_in_units_of_their_own(G, oracle, ctype, T, d):  # noqa: F811
+    """Between two chunks nothing passes but a vector: from zero the states, and always the adjoints, need no chunk's product."""
+    comp, span = (np.float32, 30) if ctype == np.complex64 else (np.float64, 250)
+    units = np.random.default_rng(d).permutation(np.linspace(-span, span, d)).astype(comp)
+    Az, bz, h0 = inputs(oracle, 1480 + d, 1, T, d, ctype, False)
+    Az.real += units[:, None] - units[None, :]
+    bz.real += units
+    h0.real += units
+    re, sg, kap, well = with_sensitivity(lambda a_, b_: oracle.affine_scan(a_, b_, return_kappa=True), [Az, bz], comp, nprobe=2)
+    compare(host(G.affine_scan(dev(Az), dev(bz))), re, sg, kap, name=f"units, from zero, T{T}d{d}", max_ill_fraction=0.25, well=well)
+    re, sg = oracle.affine_scan(Az, bz, h0=h0)
+    H = (re + 1j * np.pi * sg).astype(ctype)
+    Gh = np.random.default_rng(T + d).normal(size=H.shape).astype(comp)
+    got = [host(v).astype(np.float64) for v in G.affine_scan_backward(dev(Az), dev(bz), dev(H), dev(Gh), dev(h0))]
+    for name, g, w in zip(("A", "bias", "h0"), got, oracle.affine_scan_backward(Az, bz, Gh, h0=h0, h=H)[:3]):
+        assert np.linalg.norm(g - w) <= (1e-3 if comp == np.float32 else 1e-10) * np.linalg.norm(w), (name, np.linalg.norm(g - w) / np.linalg.norm(w))
+
+
 @pytest.mark.parametrize("T", [28, 31])
 def test_logarithms_of_16_rows(G, oracle, T):  # noqa: F811
     """One chunk, whose logarithms are taken of mantissas below 1: a last place of 2^-24 there, and one of the result's (the chunks' own walk: 2^-20)."""

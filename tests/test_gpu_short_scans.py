@@ -34,6 +34,21 @@ def test_short_scans(G, oracle, d, ctype):  # noqa: F811
             compare(last[b], re[-1], sg[-1], kap[-1], name=f"last T{T}d{d}", max_ill_fraction=0.5, well=well[-1])
 
 
+@pytest.mark.parametrize("comp,T,d,batch", [(np.float32, 24, 40, 1), (np.float32, 31, 64, 1), (np.float32, 24, 100, 1), (np.float32, 31, 128, 2),
+                                            (np.float32, 26, 66, 150), (np.float64, 24, 8, 1), (np.float64, 31, 16, 2)])
+def test_units_of_their_own(G, oracle, T, d, batch, comp):  # noqa: F811
+    """D A D^-1, D over e^+-30 (e^+-250): one chunk, without products whose columns would have to share an exponent."""
+    span = 30 if comp == np.float32 else 250
+    units = np.random.default_rng(d).permutation(np.linspace(-span, span, d))
+    z = chain(oracle, 1585 + d + T, batch, T, d, comp)
+    z.real += (units[:, None] - units[None, :]).astype(comp)
+    got, last = host(G.scan(dev(z))), host(G.reduce(dev(z)))
+    for b in {0, batch - 1}:
+        re, sg, kap, well = with_sensitivity(lambda z_: oracle.scan(z_, return_kappa=True), [z[b]], comp, nprobe=2)
+        compare(got[b], re, sg, kap, name=f"units T{T}d{d}", max_ill_fraction=0.25, well=well)
+        compare(last[b], re[-1], sg[-1], kap[-1], name=f"units, last T{T}d{d}", max_ill_fraction=0.5, well=well[-1])
+
+
 @pytest.mark.parametrize("d,former", [(64, 20), (100, 20)])
 def test_in_the_room_of_longer_chunks(G, oracle, d, former):  # noqa: F811
     T, batch = 60, 3

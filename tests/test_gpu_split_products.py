@@ -41,6 +41,49 @@ def test_products(G, oracle, shape, spread):  # noqa: F811
         assert np.all(err[plain] <= bound[plain])
 
 
+# gap: how many powers of two below its row's (A) or column's (B) largest entry, which meets a zero, lies all that counts.  Both kernels (few tiles, many)
+@pytest.mark.parametrize("gap_a,gap_b", [(0, 0), (100, 0), (0, 125), (125, 0), (140, 0), (0, 140), (70, 50)])
+@pytest.mark.parametrize("batch,n,m", [(1, 129, 40), (40, 140, 131)])
+def test_all_bits_of_small_entries(G, oracle, batch, n, m, gap_a, gap_b):  # noqa: F811
+    """Three terms a sum: without its operands' third parts (2^-17 of them) it would miss the bound, and without the lift these are lost at gaps above 110."""
+    A, B = operands(oracle, (batch, n, 5, m), 1250 + n, 0)
+    # (What counts comes out near 1, where the result's last place is 2^-23 or below.  It is a difference of logarithms from its row's largest that is rounded to
+    # floats when an operand is converted; one operand's entries lie near 2^-gap for that, the other's as far above 1, and the differences are floats.)
+    up = max(gap_a, gap_b)
+    level_a, level_b = (-up, up) if gap_a >= gap_b else (up, -up)
+    A.real += np.float32(level_a * np.log(2.0))
+    B.real += np.float32(level_b * np.log(2.0))
+    A[:, :, 0] = np.float32((level_a + gap_a) * np.log(2.0))
+    B[:, 0] = -np.inf
+    A[:, :, 1] = -np.inf
+    B[:, 1] = np.float32((level_b + gap_b) * np.log(2.0))
+    got = host(G.lmme(dev(A), dev(B)))
+    for i in range(min(batch, 3)):
+        re, sg, kap = oracle.lmme(A[i], B[i], return_kappa=True)
+        # two exponentials and their corrections (2^-22), the products left out (2^-24), three sums (2^-24 each); the logarithm's last places
+        bound = kap * 2.0 ** -21 + (1.0 + np.abs(re)) * 2.0 ** -22
+        assert np.all(np.abs(got[i].real - re) <= bound), float((np.abs(got[i].real - re) / bound).max())
+        assert np.array_equal(got[i].imag > 1, sg == 1)
+
+
+@pytest.mark.parametrize("chunk", [1, 2, 5])
+@pytest.mark.parametrize("d", [140, 260])
+def test_all_bits_in_scans(G, oracle, d, chunk):  # noqa: F811
+    """Positive matrices of two entries a row: sums of two terms, without cancellation."""
+    T = 5
+    Z = np.full((T, d, d), -np.inf, dtype=np.complex64)
+    x = si.normal_f32(si.BASE_SEED + 1460 + d, 1, T * d * 2).reshape(T, d, 2)
+    i = np.arange(d)
+    Z.real[:, i, i], Z.real[:, i, (i + 1) % d] = x[..., 0], x[..., 1]
+    re, sg, kap = oracle.scan(Z, return_kappa=True)
+    got = host(G.scan(dev(Z), chunk_len=chunk))
+    some = re > -np.inf
+    assert np.array_equal(some, got.real > -np.inf) and not got[some].imag.any()
+    bound = T * 2.0 ** -21 + (1.0 + np.abs(re[some])) * 2.0 ** -22  # (a product as above each step)
+    err = np.abs(got.real[some] - re[some])
+    assert np.all(err <= bound), float((err / bound).max())
+
+
 @pytest.mark.parametrize("batch,n,d,m", [(3, 128, 1024, 128), (1, 130, 700, 20), (2, 7, 513, 100)])
 def test_products_in_the_room_of_floats(G, oracle, batch, n, d, m):  # noqa: F811
     """A workspace for operands and product in floats: too small for three parts of the operands where the inner dimension is long."""

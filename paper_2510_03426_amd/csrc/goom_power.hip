@@ -14,9 +14,9 @@ namespace {
 
 template <typename V> __device__ inline double entry_of(V re, V im, double n) { return scaled_entry((double)re, (double)im, n); }
 
-// A [batch][d][d] GOOMs of component IO; power: factored with component F, the leading d columns on one exponent; prepared: NULL, or
-// the matrix itself on its rows' powers of two (component F), row i's power of two at exponent i; group: NULL, or that power squared
-// `squarings` times more, factored as it is
+// A [batch][d][d] GOOMs of component IO; power: mantissas of component F on their rows' powers of two, row i's at exponent i (a factored matrix
+// that every step of a chain shares; on one exponent a matrix in units of its own, D A D^-1, would lose its small columns); prepared: NULL, or the
+// matrix itself in the same form; group: NULL, or that power squared `squarings` times more
 template <typename IO, typename F, int DP>
 __global__ __launch_bounds__((DP / 16) * 64) void power_kernel(const IO *A, int d, long long exponent, unsigned char *power, unsigned char *prepared,
                                                                long long stride, int squarings, unsigned char *group, long long group_stride, int fact_cols)
@@ -121,7 +121,7 @@ __global__ __launch_bounds__((DP / 16) * 64) void power_kernel(const IO *A, int 
                 --bit;
             }
         }
-        // one exponent for the whole power: the largest row's (a zero row has none)
+        // (a zero row has no power of two)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = 16 * wave + 4 * v + g;
@@ -129,25 +129,18 @@ __global__ __launch_bounds__((DP / 16) * 64) void power_kernel(const IO *A, int 
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) some = P[row * LD + 16 * nt + c] != 0.0 ? 1.0 : some;
             some = max16(some);
-            if (c == 0) R[row] = some > 0.0 && row < d ? D[row] : kNegBig;
+            if (c == 0 && row < d) reinterpret_cast<double *>(dst + (size_t)DP * fact_cols * sizeof(F))[row] = some > 0.0 ? D[row] : kNegBig;
         }
-        __syncthreads();
-        double top = kNegBig;
-        for (int i = lane; i < DP; i += 64) top = raw_max(top, R[i]);
-#pragma unroll
-        for (int s = 1; s < 64; s <<= 1) top = raw_max(top, __shfl_xor(top, s, 64));
-        if (!(top > 0.5 * kNegBig)) top = 0.0;
         for (int e = threadIdx.x; e < d * d; e += (int)blockDim.x) {
             const int i = e / d, j = e - i * d;
-            reinterpret_cast<F *>(dst)[(size_t)i * fact_cols + j] = (F)__builtin_ldexp(P[i * LD + j], (int)Comp<double>::clamp_shift(D[i] - top));
+            reinterpret_cast<F *>(dst)[(size_t)i * fact_cols + j] = (F)P[i * LD + j];
         }
-        for (int j = threadIdx.x; j < d; j += (int)blockDim.x) reinterpret_cast<double *>(dst + (size_t)DP * fact_cols * sizeof(F))[j] = top;
         if (!group) return;
         dst = group + blockIdx.x * group_stride;
         group = nullptr;
         bit = squarings; // (that many bits, all zero)
         exponent = 0;
-        __syncthreads(); // every wave is done with R
+        __syncthreads(); // every wave is done with P and D
     }
 }
 

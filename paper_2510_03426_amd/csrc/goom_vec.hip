@@ -160,12 +160,21 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         return u > (V)kNone ? Comp<V>::ceil_(u * (V)kLog2e) : (V)kNone; // (+inf stays: its row comes out as NaN; a zero row has none)
     };
     if constexpr (SAME) {
+        [[maybe_unused]] const double *same_e = reinterpret_cast<const double *>(same0 + (size_t)DP * lfc * sizeof(R));
+        if constexpr (FACT) { // rows on their own powers of two (goom_power.hip), these relative to the largest
+            double top = kNegBig;
+            for (int i = lane; i < n_rows; i += 64) top = raw_max(top, same_e[i]);
+#pragma unroll
+            for (int s = 1; s < 64; s <<= 1) top = raw_max(top, __shfl_xor(top, s, 64));
+            same_common = top > 0.5 * kNegBig ? top : 0.0;
+        }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             if constexpr (FACT) {
+                const double e = same_e[row0 + 4 * q < n_rows ? row0 + 4 * q : n_rows - 1];
 #pragma unroll
                 for (int k = 0; k < K; ++k) same_s[q][k] = (V) * reinterpret_cast<const R *>(same0 + offset_of(q, k));
-                same_n[q] = (V)0;
+                same_n[q] = e > 0.5 * kNegBig ? (V)(e - same_common) : (V)0;
             } else if (a.left_prepared) { // converted once for all chunks (goom_power.hip)
                 const unsigned char *pp = a.left_prepared + item * a.prepared_stride;
                 const bool f64 = sizeof(R) == 8 || a.prepared_f64;
@@ -186,7 +195,6 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
                 for (int k = 0; k < K; ++k) same_s[q][k] = (V)scaled_entry((double)z[k][0], (double)z[k][1], (double)same_n[q]);
             }
         }
-        if (FACT) same_common = *reinterpret_cast<const double *>(same0 + (size_t)DP * lfc * sizeof(R));
     }
 
     auto convert = [&](const Matrix &r) {
@@ -292,7 +300,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
         }
         if constexpr (FACT && sizeof(R) == 8) {
             // A factored matrix has one power of two for all its rows: a row may be 2^-500 of it, and meet an entry of the vector as small.
-            // Where a sum comes out so low, the row is taken on a power of two of its own.
+            // Where a sum comes out so low, the row is taken on a power of two of its own.  (SAME: it is, and its entries may be as far apart.)
             const bool low = owner && Comp<V>::abs_(part) < (V)0x1p-900;
             if (__builtin_amdgcn_ballot_w64(low) != 0) {
 #pragma unroll
@@ -313,7 +321,7 @@ __global__ __launch_bounds__(NW * 64) void vec_walk_kernel(ChainArgs a)
                     for (int k = 0; k < K; ++k) p = p + Comp<V>::ldexp_(entry(k), -e) * hm[k];
                     p = sum16(p);
                     part = c == q ? p : part;
-                    n = c == q ? (V)e : n;
+                    n = c == q ? (V)e + (SAME ? same_n[SAME ? q : 0] : (V)0) : n;
                     if (K >= 8) __builtin_amdgcn_sched_barrier(0);
                 }
             }

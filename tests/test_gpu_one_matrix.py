@@ -86,6 +86,39 @@ def test_one_matrix_carries_of_any_exponent(G, d, ctype, sign):  # noqa: F811
     assert np.abs(H.real[ok] / want[ok] - 1).max() <= 4 * T * np.finfo(comp).eps
 
 
+# (from zero and of up to 63 steps, or more sequences than fill the chip: one chunk, or two, before the chunks were walked side by side)
+@pytest.mark.parametrize("ctype,T,d,batch,from_zero", [(np.complex64, 60, 64, 1, True), (np.complex64, 63, 100, 2, True), (np.complex64, 100, 64, 600, False),
+                                                       (np.complex64, 90, 40, 600, False), (np.complex64, 700, 24, 50, False), (np.complex64, 2100, 48, 1, False),
+                                                       (np.complex64, 500, 16, 3, False), (np.complex128, 200, 64, 2, False), (np.complex128, 300, 12, 2, False)])
+def test_one_matrix_in_units_of_its_own(G, oracle, ctype, T, d, batch, from_zero):  # noqa: F811
+    """D A D^-1, D b and D h0, A a rotation and D over e^+-30 (e^+-250), forward and backward: the chunks' product keeps its rows' powers of two."""
+    comp, span = (np.float32, 30) if ctype == np.complex64 else (np.float64, 250)
+    rng = np.random.default_rng(d + T)
+    units = rng.permutation(np.linspace(-span, span, d))
+    Q = np.linalg.qr(rng.standard_normal((batch, d, d)))[0]
+    Az = (np.log(np.abs(Q)) + units[:, None] - units[None, :] + 1j * np.pi * (Q < 0)).astype(ctype)
+    b, h = rng.standard_normal((batch, T, d)), rng.standard_normal((batch, d))
+    bz = (np.log(np.abs(b)) + units + 1j * np.pi * (b < 0)).astype(ctype)
+    h0 = None if from_zero else (np.log(np.abs(h)) + units + 1j * np.pi * (h < 0)).astype(ctype)
+    ends = sorted({0, batch - 1})
+    A2, b2, h2 = (None if v is None else np.ascontiguousarray(v[ends]) for v in (Az, bz, h0))
+    rep = lambda a: np.broadcast_to(a[:, None], (len(ends), T, d, d))
+    re, sg, kap = oracle.affine_scan(rep(A2), b2, h0=h2, return_kappa=True)
+    put = lambda v: None if v is None else dev(v)
+    got = host(G.affine_scan(dev(Az), dev(bz), put(h0), time_invariant=True))
+    # a state in its units: T steps of a rotation, each a rounding of d products of sizes about 1, and of the entries (a float of size 2 span: its last place)
+    unit_eps = np.finfo(comp).eps * 2 * span
+    g = np.exp(got[ends].real.astype(np.float64) - units) * np.where(got[ends].imag > 1, -1.0, 1.0)
+    w = np.exp(re - units) * np.where(sg == 1, -1.0, 1.0)
+    assert np.linalg.norm(g - w) <= 4 * T ** 0.5 * unit_eps * np.linalg.norm(w), np.linalg.norm(g - w) / np.linalg.norm(w)
+    H = got.copy()
+    H[ends] = (re + 1j * np.pi * sg).astype(ctype)
+    Gh = (rng.standard_normal(H.shape) * np.exp(H.real - units)).astype(comp)
+    got = [host(v).astype(np.float64) for v in G.affine_scan_backward(dev(Az), dev(bz), dev(H), dev(Gh), put(h0), time_invariant=True)[:2]]
+    for name, g, w in zip(("A", "bias"), got, oracle.affine_scan_backward_time_invariant(A2, b2, Gh[ends], h0=h2, h=H[ends])[:2]):
+        assert np.linalg.norm(g[ends] - w) <= 4 * T ** 0.5 * unit_eps * np.linalg.norm(w), (name, np.linalg.norm(g[ends] - w) / np.linalg.norm(w))
+
+
 def test_one_matrix_in_the_room_of_one_column_walks(G, oracle):  # noqa: F811
     """A workspace too small for the short chunks: longer ones, and the same states and gradients; nothing at all is refused."""
     T, d, batch = 1000, 64, 4

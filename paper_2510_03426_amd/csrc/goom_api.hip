@@ -1546,7 +1546,16 @@ struct LmmeBackwardPlan {
     size_t r_bytes, c_bytes, w_bytes, at_bytes, bt_bytes, x_bytes, y_bytes, lmme_bytes;
     size_t total() const { return r_bytes + c_bytes + w_bytes + at_bytes + bt_bytes + x_bytes + y_bytes + lmme_bytes; }
 };
-LmmeBackwardPlan plan_lmme_backward(int64_t batch, int n, int d, int m, int dtype, uint32_t flags)
+// The least room that goom_lmme takes, where it asks for more: float products above GOOM_MAX_DIM by either way.
+size_t lmme_least_bytes(int64_t batch, int n, int d, int m, int dtype, uint32_t flags)
+{
+    const size_t full = goom_lmme_workspace_bytes(batch, n, d, m, dtype, flags);
+    if (dtype != GOOM_C64 || full == 0 || !lmme_is_large(n, d, m)) return full;
+    const size_t floats = lmme_large_workspace_bytes(batch, n, d, m);
+    return floats < full ? floats : full;
+}
+// least: with the products in the least room that they run in
+LmmeBackwardPlan plan_lmme_backward(int64_t batch, int n, int d, int m, int dtype, uint32_t flags, bool least = false)
 {
     const size_t rb = comp_bytes(dtype), cb = 2 * rb, bt = (size_t)batch;
     LmmeBackwardPlan p;
@@ -1560,7 +1569,10 @@ LmmeBackwardPlan plan_lmme_backward(int64_t batch, int n, int d, int m, int dtyp
     }
     p.at_bytes = p.x_bytes = align_up(bt * n * d * cb, 256);
     p.bt_bytes = p.y_bytes = align_up(bt * d * m * cb, 256);
-    const size_t wa = goom_lmme_workspace_bytes(batch, n, m, d, dtype, flags), wb = goom_lmme_workspace_bytes(batch, d, n, m, dtype, flags);
+    auto room = [&](int rows, int inner, int cols) {
+        return least ? lmme_least_bytes(batch, rows, inner, cols, dtype, flags) : goom_lmme_workspace_bytes(batch, rows, inner, cols, dtype, flags);
+    };
+    const size_t wa = room(n, m, d), wb = room(d, n, m);
     p.lmme_bytes = align_up(wa > wb ? wa : wb, 256);
     return p;
 }
@@ -1590,7 +1602,8 @@ int goom_lmme_backward(goom_ctx *ctx, const void *A, const void *B, const void *
     if (!aligned(A, 16) || !aligned(B, 16) || !aligned(Cm, 16)) return fail(ctx, GOOM_EINVAL, "complex data must be 16-byte aligned");
     const size_t rb = comp_bytes(dtype);
     if (!aligned(grad_C, rb) || !aligned(grad_A, rb) || !aligned(grad_B, rb)) return fail(ctx, GOOM_EINVAL, "misaligned data pointer");
-    const LmmeBackwardPlan p = plan_lmme_backward(batch, n, d, m, dtype, flags);
+    LmmeBackwardPlan p = plan_lmme_backward(batch, n, d, m, dtype, flags);
+    if (p.total() > ws_bytes) p = plan_lmme_backward(batch, n, d, m, dtype, flags, true);
     if (int s = check_workspace(ctx, ws, ws_bytes, p.total())) return s;
     if (int s = need_ctx(ctx)) return s;
     unsigned char *w = static_cast<unsigned char *>(ws);
@@ -1629,7 +1642,8 @@ struct ScanBackwardPlan {
     int64_t lmme_slice;            // (b, t) pairs per LMME call
     size_t total() const { return c_bytes + f_bytes + init_bytes + states_bytes + scan_bytes + lmme_bytes; }
 };
-ScanBackwardPlan plan_scan_backward(int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts, bool with_init)
+// less: 1, the stacked scan's matrices held two a chunk; 2, scan and products in the least room that they run in
+ScanBackwardPlan plan_scan_backward(int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts, bool with_init, int less = 0)
 {
     const size_t rb = comp_bytes(dtype), cb = 2 * rb, bt = (size_t)batch;
     const int D = d + m;
@@ -1639,14 +1653,21 @@ ScanBackwardPlan plan_scan_backward(int64_t T, int d, int m, int64_t batch, int 
     p.f_bytes = align_up(bt * (size_t)nsteps * D * D * cb, 256) + 512;
     p.init_bytes = align_up(bt * D * m * cb, 256);
     p.states_bytes = align_up(bt * (size_t)nsteps * D * m * cb, 256);
-    p.scan_bytes = align_up(goom_scan_workspace_bytes(nsteps, D, m, batch, dtype, opts), 256);
+    size_t scan = goom_scan_workspace_bytes(nsteps, D, m, batch, dtype, opts);
+    const long long chunk = opts ? opts->chunk_len : 0;
+    if (less && dtype == GOOM_C64 && scan_split_applies(nsteps, D, m, batch)) {
+        scan = scan_split_workspace_bytes(nsteps, D, m, batch, chunk, false, true);
+        const size_t floats = scan_large_workspace_bytes(nsteps, D, m, batch, chunk, false);
+        if (less > 1 && floats < scan) scan = floats;
+    }
+    p.scan_bytes = align_up(scan, 256);
     p.lam_off = 0;
     p.pt_off = align_up(bt * (size_t)T * d * m * cb, 256);
     p.x_off = p.pt_off + align_up(bt * (size_t)T * m * d * cb, 256);
     // above 128 the product takes at most 65535 pairs per call
     const bool large = d > GOOM_MAX_DIM || m > GOOM_MAX_DIM;
     p.lmme_slice = large && batch * T > 65535 ? 65535 : batch * T;
-    p.lmme_bytes = align_up(goom_lmme_workspace_bytes(p.lmme_slice, d, m, d, dtype, 0), 256);
+    p.lmme_bytes = align_up(less > 1 ? lmme_least_bytes(p.lmme_slice, d, m, d, dtype, 0) : goom_lmme_workspace_bytes(p.lmme_slice, d, m, d, dtype, 0), 256);
     return p;
 }
 } // namespace
@@ -1767,7 +1788,8 @@ int goom_scan_backward(goom_ctx *ctx, const void *M, const void *S0, const void 
         if (int s = need_ctx(ctx)) return s;
         return run_scan_adjoint(ctx, M, S0, P, grad_P, grad_M, grad_S0, T, d, m, batch, dtype, q, w);
     }
-    const ScanBackwardPlan p = plan_scan_backward(T, d, m, batch, dtype, opts, S0 != nullptr);
+    ScanBackwardPlan p = plan_scan_backward(T, d, m, batch, dtype, opts, S0 != nullptr);
+    for (int less = 1; less <= 2 && p.total() > ws_bytes; ++less) p = plan_scan_backward(T, d, m, batch, dtype, opts, S0 != nullptr, less);
     if (int s = check_workspace(ctx, ws, ws_bytes, p.total())) return s;
     if (int s = need_ctx(ctx)) return s;
     void *c = w;

@@ -105,6 +105,45 @@ def test_products_in_the_room_of_floats(G, oracle, batch, n, d, m):  # noqa: F81
     assert run(least) == 0 and run(least - 256) != 0
 
 
+# room: what these calls asked for with all products in floats
+@pytest.mark.parametrize("batch,n,d,m,room", [(3, 128, 128, 1024, 13593600), (2, 64, 200, 700, 8040448)])
+def test_products_backward_in_the_room_of_floats(G, oracle, batch, n, d, m, room):  # noqa: F811
+    import ctypes as C
+    import torch
+    A, B = (dev(v) for v in operands(oracle, (batch, n, d, m), 1275 + n, 0))
+    P = G.lmme(A, B)
+    Gc = dev(si.normal_f32(si.BASE_SEED + 1276, 3, batch * n * m).reshape(batch, n, m))
+    want = G.lmme_backward(A, B, P, Gc)
+    assert room < G.lib.goom_lmme_backward_workspace_bytes(batch, n, d, m, 0, 0)
+    ws, got = torch.empty(room, dtype=torch.uint8, device="cuda"), [torch.empty_like(v) for v in want]
+    run = lambda size: G.lib.goom_lmme_backward(G._ctx, *(C.c_void_p(t.data_ptr()) for t in (A, B, P, Gc, *got)), batch, n, d, m, 0, 0, C.c_void_p(ws.data_ptr()), size)
+    assert run(room) == 0
+    for g, w in zip(got, want):
+        assert np.linalg.norm(host(g) - host(w)) <= 1e-5 * np.linalg.norm(host(w))
+    assert run(room // 2) != 0
+
+
+@pytest.mark.parametrize("T,d,m,batch,room", [(6, 200, 5, 1, 8686080), (12, 130, 130, 1, 30937856)])
+def test_scan_backward_in_the_room_of_floats(G, oracle, T, d, m, batch, room):  # noqa: F811
+    import ctypes as C
+    import torch
+    z = dev(np.stack([oracle.to_goom(si.normal_chain(si.BASE_SEED + 1680 + i, T, d)) for i in range(batch)]))
+    S0 = dev(oracle.to_goom(si.normal_f32(si.BASE_SEED + 1690, 1, batch * d * m).reshape(batch, d, m)))
+    P = G.scan(z, S0)
+    Gp = dev(si.normal_f32(si.BASE_SEED + 1691, 1, batch * T * d * m).reshape(batch, T, d, m))
+    want = G.scan_backward(z, P, Gp, S0)
+    full = G.lib.goom_scan_backward_workspace_bytes(T, d, m, batch, 0, None, 1)
+    assert room < full
+    ws, got = torch.empty(full, dtype=torch.uint8, device="cuda"), [torch.empty_like(v) for v in want]
+    run = lambda size: G.lib.goom_scan_backward(G._ctx, *(C.c_void_p(t.data_ptr()) for t in (z, S0, P, Gp, *got)), T, d, m, batch, 0, None, C.c_void_p(ws.data_ptr()), size)
+    assert run(full - 256) == 0  # (two converted matrices a chunk)
+    assert all(np.array_equal(host(g), host(w)) for g, w in zip(got, want))
+    assert run(room) == 0
+    for g, w in zip(got, want):  # (other products, other chunks: sums of d terms that cancel, over T steps)
+        assert np.linalg.norm(host(g) - host(w)) <= 1e-3 * np.linalg.norm(host(w))
+    assert run(room // 2) != 0
+
+
 # chunks of one step, of two, uneven ones (the last shorter: identities), a single one; states of their own width; several items
 @pytest.mark.parametrize("T,d,chunk,m,batch", [(5, 257, 1, None, 1), (7, 300, 2, None, 2), (8, 260, 3, 20, 1), (6, 130, 6, None, 2), (9, 200, 4, 300, 1), (5, 100, 2, 140, 1),
                                                (11, 140, 0, None, 1), (1, 270, 0, None, 1), (2, 384, 0, 1, 3)])

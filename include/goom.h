@@ -176,7 +176,10 @@ typedef struct goom_scan_opts {
  * phase 2 scans those chunk products, phase 3 re-walks every chunk from its incoming
  * prefix and writes all outputs.  Between steps the running product is kept as real
  * mantissas with a power-of-two exponent per column, so log-magnitudes are rounded to
- * the component type only when an output is stored.
+ * the component type only when an output is stored.  Up to d, m = GOOM_MAX_DIM a chunk's product is held with all of its columns
+ * on one exponent: entries further below its largest than the component type reaches (e^87, e^708) are lost, which
+ * matrices in units of their own notice (D A D^-1 with D over e^+-22, e^+-177); a chain of one chunk (chunk_len = T)
+ * forms no such product.
  * workspace: goom_scan_workspace_bytes(...) bytes.  For GOOM_C64 with d or m above GOOM_MAX_DIM the query asks for
  * the whole input in three bf16 parts, 6 bytes an entry of matrices padded to 128 (up to 4 GiB of them), each converted once;
  * with less room two matrices a chunk are held and converted again in the last phase (the same outputs, bit by bit), and
@@ -347,7 +350,8 @@ int goom_scaled_exp(goom_ctx *ctx, const void *z, void *scaled, void *logscale, 
  * start to end by one workgroup, every matrix read once (the results are those of a sequential
  * float evaluation; whole-number exponents are kept within +-2^28, i.e. log-magnitudes within
  * +-1.8e8, beyond which a float log-magnitude resolves nothing anyway).  Large batches of other
- * sizes are walked start to end as well (no such limit).
+ * sizes are walked start to end as well (no such limit).  A matrix per step and several chunks: the chunks' products are held as
+ * goom_scan's; one matrix for all steps: the power that the chunks share keeps an exponent for every row.
  * workspace: goom_affine_scan_workspace_bytes(...) bytes. */
 #define GOOM_AFFINE_TIME_INVARIANT 0x1u /* goom_scan_opts.flags: one matrix per batch item, A: [batch, d, d],
                                            applied at every step (the paper's state-space layer has constant
@@ -408,7 +412,8 @@ int goom_scaled_exp_backward(goom_ctx *ctx, const void *scaled, const void *grad
  * [batch, n, m], grad_A: [batch, n, d], grad_B: [batch, d, m] reals of the component type (device, caller-owned;
  * grad_A and grad_B overwritten).  Sizes and flags as for goom_lmme (flags go to both products).  workspace:
  * goom_lmme_backward_workspace_bytes(...) bytes, required: about (n m + 2 n d + 2 d m) GOOMs per batch item
- * (n m for n = d = m = 128 without GOOM_LMME_EXACT, where the product kernel transposes and exponentiates itself).
+ * (n m for n = d = m = 128 without GOOM_LMME_EXACT, where the product kernel transposes and exponentiates itself); less will do
+ * where goom_lmme takes less.
  * Errors: GOOM_EINVAL (null or misaligned pointers, sizes), GOOM_EUNSUPPORTED (sizes beyond goom_lmme's),
  * GOOM_EWORKSPACE. */
 int goom_lmme_backward(goom_ctx *ctx, const void *A, const void *B, const void *C, const void *grad_C, void *grad_A,
@@ -431,7 +436,8 @@ size_t goom_lmme_backward_workspace_bytes(int64_t batch, int n, int d, int m, in
  * S0) reals of the component type; device, caller-owned, outputs overwritten.  d + m <= GOOM_MAX_DIM_LMME.
  * opts: as for goom_scan (chunk length of the reverse scan); flags must be 0.  workspace:
  * goom_scan_backward_workspace_bytes(..., with_init = S0 != NULL) bytes, required: up to d = m = 128 two real matrices
- * (d x d and d x m) per chunk with a double beside every entry, beyond about (d + m)(d + 2 m) GOOMs per step.  Errors: GOOM_EINVAL, GOOM_EUNSUPPORTED (sizes), GOOM_EWORKSPACE. */
+ * (d x d and d x m) per chunk with a double beside every entry, beyond about (d + m)(d + 2 m) GOOMs per step
+ * and what goom_scan of the stacked matrices and goom_lmme ask for (GOOM_C64: less will do where these take less).  Errors: GOOM_EINVAL, GOOM_EUNSUPPORTED (sizes), GOOM_EWORKSPACE. */
 int goom_scan_backward(goom_ctx *ctx, const void *M, const void *S0, const void *P, const void *grad_P, void *grad_M,
                        void *grad_S0, int64_t T, int d, int m, int64_t batch, int dtype, const goom_scan_opts *opts,
                        void *workspace, size_t workspace_bytes);

@@ -73,7 +73,7 @@ struct ChainArgs {
     const unsigned char *left_prepared;
     long long prepared_stride;
     int prepared_cols, prepared_f64;
-    int left_same; // factored left factors, vector chains only: every step's matrix is the first one's, its bias column its own
+    int left_same; // factored left factors, vector chains only: every step's matrix is the first one's (rows on exponents of their own), its bias column its own
 };
 
 // chains of one state column (goom_vec.hip): GOOM or factored left factors, n, d <= dp

@@ -102,7 +102,7 @@ struct ChainLaunch {
     const void *left_prepared; // vector chains over one GOOM factor: NULL, or the factor converted beforehand (see ChainArgs)
     long long prepared_stride;
     int prepared_cols, prepared_f64;
-    int left_same;        // factored left factors, m = 1: every step's matrix is the first one's, its bias column its own
+    int left_same;        // factored left factors, m = 1: every step's matrix is the first one's (its rows on exponents of their own), its bias column its own
     const char *label;    // phase name for profiling records
 };
 int launch_chain(goom_ctx *ctx, const ChainLaunch &a);
@@ -237,8 +237,8 @@ int launch_affine_seq(goom_ctx *ctx, const void *A, const void *bias, const void
 // its adjoint, with the gradients of the matrices and (unless NULL) of the bias; scale: batch T ints, adj_bias and states: batch T 32 8-byte words
 int launch_affine_seq_adjoint(goom_ctx *ctx, const void *A, const void *bias, const void *h0, const void *H, const void *G, int *scale, void *adj_bias,
                               void *states, void *grad_A, void *grad_bias, long long T, long long batch);
-// A^exponent of one matrix per batch item, factored (component double if fact_f64 or GOOM_C128, else float; consecutive items `stride`
-// bytes apart), and, if prepared is given, the converted matrix for the vector chains (goom_power.hip)
+// A^exponent of one matrix per batch item, rows on exponents of their own (component double if fact_f64 or GOOM_C128, else float; consecutive items
+// `stride` bytes apart), and, if prepared is given, the converted matrix for the vector chains (goom_power.hip)
 int launch_matrix_power(goom_ctx *ctx, const void *A, int d, long long batch, int dtype, int fact_f64, int dp, long long exponent, void *power, void *prepared,
                         long long stride, int squarings, void *group, long long group_stride, int fact_cols);
 // the walks of the recurrence's chunks over one matrix, converted beforehand (goom_one_matrix.hip)

@@ -441,8 +441,8 @@ template <bool RAW> void launch_gemm_split(hipStream_t st, const SplitGemm &a, u
 
 // ---- rows of GOOM matrices into planes.  Row r of matrix b: 2^(log2|x| - shift), shift = the row's whole power of two less kLift.  One wave a
 // row (up to 1024 entries, sixteen a lane, in pairs), four rows a workgroup: grid (rows_padded / 4, matrices), 256 threads.  A row without entries
-// has the shift -inf; of a chain's matrices a row with an infinite entry or a NaN has inf, and no entries: the product's row is infinite
-// then, and so are all states after it.
+// has the shift -inf; of a chain's matrices a row with an infinite entry (or, if nan_shows, a NaN; it counts as zero otherwise) has inf, and no
+// entries: the product's row is infinite then, and so are all states after it.
 // A chain of matrices (L > 0): matrix b is step s = s0 + b % per_chain of chain b / per_chain = item * C + chunk, and goes to place
 // chain * places + s % places; beyond the chunk or T it is the identity.
 struct RowsArgs {
@@ -451,6 +451,7 @@ struct RowsArgs {
     float *shifts;
     int n, d, rows_padded, k_padded;
     long long T, L, C, per_chain, s0, places;
+    bool nan_shows;
 };
 __global__ __launch_bounds__(256) void split_rows_kernel(RowsArgs a)
 {
@@ -516,7 +517,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(RowsArgs a)
         mx = fmaxf(mx, fmaxf(e[r][0].x, e[r][1].x));
         bad = bad || e[r][0].x != e[r][0].x || e[r][1].x != e[r][1].x;
     }
-    if (a.L > 0 && bad) mx = -CF::neg_inf();
+    if (a.nan_shows && bad) mx = -CF::neg_inf();
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
     const float sh = ceilf(mx * kLog2eF) - kLift;
@@ -844,7 +845,7 @@ int launch_lmme_split(goom_ctx *ctx, const void *A, const void *B, void *C, long
     hipStream_t st = ctx->stream;
     const unsigned nb = (unsigned)batch;
     prof_begin(ctx, "lmme_large_scale_operands");
-    RowsArgs r{static_cast<const float2 *>(A), X, rs, n, d, p.Np, p.Kp, 0, 0, 0, 0, 0, 0};
+    RowsArgs r{static_cast<const float2 *>(A), X, rs, n, d, p.Np, p.Kp, 0, 0, 0, 0, 0, 0, false};
     hipLaunchKernelGGL(split_rows_kernel, dim3(p.Np / 4, nb), dim3(256), 0, st, r);
     hipLaunchKernelGGL(split_column_shift_kernel, dim3((p.Mp + 63) / 64, nb), dim3(256), 0, st, static_cast<const float2 *>(B), cs, d, m, p.Mp);
     hipLaunchKernelGGL(split_columns_kernel<false>, dim3(p.Mp / 32, (p.Kp + 31) / 32, nb), dim3(256), 0, st, static_cast<const float2 *>(B), cs, Y,
@@ -1009,7 +1010,8 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
     const bool all = p.places == L;
     // steps s0 .. of all chains: their matrices' planes and row shifts
     auto convert = [&](long long s0, long long per_chain) {
-        RowsArgs r{Mg, X, shifts, d, d, dp, dp, T, L, C, per_chain, s0, p.places};
+        // (a NaN shows where states as wide run in registers, and in long chains of these sizes still do; in larger products it counts as zero)
+        RowsArgs r{Mg, X, shifts, d, d, dp, dp, T, L, C, per_chain, s0, p.places, d <= 256 && m <= 256};
         hipLaunchKernelGGL(split_rows_kernel, dim3(dp / 4, (unsigned)(chains * per_chain)), dim3(256), 0, st, r);
         RelativeArgs q{shifts, rel, top, dp, per_chain, s0, p.places};
         hipLaunchKernelGGL(relative_shifts_kernel, dim3((unsigned)(chains * per_chain)), dim3(256), 0, st, q);

@@ -119,6 +119,25 @@ def test_one_matrix_in_units_of_its_own(G, oracle, ctype, T, d, batch, from_zero
         assert np.linalg.norm(g[ends] - w) <= 4 * T ** 0.5 * unit_eps * np.linalg.norm(w), (name, np.linalg.norm(g[ends] - w) / np.linalg.norm(w))
 
 
+@pytest.mark.parametrize("d", [48, 64, 100, 128])
+def test_one_matrix_rounds_no_more_than_one_chain(G, oracle, d):  # noqa: F811
+    """Sixteen chunks as the columns of a product: its sums are of sixteen terms, and these in pairs, as a lane's and sixteen lanes' are in the walk of one chain."""
+    T, batch = 192, 4
+    rng = np.random.default_rng(d)
+    Q = np.linalg.qr(rng.standard_normal((batch, d, d)))[0]
+    Az, bz, h0 = (oracle.to_goom(v.astype(np.float32)) for v in (Q, 0.1 * rng.standard_normal((batch, T, d)), rng.standard_normal((batch, d))))
+    re, sg = oracle.affine_scan(np.broadcast_to(Az[:, None], (batch, T, d, d)), bz, h0=h0)
+    w = np.exp(re) * np.where(sg == 1, -1, 1)
+    err = []
+    for chunk in (0, T):
+        got = host(G.affine_scan(dev(Az), dev(bz), dev(h0), chunk_len=chunk, time_invariant=True))
+        err.append(np.linalg.norm(np.exp(got.real.astype(np.float64)) * np.where(got.imag > 1, -1, 1) - w) / np.linalg.norm(w))
+    say(f"d={d} in chunks {err[0]:.2e}, one chain {err[1]:.2e}")
+    # Roundings of rotations add up as the root of their number: 192 steps on one side, 24 carries and a chunk of eight at most on the other, the last states'
+    # ratio 0.41, all states' less.  (Sums of d terms one after the other: 0.46 to 0.66.)
+    assert err[0] <= 0.45 * err[1]
+
+
 def test_one_matrix_in_the_room_of_one_column_walks(G, oracle):  # noqa: F811
     """A workspace too small for the short chunks: longer ones, and the same states and gradients; nothing at all is refused."""
     T, d, batch = 1000, 64, 4

@@ -1084,15 +1084,17 @@ constexpr long long kAdjointCarries = 128;
 // 1 x 60 x 64 91 / 43 (43), 1 x 300 x 64 99 / 80 (79), 1 x 1000 x 64 137 / 111 (111), 8 x 300 x 64 105 / 90 (84), 1 x 60 x 8 52 / 29 (29), 1 x 300 x 16 43 / 40 (40), 1 x
 // 60 x 128 330 / 97 (97), 1 x 1000 x 128 377 / 264 (264); complex128 1 x 60 x 64 135 / 81 (80), 1 x 300 x 24 97 / 88 (81), 1 x 30 x 100 448 / 148 (148).  Up to
 // two dozen steps one chunk takes less than three launches.  What was one chunk stays one: as for scans (plan_prefix), and float 16 x 16 has its logarithms from
-// the vector kernel then, median error 1.6e-7, in chunks from the tile's walk, 6.6e-7.  So do two chunks: the states from zero and the adjoints pass from one to the
-// other as vectors, and need no chunk's product either.
+// the vector kernel then, median error 1.6e-7, in chunks from the tile's walk, 6.6e-7.  What was two chunks needed
+// no chunk's product for the states from zero and for the adjoints, which pass from one to the other as vectors: it is one chunk now, in us, two / one / the
+// best of short ones 8 x 40 x 128 332 / 128 / 90, of 64 92 / 62 / 40, of 8 51 / 36 / 26, but float 16 x 16 (47 steps: 36 / 41 / 22).
 //
 // The backward pass is a recurrence as well, over as many carries and with groups above kAdjointCarries of them (float d = 16 and 32: as forward).  The former
 // chunks / these: complex64 1 x 60 x 64 131 / 68, 1 x 600 x 64 197 / 157, 1 x 1000 x 64 248 / 170, 1 x 60 x 128 388 / 135; complex128 1 x 30 x 100 698 / 223, 1 x 1000 x
 // 24 246 / 142.
 static long long affine_short_chunk(long long T, int d, long long batch, int dtype, bool adjoint, long long former)
 {
-    if (T < (dtype == GOOM_C64 && d <= 64 ? 28 : 24) || T <= 2 * former) return former;
+    if (T < (dtype == GOOM_C64 && d <= 64 ? 28 : 24) || T <= former) return former;
+    if (T <= 2 * former) return dtype == GOOM_C64 && d == 16 ? former : T;
     const long long r = dtype == GOOM_C64 ? (d == 16 || d == 32 ? 2 : d <= 16 ? 3 : d <= 64 ? 4 : 8) : (d <= 64 ? 8 : 12);
     const long long carries = adjoint && !(dtype == GOOM_C64 && (d == 16 || d == 32)) ? kAdjointCarries : dtype == GOOM_C64 && d == 16 ? 130 : 97; // (plan_scan's groups: from 98 chunks on)
     long long L = T > 6 * (carries + 1) ? 6 : T > 4 * (carries + 1) && carries == kAdjointCarries ? 4 : 2;

@@ -1,6 +1,5 @@
 """Spectra of chains with many chunks, walked in segments that are joined afterwards: sizes at the edges of the panels, a last chunk that is shorter, initial
-states, several items, chunks that are factored twice, directions that are weakly separated, and chains whose segments do not join (walked in order
-then)."""
+states, several items, chunks that are factored twice, and chains whose segments do not join (walked in order then)."""
 import numpy as np
 import pytest
 
@@ -23,7 +22,7 @@ def in_order(G, z, s0=None, chunk_len=0):  # noqa: F811
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("d,T,chunk,batch", [(1, 64, 1, 1), (3, 129, 2, 1), (15, 200, 2, 2), (16, 321, 5, 1), (17, 192, 3, 1), (31, 400, 4, 2), (32, 130, 2, 1), (32, 65, 1, 1),
-                                             (20, 127, 1, 3), (1, 80, 1, 1), (3, 181, 2, 1), (16, 401, 5, 1), (17, 240, 3, 1), (32, 170, 2, 1), (32, 81, 1, 1)])
+                                             (20, 127, 1, 3)])
 def test_spectrum(G, oracle, d, T, chunk, batch, dtype):  # noqa: F811
     x = np.stack([chain(2000 + d + i, T, d, dtype, 0.05) for i in range(batch)])
     z = oracle.to_goom(x)
@@ -34,6 +33,13 @@ def test_spectrum(G, oracle, d, T, chunk, batch, dtype):  # noqa: F811
         # both sum T logarithms of numbers good to a few units of 2^-52, magnified by what the joining lost (1e6 at most)
         assert np.abs(lam[i] - ref).max() <= 1e-9 * max(1.0, np.abs(ref).max())
         assert np.abs(lam[i] - kept[i]).max() <= 1e-9 * max(1.0, np.abs(ref).max())
+
+
+# from the first number of chunks on that is walked in segments, and one more
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("d,T,chunk,batch", [(1, 80, 1, 1), (3, 181, 2, 1), (16, 401, 5, 1), (17, 240, 3, 1), (32, 170, 2, 1), (32, 81, 1, 1)])
+def test_spectrum_of_few_segments(G, oracle, d, T, chunk, batch, dtype):  # noqa: F811
+    test_spectrum(G, oracle, d, T, chunk, batch, dtype)
 
 
 def growth_in_extended_precision(x):

@@ -239,9 +239,21 @@ def test_items_share_launches(G, oracle):  # noqa: F811
     assert count[0] == count[1] > 0
 
 
+def test_static_scratch(G, oracle):  # noqa: F811
+    import torch
+    for T, d in ((4, 300), (24, 300), (12, 520)):  # beside the room for it, and too large for that
+        z = dev(oracle.to_goom(si.normal_chain(si.BASE_SEED + 1500 + d, T, d)))
+        out = torch.empty_like(z)
+        G.scan_static(z, out)
+        ref = G.scan(z)
+        torch.cuda.synchronize()
+        a, b = host(out), host(ref)
+        assert np.quantile(np.abs(a.real - b.real), 0.99) < 1e-3
+
+
 # beside the room for it, too large for that (two converted matrices a chunk, longer chunks, one chunk), and too large for the products in parts
 @pytest.mark.parametrize("T,d,batch,chunk", [(4, 300, 1, 0), (24, 300, 1, 0), (12, 520, 1, 0), (60, 300, 1, 0), (6, 520, 1, 3), (3, 520, 4, None)])
-def test_static_scratch(G, oracle, T, d, batch, chunk):  # noqa: F811
+def test_static_scratch_bits(G, oracle, T, d, batch, chunk):  # noqa: F811
     import torch
     z = np.stack([oracle.to_goom(si.normal_chain(si.BASE_SEED + 1500 + d + i, T, d)) for i in range(batch)])
     out = torch.empty_like(dev(z))

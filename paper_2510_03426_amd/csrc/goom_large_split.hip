@@ -1027,7 +1027,8 @@ int run_scan_split(goom_ctx *ctx, const void *M, const void *init, void *P, long
 
     prof_begin(ctx, "scan_large_convert");
     fill_keys(keys, p.keys_count, e_round[0], (size_t)chains * rows); // (the exponents outside of the chunks' first matrices)
-    if (all) convert(0, L);
+    const long long together = chains * L <= 65535 ? L : 1; // (a grid's second dimension; chunks of two steps reach further)
+    for (long long s = 0; all && s < L; s += together) convert(s, together);
     prof_end(ctx);
 
     // ---- phase 1: chunk products, stored by rows in the last step

@@ -212,6 +212,20 @@ def test_entries_that_are_not_finite_show(G, oracle, d, value, chunk):  # noqa: 
     assert not np.any(failed[:2]) and np.all(failed[2][3]) and not np.any(np.delete(failed[2], 3, axis=0)) and np.all(failed[3:])
 
 
+def test_more_matrices_than_a_grid_is_high(G, oracle):  # noqa: F811
+    """Chunks of two steps whose matrices are all converted ahead: up to twice as many as the chains, which are at most 65535."""
+    batch, T, d, m = 33000, 2, 2, 260
+    z = dev(oracle.to_goom(si.normal_chain(si.BASE_SEED + 1470, batch * T, d)).reshape(batch, T, d, d))
+    init = dev(oracle.to_goom(si.normal_f32(si.BASE_SEED + 1471, 1, batch * d * m).reshape(batch, d, m)))
+    got = host(G.scan(z, init, chunk_len=T))
+    half = batch // 2  # (as many 128 x 128 tiles as fill the chip by far: the same kernels)
+    for part in (slice(0, half), slice(half, batch)):
+        assert np.array_equal(got[part].view(np.uint32), host(G.scan(z[part], init[part], chunk_len=T)).view(np.uint32))
+    for i in (0, batch - 1):
+        re, sg, kap, well = with_sensitivity(lambda a, b: oracle.scan(a, init=b, return_kappa=True), [host(z[i]), host(init[i])], np.float32, nprobe=1)
+        compare(got[i], re, sg, kap, name=f"item {i}", max_ill_fraction=0.05, well=well)
+
+
 def launches_of(G, run):  # noqa: F811
     """How much a call enqueues: the nodes of the graph that it is captured into."""
     import ctypes as C

@@ -1087,6 +1087,8 @@ constexpr long long kAdjointCarries = 128;
 // the vector kernel then, median error 1.6e-7, in chunks from the tile's walk, 6.6e-7.  What was two chunks needed
 // no chunk's product for the states from zero and for the adjoints, which pass from one to the other as vectors: it is one chunk now, in us, two / one / the
 // best of short ones 8 x 40 x 128 332 / 128 / 90, of 64 92 / 62 / 40, of 8 51 / 36 / 26, but float 16 x 16 (47 steps: 36 / 41 / 22).
+// Of the last eighth of batches below affine_walk_whole's line, where all lengths begin to be one chunk, two stay two, so that the line is the same for
+// short sequences, though one is faster there too: 511 x 34 x 8 54 / 34, 95 x 34 x 64 90 / 57, 55 x 34 x 100 254 / 107.
 //
 // The backward pass is a recurrence as well, over as many carries and with groups above kAdjointCarries of them (float d = 16 and 32: as forward).  The former
 // chunks / these: complex64 1 x 60 x 64 131 / 68, 1 x 600 x 64 197 / 157, 1 x 1000 x 64 248 / 170, 1 x 60 x 128 388 / 135; complex128 1 x 30 x 100 698 / 223, 1 x 1000 x
@@ -1094,7 +1096,7 @@ constexpr long long kAdjointCarries = 128;
 static long long affine_short_chunk(long long T, int d, long long batch, int dtype, bool adjoint, long long former)
 {
     if (T < (dtype == GOOM_C64 && d <= 64 ? 28 : 24) || T <= former) return former;
-    if (T <= 2 * former) return dtype == GOOM_C64 && d == 16 ? former : T;
+    if (T <= 2 * former) return (dtype == GOOM_C64 && d == 16) || affine_walk_whole(d, batch + batch / 7, dtype, nullptr) ? former : T;
     const long long r = dtype == GOOM_C64 ? (d == 16 || d == 32 ? 2 : d <= 16 ? 3 : d <= 64 ? 4 : 8) : (d <= 64 ? 8 : 12);
     const long long carries = adjoint && !(dtype == GOOM_C64 && (d == 16 || d == 32)) ? kAdjointCarries : dtype == GOOM_C64 && d == 16 ? 130 : 97; // (plan_scan's groups: from 98 chunks on)
     long long L = T > 6 * (carries + 1) ? 6 : T > 4 * (carries + 1) && carries == kAdjointCarries ? 4 : 2;
